@@ -487,7 +487,7 @@ int tutti_obj_layout(const tutti_pool *pool, const tutti_objcfg *cfg, const uint
   if (n_req > TUTTI_MAX_REQ) return TUTTI_ERANGE;
   if (!d_totals || (n_req > 0 && (!d_n_blocks || !d_extents))) return TUTTI_EINVAL;
   const LayoutArgs a = layout_args(d_n_blocks, d_extents, d_totals, bb, cfg, n_req);
-  hipLaunchKernelGGL(k_layout, dim3(1), dim3(kWave), req_lds_bytes(n_req), static_cast<hipStream_t>(stream), a);
+  hipLaunchKernelGGL(k_layout, dim3(1), dim3(n_req > kWave ? kWgThreads : kWave), req_lds_bytes(n_req), static_cast<hipStream_t>(stream), a);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
 }

@@ -1,7 +1,7 @@
 // Device code of libtutti for gfx950 (wave64).  Included once, by tutti_api.hip.
 //
 // Kernels
-//   k_layout        one wavefront: extents of all requests by a wave-level prefix scan
+//   k_layout        one workgroup: extents of all requests by a prefix scan
 //   k_sqe           submission entries from extents, four lanes per 64-byte entry
 //   k_move          pack / unpack between paged blocks and objects, extents given
 //   k_move_lds      the same for head-major pools with short rows: token tile transposed in LDS
@@ -24,6 +24,8 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "tutti.h"
 
@@ -99,19 +101,32 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, uint32_t src) {
   return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
-// Inclusive prefix sums of three values at once over the first `active` lanes of the wavefront (the other lanes
-// hold zeros and their results are not used).  One loop for the three sums keeps their cross-lane moves
-// independent and back to back, and only ceil(log2(active)) steps are taken: a single request needs none.
-__device__ __forceinline__ void wave_inclusive_scan3(uint64_t &a, uint64_t &b, uint64_t &c, uint32_t lane,
-                                                     uint32_t active) {
-  for (uint32_t d = 1; d < active; d <<= 1) {
-    const uint64_t ta = shfl_up_u64(a, d), tb = shfl_up_u64(b, d), tc = shfl_up_u64(c, d);
-    if (lane >= d) {
-      a += ta;
-      b += tb;
-      c += tc;
-    }
-  }
+// Inclusive prefix sums over the wavefront (all 64 lanes take part), by data-parallel-primitive moves: within rows of
+// 16 lanes by shifts of 1, 2, 4 and 8, then the last lane of a row broadcast to the row (or rows) behind it.  A move
+// is one VALU instruction; the same steps through __shfl_up are LDS permutes of 64+ cycles each.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_0(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROWS, 0xf, false));
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_or_0(uint64_t v) {
+  return (static_cast<uint64_t>(dpp_or_0<CTRL, ROWS>(static_cast<uint32_t>(v >> 32))) << 32) |
+         dpp_or_0<CTRL, ROWS>(static_cast<uint32_t>(v));
+}
+// SAT: sums that would pass 2^32 - 1 stay there (min(sum, 2^32 - 1) is associative, so any order of adding agrees).
+template <bool SAT, typename S>
+__device__ __forceinline__ S add_(S a, S b) {
+  return SAT ? __builtin_elementwise_add_sat(a, b) : a + b;
+}
+template <bool SAT, typename S>
+__device__ __forceinline__ S wave_scan(S v) {
+  v = add_<SAT>(v, dpp_or_0<0x111, 0xf>(v));  // row_shr:1
+  v = add_<SAT>(v, dpp_or_0<0x112, 0xf>(v));  // row_shr:2
+  v = add_<SAT>(v, dpp_or_0<0x114, 0xf>(v));  // row_shr:4
+  v = add_<SAT>(v, dpp_or_0<0x118, 0xf>(v));  // row_shr:8
+  v = add_<SAT>(v, dpp_or_0<0x142, 0xa>(v));  // row_bcast:15 into rows 1 and 3
+  v = add_<SAT>(v, dpp_or_0<0x143, 0xc>(v));  // row_bcast:31 into rows 2 and 3
+  return v;
 }
 
 // The file store of the direct-to-block mode: file f at base + (f - first_file_id)*file_stride.
@@ -129,76 +144,238 @@ struct ScanGeom {
   uint32_t chunk_bytes; // multiple of align
 };
 
-// Extents of all requests, computed by ONE wavefront (the caller passes lane = its lane id and
-// makes sure only one wave of the workgroup runs this).  64 requests per pass, running totals
-// carried between passes.  Results go to LDS and, when ext_out != nullptr, to global memory.
+// Bytes of a request's object beyond its blocks (align is a power of two, so 32 bits of the product suffice), and its
+// submission entries: ceil(obj / chunk_bytes), in 32 bits where the object is that small (the 64-bit division is ten
+// times the instructions).
+__device__ __forceinline__ uint32_t obj_pad(const ScanGeom &g, uint32_t n) {
+  return (0u - n * g.block_bytes) & (g.align - 1);
+}
+__device__ __forceinline__ uint64_t obj_chunks(const ScanGeom &g, uint64_t obj) {
+  if (obj <= 0xffffffffull - (g.chunk_bytes - 1u))
+    return (static_cast<uint32_t>(obj) + (g.chunk_bytes - 1u)) / g.chunk_bytes;
+  return (obj + g.chunk_bytes - 1) / g.chunk_bytes;
+}
+
+// What the per-request staging slot holds: the offset of the K object in the staging buffer or, in the direct-to-block
+// mode, the start of the request's file in the store (kNoFile if the store has no such file).
+__device__ __forceinline__ uint64_t stage_slot(uint64_t stage_off, const uint32_t *file_id, uint32_t fid,
+                                               const FileArgs &files) {
+  if (!file_id) return stage_off;
+  const uint32_t rel = fid - files.first_file_id;
+  return fid >= files.first_file_id && rel < files.n_files ? static_cast<uint64_t>(rel) * files.file_stride : kNoFile;
+}
+
+// Extents of all requests, by the whole workgroup; results go to LDS and, when ext_out != nullptr, to global memory.
+// Ends with a barrier.
 // In the staged mode (file_id == nullptr) the requests are taken in order while the running sum of
 // their blocks stays within table_len: the request that pushes it beyond, and every later one, gets no
 // work items (its LDS table offset is the cut, so it owns no blocks) and TUTTI_ST_BAD_EXTENT is reported
 // by the workgroup that publishes.  The published extents are the plain sums either way.
+//
+// Up to 64 requests: one wavefront, a request per lane (a single request needs no scan at all).
 __device__ __forceinline__ void wave_scan_extents(const ScanGeom g, const uint32_t *__restrict__ n_blocks, uint32_t n_req,
                                                   uint32_t lane, ReqLds l, tutti_extent *__restrict__ ext_out,
                                                   uint64_t *__restrict__ totals_out, uint32_t table_len,
-                                                  uint32_t *__restrict__ status, bool with_chunks = true,
-                                                  const uint32_t *__restrict__ file_id = nullptr,
-                                                  const FileArgs files = FileArgs{0, 0, 0}) {
-  uint64_t carry_stage = 0, carry_sqe = 0, carry_tab = 0;
-  bool cut_found = false;   // wave-uniform: some request so far ran beyond the table
-  uint32_t cut_total = 0;   // blocks of the requests in front of the first such request
-  for (uint32_t base = 0; base < n_req; base += kWave) {
-    const uint32_t r = base + lane;
-    const uint32_t n = (r < n_req) ? n_blocks[r] : 0u;
-    // direct-to-block mode: the per-request slot that holds the staging offset holds the start of the request's
-    // file in the store instead (kNoFile if the store has no such file); the published extents are unaffected
-    const uint32_t fid = (file_id && r < n_req) ? file_id[r] : 0u;
-    const uint64_t raw = static_cast<uint64_t>(n) * g.block_bytes;
-    const uint64_t obj = (raw + (g.align - 1)) & ~static_cast<uint64_t>(g.align - 1);
-    // a workgroup that only moves blocks never reads the entry bases: it skips the 64-bit division
-    const uint64_t chunks = with_chunks ? (obj + g.chunk_bytes - 1) / g.chunk_bytes : 0;
-    const uint32_t active = n_req - base < kWave ? n_req - base : kWave;  // requests of this pass
-    uint64_t inc_stage = 2 * obj, inc_sqe = 2 * chunks, inc_tab = n;
-    wave_inclusive_scan3(inc_stage, inc_sqe, inc_tab, lane, active);
-    const bool beyond = !file_id && r < n_req && carry_tab + inc_tab > table_len;
-    const uint64_t beyond_mask = __ballot(beyond);
-    if (!cut_found && beyond_mask != 0) {
-      const uint32_t first = static_cast<uint32_t>(__ffsll(static_cast<long long>(beyond_mask))) - 1u;
-      cut_total = static_cast<uint32_t>(carry_tab + shfl_u64(inc_tab - n, first));
-      cut_found = true;
+                                                  uint32_t *__restrict__ status, bool with_chunks,
+                                                  const uint32_t *__restrict__ file_id, const FileArgs files) {
+  const uint32_t r = lane;
+  const uint32_t n = (r < n_req) ? n_blocks[r] : 0u;
+  const uint32_t fid = (file_id && r < n_req) ? file_id[r] : 0u;
+  const uint64_t obj = static_cast<uint64_t>(n) * g.block_bytes + obj_pad(g, n);
+  // a workgroup that only moves blocks never reads the entry bases: it skips the division
+  const uint64_t chunks = with_chunks ? obj_chunks(g, obj) : 0;
+  uint64_t inc_stage = 2 * obj, inc_sqe = 2 * chunks, inc_tab = n;
+  if (n_req > 1) {
+    inc_stage = wave_scan<false>(inc_stage);
+    if (with_chunks) inc_sqe = wave_scan<false>(inc_sqe);
+    inc_tab = wave_scan<false>(inc_tab);
+  }
+  const bool beyond = !file_id && r < n_req && inc_tab > table_len;
+  const uint64_t beyond_mask = __ballot(beyond);
+  uint32_t cut_total = 0;  // blocks of the requests in front of the first that runs beyond the table
+  if (beyond_mask != 0) {
+    const uint32_t first = static_cast<uint32_t>(__ffsll(static_cast<long long>(beyond_mask))) - 1u;
+    cut_total = static_cast<uint32_t>(shfl_u64(inc_tab - n, first));
+  }
+  if (r < n_req) {
+    const uint64_t stage_off = inc_stage - 2 * obj;
+    const uint32_t sqe_base = static_cast<uint32_t>(inc_sqe - 2 * chunks);
+    const uint32_t table_off = static_cast<uint32_t>(inc_tab - n);
+    l.stage_off[r] = stage_slot(stage_off, file_id, fid, files);
+    l.obj_bytes[r] = obj;
+    l.table_off[r] = beyond ? cut_total : table_off;
+    l.sqe_base[r] = sqe_base;
+    if (ext_out) {
+      tutti_extent e;
+      e.stage_off = stage_off;
+      e.obj_bytes = obj;
+      e.n_blocks = n;
+      e.n_chunks = static_cast<uint32_t>(chunks);
+      e.sqe_base = sqe_base;
+      e.table_off = table_off;
+      ext_out[r] = e;
     }
-    if (r < n_req) {
-      const uint64_t stage_off = carry_stage + inc_stage - 2 * obj;
-      const uint32_t sqe_base = static_cast<uint32_t>(carry_sqe + inc_sqe - 2 * chunks);
-      const uint32_t table_off = static_cast<uint32_t>(carry_tab + inc_tab - n);
-      const uint32_t rel = fid - files.first_file_id;
-      const bool has_file = fid >= files.first_file_id && rel < files.n_files;
-      l.stage_off[r] = !file_id ? stage_off : has_file ? static_cast<uint64_t>(rel) * files.file_stride : kNoFile;
-      l.obj_bytes[r] = obj;
-      l.table_off[r] = beyond ? cut_total : table_off;
+    if (r + 1 == n_req) {
+      l.table_off[n_req] = beyond_mask != 0 ? cut_total : static_cast<uint32_t>(inc_tab);
+      l.sqe_base[n_req] = static_cast<uint32_t>(inc_sqe);
+      if (totals_out) {
+        totals_out[0] = inc_stage;
+        totals_out[1] = inc_sqe;
+      }
+    }
+  }
+  if (n_req == 0 && lane == 0) {
+    l.table_off[0] = l.sqe_base[0] = 0;
+    if (totals_out) totals_out[0] = totals_out[1] = 0;
+  }
+  if (lane == 0 && beyond_mask != 0 && totals_out && status) atomicOr(status, TUTTI_ST_BAD_EXTENT);
+}
+
+// More than 64 requests: every thread takes a run of consecutive requests (at most TUTTI_MAX_REQ / WG), whose block
+// counts it loads at once; one scan of the threads' sums per wavefront, the wavefronts' totals through LDS.  The runs
+// replace 64 requests per pass on one wavefront, each pass a load, a chain of LDS permutes and a carry behind the pass
+// before: a save of 512 requests of 1..4 blocks (8 KiB blocks, 42 MB of traffic) took 18.2 us that way and takes 10.6.
+// All workgroups scan all requests, so the instructions count too: a workgroup that only moves blocks (EXACT = false)
+// carries two 32-bit sums, blocks and padding bytes, from which the staging offset follows (2 * (blocks * block_bytes
+// + padding)).  The block sums of the staged mode saturate, which is as good as exact: every offset that is used lies
+// within table_len, and the host keeps 2 * table_len within 32 bits.  The others (align > 1 MiB, where the padding of
+// 2048 requests may need more bits, the entry writers and the publishing workgroup) carry 64-bit sums and the chunks.
+template <int WG, bool EXACT, bool SAT>
+__device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t *__restrict__ n_blocks, uint32_t n_req,
+                                                ReqLds l, tutti_extent *__restrict__ ext_out,
+                                                uint64_t *__restrict__ totals_out, uint32_t table_len,
+                                                uint32_t *__restrict__ status, const uint32_t *__restrict__ file_id,
+                                                const FileArgs files) {
+  typedef typename std::conditional<EXACT, uint64_t, uint32_t>::type S;
+  constexpr uint32_t kPer = TUTTI_MAX_REQ / WG, kWaves = WG / kWave;
+  static_assert(3 * kWaves <= kWave, "the wavefronts' totals fit the staging-offset slots of 65 requests");
+  const uint32_t lane = threadIdx.x & (kWave - 1), wave = rfl(threadIdx.x / kWave);
+  const uint32_t per = (n_req + WG - 1) / WG, r0 = threadIdx.x * per;
+  S blocks = 0, pads = 0, chunks = 0;
+  {
+    uint32_t n[kPer];  // all loads in flight together; the loops below read the counts again (from the L1 cache), which
+                       // keeps these registers free for the bytes that a restore has in flight meanwhile
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) n[k] = (k < per && r0 + k < n_req) ? n_blocks[r0 + k] : 0u;
+#pragma unroll
+    for (uint32_t k = 0; k < kPer; ++k) {
+      blocks = add_<SAT>(blocks, static_cast<S>(n[k]));
+      pads += obj_pad(g, n[k]);
+    }
+  }
+  if (EXACT) {
+#pragma unroll 1
+    for (uint32_t k = 0; k < per && r0 + k < n_req; ++k) {
+      const uint32_t n = n_blocks[r0 + k];
+      chunks += obj_chunks(g, static_cast<uint64_t>(n) * g.block_bytes + obj_pad(g, n));
+    }
+  }
+  const S blocks_in = wave_scan<SAT>(blocks), pads_in = wave_scan<false>(pads);
+  const S chunks_in = EXACT ? wave_scan<false>(chunks) : 0;
+  uint64_t *part = l.stage_off;  // the slots are written behind the second barrier
+  if (lane == kWave - 1) {
+    part[wave] = blocks_in;
+    part[kWaves + wave] = pads_in;
+    if (EXACT) part[2 * kWaves + wave] = chunks_in;
+  }
+  __syncthreads();
+  // sums in front of this thread's run: of the lanes before it (a scan result moved on by one lane, because a saturated
+  // sum cannot be subtracted from) and of the wavefronts before it
+  S t = dpp_or_0<0x138, 0xf>(blocks_in), t_all = 0;  // wave_shr:1
+  S p = pads_in - pads, p_all = 0, c = chunks_in - chunks, c_all = 0;
+#pragma unroll
+  for (uint32_t w = 0; w < kWaves; ++w) {
+    const S pt = static_cast<S>(part[w]), pp = static_cast<S>(part[kWaves + w]);
+    const S pc = EXACT ? static_cast<S>(part[2 * kWaves + w]) : 0;
+    t_all = add_<SAT>(t_all, pt);
+    p_all += pp;
+    c_all += pc;
+    if (w < wave) {
+      t = add_<SAT>(t, pt);
+      p += pp;
+      c += pc;
+    }
+  }
+  __syncthreads();
+  const bool cut = !file_id && t_all > table_len;  // the same in every thread
+  uint32_t cut_total = 0;
+  if (cut) {
+    S x = t;
+#pragma unroll 1
+    for (uint32_t k = 0; k < per && r0 + k < n_req; ++k) {  // exactly one request starts within the table and ends beyond it
+      const S next = add_<SAT>(x, static_cast<S>(n_blocks[r0 + k]));
+      if (x <= table_len && next > table_len) l.table_off[n_req] = static_cast<uint32_t>(x);
+      x = next;
+    }
+    __syncthreads();
+    cut_total = l.table_off[n_req];
+  }
+#pragma unroll 1
+  for (uint32_t k = 0; k < per && r0 + k < n_req; ++k) {
+    const uint32_t r = r0 + k, n = n_blocks[r];
+    const uint32_t pad = obj_pad(g, n);
+    const uint64_t obj = static_cast<uint64_t>(n) * g.block_bytes + pad;
+    const uint64_t stage_off = 2 * (static_cast<uint64_t>(t) * g.block_bytes + p);
+    const S next = add_<SAT>(t, static_cast<S>(n));
+    l.stage_off[r] = stage_slot(stage_off, file_id, file_id ? file_id[r] : 0u, files);
+    l.obj_bytes[r] = obj;
+    l.table_off[r] = cut && next > table_len ? cut_total : static_cast<uint32_t>(t);
+    if (EXACT) {
+      const uint64_t n_chunks = obj_chunks(g, obj);
+      const uint32_t sqe_base = static_cast<uint32_t>(2 * c);
       l.sqe_base[r] = sqe_base;
       if (ext_out) {
         tutti_extent e;
         e.stage_off = stage_off;
         e.obj_bytes = obj;
         e.n_blocks = n;
-        e.n_chunks = static_cast<uint32_t>(chunks);
+        e.n_chunks = static_cast<uint32_t>(n_chunks);
         e.sqe_base = sqe_base;
-        e.table_off = table_off;
+        e.table_off = static_cast<uint32_t>(t);
         ext_out[r] = e;
       }
+      c += n_chunks;
     }
-    carry_stage += shfl_u64(inc_stage, active - 1);  // the pass total sits in its last active lane
-    carry_sqe += shfl_u64(inc_sqe, active - 1);
-    carry_tab += shfl_u64(inc_tab, active - 1);
+    t = next;
+    p += pad;
   }
-  if (lane == 0) {
-    l.table_off[n_req] = cut_found ? cut_total : static_cast<uint32_t>(carry_tab);
-    l.sqe_base[n_req] = static_cast<uint32_t>(carry_sqe);
-    if (totals_out) {
-      totals_out[0] = carry_stage;
-      totals_out[1] = carry_sqe;
+  if (threadIdx.x == 0) {
+    if (!cut) l.table_off[n_req] = static_cast<uint32_t>(t_all);
+    if (EXACT) {
+      l.sqe_base[n_req] = static_cast<uint32_t>(2 * c_all);
+      if (totals_out) {
+        totals_out[0] = 2 * (static_cast<uint64_t>(t_all) * g.block_bytes + p_all);
+        totals_out[1] = 2 * c_all;
+        if (cut && status) atomicOr(status, TUTTI_ST_BAD_EXTENT);
+      }
     }
-    if (cut_found && totals_out && status) atomicOr(status, TUTTI_ST_BAD_EXTENT);
   }
+}
+
+// with_chunks: the workgroup writes entries or publishes (ext_out, totals_out): it needs the chunk counts as well.
+// `preload` is called in front of the scan, so that a first slice's loads are in flight meanwhile; not where more than
+// 64 requests are scanned in 64-bit sums, which leaves no registers for them (a few workgroups of a launch).
+template <int WG, typename P>
+__device__ __forceinline__ void scan_extents(const ScanGeom g, const uint32_t *__restrict__ n_blocks, uint32_t n_req,
+                                             ReqLds l, tutti_extent *__restrict__ ext_out,
+                                             uint64_t *__restrict__ totals_out, uint32_t table_len,
+                                             uint32_t *__restrict__ status, bool with_chunks,
+                                             const uint32_t *__restrict__ file_id, const FileArgs files, P preload) {
+  if (n_req > kWave && (with_chunks || g.align > (1u << 20))) {
+    wg_scan_extents<WG, true, false>(g, n_blocks, n_req, l, ext_out, totals_out, table_len, status, file_id, files);
+  } else {
+    preload();
+    if (n_req <= kWave) {
+      if (threadIdx.x < kWave)
+        wave_scan_extents(g, n_blocks, n_req, threadIdx.x, l, ext_out, totals_out, table_len, status, with_chunks,
+                          file_id, files);
+    } else if (file_id) {
+      wg_scan_extents<WG, false, false>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, file_id, files);
+    } else {
+      wg_scan_extents<WG, false, true>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, nullptr, files);
+    }
+  }
+  __syncthreads();
 }
 
 // Per-request offsets for the entry builders, from extents the caller already has (workgroup-wide, with
@@ -275,14 +452,6 @@ __device__ __forceinline__ bool lds_from_extents(const tutti_extent *__restrict_
   return !any_bad;
 }
 
-__device__ __forceinline__ uint64_t wave_inclusive_scan(uint64_t a, uint32_t lane, uint32_t active) {
-  for (uint32_t d = 1; d < active; d <<= 1) {
-    const uint64_t t = shfl_up_u64(a, d);
-    if (lane >= d) a += t;
-  }
-  return a;
-}
-
 // Per-request offsets for the copy kernels, from extents the caller hands in: every field is honoured as it
 // stands (a gap between requests, any order in the staging buffer, a table range that does not start at 0), and
 // what cannot be honoured is taken out here, once, so that the copy loop never sees it:
@@ -314,7 +483,7 @@ __device__ __forceinline__ void lds_from_caller_extents(const tutti_extent *__re
       const uint32_t r = base + lane;
       const uint32_t active = n_req - base < kWave ? n_req - base : kWave;
       const uint32_t n = r < n_req ? l.blk_off[r] : 0u;
-      const uint64_t incl = carry + wave_inclusive_scan(n, lane, active);
+      const uint64_t incl = carry + wave_scan<false>(static_cast<uint64_t>(n));
       const bool beyond = r < n_req && incl > table_len;
       const uint64_t beyond_mask = __ballot(beyond);
       if (!cut_found && beyond_mask != 0) {
@@ -1344,10 +1513,11 @@ struct LayoutArgs {
   uint32_t n_req;
 };
 
-__global__ __launch_bounds__(kWave) void k_layout(const LayoutArgs a) {
+__global__ __launch_bounds__(kWgThreads) void k_layout(const LayoutArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, a.n_req);
-  wave_scan_extents(a.geom, a.n_blocks, a.n_req, threadIdx.x, l, a.extents, a.totals, 0xffffffffu, nullptr);
+  scan_extents<kWgThreads>(a.geom, a.n_blocks, a.n_req, l, a.extents, a.totals, 0xffffffffu, nullptr, true, nullptr,
+                           FileArgs{0, 0, 0}, [] {});
 }
 
 template <int WG>
@@ -1406,13 +1576,11 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
   const bool copies = wg < w.copy_wgs;
   Preload<U> pre;
   pre.valid = false;
-  if (DIR == kUnpack && !ORD && copies) pre = preload_first<U, NT>(m, wg, w.copy_wgs);  // in flight during the scan
-  if (threadIdx.x < kWave) {
-    const bool publish = blockIdx.x == 0;
-    wave_scan_extents(a.geom, a.n_blocks, a.n_req, threadIdx.x, l, publish ? a.extents : nullptr,
-                      publish ? a.totals : nullptr, m.table_len, m.status, blockIdx.x < w.sqe_wgs);
-  }
-  __syncthreads();
+  const bool publish = blockIdx.x == 0;  // also an entry-writing workgroup: there is at least one
+  scan_extents<WG>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
+                   m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [&] {
+                     if (DIR == kUnpack && !ORD && copies) pre = preload_first<U, NT>(m, wg, w.copy_wgs);
+                   });
   SqeHead head;
   head.live = false;
   if (blockIdx.x < w.sqe_wgs) head = sqe_head(q, l, a.n_req, 0);
@@ -1484,15 +1652,13 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
   const bool copies = bx - w.copy_first < w.copy_wgs;
   Preload<U> pre;
   pre.valid = false;
-  if (DIR == kUnpack && copies && a.n_req == 1)
-    pre = preload_first_direct<U>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
-  if (threadIdx.x < kWave) {
-    const bool publish = bx == 0;
-    // chunk counts only matter for the published extents; the LDS copy gets file starts instead of staging offsets
-    wave_scan_extents(a.geom, a.n_blocks, a.n_req, threadIdx.x, l, publish ? a.extents : nullptr,
-                      publish ? a.totals : nullptr, 0xffffffffu, nullptr, publish, q.file_id, f);
-  }
-  __syncthreads();
+  const bool publish = bx == 0;
+  // chunk counts only matter for the published extents; the LDS copy gets file starts instead of staging offsets
+  scan_extents<WG>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
+                   0xffffffffu, nullptr, publish, q.file_id, f, [&] {
+                     if (DIR == kUnpack && copies && a.n_req == 1)
+                       pre = preload_first_direct<U>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
+                   });
   DirectHead head;
   head.live = false;
   if (bx < w.sqe_wgs) head = iocb_head(g, q, d, l, a.n_req, lead, w.sqe_wgs);
@@ -1504,12 +1670,9 @@ template <int DIR, int PT, int WG>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, PT)) void k_layer_lds(const MoveArgs m, const SqeArgs q, const LayoutArgs a, const Roles w) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, a.n_req);
-  if (threadIdx.x < kWave) {
-    const bool publish = blockIdx.x == 0;
-    wave_scan_extents(a.geom, a.n_blocks, a.n_req, threadIdx.x, l, publish ? a.extents : nullptr,
-                      publish ? a.totals : nullptr, m.table_len, m.status, blockIdx.x < w.sqe_wgs);
-  }
-  __syncthreads();
+  const bool publish = blockIdx.x == 0;  // also an entry-writing workgroup: there is at least one
+  scan_extents<WG>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
+                   m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [] {});
   SqeHead head;
   head.live = false;
   if (blockIdx.x < w.sqe_wgs) head = sqe_head(q, l, a.n_req, 0);

@@ -951,6 +951,70 @@ def test_max_requests(orc, H):
     H.check_everything(orc, c)
 
 
+@pytest.mark.parametrize("n_req", [64, 65, 255, 256, 257, 512, 513, 1024, 1025, 2047])
+def test_scan_of_many_requests(orc, H, n_req):
+    """The workgroup-wide scan of the fused kernels: request counts on both sides of a wavefront, of a workgroup and of
+    a thread's run; blocks that are whole alignment units and blocks that are not; the table cut in the middle."""
+    say("scan of", n_req, "requests")
+    rng = np.random.default_rng(8000 + n_req)
+    n = rng.integers(0, 4, size=n_req).astype(np.uint32)
+    n[-1] = 2
+    total = int(n.sum())
+    N = total + 5
+    table = rng.permutation(N)[:total]
+    for d, align, chunk in ((64, 4096, 4096), (40, 4096, 8192), (8, 16, 16)):
+        c = H.LayerCase(T=16, h=2, d=d, e=2, N=N, n_blocks=n, table=table, align=align, chunk=chunk, L=2,
+                        name=f"scan{n_req}d{d}")
+        for tl in (None, total - 1, total // 2, 0):
+            H.check_layer_restore(orc, c, layer=1, table_len=tl)
+            H.check_layer_save(orc, c, layer=1, table_len=tl)
+        H.check_layer_restore(orc, c, layer=1, cu_budget=3)
+        H.check_layout(orc, c)
+    n_slots = (2 * total + B.IOCB_SLOTS - 1) // B.IOCB_SLOTS
+    H.check_ring_layer(orc, c, layer=1, write=False, depth=n_slots, first_slot=0, n_slots=n_slots)
+
+
+def test_scan_of_many_requests_wide_sums(orc, H):
+    """Alignment units above 1 MiB (the padding is then summed in 64 bits), and block counts whose sum passes 2^32:
+    the requests in front of the one that runs beyond the table are restored, the published extents are plain sums."""
+    say("scan: wide sums")
+    rng = np.random.default_rng(8100)
+    n = (rng.integers(0, 8, size=70) == 0).astype(np.uint32)
+    n[[0, 69]] = 1
+    total = int(n.sum())
+    c = H.LayerCase(T=16, h=2, d=64, e=2, N=90, n_blocks=n, table=rng.permutation(90)[:total], align=2 << 20, chunk=2 << 20,
+                    name="scan_wide_align")
+    H.check_layer_restore(orc, c)
+    H.check_layer_save(orc, c)
+
+    for n_req, big in ((40, 30), (70, 50), (300, 299), (2048, 64)):
+        n = np.ones(n_req, np.uint32)
+        n[big] = n[big - 2] = 0xfffffff0
+        live = big - 2
+        c = H.LayerCase(T=1, h=1, d=8, e=2, N=400, n_blocks=n, table=rng.permutation(400)[:400], align=16, chunk=1 << 30,
+                        name=f"scan_wide_{n_req}")
+        nbytes = 32 * n_req
+        stage = torch.randint(0, 256, (nbytes,), dtype=torch.uint8, device=H.DEV)
+        k2, v2 = c.k_dev.clone(), c.v_dev.clone()
+        ext = torch.zeros(32 * n_req, dtype=torch.uint8, device=H.DEV)
+        tot = torch.zeros(2, dtype=torch.int64, device=H.DEV)
+        sqe = torch.zeros(64 * 16, dtype=torch.uint8, device=H.DEV)
+        st = H.new_status()
+        B.tutti_layer_restore(c.gpu_pool(k2, v2), c.gpu_cfg(), c.d_n_blocks, n_req, c.d_table, 400, c.d_file_id, 0, stage,
+                              nbytes, 0, 1, ext, tot, sqe, 16, 0, st)
+        torch.cuda.synchronize()
+        ok, ov = c.k_host.copy(), c.v_host.copy()
+        host = stage.cpu().numpy()
+        ids = c.table[:live].astype(np.int64)
+        ok.reshape(-1, 16)[ids] = host.reshape(-1, 2, 16)[:live, 0]
+        ov.reshape(-1, 16)[ids] = host.reshape(-1, 2, 16)[:live, 1]
+        assert np.array_equal(k2.cpu().numpy(), ok) and np.array_equal(v2.cpu().numpy(), ov)
+        o_ext, o_tot = orc.obj_layout(c.orc_pool(orc), c.orc_cfg(orc), n)
+        assert ext.cpu().numpy().tobytes() == o_ext.tobytes()
+        assert np.array_equal(tot.cpu().numpy().view(np.uint64), o_tot)
+        assert int(st.item()) == B.ST_BAD_EXTENT | B.ST_SQE_CAP
+
+
 def test_bad_block_ids_are_skipped_and_reported(orc, H):
     say("edge: bad block ids")
     table = np.array([3, 999, 5, 16, 7, 1], np.uint32)   # 999 and 16 are out of range for 16 blocks
