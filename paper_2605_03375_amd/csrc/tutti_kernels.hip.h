@@ -238,8 +238,9 @@ __device__ __forceinline__ void wave_scan_extents(const ScanGeom g, const uint32
 // All workgroups scan all requests, so the instructions count too: a workgroup that only moves blocks (EXACT = false)
 // carries two 32-bit sums, blocks and padding bytes, from which the staging offset follows (2 * (blocks * block_bytes
 // + padding)).  The block sums of the staged mode saturate, which is as good as exact: every offset that is used lies
-// within table_len, and the host keeps 2 * table_len within 32 bits.  The others (align > 1 MiB, where the padding of
-// 2048 requests may need more bits, the entry writers and the publishing workgroup) carry 64-bit sums and the chunks.
+// within table_len, and the host keeps 2 * table_len within 32 bits.  The others (the entry writers and the publishing
+// workgroup; align > 1 MiB, where the padding of 2048 requests may need more bits; the direct-to-block mode, whose
+// offsets wrap) carry 64-bit sums and the chunks.
 template <int WG, bool EXACT, bool SAT>
 __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t *__restrict__ n_blocks, uint32_t n_req,
                                                 ReqLds l, tutti_extent *__restrict__ ext_out,
@@ -361,7 +362,7 @@ __device__ __forceinline__ void scan_extents(const ScanGeom g, const uint32_t *_
                                              uint64_t *__restrict__ totals_out, uint32_t table_len,
                                              uint32_t *__restrict__ status, bool with_chunks,
                                              const uint32_t *__restrict__ file_id, const FileArgs files, P preload) {
-  if (n_req > kWave && (with_chunks || g.align > (1u << 20))) {
+  if (n_req > kWave && (with_chunks || file_id || g.align > (1u << 20))) {
     wg_scan_extents<WG, true, false>(g, n_blocks, n_req, l, ext_out, totals_out, table_len, status, file_id, files);
   } else {
     preload();
@@ -369,8 +370,6 @@ __device__ __forceinline__ void scan_extents(const ScanGeom g, const uint32_t *_
       if (threadIdx.x < kWave)
         wave_scan_extents(g, n_blocks, n_req, threadIdx.x, l, ext_out, totals_out, table_len, status, with_chunks,
                           file_id, files);
-    } else if (file_id) {
-      wg_scan_extents<WG, false, false>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, file_id, files);
     } else {
       wg_scan_extents<WG, false, true>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, nullptr, files);
     }
