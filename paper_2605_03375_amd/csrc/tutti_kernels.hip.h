@@ -1068,7 +1068,13 @@ __global__ __launch_bounds__(WG) void k_sqe_direct(const SqeArgs a, const Direct
 // on both sides).  Items are numbered in staging-buffer order (request, K then V, block, slice),
 // so neighbouring wavefronts stream neighbouring object bytes while the pool side jumps from
 // block to block as the table says.
+// Blocks that are no whole number of slices are cut into pieces instead: 1 KiB, what one wavefront instruction covers
+// (the last of a block may be shorter), and an item is U consecutive pieces, which may belong to different blocks.
+// A block of 12.5 KiB is 13 pieces instead of four slices of which the last moves 512 of its 4096 bytes; four blocks
+// of 1 KiB are one item instead of four.
 // ------------------------------------------------------------------------------------------
+constexpr uint32_t kPiece = kWave * 16u;
+
 struct MoveArgs {
   unsigned char *k_base;
   unsigned char *v_base;
@@ -1080,7 +1086,7 @@ struct MoveArgs {
   uint32_t num_blocks;
   uint32_t block_bytes;
   uint32_t table_len;
-  uint32_t slices_per_block;
+  uint32_t slices_per_block;  // slices, pieces or (through LDS) tiles
   // head-major pools only: a row is the d*e bytes of one (token, head)
   uint32_t row_bytes;
   uint32_t block_tokens;
@@ -1136,8 +1142,8 @@ __device__ __forceinline__ uint32_t hnd_offset(uint32_t o, uint32_t row_bytes, u
   return (i * T + t) * row_bytes + w;
 }
 
-// Wave-uniform description of one work item: where its slice sits on the object side and which
-// block-table entry names the pool side.
+// Description of one slice, piece or tile: where it sits on the object side and which block-table entry names the pool
+// side.  Wave-uniform, except that the pieces of an item are decoded one per lane.
 struct Item {
   unsigned char *obj_ptr;  // start of the (request, kind) object; nullptr = skip the item
   unsigned char *obj_blk;  // where block j of it sits on the object side
@@ -1157,13 +1163,14 @@ typedef const __attribute__((address_space(4))) uint32_t *const_u32_ptr;
 // indexed by the request's own table_off, and requests that cannot be honoured already have a zero-sized object.
 // ORD: the units are visited in the order a.visit lists (all K blocks, then all V blocks, each in that order);
 // a listed position that is not a block of a request that takes part is passed over.
+// u: (block, kind) unit in staging order; s: its slice, piece or tile; `report`: this thread reports what it finds out
+// of order with a unit's first part.
 template <bool SEP, bool ORD = false>
-__device__ __forceinline__ Item decode_item(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t it,
-                                            uint32_t lane) {
+__device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t u, uint32_t s,
+                                            bool report) {
   Item d;
-  const uint32_t S = a.slices_per_block;
-  const uint32_t u = it / S;  // (block, kind) unit in staging order
-  d.s = it - u * S;
+  d.s = s;
+  report = report && s == 0 && a.status != nullptr;
   const uint32_t *off = SEP ? l.blk_off : l.table_off;
   uint32_t r, toff;
   if (ORD) {
@@ -1204,7 +1211,7 @@ __device__ __forceinline__ Item decode_item(const MoveArgs &a, const ReqLds &l, 
     if (u >= a.ctx_cap) {
       d.obj_ptr = nullptr;  // beyond the IOCBs the caller gave: not recorded, not executed
     } else if (stage_off == kNoFile || end > a.file_stride || end < file_off) {
-      if (lane == 0 && d.s == 0 && a.status) atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
+      if (report) atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
       d.obj_ptr = nullptr;
     }
     return d;
@@ -1214,12 +1221,19 @@ __device__ __forceinline__ Item decode_item(const MoveArgs &a, const ReqLds &l, 
   if (!SEP && (stage_off > a.stage_cap || d.obj_bytes > (a.stage_cap - stage_off) / 2)) {
     // the request's objects do not fit: skip it, report once
     // (an ordered launch reports from its first workgroup instead: its list need not name the request's first block)
-    if (!ORD && lane == 0 && d.j == 0 && d.s == 0 && d.kind == 0 && a.status) atomicOr(a.status, TUTTI_ST_STAGE_CAP);
+    if (!ORD && report && d.j == 0 && d.kind == 0) atomicOr(a.status, TUTTI_ST_STAGE_CAP);
     d.obj_ptr = nullptr;
   } else if ((static_cast<uint64_t>(d.j) + 1) * a.block_bytes > d.obj_bytes) {
     d.obj_ptr = nullptr;  // the block would end beyond its object (caller-made extents only)
   }
   return d;
+}
+
+template <bool SEP, bool ORD = false>
+__device__ __forceinline__ Item decode_item(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t it,
+                                            uint32_t lane) {
+  const uint32_t u = it / a.slices_per_block;
+  return decode_unit<SEP, ORD>(a, l, n_req, u, it - u * a.slices_per_block, lane == 0);
 }
 
 // Block id of an item through the scalar (constant) path: the index is wave-uniform, so this is
@@ -1334,17 +1348,17 @@ __device__ __forceinline__ void store_preloaded(const MoveArgs &a, const Item &d
 // grid may hold other workgroups with other work).
 // Software-pipelined by one item: the next item is decoded and its block id requested before the
 // current item's loads and stores are issued.
-// Number of work items of a copy.  Staged mode: the scan (or the loader of caller-made extents) has already cut
+// Number of (block, kind) units of a copy.  Staged mode: the scan (or the loader of caller-made extents) has already cut
 // the requests at table_len blocks.  Direct-to-block mode: one unit per recorded context.  The host checked that
 // the bound (2 * table_len, or the contexts the IOCBs hold) times the slices per block fits 32 bits.
 template <bool SEP, bool ORD = false>
-__device__ __forceinline__ uint32_t count_items(const MoveArgs &a, const ReqLds &l, uint32_t n_req) {
-  if (ORD) return 2u * a.table_len * a.slices_per_block;  // every listed position, for K and for V
+__device__ __forceinline__ uint32_t count_units(const MoveArgs &a, const ReqLds &l, uint32_t n_req) {
+  if (ORD) return 2u * a.table_len;  // every listed position, for K and for V
   if (a.direct) {
     const uint64_t units = 2ull * l.table_off[n_req];
-    return static_cast<uint32_t>(units < a.ctx_cap ? units : a.ctx_cap) * a.slices_per_block;
+    return static_cast<uint32_t>(units < a.ctx_cap ? units : a.ctx_cap);
   }
-  return 2u * (SEP ? l.blk_off[n_req] : l.table_off[n_req]) * a.slices_per_block;
+  return 2u * (SEP ? l.blk_off[n_req] : l.table_off[n_req]);
 }
 
 template <int DIR, bool HND, int U, int NT, bool SEP, bool ORD = false>
@@ -1354,7 +1368,7 @@ __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uin
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t wave_in_wg = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t n_waves = copy_wgs * (blockDim.x / kWave);
-  const uint32_t n_items = count_items<SEP, ORD>(a, l, n_req);
+  const uint32_t n_items = count_units<SEP, ORD>(a, l, n_req) * a.slices_per_block;
 
   uint32_t it = item_wg(a, wg, copy_wgs) * (blockDim.x / kWave) + wave_in_wg;
   if (it >= n_items) return;
@@ -1385,6 +1399,120 @@ __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uin
     cur = nxt;
     id = nid;
     it = nit;
+  }
+}
+
+constexpr int kWaitVmcnt0 = 0x0f70;  // operand of s_waitcnt: vector accesses done, the other counters as they are
+
+// The value that lane `src` holds, in scalar registers.
+__device__ __forceinline__ uint32_t readlane_u32(uint32_t v, uint32_t src) {
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>(src)));
+}
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, uint32_t src) {
+  const uint32_t lo = readlane_u32(static_cast<uint32_t>(v), src);
+  return (static_cast<uint64_t>(readlane_u32(static_cast<uint32_t>(v >> 32), src)) << 32) | lo;
+}
+typedef __attribute__((address_space(1))) unsigned char *global_u8_ptr;
+__device__ __forceinline__ unsigned char *as_global(uint64_t address) {
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wold-style-cast"
+  return (unsigned char *)(global_u8_ptr)address;  // a global pointer, so that the accesses are global ones
+#pragma clang diagnostic pop
+}
+
+// The copy loop for blocks that are no whole number of slices.  A wavefront decodes its next 64 pieces at once, one per
+// lane (owner by binary search, block id, both addresses), so that the table loads of 64/U items are in flight together
+// and an item costs a few lane reads; then it moves them item by item.
+template <int DIR, bool HND, int U, int NT, bool SEP>
+__device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
+                                            uint32_t copy_wgs) {
+  constexpr uint32_t kBatch = kWave / U;  // items decoded at once
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t n_waves = copy_wgs * (blockDim.x / kWave);
+  const uint32_t ppb = a.slices_per_block;
+  const uint64_t n_pieces = static_cast<uint64_t>(count_units<SEP>(a, l, n_req)) * ppb;
+  const uint32_t n_items = static_cast<uint32_t>((n_pieces + U - 1) / U);
+  const uint32_t in_piece = lane * 16u;
+
+  for (uint64_t it = item_wg(a, wg, copy_wgs) * (blockDim.x / kWave) + rfl(threadIdx.x / kWave); it < n_items;
+       it += kBatch * static_cast<uint64_t>(n_waves)) {
+    // ---- decode: lane -> piece lane % U of item it + (lane / U) * n_waves
+    uint64_t obj = 0, blk = 0;        // where the piece sits on the two sides (head-major: blk = its block)
+    uint32_t off = 0, len = 0;        // its offset in the block, its bytes (0: skip it)
+    uint64_t tail = 0, tail_at = 0;   // pack: padding behind it
+    const uint64_t mine = it + static_cast<uint64_t>(lane / U) * n_waves;
+    if (mine * U + lane % U < n_pieces) {
+      // unit = piece / ppb without a 64-bit division: item = q * ppb + rem, piece = q * ppb * U + (rem * U + lane % U)
+      const uint32_t q = static_cast<uint32_t>(mine) / ppb;
+      const uint32_t rest = (static_cast<uint32_t>(mine) - q * ppb) * U + lane % U;
+      const uint32_t q2 = rest / ppb;
+      const Item d = decode_unit<SEP>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
+      if (d.obj_ptr != nullptr) {
+        const uint32_t id = d.tab_idx < a.table_len ? a.table[d.tab_idx] : a.num_blocks;
+        off = d.s * kPiece;
+        const uint32_t bytes = a.block_bytes - off < kPiece ? a.block_bytes - off : kPiece;
+        obj = reinterpret_cast<uint64_t>(d.obj_blk) + off;
+        if (DIR == kPack && !a.direct && d.j + 1 == d.n && d.s + 1 == ppb) {
+          tail = d.obj_bytes - static_cast<uint64_t>(d.n) * a.block_bytes;
+          tail_at = obj + bytes;
+        }
+        if (id < a.num_blocks) {
+          len = bytes;
+          blk = reinterpret_cast<uint64_t>(d.kind ? a.v_base : a.k_base) + static_cast<uint64_t>(id) * a.block_stride +
+                (HND ? 0u : off);
+        } else if (d.s == 0 && a.status) {
+          atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
+        }
+      }
+    }
+    if (DIR == kPack) {  // zero the objects' tails up to their aligned sizes (fewer than `align` bytes each)
+      for (uint64_t m = __ballot(tail != 0); m != 0; m &= m - 1) {
+        const uint32_t src = static_cast<uint32_t>(__ffsll(static_cast<long long>(m))) - 1u;
+        const uint64_t n = readlane_u64(tail, src);
+        unsigned char *end = as_global(readlane_u64(tail_at, src));
+        const u32x4 zero = {0u, 0u, 0u, 0u};
+        for (uint64_t o = in_piece; o < n; o += kPiece) st16<0>(end + o, zero);
+      }
+    }
+    const uint64_t whole = __ballot(len == kPiece);
+    // ---- move
+    const uint64_t left = (n_items - it + n_waves - 1) / n_waves;
+    for (uint32_t i = 0; i < kBatch && i < left; ++i) {
+      unsigned char *src[U], *dst[U];
+#pragma unroll
+      for (uint32_t k = 0; k < U; ++k) {
+        unsigned char *o = as_global(readlane_u64(obj, i * U + k)) + in_piece;
+        unsigned char *b = as_global(readlane_u64(blk, i * U + k));
+        b += HND ? hnd_offset(readlane_u32(off, i * U + k) + in_piece, a.row_bytes, a.block_tokens, a.num_kv_heads)
+                 : in_piece;
+        src[k] = DIR == kPack ? b : o;
+        dst[k] = DIR == kPack ? o : b;
+      }
+      u32x4 buf[U];
+      constexpr uint64_t kAll = (1ull << U) - 1;
+      if ((whole >> (i * U) & kAll) == kAll) {
+#pragma unroll
+        for (uint32_t k = 0; k < U; ++k) buf[k] = ld16<NT>(src[k]);
+#pragma unroll
+        for (uint32_t k = 0; k < U; ++k) st16<NT>(dst[k], buf[k]);
+        asm volatile("; whole item");  // (the marks keep the compiler from merging the paths' last stores, which
+                                       // would put a wait for all other stores in front of the merged one)
+      } else {  // a piece is short (the last of its block) or skipped
+        uint32_t n[U];
+#pragma unroll
+        for (uint32_t k = 0; k < U; ++k) {
+          n[k] = readlane_u32(len, i * U + k);
+          if (in_piece < n[k]) buf[k] = ld16<NT>(src[k]);
+        }
+        // one wait for all loads: left to itself the compiler waits in front of each guarded store, and with that
+        // for the stores before it (loads and stores share a counter)
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+#pragma unroll
+        for (uint32_t k = 0; k < U; ++k)
+          if (in_piece < n[k]) st16<NT>(dst[k], buf[k]);
+        asm volatile("; guarded item");
+      }
+    }
   }
 }
 
@@ -1472,7 +1600,7 @@ __device__ __forceinline__ void move_items_hnd_lds(const MoveArgs a, const ReqLd
                                                    uint32_t copy_wgs, unsigned char *tile) {
   typedef TileMove<DIR, PT, WG> TM;
   const uint32_t tid = threadIdx.x;
-  const uint32_t n_items = count_items<SEP>(a, l, n_req);
+  const uint32_t n_items = count_units<SEP>(a, l, n_req) * a.slices_per_block;
   TileGeom g;
   g.rs = a.row_shift;
   g.gs = a.row_shift + a.head_shift;
@@ -1528,16 +1656,20 @@ __global__ __launch_bounds__(WG) void k_sqe(const SqeArgs a, const ScanGeom g,
   emit_sqes(a, l, n_req, 0, gridDim.x, sqe_head(a, l, n_req, 0));
 }
 
-template <int DIR, bool HND, int U, int NT, int WG>
+// PIECES: the blocks are no whole number of slices (here and below).
+template <int DIR, bool HND, int U, int NT, int WG, bool PIECES = false>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_move(const MoveArgs a, const tutti_extent *__restrict__ ext,
                                                       uint32_t n_req) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, n_req, true);
   Preload<U> pre;
   pre.valid = false;
-  if (DIR == kUnpack) pre = preload_first<U, NT>(a, blockIdx.x, gridDim.x);
+  if (DIR == kUnpack && !PIECES) pre = preload_first<U, NT>(a, blockIdx.x, gridDim.x);
   lds_from_caller_extents(ext, n_req, l, a.table_len, a.block_bytes, a.stage_cap, a.status);
-  move_items<DIR, HND, U, NT, true>(a, l, n_req, blockIdx.x, gridDim.x, pre);
+  if (PIECES)
+    move_pieces<DIR, HND, U, NT, true>(a, l, n_req, blockIdx.x, gridDim.x);
+  else
+    move_items<DIR, HND, U, NT, true>(a, l, n_req, blockIdx.x, gridDim.x, pre);
 }
 
 template <int DIR, int PT, int WG>
@@ -1567,7 +1699,7 @@ struct Roles {
 
 // ORD (restore only): the blocks are visited in the order m.visit lists instead of staging order; the first slices
 // cannot be preloaded then (where they sit depends on the list).
-template <int DIR, bool HND, int U, int NT, int WG, bool ORD = false>
+template <int DIR, bool HND, int U, int NT, int WG, bool ORD = false, bool PIECES = false>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const MoveArgs m, const SqeArgs q, const LayoutArgs a, const Roles w) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, a.n_req);
@@ -1578,7 +1710,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
   const bool publish = blockIdx.x == 0;  // also an entry-writing workgroup: there is at least one
   scan_extents<WG>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
                    m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [&] {
-                     if (DIR == kUnpack && !ORD && copies) pre = preload_first<U, NT>(m, wg, w.copy_wgs);
+                     if (DIR == kUnpack && !ORD && !PIECES && copies) pre = preload_first<U, NT>(m, wg, w.copy_wgs);
                    });
   SqeHead head;
   head.live = false;
@@ -1590,7 +1722,12 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
           (l.stage_off[r] > m.stage_cap || l.obj_bytes[r] > (m.stage_cap - l.stage_off[r]) / 2))
         atomicOr(m.status, TUTTI_ST_STAGE_CAP);
   }
-  if (copies) move_items<DIR, HND, U, NT, false, ORD>(m, l, a.n_req, wg, w.copy_wgs, pre);
+  if (copies) {
+    if (PIECES)
+      move_pieces<DIR, HND, U, NT, false>(m, l, a.n_req, wg, w.copy_wgs);
+    else
+      move_items<DIR, HND, U, NT, false, ORD>(m, l, a.n_req, wg, w.copy_wgs, pre);
+  }
   if (blockIdx.x < w.sqe_wgs) emit_sqes(q, l, a.n_req, 0, w.sqe_wgs, head);
 }
 
@@ -1636,7 +1773,7 @@ __device__ __forceinline__ Preload<U> preload_first_direct(const MoveArgs &m, co
 // next layer's launch carries it along (`done`: the IOCBs an earlier launch on the same stream has executed; when
 // done.n_slots is not 0 the grid has one workgroup more, in front, whose first wavefront completes them and leaves,
 // so a train of layers pays for no kernel boundary between a layer's data and the next layer's).
-template <int DIR, int U, int WG>
+template <int DIR, int U, int WG, bool PIECES = false>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(const MoveArgs m, const SqeArgs q, const DirectArgs d,
                                                     const RingArgs g, const RingArgs done, const FileArgs f,
                                                     const LayoutArgs a, const Roles w) {
@@ -1655,13 +1792,18 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
   // chunk counts only matter for the published extents; the LDS copy gets file starts instead of staging offsets
   scan_extents<WG>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
                    0xffffffffu, nullptr, publish, q.file_id, f, [&] {
-                     if (DIR == kUnpack && copies && a.n_req == 1)
+                     if (DIR == kUnpack && !PIECES && copies && a.n_req == 1)
                        pre = preload_first_direct<U>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
                    });
   DirectHead head;
   head.live = false;
   if (bx < w.sqe_wgs) head = iocb_head(g, q, d, l, a.n_req, lead, w.sqe_wgs);
-  if (copies) move_items<DIR, false, U, 3, false>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
+  if (copies) {
+    if (PIECES)
+      move_pieces<DIR, false, U, 3, false>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);
+    else
+      move_items<DIR, false, U, 3, false>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
+  }
   if (bx < w.sqe_wgs) emit_iocbs(g, q, d, l, a.n_req, lead, w.sqe_wgs, head);
 }
 

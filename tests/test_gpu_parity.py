@@ -1015,6 +1015,39 @@ def test_scan_of_many_requests_wide_sums(orc, H):
         assert int(st.item()) == B.ST_BAD_EXTENT | B.ST_SQE_CAP
 
 
+@pytest.mark.parametrize("T,h,d,e", [(1, 1, 8, 2), (9, 1, 56, 2), (16, 1, 32, 2), (5, 13, 8, 2), (16, 1, 64, 2),
+                                     (16, 1, 80, 4), (1, 3, 1360, 1), (16, 5, 80, 2), (16, 2, 130, 4)])
+def test_blocks_moved_as_pieces(orc, H, T, h, d, e):
+    """Blocks that are no whole number of 4 KiB slices (16 bytes to 16.25 KiB): short last pieces, several blocks in
+    one work item, more pieces than one decode takes, skipped ids and a cut table among them, on the whole GPU and on
+    two compute units, through the staging buffer and through the files of the rings."""
+    bb = T * h * d * e
+    say("pieces of", bb, "bytes")
+    rng = np.random.default_rng(8200 + bb)
+    n = [37, 0, 1, 260, 3]
+    total = sum(n)
+    N = total + 11
+    table = rng.permutation(N)[:total].astype(np.uint32)
+    for layout in ((0, 1) if (d * e) % 16 == 0 else (0,)):
+        c = H.LayerCase(T=T, h=h, d=d, e=e, N=N, n_blocks=n, table=table, chunk=8192, L=2, layout=layout, pad=48,
+                        name=f"pieces{bb}l{layout}")
+        H.check_everything(orc, c)
+        H.check_everything(orc, c, cu_budget=2)
+        H.check_layer_restore(orc, c, table_len=total - 5)
+        H.check_layer_save(orc, c, table_len=total - 5)
+    bad = table.copy()
+    bad[[0, 36, 38, 200, total - 1]] = [N, 0xffffffff, N + 3, N, N]
+    c = H.LayerCase(T=T, h=h, d=d, e=e, N=N, n_blocks=n, table=bad, chunk=8192, L=2, name=f"pieces{bb}bad")
+    H.check_everything(orc, c)
+    align = min(4096, bb & -bb)
+    if align >= 16:
+        c = H.LayerCase(T=T, h=h, d=d, e=e, N=N, n_blocks=n, table=table, align=align, chunk=align, L=2,
+                        name=f"pieces{bb}ring")
+        for write in (False, True):
+            H.check_ring_layer(orc, c, layer=1, write=write, depth=3, first_slot=2, n_slots=1)
+        H.check_ring_layer(orc, c, layer=0, write=False, depth=3, first_slot=0, n_slots=1, cu_budget=2)
+
+
 def test_bad_block_ids_are_skipped_and_reported(orc, H):
     say("edge: bad block ids")
     table = np.array([3, 999, 5, 16, 7, 1], np.uint32)   # 999 and 16 are out of range for 16 blocks
