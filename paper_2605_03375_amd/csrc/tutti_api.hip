@@ -36,7 +36,10 @@ thread_local int t_last_hip = 0;
 
 constexpr uint32_t kDefaultWgsPerCu = 8;     // whole-GPU launches: 8 x 256 threads = 32 wavefronts per CU
 constexpr uint32_t kDefaultUnroll = 4;       // 4 x 16 B in flight per lane: 4 KiB slices
-constexpr uint32_t kBudgetUnroll = 8;        // CU-budgeted launches keep more bytes in flight per wavefront
+// CU-budgeted launches: 16 KiB per wavefront.  What a compute unit moves depends on the length of a wavefront's run of
+// loads and of stores, not on the bytes in flight: a plain cold copy on 8 / 32 / 64 compute units (1024 threads each)
+// reaches 62 / 52 / 44 GB/s per unit with 8 KiB runs, with one item in flight as with two, and 72 / 64 / 56 with 16 KiB.
+constexpr uint32_t kBudgetUnroll = 16;
 constexpr int kMaxDevices = 64;
 
 // What an experiment may change about a launch; 0 = the library's own choice.
@@ -202,9 +205,8 @@ int plan_launch(uint32_t cu_budget, uint64_t n_wave_items, Launch *out) {
     out->pieces = false;
     out->wg_threads = kBudgetWgThreads;
     out->unroll = u ? u : kBudgetUnroll;
-    const uint64_t waves = kBudgetWgThreads / kWave;
-    uint64_t need = (n_wave_items + waves - 1) / waves;
-    if (need == 0) need = 1;
+    // an item per workgroup is enough for a workgroup: the items are dealt to the workgroups first (first_item)
+    const uint64_t need = n_wave_items ? n_wave_items : 1;
     out->grid = static_cast<uint32_t>(need < cu_budget ? need : cu_budget);
     return TUTTI_OK;
   }
@@ -229,6 +231,11 @@ uint32_t whole_gpu_wgs() {
   uint32_t per_cu = tuning().wgs_per_cu;
   if (per_cu == 0) per_cu = kDefaultWgsPerCu;
   return cus > 0 ? static_cast<uint32_t>(cus) * per_cu : 0u;
+}
+
+uint64_t counted_slices(const Launch &L, uint32_t bytes) {
+  const uint64_t slice = kPiece * (L.unroll < 8 ? L.unroll : 8u);
+  return (bytes + slice - 1) / slice;
 }
 
 // Fills the kernel arguments and settles how a head-major pool is moved (L->hnd_lds, L->unroll,
@@ -302,8 +309,9 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
     m->slices_per_block = static_cast<uint32_t>(
         L->pieces ? (static_cast<uint64_t>(block_bytes) + kPiece - 1) / kPiece : slices);
   }
-  // the kernels number work items in 32 bits (groups of pieces are no more than the slices counted here)
-  if (2ull * table_len * slices > 0xffffffffull) return TUTTI_ERANGE;
+  // the kernels number work items in 32 bits; a call is refused by its slices of at most 8 KiB, which are no fewer than
+  // the items of any launch shape
+  if (2ull * table_len * (L->hnd_lds ? slices : counted_slices(*L, block_bytes)) > 0xffffffffull) return TUTTI_ERANGE;
   m->items_bound = static_cast<uint32_t>(2u * table_len * slices);
   m->xcd_contiguous = tuning().xcd_contiguous;
   // dense staging: no padding anywhere and no ragged slice, so the staging offset of an item is item * slice
@@ -311,11 +319,11 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   return TUTTI_OK;
 }
 
-// Work items of a move, counted in wavefronts' worth for plan_launch (an LDS tile occupies a whole workgroup).
+// Work items of a move, counted as plan_launch wants them (a whole-GPU launch gives an LDS tile a whole workgroup).
 uint64_t move_wave_items(const Launch &L, const MoveArgs &m) {
   const uint64_t items = 2ull * m.table_len * m.slices_per_block;
   if (L.pieces) return (items + L.unroll - 1) / L.unroll;
-  return L.hnd_lds ? items * (L.wg_threads / kWave) : items;
+  return L.hnd_lds && L.wg_threads == kWgThreads ? items * (kWgThreads / kWave) : items;
 }
 
 template <int DIR>
@@ -405,7 +413,7 @@ hipError_t with_shape(const Launch &L, F &&f) {
 #define TUTTI_SHAPE(U, NT, WG) \
   if (L.unroll == U && L.nontemporal == NT && L.wg_threads == WG) return f(Shape<U, NT, WG>{});
   TUTTI_SHAPE(4, 3, kWgThreads)
-  TUTTI_SHAPE(8, 3, kBudgetWgThreads)
+  TUTTI_SHAPE(16, 3, kBudgetWgThreads)
 #ifdef TUTTI_BENCH_BUILD
 #define TUTTI_SHAPES_NT(U, WG) TUTTI_SHAPE(U, 0, WG) TUTTI_SHAPE(U, 1, WG) TUTTI_SHAPE(U, 2, WG) TUTTI_SHAPE(U, 3, WG)
   TUTTI_SHAPES_NT(1, kWgThreads)
@@ -416,6 +424,7 @@ hipError_t with_shape(const Launch &L, F &&f) {
   TUTTI_SHAPES_NT(2, kBudgetWgThreads)
   TUTTI_SHAPES_NT(4, kBudgetWgThreads)
   TUTTI_SHAPES_NT(8, kBudgetWgThreads)
+  TUTTI_SHAPES_NT(16, kBudgetWgThreads)
 #undef TUTTI_SHAPES_NT
 #endif
 #undef TUTTI_SHAPE
@@ -805,7 +814,7 @@ int issue_io_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slots
   Launch L;
   rc = plan_launch(cu_budget, 0, &L);
   if (rc) return rc;
-  const uint32_t unroll = (L.unroll == 8) ? 8u : 4u;  // 8 KiB slices under a CU budget, 4 KiB otherwise
+  const uint32_t unroll = (L.unroll >= 8) ? 8u : 4u;  // 8 KiB slices under a CU budget, 4 KiB otherwise
   const uint32_t slice = kWave * 16u * unroll;
   IoArgs a;
   a.sgl = d_sgl_table;
@@ -903,8 +912,7 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
   m.layer = layer;
   m.file_stride = store->file_stride;
   m.ctx_cap = static_cast<uint64_t>(n_slots) * TUTTI_IOCB_SLOTS;
-  const uint64_t slice = kPiece * L.unroll;
-  if (m.ctx_cap * ((bb + slice - 1) / slice) > 0xffffffffull) return TUTTI_ERANGE;  // work items are numbered in 32 bits
+  if (m.ctx_cap * counted_slices(L, bb) > 0xffffffffull) return TUTTI_ERANGE;  // work items are numbered in 32 bits
   Launch G;
   rc = plan_launch(cu_budget, move_wave_items(L, m), &G);
   if (rc) return rc;
@@ -1432,7 +1440,7 @@ int tutti_stream_baseline(void *d_buf, uint64_t bytes, uint32_t write, uint32_t 
   Launch L;
   int rc = plan_launch(cu_budget, 0, &L);
   if (rc) return rc;
-  const uint32_t unroll = (L.unroll == 8) ? 8u : 4u;
+  const uint32_t unroll = (L.unroll >= 8) ? 8u : 4u;
   const uint64_t slice = kWave * 16ull * unroll;
   rc = plan_launch(cu_budget, (bytes + slice - 1) / slice, &L);
   if (rc) return rc;

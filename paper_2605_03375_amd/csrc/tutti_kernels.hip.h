@@ -1129,6 +1129,15 @@ __device__ __forceinline__ uint32_t item_wg(const MoveArgs &a, uint32_t wg, uint
   return (b % 8u) * per + b / 8u;
 }
 
+// The first item of this wavefront; its others follow n_waves apart.  Whole-GPU launches: the wavefronts of a workgroup
+// take neighbouring items.  CU-budgeted launches (large workgroups): neighbouring workgroups do, so that a job of few
+// items is spread over all the budgeted compute units.
+__device__ __forceinline__ uint32_t first_item(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs) {
+  const uint32_t wave = rfl(threadIdx.x / kWave);
+  if (blockDim.x == kBudgetWgThreads) return wave * copy_wgs + wg;
+  return item_wg(a, wg, copy_wgs) * (blockDim.x / kWave) + wave;
+}
+
 constexpr int kPack = 0;   // pool -> object
 constexpr int kUnpack = 1; // object -> pool
 
@@ -1301,7 +1310,8 @@ __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint3
 }
 
 // First item of a wavefront in an unpack from dense staging: its source bytes do not depend on the extents,
-// so their loads can be in flight while the workgroup is still fetching or scanning the extents.
+// so their loads can be in flight while the workgroup is still fetching or scanning the extents.  (Whole-GPU launches
+// only: under a CU budget a wavefront has many items, and 16 loads in flight need the registers.)
 template <int U>
 struct Preload {
   u32x4 buf[U];
@@ -1313,7 +1323,7 @@ template <int U, int NT>
 __device__ __forceinline__ Preload<U> preload_first(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint32_t it = item_wg(a, wg, copy_wgs) * (blockDim.x / kWave) + rfl(threadIdx.x / kWave);
+  const uint32_t it = first_item(a, wg, copy_wgs);
   Preload<U> p;
   p.valid = a.dense != 0 && it < a.items_bound && (static_cast<uint64_t>(it) + 1) * kSlice <= a.stage_cap;
   p.src = a.stage + static_cast<uint64_t>(it) * kSlice;
@@ -1366,11 +1376,10 @@ __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uin
                                            uint32_t copy_wgs, const Preload<U> &pre) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint32_t wave_in_wg = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t n_waves = copy_wgs * (blockDim.x / kWave);
   const uint32_t n_items = count_units<SEP, ORD>(a, l, n_req) * a.slices_per_block;
 
-  uint32_t it = item_wg(a, wg, copy_wgs) * (blockDim.x / kWave) + wave_in_wg;
+  uint32_t it = first_item(a, wg, copy_wgs);
   if (it >= n_items) return;
   Item cur = decode_item<SEP, ORD>(a, l, n_req, it, lane);
   uint32_t id = load_block_id(a, cur);
@@ -1434,7 +1443,7 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
   const uint32_t n_items = static_cast<uint32_t>((n_pieces + U - 1) / U);
   const uint32_t in_piece = lane * 16u;
 
-  for (uint64_t it = item_wg(a, wg, copy_wgs) * (blockDim.x / kWave) + rfl(threadIdx.x / kWave); it < n_items;
+  for (uint64_t it = first_item(a, wg, copy_wgs); it < n_items;
        it += kBatch * static_cast<uint64_t>(n_waves)) {
     // ---- decode: lane -> piece lane % U of item it + (lane / U) * n_waves
     uint64_t obj = 0, blk = 0;        // where the piece sits on the two sides (head-major: blk = its block)
@@ -1478,38 +1487,33 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
     // ---- move
     const uint64_t left = (n_items - it + n_waves - 1) / n_waves;
     for (uint32_t i = 0; i < kBatch && i < left; ++i) {
-      unsigned char *src[U], *dst[U];
-#pragma unroll
-      for (uint32_t k = 0; k < U; ++k) {
-        unsigned char *o = as_global(readlane_u64(obj, i * U + k)) + in_piece;
-        unsigned char *b = as_global(readlane_u64(blk, i * U + k));
-        b += HND ? hnd_offset(readlane_u32(off, i * U + k) + in_piece, a.row_bytes, a.block_tokens, a.num_kv_heads)
-                 : in_piece;
-        src[k] = DIR == kPack ? b : o;
-        dst[k] = DIR == kPack ? o : b;
-      }
+      // the two sides of piece k of the item (worked out where they are used: 2 * U addresses at once would not fit)
+      const auto obj_at = [&](uint32_t k) { return as_global(readlane_u64(obj, i * U + k)) + in_piece; };
+      const auto blk_at = [&](uint32_t k) {
+        return as_global(readlane_u64(blk, i * U + k)) +
+               (HND ? hnd_offset(readlane_u32(off, i * U + k) + in_piece, a.row_bytes, a.block_tokens, a.num_kv_heads)
+                    : in_piece);
+      };
       u32x4 buf[U];
       constexpr uint64_t kAll = (1ull << U) - 1;
       if ((whole >> (i * U) & kAll) == kAll) {
 #pragma unroll
-        for (uint32_t k = 0; k < U; ++k) buf[k] = ld16<NT>(src[k]);
+        for (uint32_t k = 0; k < U; ++k) buf[k] = ld16<NT>(DIR == kPack ? blk_at(k) : obj_at(k));
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (uint32_t k = 0; k < U; ++k) st16<NT>(dst[k], buf[k]);
+        for (uint32_t k = 0; k < U; ++k) st16<NT>(DIR == kPack ? obj_at(k) : blk_at(k), buf[k]);
         asm volatile("; whole item");  // (the marks keep the compiler from merging the paths' last stores, which
                                        // would put a wait for all other stores in front of the merged one)
       } else {  // a piece is short (the last of its block) or skipped
-        uint32_t n[U];
 #pragma unroll
-        for (uint32_t k = 0; k < U; ++k) {
-          n[k] = readlane_u32(len, i * U + k);
-          if (in_piece < n[k]) buf[k] = ld16<NT>(src[k]);
-        }
+        for (uint32_t k = 0; k < U; ++k)
+          if (in_piece < readlane_u32(len, i * U + k)) buf[k] = ld16<NT>(DIR == kPack ? blk_at(k) : obj_at(k));
         // one wait for all loads: left to itself the compiler waits in front of each guarded store, and with that
         // for the stores before it (loads and stores share a counter)
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
 #pragma unroll
         for (uint32_t k = 0; k < U; ++k)
-          if (in_piece < n[k]) st16<NT>(dst[k], buf[k]);
+          if (in_piece < readlane_u32(len, i * U + k)) st16<NT>(DIR == kPack ? obj_at(k) : blk_at(k), buf[k]);
         asm volatile("; guarded item");
       }
     }
@@ -1664,7 +1668,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_move(const Mo
   const ReqLds l = carve_lds(smem, n_req, true);
   Preload<U> pre;
   pre.valid = false;
-  if (DIR == kUnpack && !PIECES) pre = preload_first<U, NT>(a, blockIdx.x, gridDim.x);
+  if (DIR == kUnpack && !PIECES && WG == kWgThreads) pre = preload_first<U, NT>(a, blockIdx.x, gridDim.x);
   lds_from_caller_extents(ext, n_req, l, a.table_len, a.block_bytes, a.stage_cap, a.status);
   if (PIECES)
     move_pieces<DIR, HND, U, NT, true>(a, l, n_req, blockIdx.x, gridDim.x);
@@ -1710,7 +1714,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
   const bool publish = blockIdx.x == 0;  // also an entry-writing workgroup: there is at least one
   scan_extents<WG>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
                    m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [&] {
-                     if (DIR == kUnpack && !ORD && !PIECES && copies) pre = preload_first<U, NT>(m, wg, w.copy_wgs);
+                     if (DIR == kUnpack && !ORD && !PIECES && WG == kWgThreads && copies) pre = preload_first<U, NT>(m, wg, w.copy_wgs);
                    });
   SqeHead head;
   head.live = false;
@@ -1742,7 +1746,7 @@ __device__ __forceinline__ Preload<U> preload_first_direct(const MoveArgs &m, co
                                                            uint32_t copy_wgs) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint32_t it = item_wg(m, wg, copy_wgs) * (blockDim.x / kWave) + rfl(threadIdx.x / kWave);
+  const uint32_t it = first_item(m, wg, copy_wgs);
   Preload<U> p;
   p.valid = false;
   if (m.block_bytes % kSlice != 0) return p;
@@ -1792,7 +1796,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
   // chunk counts only matter for the published extents; the LDS copy gets file starts instead of staging offsets
   scan_extents<WG>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
                    0xffffffffu, nullptr, publish, q.file_id, f, [&] {
-                     if (DIR == kUnpack && !PIECES && copies && a.n_req == 1)
+                     if (DIR == kUnpack && !PIECES && WG == kWgThreads && copies && a.n_req == 1)
                        pre = preload_first_direct<U>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
                    });
   DirectHead head;
