@@ -171,6 +171,7 @@ LayoutArgs layout_args(const uint32_t *d_n_blocks, tutti_extent *d_extents, uint
 }
 
 struct Launch {
+  uint32_t cus;          // compute units of the device (asked for once per call)
   uint32_t grid;
   uint32_t wg_threads;   // kWgThreads, or kBudgetWgThreads under a CU budget
   uint32_t unroll;
@@ -188,49 +189,62 @@ uint32_t log2u(uint32_t x) {
   return n;
 }
 
+// Workgroups of a whole-GPU launch that fills every place (what plan_launch caps its grid at).
+uint32_t whole_gpu_wgs(const Launch &L) {
+  const uint32_t per_cu = tuning().wgs_per_cu;
+  return L.cus * (per_cu ? per_cu : kDefaultWgsPerCu);
+}
+
 // Launch shape.  Whole GPU (cu_budget = 0): persistent 256-thread workgroups, enough for every
 // item to have its own wavefront, at most wgs_per_cu per CU.  Under a CU budget B: B workgroups of
 // 1024 threads, i.e. one full-size workgroup per budgeted CU, so the launch occupies at most B
 // compute units and a concurrent compute kernel keeps the others to itself.
+void size_grid(uint32_t cu_budget, uint64_t n_wave_items, Launch *out) {
+  if (cu_budget) {
+    // an item per workgroup is enough for a workgroup: the items are dealt to the workgroups first (first_item)
+    const uint64_t need = n_wave_items ? n_wave_items : 1;
+    out->grid = static_cast<uint32_t>(need < cu_budget ? need : cu_budget);
+    return;
+  }
+  const uint64_t cap = whole_gpu_wgs(*out);
+  const uint64_t waves = kWgThreads / kWave;
+  uint64_t need = (n_wave_items + waves - 1) / waves;
+  if (need == 0) need = 1;
+  out->grid = static_cast<uint32_t>(need < cap ? need : cap);
+}
+
 int plan_launch(uint32_t cu_budget, uint64_t n_wave_items, Launch *out) {
   const int cus = cu_count();
   if (cus < 0) return cus;
   if (cu_budget > static_cast<uint32_t>(cus)) return TUTTI_ERANGE;
   const Tuning t = tuning();
-  uint32_t u = t.unroll;
+  out->cus = static_cast<uint32_t>(cus);
   out->nontemporal = t.nontemporal & 3u;
-  if (cu_budget) {
-    out->hnd_lds = false;
-    out->tile_lds = 0;
-    out->pieces = false;
-    out->wg_threads = kBudgetWgThreads;
-    out->unroll = u ? u : kBudgetUnroll;
-    // an item per workgroup is enough for a workgroup: the items are dealt to the workgroups first (first_item)
-    const uint64_t need = n_wave_items ? n_wave_items : 1;
-    out->grid = static_cast<uint32_t>(need < cu_budget ? need : cu_budget);
-    return TUTTI_OK;
-  }
-  uint32_t per_cu = t.wgs_per_cu;
-  if (per_cu == 0) per_cu = kDefaultWgsPerCu;
-  const uint64_t cap = static_cast<uint64_t>(cus) * per_cu;
-  const uint64_t waves = kWgThreads / kWave;
-  uint64_t need = (n_wave_items + waves - 1) / waves;
-  if (need == 0) need = 1;
   out->hnd_lds = false;
   out->tile_lds = 0;
   out->pieces = false;
-  out->wg_threads = kWgThreads;
-  out->unroll = u ? u : kDefaultUnroll;
-  out->grid = static_cast<uint32_t>(need < cap ? need : cap);
+  out->wg_threads = cu_budget ? kBudgetWgThreads : kWgThreads;
+  out->unroll = t.unroll ? t.unroll : cu_budget ? kBudgetUnroll : kDefaultUnroll;
+  size_grid(cu_budget, n_wave_items, out);
   return TUTTI_OK;
 }
 
-// Workgroups of a whole-GPU launch that fills every place (what plan_launch caps its grid at).
-uint32_t whole_gpu_wgs() {
-  const int cus = cu_count();
-  uint32_t per_cu = tuning().wgs_per_cu;
-  if (per_cu == 0) per_cu = kDefaultWgsPerCu;
-  return cus > 0 ? static_cast<uint32_t>(cus) * per_cu : 0u;
+uint64_t whole_gpu_waves(const Launch &L) { return static_cast<uint64_t>(whole_gpu_wgs(L)) * (kWgThreads / kWave); }
+
+// How long a whole-GPU restore holds its first stores back, by the share of the chip's wavefronts that have an item (the
+// figures stand at hold_back).
+uint32_t restore_pause(const Launch &L, uint64_t wave_items) {
+  if (L.wg_threads != kWgThreads || L.hnd_lds) return 0;
+  if (8 * wave_items > 6 * whole_gpu_waves(L)) return 6;
+  return 8 * wave_items > 5 * whole_gpu_waves(L) ? 2 : 0;
+}
+
+// One request on the path that is made for it (move_request): blocks of whole slices in staging order; a restore only
+// while it leaves half of the chip's wavefronts free.
+template <int DIR>
+bool one_request_path(const Launch &L, const MoveArgs &m, uint32_t n_req, uint64_t wave_items) {
+  if (n_req != 1 || L.pieces || L.hnd_lds || m.visit) return false;
+  return DIR == kPack || L.wg_threads != kWgThreads || 2 * wave_items < whole_gpu_waves(L);
 }
 
 uint64_t counted_slices(const Launch &L, uint32_t bytes) {
@@ -262,6 +276,7 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   m->file_stride = 0;
   m->ctx_cap = 0;
   m->visit = nullptr;
+  m->pause = 0;
 
   L->hnd_lds = false;
   L->tile_lds = 0;
@@ -360,10 +375,7 @@ Roles make_roles(const Launch &L, uint64_t entry_quarters, uint32_t *grid) {
   if (need < 1) need = 1;
   uint64_t limit = L.grid;
   if (L.wg_threads == kWgThreads) {
-    uint32_t per_cu = tuning().wgs_per_cu;
-    if (per_cu == 0) per_cu = kDefaultWgsPerCu;
-    const int cus = cu_count();
-    const uint64_t cap = cus > 0 ? static_cast<uint64_t>(cus) * per_cu : L.grid;
+    const uint64_t cap = whole_gpu_wgs(L);
     if (cap > limit) limit = cap;
   }
   Roles w;
@@ -380,13 +392,16 @@ hipError_t launch_layer_lds(const Launch &L, uint64_t entry_quarters, uint32_t l
   uint32_t n_wgs = 0;
   const Roles w = make_roles(L, entry_quarters, &n_wgs);
   const dim3 grid(n_wgs);
+  const bool many = a.n_req > kWave;
+#define TUTTI_LDS_LAUNCH(PT, WG, REQS) \
+  hipLaunchKernelGGL((k_layer_lds<DIR, PT, WG, REQS>), grid, dim3(WG), lds, s, m, q, a, w)
 #define TUTTI_LDS_CASE(PT)                                                                                        \
   case PT:                                                                                                        \
-    if (L.wg_threads == kWgThreads)                                                                               \
-      hipLaunchKernelGGL((k_layer_lds<DIR, PT, kWgThreads>), grid, dim3(kWgThreads), lds, s, m, q, a, w);         \
-    else                                                                                                          \
-      hipLaunchKernelGGL((k_layer_lds<DIR, PT, kBudgetWgThreads>), grid, dim3(kBudgetWgThreads), lds, s, m, q, a, \
-                         w);                                                                                      \
+    if (L.wg_threads == kWgThreads) {                                                                             \
+      if (many) TUTTI_LDS_LAUNCH(PT, kWgThreads, kMany); else TUTTI_LDS_LAUNCH(PT, kWgThreads, kFew);              \
+    } else {                                                                                                      \
+      if (many) TUTTI_LDS_LAUNCH(PT, kBudgetWgThreads, kMany); else TUTTI_LDS_LAUNCH(PT, kBudgetWgThreads, kFew);  \
+    }                                                                                                             \
     break;
   switch (L.unroll) {
     TUTTI_LDS_CASE(1)
@@ -397,6 +412,7 @@ hipError_t launch_layer_lds(const Launch &L, uint64_t entry_quarters, uint32_t l
       return hipErrorInvalidValue;
   }
 #undef TUTTI_LDS_CASE
+#undef TUTTI_LDS_LAUNCH
   return hipGetLastError();
 }
 
@@ -444,6 +460,32 @@ hipError_t launch_move(const Launch &L, uint32_t lds, hipStream_t s, const MoveA
   });
 }
 
+// The kernels for one and for at most 64 requests exist in the product's shapes only; those for any number serve the
+// others too.
+template <typename S>
+constexpr bool has_few = S::NT == 3 && ((S::U == kDefaultUnroll && S::WG == kWgThreads) ||
+                                        (S::U == kBudgetUnroll && S::WG == kBudgetWgThreads));
+
+template <typename S, int DIR, bool HND, int REQS>
+hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStream_t s, const MoveArgs &m,
+                              const SqeArgs &q, const LayoutArgs &a, const Roles &w) {
+  const dim3 grid(n_wgs), block(S::WG);
+  if constexpr (REQS != kOne) {
+    if constexpr (DIR == kUnpack) {
+      if (m.visit) {  // the caller's visiting order
+        hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>), grid, block, lds, s, m, q, a, w);
+        return hipGetLastError();
+      }
+    }
+    if (pieces) {
+      hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, false, true>), grid, block, lds, s, m, q, a, w);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS>), grid, block, lds, s, m, q, a, w);
+  return hipGetLastError();
+}
+
 template <int DIR, bool HND>
 hipError_t launch_layer(const Launch &L, uint64_t entry_quarters, uint32_t lds, hipStream_t s, const MoveArgs &m,
                         const SqeArgs &q, const LayoutArgs &a) {
@@ -451,20 +493,28 @@ hipError_t launch_layer(const Launch &L, uint64_t entry_quarters, uint32_t lds, 
   const Roles w = make_roles(L, entry_quarters, &n_wgs);
   return with_shape(L, [&](auto sh) {
     using S = decltype(sh);
-    if constexpr (DIR == kUnpack) {
-      if (m.visit) {  // the caller's visiting order
-        hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, true>), dim3(n_wgs), dim3(S::WG), lds, s, m, q, a,
-                           w);
-        return hipGetLastError();
-      }
+    if constexpr (has_few<S>) {
+      if (one_request_path<DIR>(L, m, a.n_req, move_wave_items(L, m)))
+        return launch_layer_shape<S, DIR, HND, kOne>(false, n_wgs, lds, s, m, q, a, w);
+      if (a.n_req <= kWave) return launch_layer_shape<S, DIR, HND, kFew>(L.pieces, n_wgs, lds, s, m, q, a, w);
     }
-    if (L.pieces)
-      hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, false, true>), dim3(n_wgs), dim3(S::WG), lds, s, m, q, a,
-                         w);
-    else
-      hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG>), dim3(n_wgs), dim3(S::WG), lds, s, m, q, a, w);
-    return hipGetLastError();
+    return launch_layer_shape<S, DIR, HND, kMany>(L.pieces, n_wgs, lds, s, m, q, a, w);
   });
+}
+
+template <typename S, int DIR, int REQS>
+hipError_t launch_ring_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStream_t s, const MoveArgs &m,
+                             const SqeArgs &q, const DirectArgs &d, const RingArgs &g, const RingArgs &done,
+                             const FileArgs &f, const LayoutArgs &a, const Roles &w) {
+  const dim3 grid(n_wgs), block(S::WG);
+  if constexpr (REQS != kOne) {
+    if (pieces) {
+      hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG, REQS, true>), grid, block, lds, s, m, q, d, g, done, f, a, w);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG, REQS>), grid, block, lds, s, m, q, d, g, done, f, a, w);
+  return hipGetLastError();
 }
 
 template <int DIR>
@@ -489,10 +539,7 @@ int move_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const tutti_exte
   MoveArgs m;
   rc = fill_move_args(pool, bb, d_block_table, table_len, d_stage, stage_cap, d_status, n_req, cfg->align, false, &L, &m);
   if (rc) return rc;
-  Launch G;
-  rc = plan_launch(cu_budget, move_wave_items(L, m), &G);
-  if (rc) return rc;
-  L.grid = G.grid;
+  size_grid(cu_budget, move_wave_items(L, m), &L);
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e;
   if (L.hnd_lds) {
@@ -596,10 +643,8 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
   rc = fill_move_args(pool, bb, d_block_table, table_len, d_stage, stage_cap, d_status, n_req, cfg->align, d_visit != nullptr, &L, &m);
   if (rc) return rc;
   if (!L.hnd_lds) m.visit = d_visit;  // the tiles of the through-LDS path keep staging order
-  Launch G;
-  rc = plan_launch(cu_budget, move_wave_items(L, m), &G);
-  if (rc) return rc;
-  L.grid = G.grid;
+  size_grid(cu_budget, move_wave_items(L, m), &L);
+  if (DIR == kUnpack) m.pause = restore_pause(L, move_wave_items(L, m));
   // one lane per 16-byte quarter of an entry; no more entries than the capacity, nor than the table can give
   // (every request has at most obj/chunk + 1 chunks per object, and obj < blocks*block_bytes + align <= ... + chunk)
   uint64_t max_entries = 2ull * ((static_cast<uint64_t>(table_len) * bb) / cfg->chunk_bytes + 2ull * n_req);
@@ -814,8 +859,7 @@ int issue_io_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slots
   Launch L;
   rc = plan_launch(cu_budget, 0, &L);
   if (rc) return rc;
-  const uint32_t unroll = (L.unroll >= 8) ? 8u : 4u;  // 8 KiB slices under a CU budget, 4 KiB otherwise
-  const uint32_t slice = kWave * 16u * unroll;
+  L.unroll = L.wg_threads == kWgThreads ? kDefaultUnroll : kBudgetUnroll;  // the I/O kernel has one shape of each kind
   IoArgs a;
   a.sgl = d_sgl_table;
   a.store_base = static_cast<unsigned char *>(store->base);
@@ -826,27 +870,25 @@ int issue_io_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slots
   a.first_file_id = store->first_file_id;
   a.n_files = store->n_files;
   a.max_len = max_len;
-  a.slices = static_cast<uint32_t>((static_cast<uint64_t>(max_len) + slice - 1) / slice);
-  const uint64_t items = static_cast<uint64_t>(n_slots) * TUTTI_IOCB_SLOTS * a.slices;
-  if (items > 0xffffffffull) return TUTTI_ERANGE;
-  rc = plan_launch(cu_budget, items, &L);
-  if (rc) return rc;
+  const uint32_t slice = kPiece * L.unroll;
+  const bool pieces = max_len % slice != 0;
+  a.parts = pieces ? static_cast<uint32_t>((static_cast<uint64_t>(max_len) + kPiece - 1) / kPiece) : max_len / slice;
+  const uint64_t contexts = static_cast<uint64_t>(n_slots) * TUTTI_IOCB_SLOTS;
+  if (contexts * counted_slices(L, max_len) > 0xffffffffull) return TUTTI_ERANGE;
+  size_grid(cu_budget, pieces ? (contexts * a.parts + L.unroll - 1) / L.unroll : contexts * a.parts, &L);
   // a chained launch: one more workgroup in front; a whole-GPU grid gives it one of its places
   const uint32_t lead = done_n > 0 ? 1u : 0u;
-  if (lead && cu_budget == 0 && L.grid > 1 && L.grid == whole_gpu_wgs()) L.grid -= 1;
+  if (lead && cu_budget == 0 && L.grid > 1 && L.grid == whole_gpu_wgs(L)) L.grid -= 1;
   RingArgs g{ring->d_sq, static_cast<tutti_cq_hdr *>(ring->d_cq), ring->depth, first_slot, n_slots};
   const dim3 grid(L.grid + lead);
+#define TUTTI_ISSUE(U, WG, PIECES) \
+  hipLaunchKernelGGL((k_issue_io<U, WG, PIECES>), grid, dim3(WG), 0, s, g, gd, a)
   if (L.wg_threads == kWgThreads) {
-    if (unroll == 8)
-      hipLaunchKernelGGL((k_issue_io<8, kWgThreads>), grid, dim3(kWgThreads), 0, s, g, gd, a);
-    else
-      hipLaunchKernelGGL((k_issue_io<4, kWgThreads>), grid, dim3(kWgThreads), 0, s, g, gd, a);
+    if (pieces) TUTTI_ISSUE(kDefaultUnroll, kWgThreads, true); else TUTTI_ISSUE(kDefaultUnroll, kWgThreads, false);
   } else {
-    if (unroll == 8)
-      hipLaunchKernelGGL((k_issue_io<8, kBudgetWgThreads>), grid, dim3(kBudgetWgThreads), 0, s, g, gd, a);
-    else
-      hipLaunchKernelGGL((k_issue_io<4, kBudgetWgThreads>), grid, dim3(kBudgetWgThreads), 0, s, g, gd, a);
+    if (pieces) TUTTI_ISSUE(kBudgetUnroll, kBudgetWgThreads, true); else TUTTI_ISSUE(kBudgetUnroll, kBudgetWgThreads, false);
   }
+#undef TUTTI_ISSUE
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e);
   if (!complete) return TUTTI_OK;
@@ -913,14 +955,12 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
   m.file_stride = store->file_stride;
   m.ctx_cap = static_cast<uint64_t>(n_slots) * TUTTI_IOCB_SLOTS;
   if (m.ctx_cap * counted_slices(L, bb) > 0xffffffffull) return TUTTI_ERANGE;  // work items are numbered in 32 bits
-  Launch G;
-  rc = plan_launch(cu_budget, move_wave_items(L, m), &G);
-  if (rc) return rc;
-  L.grid = G.grid;
+  size_grid(cu_budget, move_wave_items(L, m), &L);
+  if (DIR == kUnpack) m.pause = restore_pause(L, move_wave_items(L, m));
   // a chained launch has one more workgroup in front (it completes the earlier call's IOCBs and leaves); a
   // whole-GPU grid gives it one of its places, so that every workgroup is still resident from the start
   const uint32_t lead = done_n > 0 ? 1u : 0u;
-  if (lead && cu_budget == 0 && L.grid > 1 && L.grid == whole_gpu_wgs()) L.grid -= 1;
+  if (lead && cu_budget == 0 && L.grid > 1 && L.grid == whole_gpu_wgs(L)) L.grid -= 1;
   // contexts to record: no more than the IOCBs hold, no more than two per table position
   uint64_t n_ctx = static_cast<uint64_t>(n_slots) * TUTTI_IOCB_SLOTS;
   if (n_ctx > 2ull * table_len) n_ctx = 2ull * table_len;
@@ -941,13 +981,12 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
   R.nontemporal = 3;  // the ring kernels have one cache policy
   hipError_t e = with_shape(R, [&](auto sh) {
     using S = decltype(sh);
-    if (R.pieces)
-      hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG, true>), dim3(n_wgs + lead), dim3(S::WG), lds, s, m, q, d, g, gd,
-                         f, a, w);
-    else
-      hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG>), dim3(n_wgs + lead), dim3(S::WG), lds, s, m, q, d, g, gd, f, a,
-                         w);
-    return hipGetLastError();
+    if constexpr (has_few<S>) {
+      if (one_request_path<DIR>(R, m, n_req, move_wave_items(R, m)))
+        return launch_ring_shape<S, DIR, kOne>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+      if (n_req <= kWave) return launch_ring_shape<S, DIR, kFew>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+    }
+    return launch_ring_shape<S, DIR, kMany>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
   });
   if (e != hipSuccess) return hip_fail(e);
   if (!complete) return TUTTI_OK;
@@ -1627,17 +1666,17 @@ int tutti_resident_wgs_per_cu(uint32_t which) {
   int n = 0;
   hipError_t e;
   switch (which) {
-    case 0: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kUnpack, false, 4, 3, kWgThreads>, kWgThreads, lds); break;
-    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kPack, false, 4, 3, kWgThreads>, kWgThreads, lds); break;
+    case 0: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kUnpack, false, 4, 3, kWgThreads, kOne>, kWgThreads, lds); break;
+    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kPack, false, 4, 3, kWgThreads, kOne>, kWgThreads, lds); break;
     case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_move<kUnpack, false, 4, 3, kWgThreads>, kWgThreads, lds); break;
     case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_move<kPack, false, 4, 3, kWgThreads>, kWgThreads, lds); break;
-    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_ring<kUnpack, 4, kWgThreads>, kWgThreads, lds); break;
-    case 5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_ring<kPack, 4, kWgThreads>, kWgThreads, lds); break;
-    case 6: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kUnpack, true, 4, 3, kWgThreads>, kWgThreads, lds); break;
-    case 7: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kPack, true, 4, 3, kWgThreads>, kWgThreads, lds); break;
-    case 8: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_lds<kUnpack, 4, kWgThreads>, kWgThreads, lds_tile); break;
-    case 9: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_lds<kPack, 4, kWgThreads>, kWgThreads, lds_tile); break;
-    case 10: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_issue_io<4, kWgThreads>, kWgThreads, 0); break;
+    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_ring<kUnpack, 4, kWgThreads, kOne>, kWgThreads, lds); break;
+    case 5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_ring<kPack, 4, kWgThreads, kOne>, kWgThreads, lds); break;
+    case 6: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kUnpack, true, 4, 3, kWgThreads, kOne>, kWgThreads, lds); break;
+    case 7: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kPack, true, 4, 3, kWgThreads, kOne>, kWgThreads, lds); break;
+    case 8: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_lds<kUnpack, 4, kWgThreads, kFew>, kWgThreads, lds_tile); break;
+    case 9: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_lds<kPack, 4, kWgThreads, kFew>, kWgThreads, lds_tile); break;
+    case 10: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_issue_io<kDefaultUnroll, kWgThreads, false>, kWgThreads, 0); break;
     default: return TUTTI_EINVAL;
   }
   return e == hipSuccess ? n : hip_fail(e);

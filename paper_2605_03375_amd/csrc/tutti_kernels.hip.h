@@ -46,6 +46,27 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // A wave-uniform 32-bit value moved to a scalar register.
 __device__ __forceinline__ uint32_t rfl(uint32_t v) { return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(v)); }
 
+// The same if the value is known to be wave-uniform (what comes out of LDS or through vector loads is not, to the
+// compiler: kept uniform, the arithmetic behind it goes to the scalar unit and its branches are scalar ones).
+template <bool UNI>
+__device__ __forceinline__ uint32_t uni(uint32_t v) {
+  return UNI ? rfl(v) : v;
+}
+template <bool UNI>
+__device__ __forceinline__ uint64_t uni(uint64_t v) {
+  return UNI ? (static_cast<uint64_t>(rfl(static_cast<uint32_t>(v >> 32))) << 32) | rfl(static_cast<uint32_t>(v)) : v;
+}
+
+// Wave-uniform words (counts, block ids, visiting order) are fetched through the scalar (constant) path: one s_load per
+// wavefront, counted apart from the vector loads and stores in flight: it neither queues behind them nor waits for them.
+typedef const __attribute__((address_space(4))) uint32_t *const_u32_ptr;
+__device__ __forceinline__ const_u32_ptr as_const(const uint32_t *p) {
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wold-style-cast"
+  return (const_u32_ptr)p;
+#pragma clang diagnostic pop
+}
+
 // NT is a bit mask: bit 0 = non-temporal loads, bit 1 = non-temporal stores.
 template <int NT>
 __device__ __forceinline__ u32x4 ld16(const unsigned char *p) {
@@ -172,15 +193,14 @@ __device__ __forceinline__ uint64_t stage_slot(uint64_t stage_off, const uint32_
 // work items (its LDS table offset is the cut, so it owns no blocks) and TUTTI_ST_BAD_EXTENT is reported
 // by the workgroup that publishes.  The published extents are the plain sums either way.
 //
-// Up to 64 requests: one wavefront, a request per lane (a single request needs no scan at all).
-__device__ __forceinline__ void wave_scan_extents(const ScanGeom g, const uint32_t *__restrict__ n_blocks, uint32_t n_req,
+// Up to 64 requests: one wavefront, a request per lane (a single request needs no scan at all); n and fid: the block
+// count and file id of the lane's request.
+__device__ __forceinline__ void wave_scan_extents(const ScanGeom g, uint32_t n, uint32_t fid, uint32_t n_req,
                                                   uint32_t lane, ReqLds l, tutti_extent *__restrict__ ext_out,
                                                   uint64_t *__restrict__ totals_out, uint32_t table_len,
                                                   uint32_t *__restrict__ status, bool with_chunks,
                                                   const uint32_t *__restrict__ file_id, const FileArgs files) {
   const uint32_t r = lane;
-  const uint32_t n = (r < n_req) ? n_blocks[r] : 0u;
-  const uint32_t fid = (file_id && r < n_req) ? file_id[r] : 0u;
   const uint64_t obj = static_cast<uint64_t>(n) * g.block_bytes + obj_pad(g, n);
   // a workgroup that only moves blocks never reads the entry bases: it skips the division
   const uint64_t chunks = with_chunks ? obj_chunks(g, obj) : 0;
@@ -354,25 +374,34 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
 }
 
 // with_chunks: the workgroup writes entries or publishes (ext_out, totals_out): it needs the chunk counts as well.
-// `preload` is called in front of the scan, so that a first slice's loads are in flight meanwhile; not where more than
-// 64 requests are scanned in 64-bit sums, which leaves no registers for them (a few workgroups of a launch).
-template <int WG, typename P>
+// `preload` requests a first slice's bytes, so that they are on their way during the scan.  Up to 64 requests: in front
+// of the loads of the counts, which return behind the scanning wavefront's slice, so that no wavefront of the workgroup
+// stores before (see hold_back).  More requests: behind the scan (600 requests, 49 MB: 20.3 us against 22.0 in front of
+// it); in the 64-bit scan (a few workgroups of a launch) not at all, it leaves no registers.
+// REQS = kFew: the host knows of at most 64 requests.  A kernel of its own, because the other scans' arguments push the
+// scalar registers over their limit, and the kernel then starts with four rounds of argument loads and spills instead
+// of one (a 256 KiB restore: 3.6 us against 4.2).
+constexpr int kOne = 1, kFew = 2, kMany = 3;  // requests a kernel is for: one, up to 64, any number
+
+template <int WG, int REQS, typename P>
 __device__ __forceinline__ void scan_extents(const ScanGeom g, const uint32_t *__restrict__ n_blocks, uint32_t n_req,
                                              ReqLds l, tutti_extent *__restrict__ ext_out,
                                              uint64_t *__restrict__ totals_out, uint32_t table_len,
                                              uint32_t *__restrict__ status, bool with_chunks,
                                              const uint32_t *__restrict__ file_id, const FileArgs files, P preload) {
-  if (n_req > kWave && (with_chunks || file_id || g.align > (1u << 20))) {
+  if (REQS == kFew || n_req <= kWave) {
+    preload();
+    if (threadIdx.x < kWave) {
+      const uint32_t n = threadIdx.x < n_req ? n_blocks[threadIdx.x] : 0u;
+      const uint32_t fid = file_id && threadIdx.x < n_req ? file_id[threadIdx.x] : 0u;
+      wave_scan_extents(g, n, fid, n_req, threadIdx.x, l, ext_out, totals_out, table_len, status, with_chunks, file_id,
+                        files);
+    }
+  } else if (with_chunks || file_id || g.align > (1u << 20)) {
     wg_scan_extents<WG, true, false>(g, n_blocks, n_req, l, ext_out, totals_out, table_len, status, file_id, files);
   } else {
+    wg_scan_extents<WG, false, true>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, nullptr, files);
     preload();
-    if (n_req <= kWave) {
-      if (threadIdx.x < kWave)
-        wave_scan_extents(g, n_blocks, n_req, threadIdx.x, l, ext_out, totals_out, table_len, status, with_chunks,
-                          file_id, files);
-    } else {
-      wg_scan_extents<WG, false, true>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, nullptr, files);
-    }
   }
   __syncthreads();
 }
@@ -520,11 +549,12 @@ __device__ __forceinline__ void lds_from_caller_extents(const tutti_extent *__re
 // Largest r in [0, n) with a[r] <= key, for a non-decreasing a with a[0] <= key.  Empty
 // requests share their offset with the next one, so the answer is never an empty request
 // when key is below the total.
+template <bool UNI = false>
 __device__ __forceinline__ uint32_t find_owner(const uint32_t *a, uint32_t n, uint32_t key) {
   uint32_t lo = 0, hi = n;
   while (hi - lo > 1) {
     const uint32_t mid = (lo + hi) >> 1;
-    if (a[mid] <= key)
+    if (uni<UNI>(a[mid]) <= key)
       lo = mid;
     else
       hi = mid;
@@ -868,6 +898,69 @@ __global__ __launch_bounds__(WG) void k_iocb_fill(const RingArgs g, const SqeArg
   emit_iocbs(g, a, d, l, n_req, 0, gridDim.x, iocb_head(g, a, d, l, n_req, 0, gridDim.x));
 }
 
+constexpr uint32_t kPiece = kWave * 16u;  // what one wavefront instruction of 16 bytes per lane covers: 1 KiB
+
+constexpr int kWaitVmcnt0 = 0x0f70;  // operand of s_waitcnt: vector accesses done, the other counters as they are
+
+// The value that lane `src` holds, in scalar registers.
+__device__ __forceinline__ uint32_t readlane_u32(uint32_t v, uint32_t src) {
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>(src)));
+}
+__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, uint32_t src) {
+  const uint32_t lo = readlane_u32(static_cast<uint32_t>(v), src);
+  return (static_cast<uint64_t>(readlane_u32(static_cast<uint32_t>(v >> 32), src)) << 32) | lo;
+}
+typedef __attribute__((address_space(1))) unsigned char *global_u8_ptr;
+__device__ __forceinline__ unsigned char *as_global(uint64_t address) {
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wold-style-cast"
+  return (unsigned char *)(global_u8_ptr)address;  // a global pointer, so that the accesses are global ones
+#pragma clang diagnostic pop
+}
+
+// Moves item i of a batch that the lanes have decoded: G parts of U/G KiB each, part g decoded by lane i * G + g.
+// `len`: bytes of the lane's part (0 = skip it), `whole`: the lanes whose part is of full length; src(g, o), dst(g, o):
+// the address o bytes into part g on either side (worked out where they are used: all at once they would not fit the
+// registers).  U loads in flight, then U stores.  Where a part is short, the lanes beyond it load its first 16 bytes
+// again and store nothing (src of a part to skip is any readable 16 bytes): guarded loads end in a wait each.
+template <int U, int G, int NT, typename Src, typename Dst>
+__device__ __forceinline__ void move_decoded(uint32_t i, uint64_t whole, uint32_t len, Src src, Dst dst) {
+  constexpr uint32_t P = U / G;
+  constexpr uint64_t kAll = (1ull << G) - 1;
+  const uint32_t o = (threadIdx.x & (kWave - 1)) * 16u;
+  u32x4 buf[U];
+  if ((whole >> (i * G) & kAll) == kAll) {
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) buf[u] = ld16<NT>(src(u / P, o + u % P * kPiece));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) st16<NT>(dst(u / P, o + u % P * kPiece), buf[u]);
+    asm volatile("; whole item");  // (the marks keep the compiler from merging the paths' last stores, which
+                                   // would put a wait for all other stores in front of the merged one)
+  } else {
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t at = o + u % P * kPiece;
+      buf[u] = ld16<NT>(src(u / P, at < readlane_u32(len, i * G + u / P) ? at : 0u));
+    }
+    // one wait for all loads: left to itself the compiler waits in front of each guarded store, and with that
+    // for the stores before it (loads and stores share a counter)
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      const uint32_t at = o + u % P * kPiece;
+      if (at < readlane_u32(len, i * G + u / P)) st16<NT>(dst(u / P, at), buf[u]);
+    }
+    asm volatile("; guarded item");
+  }
+}
+
+// `v` in the lanes of `live`, the value of the first of them in the others.
+__device__ __forceinline__ uint64_t or_first(uint64_t v, uint64_t live) {
+  const uint64_t first = readlane_u64(v, static_cast<uint32_t>(__ffsll(static_cast<long long>(live))) - 1u);
+  return (live >> (threadIdx.x & (kWave - 1)) & 1u) != 0 ? v : first;
+}
+
 struct IoArgs {
   const tutti_sgl *sgl;
   unsigned char *store_base;
@@ -878,43 +971,30 @@ struct IoArgs {
   uint32_t first_file_id;
   uint32_t n_files;
   uint32_t max_len;
-  uint32_t slices;  // ceil(max_len / slice bytes)
+  uint32_t parts;  // per context: slices or pieces that cover max_len
 };
 
-// One slice of one context, resolved: where its bytes come from and go to.  Wave-uniform.
-struct IoItem {
-  const unsigned char *src;  // nullptr: nothing to move (empty slot, no-op or rejected context, slice beyond len)
-  unsigned char *dst;
-  uint32_t len;              // bytes of the context
-  uint32_t in_ctx;           // first byte of the slice within the context
+// One part of one context, resolved: where its bytes come from and go to.
+struct IoPart {
+  uint64_t src, dst;
+  uint32_t len;  // bytes of the part; 0: nothing to move (empty slot, no-op or rejected context, part beyond its length)
 };
 
-// Everything between the item number and the two addresses: IOCB header, context, SGL descriptor, validity.
-// Three dependent loads (header and context together, then the descriptor), all of wave-uniform words.
-template <int U>
-__device__ __forceinline__ IoItem io_decode(const RingArgs &g, const IoArgs &a, uint32_t it, uint32_t per_iocb,
-                                            uint32_t lane) {
-  constexpr uint32_t kSlice = kWave * 16u * U;
-  IoItem r;
-  r.src = nullptr;
-  r.dst = nullptr;
+// Everything between a part's number and its two addresses: IOCB header and context, SGL descriptor, validity.
+__device__ __forceinline__ IoPart io_decode(const RingArgs &g, const IoArgs &a, uint32_t ctx, uint32_t part,
+                                            uint32_t part_bytes) {
+  IoPart r;
+  r.src = r.dst = 0;
   r.len = 0;
-  const uint32_t b = it / per_iocb;
-  const uint32_t rem = it - b * per_iocb;
-  const uint32_t k = rem / a.slices;
-  const uint32_t s = rem - k * a.slices;
-  r.in_ctx = s * kSlice;
+  const uint32_t b = ctx / TUTTI_IOCB_SLOTS, k = ctx % TUTTI_IOCB_SLOTS;
   const tutti_iocb *io = &g.sq[(g.first_slot + b) % g.depth];
   const u32x4 hdr = *reinterpret_cast<const u32x4 *>(&io->hdr);  // iocb_idx, num_ioctx, state, done
   const u32x4 *e = reinterpret_cast<const u32x4 *>(&io->ioctx[k]);
   const u32x4 q0 = e[0], q1 = e[1];
-  const uint32_t num = rfl(hdr.y), state = rfl(hdr.z);
-  if (state != TUTTI_IOCB_FILLED || k >= num) return r;  // nothing submitted in this slot / position
-  const uint32_t opcode = rfl(q0.x) & 0xffu;
-  const uint32_t file_id = rfl(q0.y);
-  const uint64_t file_off = (static_cast<uint64_t>(rfl(q0.w)) << 32) | rfl(q0.z);
-  const uint64_t addr = (static_cast<uint64_t>(rfl(q1.y)) << 32) | rfl(q1.x);
-  const uint32_t len = rfl(q1.z);
+  if (hdr.z != TUTTI_IOCB_FILLED || k >= hdr.y) return r;  // nothing submitted in this slot / position
+  const uint32_t opcode = q0.x & 0xffu, file_id = q0.y, len = q1.z;
+  const uint64_t file_off = (static_cast<uint64_t>(q0.w) << 32) | q0.z;
+  const uint64_t addr = (static_cast<uint64_t>(q1.y) << 32) | q1.x;
   if (len == 0) return r;  // a no-op context
   bool ok = (opcode == TUTTI_OP_READ || opcode == TUTTI_OP_WRITE) && addr >= a.sgl_table_addr &&
             ((addr - a.sgl_table_addr) & 15u) == 0 && len <= a.max_len && (len & 15u) == 0 && (file_off & 15u) == 0;
@@ -923,77 +1003,81 @@ __device__ __forceinline__ IoItem io_decode(const RingArgs &g, const IoArgs &a, 
   uint64_t blk_addr = 0;
   if (ok) {
     const u32x4 dsc = *reinterpret_cast<const u32x4 *>(&a.sgl[di]);
-    blk_addr = (static_cast<uint64_t>(rfl(dsc.y)) << 32) | rfl(dsc.x);
-    ok = len <= rfl(dsc.z) && (blk_addr & 15u) == 0;
+    blk_addr = (static_cast<uint64_t>(dsc.y) << 32) | dsc.x;
+    ok = len <= dsc.z && (blk_addr & 15u) == 0;
   }
   ok = ok && file_id >= a.first_file_id && file_id - a.first_file_id < a.n_files &&
        file_off + len <= a.file_stride && file_off + len >= file_off;
   if (!ok) {
-    if (lane == 0 && s == 0 && a.status) atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
+    if (part == 0 && a.status) atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
     return r;
   }
-  if (r.in_ctx >= len) return r;  // the context is shorter than max_len: this slice holds none of it
-  unsigned char *blk = reinterpret_cast<unsigned char *>(blk_addr);
-  unsigned char *fil = a.store_base + static_cast<uint64_t>(file_id - a.first_file_id) * a.file_stride + file_off;
-  const bool rd = opcode == TUTTI_OP_READ;
-  r.src = rd ? fil : blk;
-  r.dst = rd ? blk : fil;
-  r.len = len;
+  const uint32_t in_ctx = part * part_bytes;
+  if (in_ctx >= len) return r;  // the context is shorter than max_len: this part holds none of it
+  const uint64_t blk = blk_addr + in_ctx;
+  const uint64_t fil = reinterpret_cast<uint64_t>(a.store_base) +
+                       static_cast<uint64_t>(file_id - a.first_file_id) * a.file_stride + file_off + in_ctx;
+  r.src = opcode == TUTTI_OP_READ ? fil : blk;
+  r.dst = opcode == TUTTI_OP_READ ? blk : fil;
+  r.len = len - in_ctx < part_bytes ? len - in_ctx : part_bytes;
   return r;
 }
 
-// The I/O kernel: one wavefront per slice of one context, no inter-wave communication.  Software-pipelined by
-// one item: the loads of the current slice are issued, then the next item is resolved (its header, context and
-// descriptor loads run under the data loads), then the current slice is stored.  Completion is published by
-// k_complete, enqueued right behind it on the same stream: counting finished items with atomics on the IOCB
-// header serialises on one address (measured: 1.5 ms per 4096-context layer instead of 55 us), and a kernel
-// boundary already is the "all contexts done" event.
 __device__ __forceinline__ void complete_iocbs(const RingArgs g, uint32_t lane);  // defined below
 
+// The I/O kernel: no inter-wave communication.  A context is cut into slices of U KiB or, where those do not fill
+// max_len exactly, into pieces of 1 KiB; a work item is one slice or U consecutive pieces, moved by one wavefront.  A
+// wavefront resolves its next 64 slices or pieces at once, one per lane: the three dependent loads behind each (header
+// and context together, then the descriptor) are paid once per batch, with all lanes' loads in flight together and no
+// data loads in front of them; resolved item by item they queue behind the current item's data.  On 32 compute units
+// (33.5 MB to write from 32 KiB blocks) that and the 16 KiB slices took the kernel from 49 us to 42 us.
+// Completion is published by k_complete, enqueued right behind it on the same stream: counting finished items with
+// atomics on the IOCB header serialises on one address (measured: 1.5 ms per 4096-context layer instead of 55 us), and
+// a kernel boundary already is the "all contexts done" event.
 // `done`: IOCBs that an earlier launch on the same stream has executed; when done.n_slots is not 0 the grid has one
 // workgroup more, in front, whose first wavefront completes them and leaves (see k_layer_ring).
-template <int U, int WG>
+template <int U, int WG, bool PIECES>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_issue_io(const RingArgs g, const RingArgs done,
                                                                              const IoArgs a) {
-  constexpr uint32_t kSlice = kWave * 16u * U;
+  constexpr uint32_t G = PIECES ? U : 1, kBatch = kWave / G;  // parts of an item, items decoded at once
+  constexpr uint32_t kPart = PIECES ? kPiece : U * kPiece;
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint32_t wave_in_wg = rfl(threadIdx.x / kWave);
   const uint32_t lead = done.n_slots != 0 ? 1u : 0u;
   if (lead && blockIdx.x == 0) {
     if (threadIdx.x < kWave) complete_iocbs(done, threadIdx.x);
     return;
   }
-  const uint32_t n_waves = (gridDim.x - lead) * (blockDim.x / kWave);
-  const uint32_t per_iocb = TUTTI_IOCB_SLOTS * a.slices;
-  const uint32_t n_items = g.n_slots * per_iocb;  // the host checked this fits 32 bits
+  const uint32_t wgs = gridDim.x - lead, wg = blockIdx.x - lead, wave = rfl(threadIdx.x / kWave);
+  const uint32_t n_waves = wgs * (WG / kWave);
+  const uint64_t n_parts = static_cast<uint64_t>(g.n_slots) * TUTTI_IOCB_SLOTS * a.parts;
+  const uint32_t n_items = static_cast<uint32_t>((n_parts + G - 1) / G);  // the host checked this fits 32 bits
 
-  uint32_t it = (blockIdx.x - lead) * (blockDim.x / kWave) + wave_in_wg;
-  if (it >= n_items) return;
-  IoItem cur = io_decode<U>(g, a, it, per_iocb, lane);
-  for (;;) {
-    const uint32_t nit = it + n_waves;
-    const bool more = nit < n_items;
-    const bool whole = cur.src != nullptr && cur.in_ctx + kSlice <= cur.len;
-    const uint32_t o0 = cur.in_ctx + lane * 16u;
-    u32x4 buf[U];
-    if (whole) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) buf[u] = ld16<3>(cur.src + o0 + u * (kWave * 16u));
+  // (as first_item: a budgeted launch deals neighbouring items to neighbouring workgroups)
+  for (uint64_t it = WG == kWgThreads ? wg * (WG / kWave) + wave : wave * wgs + wg; it < n_items;
+       it += kBatch * static_cast<uint64_t>(n_waves)) {
+    IoPart d;
+    d.src = d.dst = 0;
+    d.len = 0;
+    const uint64_t mine = it + static_cast<uint64_t>(lane / G) * n_waves;
+    if (mine * G + lane % G < n_parts) {
+      // part number / parts per context without a 64-bit division (see move_pieces)
+      const uint32_t q = static_cast<uint32_t>(mine) / a.parts;
+      const uint32_t rest = (static_cast<uint32_t>(mine) - q * a.parts) * G + lane % G;
+      const uint32_t q2 = rest / a.parts;
+      d = io_decode(g, a, q * G + q2, rest - q2 * a.parts, kPart);
     }
-    IoItem nxt = cur;
-    if (more) nxt = io_decode<U>(g, a, nit, per_iocb, lane);
-    if (whole) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) st16<3>(cur.dst + o0 + u * (kWave * 16u), buf[u]);
-    } else if (cur.src != nullptr) {  // ragged last slice of a context
-      for (int u = 0; u < U; ++u) {
-        const uint32_t o = o0 + u * (kWave * 16u);
-        if (o < cur.len) st16<3>(cur.dst + o, ld16<3>(cur.src + o));
-      }
+    const uint64_t live = __ballot(d.len != 0), whole = __ballot(d.len == kPart);
+    if (live == 0) continue;
+    d.src = or_first(d.src, live);
+    const uint64_t left = (n_items - it + n_waves - 1) / n_waves;
+#pragma unroll 1
+    for (uint32_t i = 0; i < kBatch && i < left; ++i) {
+      constexpr uint64_t kAll = (1ull << G) - 1;
+      if ((live >> (i * G) & kAll) == 0) continue;
+      move_decoded<U, G, 3>(
+          i, whole, d.len, [&](uint32_t p, uint32_t o) { return as_global(readlane_u64(d.src, i * G + p)) + o; },
+          [&](uint32_t p, uint32_t o) { return as_global(readlane_u64(d.dst, i * G + p)) + o; });
     }
-    if (!more) break;
-    cur = nxt;
-    it = nit;
   }
 }
 
@@ -1073,8 +1157,6 @@ __global__ __launch_bounds__(WG) void k_sqe_direct(const SqeArgs a, const Direct
 // A block of 12.5 KiB is 13 pieces instead of four slices of which the last moves 512 of its 4096 bytes; four blocks
 // of 1 KiB are one item instead of four.
 // ------------------------------------------------------------------------------------------
-constexpr uint32_t kPiece = kWave * 16u;
-
 struct MoveArgs {
   unsigned char *k_base;
   unsigned char *v_base;
@@ -1102,6 +1184,7 @@ struct MoveArgs {
   // staging bytes [it*slice, (it+1)*slice) whatever the extents are; items_bound = 2 * table_len * slices
   uint32_t dense;
   uint32_t items_bound;
+  uint32_t pause;  // restore: how long the first stores are held back (hold_back)
   // workgroup -> item mapping: 0 = workgroup b starts at item 4b (neighbouring workgroups, which the
   // dispatcher deals round-robin to the 8 XCDs, take neighbouring 16 KiB); 1 = each XCD takes one
   // contiguous eighth of the copy workgroups' items
@@ -1120,6 +1203,14 @@ struct MoveArgs {
 };
 
 
+struct LayoutArgs {
+  const uint32_t *n_blocks;
+  tutti_extent *extents;
+  uint64_t *totals;
+  ScanGeom geom;
+  uint32_t n_req;
+};
+
 // The workgroup index used for item numbering (see MoveArgs::xcd_contiguous).
 __device__ __forceinline__ uint32_t item_wg(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs) {
   const uint32_t b = wg;  // index among the copy workgroups
@@ -1132,10 +1223,11 @@ __device__ __forceinline__ uint32_t item_wg(const MoveArgs &a, uint32_t wg, uint
 // The first item of this wavefront; its others follow n_waves apart.  Whole-GPU launches: the wavefronts of a workgroup
 // take neighbouring items.  CU-budgeted launches (large workgroups): neighbouring workgroups do, so that a job of few
 // items is spread over all the budgeted compute units.
+template <int WG>
 __device__ __forceinline__ uint32_t first_item(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs) {
   const uint32_t wave = rfl(threadIdx.x / kWave);
-  if (blockDim.x == kBudgetWgThreads) return wave * copy_wgs + wg;
-  return item_wg(a, wg, copy_wgs) * (blockDim.x / kWave) + wave;
+  if (WG == kBudgetWgThreads) return wave * copy_wgs + wg;
+  return item_wg(a, wg, copy_wgs) * (WG / kWave) + wave;
 }
 
 constexpr int kPack = 0;   // pool -> object
@@ -1164,17 +1256,13 @@ struct Item {
   uint32_t kind;
 };
 
-// Wave-uniform words (block ids, visiting order) are fetched through the scalar (constant) path: one s_load per
-// wavefront, counted apart from the vector loads and stores in flight, so waiting for it does not wait for them.
-typedef const __attribute__((address_space(4))) uint32_t *const_u32_ptr;
-
 // SEP: the extents came from the caller (lds_from_caller_extents): items are numbered by blk_off, the table is
 // indexed by the request's own table_off, and requests that cannot be honoured already have a zero-sized object.
 // ORD: the units are visited in the order a.visit lists (all K blocks, then all V blocks, each in that order);
 // a listed position that is not a block of a request that takes part is passed over.
 // u: (block, kind) unit in staging order; s: its slice, piece or tile; `report`: this thread reports what it finds out
-// of order with a unit's first part.
-template <bool SEP, bool ORD = false>
+// of order with a unit's first part.  UNI: u and s are wave-uniform.
+template <bool UNI, bool SEP, bool ORD = false>
 __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t u, uint32_t s,
                                             bool report) {
   Item d;
@@ -1184,33 +1272,30 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
   uint32_t r, toff;
   if (ORD) {
     d.kind = u >= a.table_len ? 1u : 0u;
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Wold-style-cast"
-    const_u32_ptr vis = (const_u32_ptr)a.visit;
-#pragma clang diagnostic pop
+    const_u32_ptr vis = as_const(a.visit);
     const uint32_t pos = vis[rfl(u - d.kind * a.table_len)];  // wave-uniform index: one scalar load
-    if (pos >= l.table_off[n_req]) {  // beyond the blocks of the requests that take part
+    if (pos >= uni<UNI>(l.table_off[n_req])) {  // beyond the blocks of the requests that take part
       d.obj_ptr = nullptr;
       d.obj_blk = nullptr;
       d.obj_bytes = 0;
       d.tab_idx = d.n = d.j = 0;
       return d;
     }
-    r = find_owner(l.table_off, n_req, pos);
-    toff = l.table_off[r];
-    d.n = l.table_off[r + 1] - toff;
+    r = find_owner<UNI>(l.table_off, n_req, pos);
+    toff = uni<UNI>(l.table_off[r]);
+    d.n = uni<UNI>(l.table_off[r + 1]) - toff;
     d.j = pos - toff;
   } else {
-    r = find_owner(off, n_req, u >> 1);
-    toff = off[r];
-    d.n = off[r + 1] - toff;
+    r = find_owner<UNI>(off, n_req, u >> 1);
+    toff = uni<UNI>(off[r]);
+    d.n = uni<UNI>(off[r + 1]) - toff;
     const uint32_t v = u - 2u * toff;
     d.kind = v >= d.n ? 1u : 0u;
     d.j = v - d.kind * d.n;
   }
-  d.obj_bytes = l.obj_bytes[r];
-  d.tab_idx = (SEP ? l.table_off[r] : toff) + d.j;
-  const uint64_t stage_off = l.stage_off[r];
+  d.obj_bytes = uni<UNI>(l.obj_bytes[r]);
+  d.tab_idx = (SEP ? uni<UNI>(l.table_off[r]) : toff) + d.j;
+  const uint64_t stage_off = uni<UNI>(l.stage_off[r]);
   if (a.direct) {
     // same arithmetic as the context's file offset (direct_entry_quarter), then the I/O kernel's checks
     const uint64_t file_off = (2ull * a.layer + d.kind) * d.obj_bytes + static_cast<uint64_t>(d.j) * a.block_bytes;
@@ -1242,22 +1327,20 @@ template <bool SEP, bool ORD = false>
 __device__ __forceinline__ Item decode_item(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t it,
                                             uint32_t lane) {
   const uint32_t u = it / a.slices_per_block;
-  return decode_unit<SEP, ORD>(a, l, n_req, u, it - u * a.slices_per_block, lane == 0);
+  return decode_unit<false, SEP, ORD>(a, l, n_req, u, it - u * a.slices_per_block, lane == 0);
 }
 
 // Block id of an item through the scalar (constant) path: the index is wave-uniform, so this is
 // one s_load that overlaps the vector loads and stores of the item before it.
 __device__ __forceinline__ uint32_t load_block_id(const MoveArgs &a, const Item &d) {
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Wold-style-cast"
-  const_u32_ptr tab = (const_u32_ptr)a.table;
-#pragma clang diagnostic pop
+  const_u32_ptr tab = as_const(a.table);
   const uint32_t idx = __builtin_amdgcn_readfirstlane(d.tab_idx);  // uniform by construction
   const bool ok = __builtin_amdgcn_readfirstlane(d.obj_ptr != nullptr && idx < a.table_len ? 1 : 0) != 0;
   return ok ? tab[idx] : a.num_blocks;
 }
 
-template <int DIR, bool HND, int U, int NT>
+// ORD: the block need not be a whole number of slices (the others are moved as pieces then).
+template <int DIR, bool HND, int U, int NT, bool ORD>
 __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint32_t id, uint32_t lane) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   if (d.obj_ptr == nullptr) return;
@@ -1266,7 +1349,7 @@ __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint3
     unsigned char *blk_ptr = (d.kind ? a.v_base : a.k_base) + static_cast<uint64_t>(id) * a.block_stride;
     unsigned char *obj_blk = d.obj_blk;
     const uint32_t o0 = in_blk + lane * 16u;  // this lane's first 16 bytes, canonical offset in the block
-    if (in_blk + kSlice <= a.block_bytes) {
+    if (!ORD || in_blk + kSlice <= a.block_bytes) {
       // whole slice inside the block: U independent loads in flight, then U stores
       u32x4 buf[U];
 #pragma unroll
@@ -1309,6 +1392,16 @@ __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint3
   }
 }
 
+// A whole-GPU restore reads its first slices, up to 32 MiB, in one burst; stores that start among those reads cost more
+// (the memory turns between reading and writing) than the same stores a little later.  So where a launch fills the chip
+// its first stores are held back for `pause` * 512 clocks (0.21 us each) behind the scan's barrier; the lines lie where
+// the sweep below crosses, in restore_pause.  Restore of one request, cold, in us, pause 0 / 2 / 6: 5K tokens (0.63 of
+// the chip's wavefronts) 7.8 / 8.1 / 8.4, 6K (0.75) 9.9 / 9.0 / 9.4, 7K (0.88) 12.0 / 12.2 / 10.5, 8K (one item each)
+// 13.3 / 13.5 / 11.8, 12K 18.7 / 18.7 / 17.3, 16K 23.3 / 23.5 / 23.0, 32K 43.8 / 43.7 / 43.9.
+__device__ __forceinline__ void hold_back(uint32_t pause) {
+  for (uint32_t i = 0; i < pause; ++i) __builtin_amdgcn_s_sleep(8);
+}
+
 // First item of a wavefront in an unpack from dense staging: its source bytes do not depend on the extents,
 // so their loads can be in flight while the workgroup is still fetching or scanning the extents.  (Whole-GPU launches
 // only: under a CU budget a wavefront has many items, and 16 loads in flight need the registers.)
@@ -1319,11 +1412,11 @@ struct Preload {
   bool valid;
 };
 
-template <int U, int NT>
+template <int U, int NT, int WG>
 __device__ __forceinline__ Preload<U> preload_first(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint32_t it = first_item(a, wg, copy_wgs);
+  const uint32_t it = first_item<WG>(a, wg, copy_wgs);
   Preload<U> p;
   p.valid = a.dense != 0 && it < a.items_bound && (static_cast<uint64_t>(it) + 1) * kSlice <= a.stage_cap;
   p.src = a.stage + static_cast<uint64_t>(it) * kSlice;
@@ -1365,21 +1458,21 @@ template <bool SEP, bool ORD = false>
 __device__ __forceinline__ uint32_t count_units(const MoveArgs &a, const ReqLds &l, uint32_t n_req) {
   if (ORD) return 2u * a.table_len;  // every listed position, for K and for V
   if (a.direct) {
-    const uint64_t units = 2ull * l.table_off[n_req];
+    const uint64_t units = 2ull * rfl(l.table_off[n_req]);
     return static_cast<uint32_t>(units < a.ctx_cap ? units : a.ctx_cap);
   }
-  return 2u * (SEP ? l.blk_off[n_req] : l.table_off[n_req]);
+  return 2u * rfl(SEP ? l.blk_off[n_req] : l.table_off[n_req]);
 }
 
-template <int DIR, bool HND, int U, int NT, bool SEP, bool ORD = false>
+template <int DIR, bool HND, int U, int NT, int WG, bool SEP, bool ORD = false>
 __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                            uint32_t copy_wgs, const Preload<U> &pre) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint32_t n_waves = copy_wgs * (blockDim.x / kWave);
+  const uint32_t n_waves = copy_wgs * (WG / kWave);
   const uint32_t n_items = count_units<SEP, ORD>(a, l, n_req) * a.slices_per_block;
 
-  uint32_t it = first_item(a, wg, copy_wgs);
+  uint32_t it = first_item<WG>(a, wg, copy_wgs);
   if (it >= n_items) return;
   Item cur = decode_item<SEP, ORD>(a, l, n_req, it, lane);
   uint32_t id = load_block_id(a, cur);
@@ -1402,7 +1495,7 @@ __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uin
     if (preloaded)
       store_preloaded<HND, U, NT>(a, cur, id, lane, pre);
     else
-      move_one<DIR, HND, U, NT>(a, cur, id, lane);
+      move_one<DIR, HND, U, NT, ORD>(a, cur, id, lane);
     first = false;
     if (!more) break;
     cur = nxt;
@@ -1411,39 +1504,171 @@ __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uin
   }
 }
 
-constexpr int kWaitVmcnt0 = 0x0f70;  // operand of s_waitcnt: vector accesses done, the other counters as they are
+// ------------------------------------------------------------------------------------------
+// One request (the whole prefix of one prompt, the common call).  Everything an item needs follows from the block count,
+// one scalar load away: there is no scan, nothing goes through LDS, no wavefront waits for another one, and the
+// arguments fit the scalar registers.  Through the general path the first store of a wavefront stands behind the scan, a
+// barrier, a binary search in LDS and a dozen reloads of spilled arguments.  Kernel time in us, general path / this one:
+// restore of 256 KiB 3.7 / 2.7, of 4 MiB (1K tokens) 4.8 / 4.1; save of 24 MiB 11.4 / 10.7, of 128 MiB (32K tokens)
+// 46.9 / 45.6, of 512 MiB 185.6 / 183.4.  A restore that fills half the chip or more takes the general path: its stores
+// would start among the other wavefronts' first loads (hold_back), 32K tokens 43.8 / 44.9.
+// ------------------------------------------------------------------------------------------
+struct OneReq {
+  unsigned char *base;  // the staging buffer, or the request's file
+  uint64_t lo;          // where the K object starts in it; the V object follows obj_bytes later
+  uint64_t obj_bytes;
+  uint64_t room;        // size of the file (0: the store has no such file)
+  uint32_t n;           // blocks to move (0: the request is skipped)
+  uint32_t units;       // (block, kind) units to move
+};
 
-// The value that lane `src` holds, in scalar registers.
-__device__ __forceinline__ uint32_t readlane_u32(uint32_t v, uint32_t src) {
-  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), static_cast<int>(src)));
+// The request's extent: published by workgroup 0, put into LDS by the workgroups that write entries (which alone pass
+// the barrier).  Staged: a request whose blocks run beyond the table, or whose objects do not fit, is skipped and
+// reported.  Direct-to-block mode (file_id != nullptr): a block beyond the file, or every block if the store has no
+// such file, is skipped and reported by the loop.
+__device__ __forceinline__ OneReq one_request(const MoveArgs &m, const LayoutArgs &a, const ReqLds &l, bool publish,
+                                              bool entries, const uint32_t *file_id, const FileArgs f) {
+  OneReq q;
+  const uint32_t n = as_const(a.n_blocks)[0];
+  const uint64_t obj = static_cast<uint64_t>(n) * a.geom.block_bytes + obj_pad(a.geom, n);
+  const bool cut = !file_id && n > m.table_len;
+  uint64_t at = 0;
+  q.base = m.stage;
+  q.lo = 0;
+  q.obj_bytes = obj;
+  q.room = m.stage_cap;
+  q.n = cut ? 0 : n;
+  q.units = 2u * q.n;
+  uint32_t flags = 0;
+  if (file_id) {
+    const uint32_t fid = as_const(file_id)[0], rel = fid - f.first_file_id;
+    const bool has_file = fid >= f.first_file_id && rel < f.n_files;
+    at = has_file ? static_cast<uint64_t>(rel) * f.file_stride : kNoFile;
+    if (has_file) q.base += at;
+    q.lo = 2ull * m.layer * obj;
+    q.room = has_file ? f.file_stride : 0;
+    q.units = static_cast<uint32_t>(2ull * n < m.ctx_cap ? 2ull * n : m.ctx_cap);
+  } else {
+    if (cut) flags |= TUTTI_ST_BAD_EXTENT;
+    if (!cut && n != 0 && obj > m.stage_cap / 2) {
+      flags |= TUTTI_ST_STAGE_CAP;
+      q.n = q.units = 0;
+    }
+  }
+  if (entries) {
+    if (threadIdx.x == 0) {
+      const uint32_t chunks = static_cast<uint32_t>(obj_chunks(a.geom, obj));
+      l.stage_off[0] = at;
+      l.obj_bytes[0] = obj;
+      l.table_off[0] = l.sqe_base[0] = 0;
+      l.table_off[1] = cut ? 0u : n;
+      l.sqe_base[1] = 2u * chunks;
+      if (publish) {
+        tutti_extent e;
+        e.stage_off = 0;
+        e.obj_bytes = obj;
+        e.n_blocks = n;
+        e.n_chunks = chunks;
+        e.sqe_base = 0;
+        e.table_off = 0;
+        a.extents[0] = e;
+        a.totals[0] = 2 * obj;
+        a.totals[1] = 2 * obj_chunks(a.geom, obj);
+        if (flags != 0 && m.status) atomicOr(m.status, flags);
+      }
+    }
+    __syncthreads();
+  }
+  return q;
 }
-__device__ __forceinline__ uint64_t readlane_u64(uint64_t v, uint32_t src) {
-  const uint32_t lo = readlane_u32(static_cast<uint32_t>(v), src);
-  return (static_cast<uint64_t>(readlane_u32(static_cast<uint32_t>(v >> 32), src)) << 32) | lo;
-}
-typedef __attribute__((address_space(1))) unsigned char *global_u8_ptr;
-__device__ __forceinline__ unsigned char *as_global(uint64_t address) {
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Wold-style-cast"
-  return (unsigned char *)(global_u8_ptr)address;  // a global pointer, so that the accesses are global ones
-#pragma clang diagnostic pop
+
+// The copy loop of one request whose blocks are a whole number of slices; the next item's block id is requested before
+// the current item's loads and stores are issued.
+template <int DIR, bool HND, int U, int NT, int WG>
+__device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q, uint32_t wg, uint32_t copy_wgs,
+                                             const Preload<U> &pre) {
+  constexpr uint32_t kSlice = U * kPiece;
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t n_waves = copy_wgs * (WG / kWave);
+  const uint32_t S = a.slices_per_block;
+  const uint32_t n_items = q.units * S;
+  const const_u32_ptr table = as_const(a.table);
+  uint32_t it = first_item<WG>(a, wg, copy_wgs);
+  if (it >= n_items) return;
+  uint32_t u = it / S;
+  uint32_t j = u >= q.n ? u - q.n : u;
+  uint32_t id = j < a.table_len ? table[j] : a.num_blocks;
+  bool first = DIR == kUnpack && pre.valid;
+  for (;;) {
+    const uint32_t kind = u >= q.n ? 1u : 0u, part = it - u * S;
+    const uint32_t nit = it + n_waves;
+    const bool more = nit < n_items && nit > it;
+    uint32_t nu = u, nj = j, nid = a.num_blocks;
+    if (more) {
+      nu = nit / S;
+      nj = nu >= q.n ? nu - q.n : nu;
+      if (nj < a.table_len) nid = table[nj];
+    }
+    const uint64_t at = q.lo + kind * q.obj_bytes + static_cast<uint64_t>(j) * a.block_bytes;
+    const bool fits = !a.direct || (at + a.block_bytes >= at && at + a.block_bytes <= q.room);
+    if (fits && id < a.num_blocks) {
+      unsigned char *blk = (kind ? a.v_base : a.k_base) + static_cast<uint64_t>(id) * a.block_stride;
+      unsigned char *obj = q.base + at;
+      const uint32_t o0 = part * kSlice + lane * 16u;
+      if (DIR == kUnpack && first) {
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          const uint32_t o = o0 + k * kPiece;
+          st16<NT>(blk + (HND ? hnd_offset(o, a.row_bytes, a.block_tokens, a.num_kv_heads) : o), pre.buf[k]);
+        }
+      } else {
+        u32x4 buf[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          const uint32_t o = o0 + k * kPiece;
+          buf[k] = ld16<NT>(DIR == kPack ? blk + (HND ? hnd_offset(o, a.row_bytes, a.block_tokens, a.num_kv_heads) : o)
+                                         : obj + o);
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+          const uint32_t o = o0 + k * kPiece;
+          st16<NT>(DIR == kPack ? obj + o
+                                : blk + (HND ? hnd_offset(o, a.row_bytes, a.block_tokens, a.num_kv_heads) : o),
+                   buf[k]);
+        }
+      }
+    } else if (lane == 0 && part == 0 && a.status) {
+      atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
+    }
+    if (DIR == kPack && !a.direct && j + 1 == q.n && part + 1 == S) {  // zero the object's tail up to its aligned size
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      for (uint64_t o = static_cast<uint64_t>(q.n) * a.block_bytes + lane * 16ull; o < q.obj_bytes; o += kPiece)
+        st16<0>(q.base + kind * q.obj_bytes + o, zero);
+    }
+    if (!more) break;
+    first = false;
+    it = nit;
+    u = nu;
+    j = nj;
+    id = nid;
+  }
 }
 
 // The copy loop for blocks that are no whole number of slices.  A wavefront decodes its next 64 pieces at once, one per
 // lane (owner by binary search, block id, both addresses), so that the table loads of 64/U items are in flight together
 // and an item costs a few lane reads; then it moves them item by item.
-template <int DIR, bool HND, int U, int NT, bool SEP>
+template <int DIR, bool HND, int U, int NT, int WG, bool SEP>
 __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                             uint32_t copy_wgs) {
   constexpr uint32_t kBatch = kWave / U;  // items decoded at once
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint32_t n_waves = copy_wgs * (blockDim.x / kWave);
+  const uint32_t n_waves = copy_wgs * (WG / kWave);
   const uint32_t ppb = a.slices_per_block;
   const uint64_t n_pieces = static_cast<uint64_t>(count_units<SEP>(a, l, n_req)) * ppb;
   const uint32_t n_items = static_cast<uint32_t>((n_pieces + U - 1) / U);
   const uint32_t in_piece = lane * 16u;
 
-  for (uint64_t it = first_item(a, wg, copy_wgs); it < n_items;
+  for (uint64_t it = first_item<WG>(a, wg, copy_wgs); it < n_items;
        it += kBatch * static_cast<uint64_t>(n_waves)) {
     // ---- decode: lane -> piece lane % U of item it + (lane / U) * n_waves
     uint64_t obj = 0, blk = 0;        // where the piece sits on the two sides (head-major: blk = its block)
@@ -1455,7 +1680,7 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
       const uint32_t q = static_cast<uint32_t>(mine) / ppb;
       const uint32_t rest = (static_cast<uint32_t>(mine) - q * ppb) * U + lane % U;
       const uint32_t q2 = rest / ppb;
-      const Item d = decode_unit<SEP>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
+      const Item d = decode_unit<false, SEP>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
       if (d.obj_ptr != nullptr) {
         const uint32_t id = d.tab_idx < a.table_len ? a.table[d.tab_idx] : a.num_blocks;
         off = d.s * kPiece;
@@ -1483,39 +1708,27 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
         for (uint64_t o = in_piece; o < n; o += kPiece) st16<0>(end + o, zero);
       }
     }
-    const uint64_t whole = __ballot(len == kPiece);
+    const uint64_t live = __ballot(len != 0), whole = __ballot(len == kPiece);
+    if (live == 0) continue;
+    if (len == 0) off = 0;
+    if (DIR == kPack)
+      blk = or_first(blk, live);
+    else
+      obj = or_first(obj, live);
     // ---- move
     const uint64_t left = (n_items - it + n_waves - 1) / n_waves;
+#pragma unroll 1
     for (uint32_t i = 0; i < kBatch && i < left; ++i) {
-      // the two sides of piece k of the item (worked out where they are used: 2 * U addresses at once would not fit)
-      const auto obj_at = [&](uint32_t k) { return as_global(readlane_u64(obj, i * U + k)) + in_piece; };
-      const auto blk_at = [&](uint32_t k) {
+      if ((live >> (i * U) & ((1ull << U) - 1)) == 0) continue;
+      const auto obj_at = [&](uint32_t k, uint32_t o) { return as_global(readlane_u64(obj, i * U + k)) + o; };
+      const auto blk_at = [&](uint32_t k, uint32_t o) {
         return as_global(readlane_u64(blk, i * U + k)) +
-               (HND ? hnd_offset(readlane_u32(off, i * U + k) + in_piece, a.row_bytes, a.block_tokens, a.num_kv_heads)
-                    : in_piece);
+               (HND ? hnd_offset(readlane_u32(off, i * U + k) + o, a.row_bytes, a.block_tokens, a.num_kv_heads) : o);
       };
-      u32x4 buf[U];
-      constexpr uint64_t kAll = (1ull << U) - 1;
-      if ((whole >> (i * U) & kAll) == kAll) {
-#pragma unroll
-        for (uint32_t k = 0; k < U; ++k) buf[k] = ld16<NT>(DIR == kPack ? blk_at(k) : obj_at(k));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (uint32_t k = 0; k < U; ++k) st16<NT>(DIR == kPack ? obj_at(k) : blk_at(k), buf[k]);
-        asm volatile("; whole item");  // (the marks keep the compiler from merging the paths' last stores, which
-                                       // would put a wait for all other stores in front of the merged one)
-      } else {  // a piece is short (the last of its block) or skipped
-#pragma unroll
-        for (uint32_t k = 0; k < U; ++k)
-          if (in_piece < readlane_u32(len, i * U + k)) buf[k] = ld16<NT>(DIR == kPack ? blk_at(k) : obj_at(k));
-        // one wait for all loads: left to itself the compiler waits in front of each guarded store, and with that
-        // for the stores before it (loads and stores share a counter)
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-#pragma unroll
-        for (uint32_t k = 0; k < U; ++k)
-          if (in_piece < readlane_u32(len, i * U + k)) st16<NT>(DIR == kPack ? obj_at(k) : blk_at(k), buf[k]);
-        asm volatile("; guarded item");
-      }
+      if (DIR == kPack)
+        move_decoded<U, U, NT>(i, whole, len, blk_at, obj_at);
+      else
+        move_decoded<U, U, NT>(i, whole, len, obj_at, blk_at);
     }
   }
 }
@@ -1636,18 +1849,10 @@ __device__ __forceinline__ void move_items_hnd_lds(const MoveArgs a, const ReqLd
 
 __host__ __device__ constexpr uint32_t align16(uint32_t x) { return (x + 15u) & ~15u; }
 
-struct LayoutArgs {
-  const uint32_t *n_blocks;
-  tutti_extent *extents;
-  uint64_t *totals;
-  ScanGeom geom;
-  uint32_t n_req;
-};
-
 __global__ __launch_bounds__(kWgThreads) void k_layout(const LayoutArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, a.n_req);
-  scan_extents<kWgThreads>(a.geom, a.n_blocks, a.n_req, l, a.extents, a.totals, 0xffffffffu, nullptr, true, nullptr,
+  scan_extents<kWgThreads, kMany>(a.geom, a.n_blocks, a.n_req, l, a.extents, a.totals, 0xffffffffu, nullptr, true, nullptr,
                            FileArgs{0, 0, 0}, [] {});
 }
 
@@ -1668,12 +1873,12 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_move(const Mo
   const ReqLds l = carve_lds(smem, n_req, true);
   Preload<U> pre;
   pre.valid = false;
-  if (DIR == kUnpack && !PIECES && WG == kWgThreads) pre = preload_first<U, NT>(a, blockIdx.x, gridDim.x);
+  if (DIR == kUnpack && !PIECES && WG == kWgThreads) pre = preload_first<U, NT, WG>(a, blockIdx.x, gridDim.x);
   lds_from_caller_extents(ext, n_req, l, a.table_len, a.block_bytes, a.stage_cap, a.status);
   if (PIECES)
-    move_pieces<DIR, HND, U, NT, true>(a, l, n_req, blockIdx.x, gridDim.x);
+    move_pieces<DIR, HND, U, NT, WG, true>(a, l, n_req, blockIdx.x, gridDim.x);
   else
-    move_items<DIR, HND, U, NT, true>(a, l, n_req, blockIdx.x, gridDim.x, pre);
+    move_items<DIR, HND, U, NT, WG, true>(a, l, n_req, blockIdx.x, gridDim.x, pre);
 }
 
 template <int DIR, int PT, int WG>
@@ -1703,7 +1908,7 @@ struct Roles {
 
 // ORD (restore only): the blocks are visited in the order m.visit lists instead of staging order; the first slices
 // cannot be preloaded then (where they sit depends on the list).
-template <int DIR, bool HND, int U, int NT, int WG, bool ORD = false, bool PIECES = false>
+template <int DIR, bool HND, int U, int NT, int WG, int REQS, bool ORD = false, bool PIECES = false>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const MoveArgs m, const SqeArgs q, const LayoutArgs a, const Roles w) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, a.n_req);
@@ -1712,10 +1917,22 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
   Preload<U> pre;
   pre.valid = false;
   const bool publish = blockIdx.x == 0;  // also an entry-writing workgroup: there is at least one
-  scan_extents<WG>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
+  if constexpr (REQS == kOne) {
+    if (DIR == kUnpack && WG == kWgThreads && copies) pre = preload_first<U, NT, WG>(m, wg, w.copy_wgs);
+    const bool entries = blockIdx.x < w.sqe_wgs;
+    const OneReq one = one_request(m, a, l, publish, entries, nullptr, FileArgs{0, 0, 0});
+    SqeHead one_head;
+    one_head.live = false;
+    if (entries) one_head = sqe_head(q, l, 1, 0);
+    if (copies) move_request<DIR, HND, U, NT, WG>(m, one, wg, w.copy_wgs, pre);
+    if (entries) emit_sqes(q, l, 1, 0, w.sqe_wgs, one_head);
+    return;
+  }
+  scan_extents<WG, REQS>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
                    m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [&] {
-                     if (DIR == kUnpack && !ORD && !PIECES && WG == kWgThreads && copies) pre = preload_first<U, NT>(m, wg, w.copy_wgs);
+                     if (DIR == kUnpack && !ORD && !PIECES && WG == kWgThreads && copies) pre = preload_first<U, NT, WG>(m, wg, w.copy_wgs);
                    });
+  if (REQS == kFew && DIR == kUnpack && !ORD && !PIECES && WG == kWgThreads && copies) hold_back(m.pause);
   SqeHead head;
   head.live = false;
   if (blockIdx.x < w.sqe_wgs) head = sqe_head(q, l, a.n_req, 0);
@@ -1728,9 +1945,9 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
   }
   if (copies) {
     if (PIECES)
-      move_pieces<DIR, HND, U, NT, false>(m, l, a.n_req, wg, w.copy_wgs);
+      move_pieces<DIR, HND, U, NT, WG, false>(m, l, a.n_req, wg, w.copy_wgs);
     else
-      move_items<DIR, HND, U, NT, false, ORD>(m, l, a.n_req, wg, w.copy_wgs, pre);
+      move_items<DIR, HND, U, NT, WG, false, ORD>(m, l, a.n_req, wg, w.copy_wgs, pre);
   }
   if (blockIdx.x < w.sqe_wgs) emit_sqes(q, l, a.n_req, 0, w.sqe_wgs, head);
 }
@@ -1740,13 +1957,13 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
 // alignment units in this mode), which takes two words from memory, the block count and the file id, and no scan.
 // Every wavefront fetches them itself through the scalar path and has its loads in flight while the workgroup's
 // first wavefront scans and the barrier is crossed; move_items checks the address against the decoded one.
-template <int U>
+template <int U, int WG>
 __device__ __forceinline__ Preload<U> preload_first_direct(const MoveArgs &m, const uint32_t *n_blocks,
                                                            const uint32_t *file_id, const FileArgs f, uint32_t wg,
                                                            uint32_t copy_wgs) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint32_t it = first_item(m, wg, copy_wgs);
+  const uint32_t it = first_item<WG>(m, wg, copy_wgs);
   Preload<U> p;
   p.valid = false;
   if (m.block_bytes % kSlice != 0) return p;
@@ -1777,7 +1994,7 @@ __device__ __forceinline__ Preload<U> preload_first_direct(const MoveArgs &m, co
 // next layer's launch carries it along (`done`: the IOCBs an earlier launch on the same stream has executed; when
 // done.n_slots is not 0 the grid has one workgroup more, in front, whose first wavefront completes them and leaves,
 // so a train of layers pays for no kernel boundary between a layer's data and the next layer's).
-template <int DIR, int U, int WG, bool PIECES = false>
+template <int DIR, int U, int WG, int REQS, bool PIECES = false>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(const MoveArgs m, const SqeArgs q, const DirectArgs d,
                                                     const RingArgs g, const RingArgs done, const FileArgs f,
                                                     const LayoutArgs a, const Roles w) {
@@ -1793,30 +2010,43 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
   Preload<U> pre;
   pre.valid = false;
   const bool publish = bx == 0;
+  if constexpr (REQS == kOne) {
+    if (DIR == kUnpack && WG == kWgThreads && copies)
+      pre = preload_first_direct<U, WG>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
+    const bool entries = bx < w.sqe_wgs;
+    const OneReq one = one_request(m, a, l, publish, entries, q.file_id, f);
+    DirectHead one_head;
+    one_head.live = false;
+    if (entries) one_head = iocb_head(g, q, d, l, 1, lead, w.sqe_wgs);
+    if (copies) move_request<DIR, false, U, 3, WG>(m, one, bx - w.copy_first, w.copy_wgs, pre);
+    if (entries) emit_iocbs(g, q, d, l, 1, lead, w.sqe_wgs, one_head);
+    return;
+  }
   // chunk counts only matter for the published extents; the LDS copy gets file starts instead of staging offsets
-  scan_extents<WG>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
+  scan_extents<WG, REQS>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
                    0xffffffffu, nullptr, publish, q.file_id, f, [&] {
                      if (DIR == kUnpack && !PIECES && WG == kWgThreads && copies && a.n_req == 1)
-                       pre = preload_first_direct<U>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
+                       pre = preload_first_direct<U, WG>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
                    });
+  if (REQS == kFew && DIR == kUnpack && !PIECES && WG == kWgThreads && copies) hold_back(m.pause);
   DirectHead head;
   head.live = false;
   if (bx < w.sqe_wgs) head = iocb_head(g, q, d, l, a.n_req, lead, w.sqe_wgs);
   if (copies) {
     if (PIECES)
-      move_pieces<DIR, false, U, 3, false>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);
+      move_pieces<DIR, false, U, 3, WG, false>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);
     else
-      move_items<DIR, false, U, 3, false>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
+      move_items<DIR, false, U, 3, WG, false>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
   }
   if (bx < w.sqe_wgs) emit_iocbs(g, q, d, l, a.n_req, lead, w.sqe_wgs, head);
 }
 
-template <int DIR, int PT, int WG>
+template <int DIR, int PT, int WG, int REQS>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, PT)) void k_layer_lds(const MoveArgs m, const SqeArgs q, const LayoutArgs a, const Roles w) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, a.n_req);
   const bool publish = blockIdx.x == 0;  // also an entry-writing workgroup: there is at least one
-  scan_extents<WG>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
+  scan_extents<WG, REQS>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
                    m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [] {});
   SqeHead head;
   head.live = false;

@@ -1046,6 +1046,44 @@ def test_blocks_moved_as_pieces(orc, H, T, h, d, e):
         for write in (False, True):
             H.check_ring_layer(orc, c, layer=1, write=write, depth=3, first_slot=2, n_slots=1)
         H.check_ring_layer(orc, c, layer=0, write=False, depth=3, first_slot=0, n_slots=1, cu_budget=2)
+        for opcode, budget in ((B.OP_READ, 0), (B.OP_WRITE, 0), (B.OP_READ, 2), (B.OP_WRITE, 2)):
+            H.check_rings(orc, c, 1, opcode, depth=3, first_slot=1, n_slots=2, cu_budget=budget)
+
+
+@pytest.mark.parametrize("n", [0, 1, 1023, 2047, 2048, 2561, 3073, 4096, 4097])
+def test_one_request_on_both_sides_of_each_rule(orc, H, n):
+    """One request of whole-slice blocks (4 KiB: 2n items) around the sizes where the launch changes: half, 5/8 and 3/4
+    of the 8192 wavefronts a whole-GPU launch holds, one pass and several; bad ids, a cut table, a staging buffer that is
+    too small, and the rings with a missing or short file and too few IOCBs."""
+    say("one request of", n, "blocks")
+    rng = np.random.default_rng(8300 + n)
+    N = n + 7
+    table = rng.permutation(N)[:n].astype(np.uint32)
+    for layout in (0, 1):
+        c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=[n], table=table, chunk=65536, L=2, layout=layout,
+                        align=8192, name=f"one{n}l{layout}")
+        H.check_layer_restore(orc, c, layer=1)
+        H.check_layer_save(orc, c, layer=1)
+    H.check_layer_restore(orc, c, layer=1, cu_budget=3)
+    H.check_layer_save(orc, c, layer=1, cu_budget=3)
+    c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=[n], table=table, chunk=65536, L=2, name=f"one{n}ring")
+    n_slots = 2 * n // B.IOCB_SLOTS + 1
+    for write in (False, True):
+        H.check_ring_layer(orc, c, layer=1, write=write, depth=n_slots + 1, first_slot=1, n_slots=n_slots)
+    if n == 0:
+        return
+    H.check_layer_restore(orc, c, table_len=n - 1)
+    H.check_layer_save(orc, c, table_len=n - 1)
+    H.check_layer_restore(orc, c, stage_cap=2 * n * 4096 - 16)
+    H.check_layer_save(orc, c, stage_cap=2 * n * 4096 - 16)
+    H.check_ring_layer(orc, c, layer=1, write=False, depth=n_slots, first_slot=0, n_slots=n_slots, first_file_id=2000)
+    if n > 1023:
+        H.check_ring_layer(orc, c, layer=0, write=False, depth=2, first_slot=1, n_slots=1)
+    bad = table.copy()
+    bad[[0, n // 2, n - 1]] = [N, 0xffffffff, N]
+    c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=[n], table=bad, chunk=65536, L=2, name=f"one{n}bad")
+    H.check_layer_restore(orc, c)
+    H.check_layer_save(orc, c)
 
 
 def test_bad_block_ids_are_skipped_and_reported(orc, H):
