@@ -295,8 +295,12 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
       const uint64_t lds = static_cast<uint64_t>(align16(req_lds_bytes(n_req))) + static_cast<uint64_t>(tile_tokens) * pitch;
       const bool fits = tile_bytes % (L->wg_threads * 16u) == 0 && per_thread >= 1 && per_thread <= 8 &&
                         is_pow2(per_thread) && lds <= kDynLdsCap;
-      // worth it when a row is shorter than a 128-byte line (or when asked for)
-      if (fits && (mode == 2 || row < 128)) {
+      // Worth it when a row is shorter than a 128-byte line (or when asked for).  Under a CU budget a workgroup has one
+      // tile in flight at a time, and only rows of 16 bytes are worth that: through LDS / direct on 32 compute units,
+      // save and restore in us, rows of 64 bytes 88 / 52 and 82 / 51 (66 MB), 32 bytes 88 / 74 and 83 / 65, 16 bytes
+      // 53 / 58 and 49 / 55 (39 MB).
+      const uint32_t short_row = L->wg_threads == kWgThreads ? 128 : 32;
+      if (fits && (mode == 2 || row < short_row)) {
         L->hnd_lds = true;
         L->unroll = per_thread;
         L->tile_lds = tile_tokens * pitch;
