@@ -315,7 +315,7 @@ int tutti_iocb_fill_direct(const tutti_ring *ring, uint32_t first_slot, uint32_t
  * at first_slot: resolves the SGL descriptor the context names (index (addr - sgl_table_addr)/16 into
  * d_sgl_table of n_desc descriptors, whose addr fields must be device addresses here), then moves len
  * bytes between that block and the request's GPU file at file_off (READ: file -> block, WRITE: block ->
- * file), one wavefront per 4 or 8 KiB slice.  A one-wavefront completion kernel enqueued right behind the
+ * file), one wavefront per 4 or 16 KiB.  A one-wavefront completion kernel enqueued right behind the
  * I/O kernel then marks every executed IOCB DONE (done = num_ioctx) and appends its index to the CQ, in slot
  * order: the kernel boundary is the "all contexts finished" event (counting finished contexts with atomics on
  * the IOCB header was measured 28x slower).  max_len bounds the length of any context (the pool's block size).
