@@ -271,7 +271,6 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   m->block_tokens = pool->block_tokens;
   m->num_kv_heads = pool->num_kv_heads;
   m->row_shift = m->head_shift = m->token_shift = m->tile_shift = m->lds_pitch = 0;
-  m->direct = 0;
   m->layer = 0;
   m->file_stride = 0;
   m->ctx_cap = 0;
@@ -954,7 +953,6 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
   rc = fill_move_args(&raw, bb, d_block_table, table_len, store->base, 0, d_status, n_req, cfg->align, false, &L, &m);
   if (rc) return rc;
   m.dense = 0;
-  m.direct = 1;
   m.layer = layer;
   m.file_stride = store->file_stride;
   m.ctx_cap = static_cast<uint64_t>(n_slots) * TUTTI_IOCB_SLOTS;

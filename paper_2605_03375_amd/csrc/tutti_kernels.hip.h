@@ -1189,11 +1189,10 @@ struct MoveArgs {
   // dispatcher deals round-robin to the 8 XCDs, take neighbouring 16 KiB); 1 = each XCD takes one
   // contiguous eighth of the copy workgroups' items
   uint32_t xcd_contiguous;
-  // direct-to-block mode (the rings' one-launch layer path): `stage` is the base of the file store, the
+  // direct-to-block mode (the rings' one-launch layer path, DIRECT below): `stage` is the base of the file store, the
   // per-request staging offsets in LDS hold the start of each request's file in it (kNoFile if the store has no
   // such file), and the object side of (request, kind, block j) is the file offset of the context that
   // emit_iocbs records for it; only the first ctx_cap contexts were recorded and are executed
-  uint32_t direct;
   uint32_t layer;
   uint64_t file_stride;
   uint64_t ctx_cap;
@@ -1243,6 +1242,53 @@ __device__ __forceinline__ uint32_t hnd_offset(uint32_t o, uint32_t row_bytes, u
   return (i * T + t) * row_bytes + w;
 }
 
+// The offsets in the block of a lane's 16-byte units, whose canonical offsets o, o + 1 KiB, o + 2 KiB, ... lie a piece
+// apart: as they are, or (head-major) with the row and head of the first unit found by division and those of the others
+// by addition.  Divided out for 16 units at a time they stand beside 64 data registers, and the kernel spills.
+template <bool HND>
+struct BlockWalk {
+  uint32_t at;
+  __device__ __forceinline__ BlockWalk(const MoveArgs &, uint32_t o) : at(o) {}
+  __device__ __forceinline__ uint32_t next() {
+    const uint32_t now = at;
+    at += kPiece;
+    return now;
+  }
+};
+
+template <>
+struct BlockWalk<true> {
+  uint32_t at, w, i;                          // offset in the block, byte in the row, head
+  uint32_t row, h, dw, di, step, up, around;  // the same in every lane
+  __device__ __forceinline__ BlockWalk(const MoveArgs &a, uint32_t o) : row(a.row_bytes), h(a.num_kv_heads) {
+    const uint32_t r = o / row, t = r / h, rows = kPiece / row, tokens = rows / h;
+    w = o - r * row;
+    i = r - t * h;
+    at = (i * a.block_tokens + t) * row + w;
+    dw = kPiece - rows * row;
+    di = rows - tokens * h;
+    step = (di * a.block_tokens + tokens) * row + dw;
+    up = (a.block_tokens - 1) * row;           // the next head's row instead of `row` bytes further on
+    around = row - h * a.block_tokens * row;   // the next token's first head instead of head h
+  }
+  __device__ __forceinline__ uint32_t next() {
+    const uint32_t now = at;
+    at += step;
+    w += dw;
+    i += di;
+    if (w >= row) {
+      w -= row;
+      i += 1;
+      at += up;
+    }
+    if (i >= h) {  // i is below 2h: both addends are below h, plus one
+      i -= h;
+      at += around;
+    }
+    return now;
+  }
+};
+
 // Description of one slice, piece or tile: where it sits on the object side and which block-table entry names the pool
 // side.  Wave-uniform, except that the pieces of an item are decoded one per lane.
 struct Item {
@@ -1262,7 +1308,7 @@ struct Item {
 // a listed position that is not a block of a request that takes part is passed over.
 // u: (block, kind) unit in staging order; s: its slice, piece or tile; `report`: this thread reports what it finds out
 // of order with a unit's first part.  UNI: u and s are wave-uniform.
-template <bool UNI, bool SEP, bool ORD = false>
+template <bool UNI, bool SEP, bool ORD, bool DIRECT>
 __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t u, uint32_t s,
                                             bool report) {
   Item d;
@@ -1296,7 +1342,7 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
   d.obj_bytes = uni<UNI>(l.obj_bytes[r]);
   d.tab_idx = (SEP ? uni<UNI>(l.table_off[r]) : toff) + d.j;
   const uint64_t stage_off = uni<UNI>(l.stage_off[r]);
-  if (a.direct) {
+  if (DIRECT) {
     // same arithmetic as the context's file offset (direct_entry_quarter), then the I/O kernel's checks
     const uint64_t file_off = (2ull * a.layer + d.kind) * d.obj_bytes + static_cast<uint64_t>(d.j) * a.block_bytes;
     const uint64_t end = file_off + a.block_bytes;
@@ -1323,11 +1369,11 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
   return d;
 }
 
-template <bool SEP, bool ORD = false>
+template <bool SEP, bool ORD = false, bool DIRECT = false>
 __device__ __forceinline__ Item decode_item(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t it,
                                             uint32_t lane) {
   const uint32_t u = it / a.slices_per_block;
-  return decode_unit<false, SEP, ORD>(a, l, n_req, u, it - u * a.slices_per_block, lane == 0);
+  return decode_unit<false, SEP, ORD, DIRECT>(a, l, n_req, u, it - u * a.slices_per_block, lane == 0);
 }
 
 // Block id of an item through the scalar (constant) path: the index is wave-uniform, so this is
@@ -1340,7 +1386,7 @@ __device__ __forceinline__ uint32_t load_block_id(const MoveArgs &a, const Item 
 }
 
 // ORD: the block need not be a whole number of slices (the others are moved as pieces then).
-template <int DIR, bool HND, int U, int NT, bool ORD>
+template <int DIR, bool HND, int U, int NT, bool ORD, bool DIRECT>
 __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint32_t id, uint32_t lane) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   if (d.obj_ptr == nullptr) return;
@@ -1352,22 +1398,11 @@ __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint3
     if (!ORD || in_blk + kSlice <= a.block_bytes) {
       // whole slice inside the block: U independent loads in flight, then U stores
       u32x4 buf[U];
+      BlockWalk<HND> in_pool(a, o0);
 #pragma unroll
-      for (int k = 0; k < U; ++k) {
-        const uint32_t o = o0 + k * (kWave * 16u);
-        if (DIR == kPack)
-          buf[k] = ld16<NT>(blk_ptr + (HND ? hnd_offset(o, a.row_bytes, a.block_tokens, a.num_kv_heads) : o));
-        else
-          buf[k] = ld16<NT>(obj_blk + o);
-      }
+      for (int k = 0; k < U; ++k) buf[k] = ld16<NT>(DIR == kPack ? blk_ptr + in_pool.next() : obj_blk + o0 + k * kPiece);
 #pragma unroll
-      for (int k = 0; k < U; ++k) {
-        const uint32_t o = o0 + k * (kWave * 16u);
-        if (DIR == kPack)
-          st16<NT>(obj_blk + o, buf[k]);
-        else
-          st16<NT>(blk_ptr + (HND ? hnd_offset(o, a.row_bytes, a.block_tokens, a.num_kv_heads) : o), buf[k]);
-      }
+      for (int k = 0; k < U; ++k) st16<NT>(DIR == kPack ? obj_blk + o0 + k * kPiece : blk_ptr + in_pool.next(), buf[k]);
     } else {
       // ragged last slice of a block: one guarded 16-byte move at a time
       for (int k = 0; k < U; ++k) {
@@ -1384,7 +1419,7 @@ __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint3
   } else if (lane == 0 && d.s == 0 && a.status) {
     atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
   }
-  if (DIR == kPack && !a.direct && d.j + 1 == d.n && d.s + 1 == a.slices_per_block) {
+  if (DIR == kPack && !DIRECT && d.j + 1 == d.n && d.s + 1 == a.slices_per_block) {
     // zero the tail of the object up to its aligned size (fewer than `align` bytes)
     const uint64_t used = static_cast<uint64_t>(d.n) * a.block_bytes;
     const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -1436,12 +1471,9 @@ __device__ __forceinline__ void store_preloaded(const MoveArgs &a, const Item &d
   if (d.obj_ptr == nullptr) return;
   if (id < a.num_blocks) {
     unsigned char *blk_ptr = (d.kind ? a.v_base : a.k_base) + static_cast<uint64_t>(id) * a.block_stride;
-    const uint32_t o0 = d.s * kSlice + lane * 16u;
+    BlockWalk<HND> in_pool(a, d.s * kSlice + lane * 16u);
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const uint32_t o = o0 + k * (kWave * 16u);
-      st16<NT>(blk_ptr + (HND ? hnd_offset(o, a.row_bytes, a.block_tokens, a.num_kv_heads) : o), p.buf[k]);
-    }
+    for (int k = 0; k < U; ++k) st16<NT>(blk_ptr + in_pool.next(), p.buf[k]);
   } else if (lane == 0 && d.s == 0 && a.status) {
     atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
   }
@@ -1454,27 +1486,27 @@ __device__ __forceinline__ void store_preloaded(const MoveArgs &a, const Item &d
 // Number of (block, kind) units of a copy.  Staged mode: the scan (or the loader of caller-made extents) has already cut
 // the requests at table_len blocks.  Direct-to-block mode: one unit per recorded context.  The host checked that
 // the bound (2 * table_len, or the contexts the IOCBs hold) times the slices per block fits 32 bits.
-template <bool SEP, bool ORD = false>
+template <bool SEP, bool ORD = false, bool DIRECT = false>
 __device__ __forceinline__ uint32_t count_units(const MoveArgs &a, const ReqLds &l, uint32_t n_req) {
   if (ORD) return 2u * a.table_len;  // every listed position, for K and for V
-  if (a.direct) {
+  if (DIRECT) {
     const uint64_t units = 2ull * rfl(l.table_off[n_req]);
     return static_cast<uint32_t>(units < a.ctx_cap ? units : a.ctx_cap);
   }
   return 2u * rfl(SEP ? l.blk_off[n_req] : l.table_off[n_req]);
 }
 
-template <int DIR, bool HND, int U, int NT, int WG, bool SEP, bool ORD = false>
+template <int DIR, bool HND, int U, int NT, int WG, bool SEP, bool ORD, bool DIRECT>
 __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                            uint32_t copy_wgs, const Preload<U> &pre) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t n_waves = copy_wgs * (WG / kWave);
-  const uint32_t n_items = count_units<SEP, ORD>(a, l, n_req) * a.slices_per_block;
+  const uint32_t n_items = count_units<SEP, ORD, DIRECT>(a, l, n_req) * a.slices_per_block;
 
   uint32_t it = first_item<WG>(a, wg, copy_wgs);
   if (it >= n_items) return;
-  Item cur = decode_item<SEP, ORD>(a, l, n_req, it, lane);
+  Item cur = decode_item<SEP, ORD, DIRECT>(a, l, n_req, it, lane);
   uint32_t id = load_block_id(a, cur);
   bool first = true;
   for (;;) {
@@ -1483,19 +1515,19 @@ __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uin
     Item nxt = cur;
     uint32_t nid = a.num_blocks;
     if (more) {
-      nxt = decode_item<SEP, ORD>(a, l, n_req, nit, lane);
+      nxt = decode_item<SEP, ORD, DIRECT>(a, l, n_req, nit, lane);
       nid = load_block_id(a, nxt);
     }
     // the preloaded bytes were read where the item's slice sits when the extents are the library's own; extents
     // from the caller (and the files of the direct-to-block mode) may put it elsewhere: then the slice is loaded
     // from where they say
     const bool preloaded = DIR == kUnpack && first && pre.valid &&
-                           ((!SEP && !ORD && !a.direct) ||
+                           ((!SEP && !ORD && !DIRECT) ||
                             cur.obj_blk + static_cast<uint64_t>(cur.s) * kSlice == pre.src);
     if (preloaded)
       store_preloaded<HND, U, NT>(a, cur, id, lane, pre);
     else
-      move_one<DIR, HND, U, NT, ORD>(a, cur, id, lane);
+      move_one<DIR, HND, U, NT, ORD, DIRECT>(a, cur, id, lane);
     first = false;
     if (!more) break;
     cur = nxt;
@@ -1584,7 +1616,7 @@ __device__ __forceinline__ OneReq one_request(const MoveArgs &m, const LayoutArg
 
 // The copy loop of one request whose blocks are a whole number of slices; the next item's block id is requested before
 // the current item's loads and stores are issued.
-template <int DIR, bool HND, int U, int NT, int WG>
+template <int DIR, bool HND, int U, int NT, int WG, bool DIRECT>
 __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q, uint32_t wg, uint32_t copy_wgs,
                                              const Preload<U> &pre) {
   constexpr uint32_t kSlice = U * kPiece;
@@ -1610,37 +1642,26 @@ __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q,
       if (nj < a.table_len) nid = table[nj];
     }
     const uint64_t at = q.lo + kind * q.obj_bytes + static_cast<uint64_t>(j) * a.block_bytes;
-    const bool fits = !a.direct || (at + a.block_bytes >= at && at + a.block_bytes <= q.room);
+    const bool fits = !DIRECT || (at + a.block_bytes >= at && at + a.block_bytes <= q.room);
     if (fits && id < a.num_blocks) {
       unsigned char *blk = (kind ? a.v_base : a.k_base) + static_cast<uint64_t>(id) * a.block_stride;
       unsigned char *obj = q.base + at;
       const uint32_t o0 = part * kSlice + lane * 16u;
+      BlockWalk<HND> in_pool(a, o0);
       if (DIR == kUnpack && first) {
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-          const uint32_t o = o0 + k * kPiece;
-          st16<NT>(blk + (HND ? hnd_offset(o, a.row_bytes, a.block_tokens, a.num_kv_heads) : o), pre.buf[k]);
-        }
+        for (int k = 0; k < U; ++k) st16<NT>(blk + in_pool.next(), pre.buf[k]);
       } else {
         u32x4 buf[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-          const uint32_t o = o0 + k * kPiece;
-          buf[k] = ld16<NT>(DIR == kPack ? blk + (HND ? hnd_offset(o, a.row_bytes, a.block_tokens, a.num_kv_heads) : o)
-                                         : obj + o);
-        }
+        for (int k = 0; k < U; ++k) buf[k] = ld16<NT>(DIR == kPack ? blk + in_pool.next() : obj + o0 + k * kPiece);
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-          const uint32_t o = o0 + k * kPiece;
-          st16<NT>(DIR == kPack ? obj + o
-                                : blk + (HND ? hnd_offset(o, a.row_bytes, a.block_tokens, a.num_kv_heads) : o),
-                   buf[k]);
-        }
+        for (int k = 0; k < U; ++k) st16<NT>(DIR == kPack ? obj + o0 + k * kPiece : blk + in_pool.next(), buf[k]);
       }
     } else if (lane == 0 && part == 0 && a.status) {
       atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
     }
-    if (DIR == kPack && !a.direct && j + 1 == q.n && part + 1 == S) {  // zero the object's tail up to its aligned size
+    if (DIR == kPack && !DIRECT && j + 1 == q.n && part + 1 == S) {  // zero the object's tail up to its aligned size
       const u32x4 zero = {0u, 0u, 0u, 0u};
       for (uint64_t o = static_cast<uint64_t>(q.n) * a.block_bytes + lane * 16ull; o < q.obj_bytes; o += kPiece)
         st16<0>(q.base + kind * q.obj_bytes + o, zero);
@@ -1657,14 +1678,14 @@ __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q,
 // The copy loop for blocks that are no whole number of slices.  A wavefront decodes its next 64 pieces at once, one per
 // lane (owner by binary search, block id, both addresses), so that the table loads of 64/U items are in flight together
 // and an item costs a few lane reads; then it moves them item by item.
-template <int DIR, bool HND, int U, int NT, int WG, bool SEP>
+template <int DIR, bool HND, int U, int NT, int WG, bool SEP, bool DIRECT>
 __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                             uint32_t copy_wgs) {
   constexpr uint32_t kBatch = kWave / U;  // items decoded at once
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t n_waves = copy_wgs * (WG / kWave);
   const uint32_t ppb = a.slices_per_block;
-  const uint64_t n_pieces = static_cast<uint64_t>(count_units<SEP>(a, l, n_req)) * ppb;
+  const uint64_t n_pieces = static_cast<uint64_t>(count_units<SEP, false, DIRECT>(a, l, n_req)) * ppb;
   const uint32_t n_items = static_cast<uint32_t>((n_pieces + U - 1) / U);
   const uint32_t in_piece = lane * 16u;
 
@@ -1680,13 +1701,13 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
       const uint32_t q = static_cast<uint32_t>(mine) / ppb;
       const uint32_t rest = (static_cast<uint32_t>(mine) - q * ppb) * U + lane % U;
       const uint32_t q2 = rest / ppb;
-      const Item d = decode_unit<false, SEP>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
+      const Item d = decode_unit<false, SEP, false, DIRECT>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
       if (d.obj_ptr != nullptr) {
         const uint32_t id = d.tab_idx < a.table_len ? a.table[d.tab_idx] : a.num_blocks;
         off = d.s * kPiece;
         const uint32_t bytes = a.block_bytes - off < kPiece ? a.block_bytes - off : kPiece;
         obj = reinterpret_cast<uint64_t>(d.obj_blk) + off;
-        if (DIR == kPack && !a.direct && d.j + 1 == d.n && d.s + 1 == ppb) {
+        if (DIR == kPack && !DIRECT && d.j + 1 == d.n && d.s + 1 == ppb) {
           tail = d.obj_bytes - static_cast<uint64_t>(d.n) * a.block_bytes;
           tail_at = obj + bytes;
         }
@@ -1876,9 +1897,9 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_move(const Mo
   if (DIR == kUnpack && !PIECES && WG == kWgThreads) pre = preload_first<U, NT, WG>(a, blockIdx.x, gridDim.x);
   lds_from_caller_extents(ext, n_req, l, a.table_len, a.block_bytes, a.stage_cap, a.status);
   if (PIECES)
-    move_pieces<DIR, HND, U, NT, WG, true>(a, l, n_req, blockIdx.x, gridDim.x);
+    move_pieces<DIR, HND, U, NT, WG, true, false>(a, l, n_req, blockIdx.x, gridDim.x);
   else
-    move_items<DIR, HND, U, NT, WG, true>(a, l, n_req, blockIdx.x, gridDim.x, pre);
+    move_items<DIR, HND, U, NT, WG, true, false, false>(a, l, n_req, blockIdx.x, gridDim.x, pre);
 }
 
 template <int DIR, int PT, int WG>
@@ -1924,7 +1945,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     SqeHead one_head;
     one_head.live = false;
     if (entries) one_head = sqe_head(q, l, 1, 0);
-    if (copies) move_request<DIR, HND, U, NT, WG>(m, one, wg, w.copy_wgs, pre);
+    if (copies) move_request<DIR, HND, U, NT, WG, false>(m, one, wg, w.copy_wgs, pre);
     if (entries) emit_sqes(q, l, 1, 0, w.sqe_wgs, one_head);
     return;
   }
@@ -1945,9 +1966,9 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
   }
   if (copies) {
     if (PIECES)
-      move_pieces<DIR, HND, U, NT, WG, false>(m, l, a.n_req, wg, w.copy_wgs);
+      move_pieces<DIR, HND, U, NT, WG, false, false>(m, l, a.n_req, wg, w.copy_wgs);
     else
-      move_items<DIR, HND, U, NT, WG, false, ORD>(m, l, a.n_req, wg, w.copy_wgs, pre);
+      move_items<DIR, HND, U, NT, WG, false, ORD, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
   }
   if (blockIdx.x < w.sqe_wgs) emit_sqes(q, l, a.n_req, 0, w.sqe_wgs, head);
 }
@@ -2018,7 +2039,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
     DirectHead one_head;
     one_head.live = false;
     if (entries) one_head = iocb_head(g, q, d, l, 1, lead, w.sqe_wgs);
-    if (copies) move_request<DIR, false, U, 3, WG>(m, one, bx - w.copy_first, w.copy_wgs, pre);
+    if (copies) move_request<DIR, false, U, 3, WG, true>(m, one, bx - w.copy_first, w.copy_wgs, pre);
     if (entries) emit_iocbs(g, q, d, l, 1, lead, w.sqe_wgs, one_head);
     return;
   }
@@ -2034,9 +2055,9 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
   if (bx < w.sqe_wgs) head = iocb_head(g, q, d, l, a.n_req, lead, w.sqe_wgs);
   if (copies) {
     if (PIECES)
-      move_pieces<DIR, false, U, 3, WG, false>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);
+      move_pieces<DIR, false, U, 3, WG, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);
     else
-      move_items<DIR, false, U, 3, WG, false>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
+      move_items<DIR, false, U, 3, WG, false, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
   }
   if (bx < w.sqe_wgs) emit_iocbs(g, q, d, l, a.n_req, lead, w.sqe_wgs, head);
 }
