@@ -974,6 +974,26 @@ def test_scan_of_many_requests(orc, H, n_req):
     H.check_ring_layer(orc, c, layer=1, write=False, depth=n_slots, first_slot=0, n_slots=n_slots)
 
 
+@pytest.mark.parametrize("n_req", [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 63, 64])
+def test_scan_of_few_requests(orc, H, n_req):
+    """The scan of one wavefront takes as many steps as there are requests to sum over: request counts on both sides of
+    each step, padded objects, the table cut in the middle, extents from the library and from the caller, and the rings."""
+    say("scan of", n_req, "requests")
+    rng = np.random.default_rng(8400 + n_req)
+    n = rng.integers(1, 6, size=n_req).astype(np.uint32)
+    total = int(n.sum())
+    table = rng.permutation(total + 5)[:total]
+    for d, align, chunk in ((64, 8192, 8192), (40, 4096, 8192), (64, 4096, 4096)):
+        c = H.LayerCase(T=16, h=2, d=d, e=2, N=total + 5, n_blocks=n, table=table, align=align, chunk=chunk, L=2,
+                        name=f"few{n_req}d{d}a{align}")
+        H.check_everything(orc, c)
+        for tl in (total - 1, total // 2):
+            H.check_layer_restore(orc, c, layer=1, table_len=tl)
+            H.check_layer_save(orc, c, layer=1, table_len=tl)
+    for write in (False, True):
+        H.check_ring_layer(orc, c, layer=1, write=write, depth=3, first_slot=1, n_slots=2)
+
+
 def test_scan_of_many_requests_wide_sums(orc, H):
     """Alignment units above 1 MiB (the padding is then summed in 64 bits), and block counts whose sum passes 2^32:
     the requests in front of the one that runs beyond the table are restored, the published extents are plain sums."""
