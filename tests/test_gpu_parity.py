@@ -974,6 +974,18 @@ def test_scan_of_many_requests(orc, H, n_req):
     H.check_ring_layer(orc, c, layer=1, write=False, depth=n_slots, first_slot=0, n_slots=n_slots)
 
 
+@pytest.mark.parametrize("blocks,n_slots", [(1500, 2), (64 * 1024, 63), (64 * 1024, 64), (64 * 1024 + 1, 65), (70000, 69),
+                                            (3000, 130), (70000, 130)])
+def test_completion_of_many_iocbs(orc, H, blocks, n_slots):
+    """One completion of up to 64 IOCBs, of more than one pass of them, and with slots that nothing was submitted in, on a
+    ring whose range wraps: headers, CQ order and tail against the oracle, in one call and as a train of two layers."""
+    say("completion of", n_slots, "IOCBs,", blocks, "blocks")
+    c = H.LayerCase(T=1, h=1, d=8, e=2, N=blocks, n_blocks=[blocks], table=np.random.default_rng(blocks).permutation(blocks),
+                    align=16, chunk=16, L=2, name=f"complete{n_slots}")
+    H.check_ring_layer(orc, c, layer=1, write=False, depth=n_slots + 3, first_slot=n_slots - 1, n_slots=n_slots)
+    H.check_ring_layer_train(orc, c, [1, 0], True, depth=2 * n_slots + 1, n_slots=n_slots, first_slot=n_slots)
+
+
 @pytest.mark.parametrize("n_req", [1, 2, 3, 4, 5, 8, 9, 16, 17, 32, 33, 63, 64])
 def test_scan_of_few_requests(orc, H, n_req):
     """The scan of one wavefront takes as many steps as there are requests to sum over: request counts on both sides of
