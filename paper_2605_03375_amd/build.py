@@ -11,7 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtutti.so")
 BENCH_LIB = os.path.join(HERE, "libtutti_bench.so")  # the same sources with the measurement aids compiled in
 SOURCES = [os.path.join(CSRC, "tutti_api.hip"), os.path.join(CSRC, "tutti_host.cpp")]
-DEPS = SOURCES + [os.path.join(CSRC, "tutti_kernels.hip.h"), os.path.join(ROOT, "include", "tutti.h"),
+DEPS = SOURCES + [os.path.join(CSRC, "tutti_kernels.hip.h"), os.path.join(CSRC, "launch_rules.h"),
+                  os.path.join(ROOT, "include", "tutti.h"),
                   os.path.join(ROOT, "include", "tutti_bench.h")]
 
 HIPCC_FLAGS = [

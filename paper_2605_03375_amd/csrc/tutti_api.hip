@@ -231,14 +231,6 @@ int plan_launch(uint32_t cu_budget, uint64_t n_wave_items, Launch *out) {
 
 uint64_t whole_gpu_waves(const Launch &L) { return static_cast<uint64_t>(whole_gpu_wgs(L)) * (kWgThreads / kWave); }
 
-// How long a whole-GPU restore holds its first stores back, by the share of the chip's wavefronts that have an item (the
-// figures stand at hold_back).
-uint32_t restore_pause(const Launch &L, uint64_t wave_items) {
-  if (L.wg_threads != kWgThreads || L.hnd_lds) return 0;
-  if (8 * wave_items > 6 * whole_gpu_waves(L)) return 6;
-  return 8 * wave_items > 5 * whole_gpu_waves(L) ? 2 : 0;
-}
-
 // One request on the path that is made for it (move_request): blocks of whole slices in staging order; a restore only
 // while it leaves half of the chip's wavefronts free.
 template <int DIR>
@@ -275,7 +267,7 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   m->file_stride = 0;
   m->ctx_cap = 0;
   m->visit = nullptr;
-  m->pause = 0;
+  m->chip_waves = L->wg_threads == kWgThreads ? static_cast<uint32_t>(whole_gpu_waves(*L)) : 0;
 
   L->hnd_lds = false;
   L->tile_lds = 0;
@@ -647,7 +639,6 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
   if (rc) return rc;
   if (!L.hnd_lds) m.visit = d_visit;  // the tiles of the through-LDS path keep staging order
   size_grid(cu_budget, move_wave_items(L, m), &L);
-  if (DIR == kUnpack) m.pause = restore_pause(L, move_wave_items(L, m));
   // one lane per 16-byte quarter of an entry; no more entries than the capacity, nor than the table can give
   // (every request has at most obj/chunk + 1 chunks per object, and obj < blocks*block_bytes + align <= ... + chunk)
   uint64_t max_entries = 2ull * ((static_cast<uint64_t>(table_len) * bb) / cfg->chunk_bytes + 2ull * n_req);
@@ -958,7 +949,6 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
   m.ctx_cap = static_cast<uint64_t>(n_slots) * TUTTI_IOCB_SLOTS;
   if (m.ctx_cap * counted_slices(L, bb) > 0xffffffffull) return TUTTI_ERANGE;  // work items are numbered in 32 bits
   size_grid(cu_budget, move_wave_items(L, m), &L);
-  if (DIR == kUnpack) m.pause = restore_pause(L, move_wave_items(L, m));
   // a chained launch has one more workgroup in front (it completes the earlier call's IOCBs and leaves); a
   // whole-GPU grid gives it one of its places, so that every workgroup is still resident from the start
   const uint32_t lead = done_n > 0 ? 1u : 0u;

@@ -27,6 +27,7 @@
 
 #include <type_traits>
 
+#include "launch_rules.h"
 #include "tutti.h"
 
 namespace tutti {
@@ -1207,7 +1208,7 @@ struct MoveArgs {
   // staging bytes [it*slice, (it+1)*slice) whatever the extents are; items_bound = 2 * table_len * slices
   uint32_t dense;
   uint32_t items_bound;
-  uint32_t pause;  // restore: how long the first stores are held back (hold_back)
+  uint32_t chip_waves;  // whole-GPU restore: wavefronts that the chip holds (hold_back_pause); 0 = never hold back
   // workgroup -> item mapping: 0 = workgroup b starts at item 4b (neighbouring workgroups, which the
   // dispatcher deals round-robin to the 8 XCDs, take neighbouring 16 KiB); 1 = each XCD takes one
   // contiguous eighth of the copy workgroups' items
@@ -1450,12 +1451,7 @@ __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint3
   }
 }
 
-// A whole-GPU restore reads its first slices, up to 32 MiB, in one burst; stores that start among those reads cost more
-// (the memory turns between reading and writing) than the same stores a little later.  So where a launch fills the chip
-// its first stores are held back for `pause` * 512 clocks (0.21 us each) behind the scan's barrier; the lines lie where
-// the sweep below crosses, in restore_pause.  Restore of one request, cold, in us, pause 0 / 2 / 6: 5K tokens (0.63 of
-// the chip's wavefronts) 7.8 / 8.1 / 8.4, 6K (0.75) 9.9 / 9.0 / 9.4, 7K (0.88) 12.0 / 12.2 / 10.5, 8K (one item each)
-// 13.3 / 13.5 / 11.8, 12K 18.7 / 18.7 / 17.3, 16K 23.3 / 23.5 / 23.0, 32K 43.8 / 43.7 / 43.9.
+// Holds the stores of a wavefront that has read ahead back (hold_back_pause).
 __device__ __forceinline__ void hold_back(uint32_t pause) {
   for (uint32_t i = 0; i < pause; ++i) __builtin_amdgcn_s_sleep(8);
 }
@@ -1976,7 +1972,8 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
                    m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [&] {
                      if (DIR == kUnpack && !ORD && !PIECES && WG == kWgThreads && copies) pre = preload_first<U, NT, WG>(m, wg, w.copy_wgs);
                    });
-  if (REQS == kFew && DIR == kUnpack && !ORD && !PIECES && WG == kWgThreads && copies) hold_back(m.pause);
+  if (REQS == kFew && DIR == kUnpack && pre.valid)
+    hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, a.n_req, false));
   SqeHead head;
   head.live = false;
   if (blockIdx.x < w.sqe_wgs) head = sqe_head(q, l, a.n_req, 0);
@@ -2072,7 +2069,8 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
                      if (DIR == kUnpack && !PIECES && WG == kWgThreads && copies && a.n_req == 1)
                        pre = preload_first_direct<U, WG>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
                    });
-  if (REQS == kFew && DIR == kUnpack && !PIECES && WG == kWgThreads && copies) hold_back(m.pause);
+  if (REQS == kFew && DIR == kUnpack && pre.valid)
+    hold_back(hold_back_pause(count_units<false, false, true>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, 1, true));
   DirectHead head;
   head.live = false;
   if (bx < w.sqe_wgs) head = iocb_head(g, q, d, l, a.n_req, lead, w.sqe_wgs);

@@ -1,0 +1,47 @@
+"""CPU tests of the rules by which a call's kernel and launch shape are chosen (csrc/launch_rules.h)."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SOURCE = """
+#include "launch_rules.h"
+extern "C" unsigned pause_of(unsigned items, unsigned chip, unsigned n_req, int file) {
+  return tutti::hold_back_pause(items, chip, n_req, file != 0);
+}
+"""
+CHIP = 8192  # wavefronts of a whole-GPU launch on 256 compute units
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src, lib = d / "rules.cpp", d / "rules.so"
+    src.write_text(SOURCE)
+    subprocess.run(["g++", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC",
+                    f"-I{ROOT}/paper_2605_03375_amd/csrc", str(src), "-o", str(lib)], check=True)
+    return ctypes.CDLL(str(lib))
+
+
+@pytest.mark.parametrize("file", [0, 1])
+@pytest.mark.parametrize("n_req", [1, 2, 8, 64])
+def test_stores_are_held_back_by_the_items_there_are(rules, n_req, file):
+    """Never for a job that leaves a third of the chip free (whatever its table could hold) or that gives a wavefront
+    more than two items; never without a chip size (under a budget)."""
+    for items in (0, 1, 64, 1024, CHIP // 2, CHIP * 21 // 32, 2 * CHIP + 1, 4 * CHIP, 0x7fffffff, 0xffffffff):
+        assert rules.pause_of(items, CHIP, n_req, file) == 0
+    for items in (0, 1, CHIP, 0xffffffff):
+        assert rules.pause_of(items, 0, n_req, file) == 0
+    for items in range(CHIP // 2, 2 * CHIP + 64, 16):
+        assert rules.pause_of(items, CHIP, n_req, file) <= 7
+
+
+def test_more_requests_are_held_back_less(rules):
+    for items in range(0, 3 * CHIP, 64):
+        pauses = [rules.pause_of(items, CHIP, n, 0) for n in range(1, 65)]
+        assert pauses == sorted(pauses, reverse=True)
+    assert [rules.pause_of(CHIP, CHIP, n, 0) for n in (1, 2, 8, 64)] == [7, 7, 6, 5]
+    assert [rules.pause_of(CHIP * 7 // 8, CHIP, n, 0) for n in (1, 2, 8, 64)] == [6, 5, 4, 3]
+    assert [rules.pause_of(CHIP * 3 // 4, CHIP, n, 0) for n in (1, 2, 8, 64)] == [2, 2, 1, 0]
