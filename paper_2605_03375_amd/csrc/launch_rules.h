@@ -32,4 +32,26 @@ constexpr uint32_t hold_back_pause(uint32_t items, uint32_t chip_waves, uint32_t
   return steps < 4 ? 2 - steps / 2 : 0;
 }
 
+// Slice of a CU-budgeted copy of `blocks` blocks (K and V each), in pieces of 1 KiB.  What a compute unit moves depends on
+// the length of a wavefront's run of loads and of stores, not on the bytes in flight: a plain cold copy on 8 / 32 / 64
+// compute units (1024 threads each) reaches 62 / 52 / 44 GB/s per unit with 8 KiB runs, with one item in flight as with
+// two, and 72 / 64 / 56 with 16 KiB.  But a longer run also ends later: up to about 1024 items, in a working set that the
+// last-level cache holds, 8 KiB are the better where the launch reads its first slices ahead (`ahead`), and without that
+// unless every wavefront gets one item at most or the compute units are many.  16 / 8 KiB, us, 32 KiB blocks:
+//   restore of 4 requests   64 blocks on 32 units 6.5 / 5.1    128 on 64  7.9 / 5.7    128 on 8  31.0 / 30.4
+//                          256 on 32  20.2 / 20.5             384 on 8  90.9 / 92.4   1024 on 32  71.5 / 79.4
+//   save of 4 requests      64 on 8  14.2 / 15.4               64 on 32  6.3 / 7.0     128 on 8  32.4 / 29.2
+//                          256 on 8  64.0 / 60.9              384 on 8  95.1 / 93.8   1024 on 32  72.8 / 80.4
+//                          256 on 64  12.9 / 13.2
+// Blocks that are no whole number of slices: slices of 8 KiB if those fit (8 KiB blocks, 4096 on 8 units, restore 261 us
+// as pieces, 256 as slices; but saves on many units: 256 of 40 KiB on 64 16.8 and 19.1), pieces otherwise (16 at a time);
+// a visiting order keeps slices, of 8 KiB.
+constexpr uint32_t budget_units(bool ahead, uint32_t block_bytes, uint32_t blocks, uint32_t cu_budget, bool ordered) {
+  if (block_bytes % 8192 != 0) return ordered ? 8 : 16;
+  const uint64_t items = 2ull * blocks * (block_bytes / 8192) / 2;
+  if (block_bytes % 16384 != 0) return !ordered && !ahead && cu_budget > 32 && items > 1024 ? 16 : 8;
+  const uint32_t one_each = cu_budget > 16 ? 16 * cu_budget : 256;
+  return items > 1024 || (!ahead && (items <= one_each || cu_budget > 32)) ? 16 : 8;
+}
+
 }  // namespace tutti

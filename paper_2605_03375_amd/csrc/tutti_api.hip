@@ -36,10 +36,7 @@ thread_local int t_last_hip = 0;
 
 constexpr uint32_t kDefaultWgsPerCu = 8;     // whole-GPU launches: 8 x 256 threads = 32 wavefronts per CU
 constexpr uint32_t kDefaultUnroll = 4;       // 4 x 16 B in flight per lane: 4 KiB slices
-// CU-budgeted launches: 16 KiB per wavefront.  What a compute unit moves depends on the length of a wavefront's run of
-// loads and of stores, not on the bytes in flight: a plain cold copy on 8 / 32 / 64 compute units (1024 threads each)
-// reaches 62 / 52 / 44 GB/s per unit with 8 KiB runs, with one item in flight as with two, and 72 / 64 / 56 with 16 KiB.
-constexpr uint32_t kBudgetUnroll = 16;
+constexpr uint32_t kBudgetUnroll = 16;       // CU-budgeted launches: 16 KiB, or 8 KiB where budget_units says so
 constexpr int kMaxDevices = 64;
 
 // What an experiment may change about a launch; 0 = the library's own choice.
@@ -231,12 +228,15 @@ int plan_launch(uint32_t cu_budget, uint64_t n_wave_items, Launch *out) {
 
 uint64_t whole_gpu_waves(const Launch &L) { return static_cast<uint64_t>(whole_gpu_wgs(L)) * (kWgThreads / kWave); }
 
-// One request on the path that is made for it (move_request): blocks of whole slices in staging order; a restore only
-// while it leaves half of the chip's wavefronts free.
+// One request on the path that is made for it (move_request): blocks of whole slices in staging order; a restore that
+// reads ahead only while it leaves half of the launch's wavefronts free (64 blocks of 32 KiB on 32 compute units, one
+// item for each wavefront: 6.0 us, through the scan 5.1).
 template <int DIR>
 bool one_request_path(const Launch &L, const MoveArgs &m, uint32_t n_req, uint64_t wave_items) {
   if (n_req != 1 || L.pieces || L.hnd_lds || m.visit) return false;
-  return DIR == kPack || L.wg_threads != kWgThreads || 2 * wave_items < whole_gpu_waves(L);
+  if (DIR == kPack || !reads_ahead(static_cast<int>(L.unroll))) return true;
+  const uint64_t waves = L.wg_threads == kWgThreads ? whole_gpu_waves(L) : L.grid * (kBudgetWgThreads / kWave);
+  return 2 * wave_items < waves;
 }
 
 uint64_t counted_slices(const Launch &L, uint32_t bytes) {
@@ -245,10 +245,11 @@ uint64_t counted_slices(const Launch &L, uint32_t bytes) {
 }
 
 // Fills the kernel arguments and settles how a head-major pool is moved (L->hnd_lds, L->unroll,
-// L->tile_lds).  L must already hold the workgroup size and default unroll from plan_launch.
+// L->tile_lds).  L must already hold the workgroup size and default unroll from plan_launch.  `ahead`: the first slices
+// are read before the requests are known (restores); `ordered`: in a caller's visiting order.
 int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t *d_block_table, uint32_t table_len,
                    const void *d_stage, uint64_t stage_cap, uint32_t *d_status, uint32_t n_req, uint32_t align,
-                   bool ordered, Launch *L, MoveArgs *m) {
+                   uint32_t cu_budget, bool ahead, bool ordered, Launch *L, MoveArgs *m) {
   m->k_base = static_cast<unsigned char *>(pool->k_base);
   m->v_base = static_cast<unsigned char *>(pool->v_base);
   m->stage = static_cast<unsigned char *>(const_cast<void *>(d_stage));
@@ -308,9 +309,11 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   // blocks) where they do not.  Measured, save / restore in us, slices (the last one short) -> pieces: blocks of 1 KiB
   // 32.0 -> 30.7 / 31.0 -> 30.2 (164 MB of traffic), 3 KiB 70.7 -> 66.3 / 65.9 -> 61.9 (369 MB), 5 KiB 76.9 -> 73.7 /
   // 70.3 -> 68.4 (410 MB), 12.5 KiB 57.4 -> 56.8 / 53.5 -> 52.5 (308 MB); 4 KiB under a budget of 32 compute units,
-  // where a slice is 8 KiB, 99.2 -> 83.3 / 96.0 -> 83.0 (134 MB).  Where slices fill the blocks their loop is the
+  // as half slices of 8 KiB, 99.2 -> 83.3 / 96.0 -> 83.0 (134 MB).  Where slices fill the blocks their loop is the
   // faster one (32 KiB restore: 43.8 against 45.3): it needs one owner, one id and one address per 4 KiB and reads the
   // first slices ahead of the scan.  A visiting order keeps the slices, whatever the block size.
+  if (!L->hnd_lds && cu_budget && tuning().unroll == 0)
+    L->unroll = budget_units(ahead, block_bytes, table_len, cu_budget, ordered);
   const uint32_t slice = kPiece * L->unroll;
   uint64_t slices = m->slices_per_block;
   if (!L->hnd_lds) {
@@ -424,6 +427,7 @@ hipError_t with_shape(const Launch &L, F &&f) {
 #define TUTTI_SHAPE(U, NT, WG) \
   if (L.unroll == U && L.nontemporal == NT && L.wg_threads == WG) return f(Shape<U, NT, WG>{});
   TUTTI_SHAPE(4, 3, kWgThreads)
+  TUTTI_SHAPE(8, 3, kBudgetWgThreads)
   TUTTI_SHAPE(16, 3, kBudgetWgThreads)
 #ifdef TUTTI_BENCH_BUILD
 #define TUTTI_SHAPES_NT(U, WG) TUTTI_SHAPE(U, 0, WG) TUTTI_SHAPE(U, 1, WG) TUTTI_SHAPE(U, 2, WG) TUTTI_SHAPE(U, 3, WG)
@@ -442,24 +446,36 @@ hipError_t with_shape(const Launch &L, F &&f) {
   return hipErrorInvalidValue;
 }
 
+// The kernels for one and for at most 64 requests exist in the product's shapes only; those for any number serve the
+// others too.
+template <typename S>
+constexpr bool has_few = S::NT == 3 && ((S::U == kDefaultUnroll && S::WG == kWgThreads) ||
+                                        (S::U >= 8 && S::WG == kBudgetWgThreads));
+
+// Under a budget pieces are moved 16 at a time (the measurement build has every combination).
+#ifdef TUTTI_BENCH_BUILD
+template <typename S>
+constexpr bool has_pieces = true;
+#else
+template <typename S>
+constexpr bool has_pieces = S::WG == kWgThreads || S::U == kBudgetUnroll;
+#endif
+
 template <int DIR, bool HND>
 hipError_t launch_move(const Launch &L, uint32_t lds, hipStream_t s, const MoveArgs &m, const tutti_extent *ext,
                        uint32_t n_req) {
   return with_shape(L, [&](auto sh) {
     using S = decltype(sh);
-    if (L.pieces)
-      hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG, true>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req);
-    else
-      hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req);
+    if constexpr (has_pieces<S>) {
+      if (L.pieces) {
+        hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG, true>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req);
+        return hipGetLastError();
+      }
+    }
+    hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req);
     return hipGetLastError();
   });
 }
-
-// The kernels for one and for at most 64 requests exist in the product's shapes only; those for any number serve the
-// others too.
-template <typename S>
-constexpr bool has_few = S::NT == 3 && ((S::U == kDefaultUnroll && S::WG == kWgThreads) ||
-                                        (S::U == kBudgetUnroll && S::WG == kBudgetWgThreads));
 
 template <typename S, int DIR, bool HND, int REQS>
 hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStream_t s, const MoveArgs &m,
@@ -472,9 +488,11 @@ hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStre
         return hipGetLastError();
       }
     }
-    if (pieces) {
-      hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, false, true>), grid, block, lds, s, m, q, a, w);
-      return hipGetLastError();
+    if constexpr (has_pieces<S>) {
+      if (pieces) {
+        hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, false, true>), grid, block, lds, s, m, q, a, w);
+        return hipGetLastError();
+      }
     }
   }
   hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS>), grid, block, lds, s, m, q, a, w);
@@ -502,7 +520,7 @@ hipError_t launch_ring_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStrea
                              const SqeArgs &q, const DirectArgs &d, const RingArgs &g, const RingArgs &done,
                              const FileArgs &f, const LayoutArgs &a, const Roles &w) {
   const dim3 grid(n_wgs), block(S::WG);
-  if constexpr (REQS != kOne) {
+  if constexpr (REQS != kOne && has_pieces<S>) {
     if (pieces) {
       hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG, REQS, true>), grid, block, lds, s, m, q, d, g, done, f, a, w);
       return hipGetLastError();
@@ -532,7 +550,8 @@ int move_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const tutti_exte
   rc = plan_launch(cu_budget, 0, &L);
   if (rc) return rc;
   MoveArgs m;
-  rc = fill_move_args(pool, bb, d_block_table, table_len, d_stage, stage_cap, d_status, n_req, cfg->align, false, &L, &m);
+  rc = fill_move_args(pool, bb, d_block_table, table_len, d_stage, stage_cap, d_status, n_req, cfg->align, cu_budget,
+                      DIR == kUnpack && bb % cfg->align == 0, false, &L, &m);
   if (rc) return rc;
   size_grid(cu_budget, move_wave_items(L, m), &L);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -635,7 +654,8 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
   rc = plan_launch(cu_budget, 0, &L);
   if (rc) return rc;
   MoveArgs m;
-  rc = fill_move_args(pool, bb, d_block_table, table_len, d_stage, stage_cap, d_status, n_req, cfg->align, d_visit != nullptr, &L, &m);
+  rc = fill_move_args(pool, bb, d_block_table, table_len, d_stage, stage_cap, d_status, n_req, cfg->align, cu_budget,
+                      DIR == kUnpack && bb % cfg->align == 0, d_visit != nullptr, &L, &m);
   if (rc) return rc;
   if (!L.hnd_lds) m.visit = d_visit;  // the tiles of the through-LDS path keep staging order
   size_grid(cu_budget, move_wave_items(L, m), &L);
@@ -941,7 +961,8 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
   tutti_pool raw = *pool;  // blocks travel as raw bytes: no head-major handling
   raw.pool_layout = TUTTI_LAYOUT_NHD;
   MoveArgs m;
-  rc = fill_move_args(&raw, bb, d_block_table, table_len, store->base, 0, d_status, n_req, cfg->align, false, &L, &m);
+  rc = fill_move_args(&raw, bb, d_block_table, table_len, store->base, 0, d_status, n_req, cfg->align, cu_budget,
+                      DIR == kUnpack && n_req == 1, false, &L, &m);
   if (rc) return rc;
   m.dense = 0;
   m.layer = layer;

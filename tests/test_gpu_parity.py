@@ -1082,6 +1082,37 @@ def test_blocks_moved_as_pieces(orc, H, T, h, d, e):
             H.check_rings(orc, c, 1, opcode, depth=3, first_slot=1, n_slots=2, cu_budget=budget)
 
 
+@pytest.mark.parametrize("T,h,d,e,layout", [(16, 1, 128, 2, 0), (16, 2, 128, 2, 0), (16, 5, 80, 2, 0), (16, 4, 128, 2, 0),
+                                            (16, 6, 128, 2, 0), (16, 5, 128, 2, 0), (16, 16, 32, 1, 1), (16, 32, 32, 1, 1),
+                                            (16, 8, 64, 1, 1), (16, 16, 64, 1, 1), (16, 24, 64, 1, 1), (8, 32, 64, 2, 1),
+                                            (32, 32, 16, 1, 1), (16, 3, 48, 16, 1)])
+def test_slices_under_a_budget(orc, H, T, h, d, e, layout):
+    """Blocks of 4 to 36 KiB under a CU budget, token-major and head-major with rows of 16 to 768 bytes: slices of 8 and of
+    16 KiB, pieces and tiles; jobs that give some wavefronts an item, every one, and several; with a visiting order, of one
+    request and of three, padded objects, a skipped id, and (token-major) through the rings."""
+    bb = T * h * d * e
+    say("budget slices of", bb, "bytes, rows of", d * e, "layout", layout)
+    rng = np.random.default_rng(8500 + bb + layout + d)
+    for blocks in (5, 16 * 3 * 8192 // (2 * bb) + 1, 17 * (1 << 20) // (2 * bb) + 3):
+        N = blocks + 9
+        table = rng.permutation(N)[:blocks].astype(np.uint32)
+        if blocks > 5:
+            table[blocks // 2] = N
+        for n in ([blocks], [blocks - 4, 0, 4]):
+            c = H.LayerCase(T=T, h=h, d=d, e=e, N=N, n_blocks=n, table=table, L=2, layout=layout, align=4096, chunk=65536,
+                            pad=32, name=f"budget{bb}l{layout}n{len(n)}")
+            H.check_layer_restore(orc, c, layer=1, cu_budget=3)
+            H.check_layer_save(orc, c, layer=1, cu_budget=3)
+            H.check_layer_restore(orc, c, cu_budget=3, visit=rng.permutation(blocks).astype(np.uint32))
+        H.check_layer_save(orc, c, cu_budget=40)
+        H.check_layer_restore(orc, c, cu_budget=40)
+        if layout == 0 and bb % 4096 == 0:
+            n_slots = 2 * blocks // B.IOCB_SLOTS + 1
+            for write in (False, True):
+                H.check_ring_layer(orc, c, layer=1, write=write, depth=n_slots + 1, first_slot=1, n_slots=n_slots, cu_budget=3)
+    H.check_everything(orc, c, cu_budget=3)
+
+
 @pytest.mark.parametrize("n", [0, 1, 1023, 2047, 2048, 2561, 3073, 4096, 4097])
 def test_one_request_on_both_sides_of_each_rule(orc, H, n):
     """One request of whole-slice blocks (4 KiB: 2n items) around the sizes where the launch changes: half, 5/8 and 3/4

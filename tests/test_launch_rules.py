@@ -11,6 +11,9 @@ SOURCE = """
 extern "C" unsigned pause_of(unsigned items, unsigned chip, unsigned n_req, int file) {
   return tutti::hold_back_pause(items, chip, n_req, file != 0);
 }
+extern "C" unsigned units_of(int ahead, unsigned block_bytes, unsigned blocks, unsigned budget, int ordered) {
+  return tutti::budget_units(ahead != 0, block_bytes, blocks, budget, ordered != 0);
+}
 """
 CHIP = 8192  # wavefronts of a whole-GPU launch on 256 compute units
 
@@ -45,3 +48,22 @@ def test_more_requests_are_held_back_less(rules):
     assert [rules.pause_of(CHIP, CHIP, n, 0) for n in (1, 2, 8, 64)] == [7, 7, 6, 5]
     assert [rules.pause_of(CHIP * 7 // 8, CHIP, n, 0) for n in (1, 2, 8, 64)] == [6, 5, 4, 3]
     assert [rules.pause_of(CHIP * 3 // 4, CHIP, n, 0) for n in (1, 2, 8, 64)] == [2, 2, 1, 0]
+
+
+@pytest.mark.parametrize("ahead", [0, 1])
+@pytest.mark.parametrize("budget", [1, 8, 16, 32, 64, 256])
+def test_slices_under_a_budget(rules, ahead, budget):
+    """A visiting order never cuts a block of whole 8 KiB slices into anything else, and gets 8 KiB slices otherwise;
+    without one a slice fills the blocks, or the block goes as pieces 16 at a time."""
+    for kib4 in range(1, 65):
+        for extra in (0, 16, 512, 1024):
+            block = 4096 * kib4 + extra
+            for blocks in (0, 1, 64, 512, 513, 4096, 1 << 20, 0xffffffff):
+                u = rules.units_of(ahead, block, blocks, budget, 1)
+                assert u in (8, 16) and (u == 8 or block % 16384 == 0)
+                v = rules.units_of(ahead, block, blocks, budget, 0)
+                assert v in (8, 16) and (v == 16 or block % 8192 == 0)
+                if ahead and block % 16384 == 8192:
+                    assert v == 8
+    for blocks in (1, 64, 256, 512):
+        assert rules.units_of(1, 32768, blocks, 32, 0) == (16 if blocks > 256 else 8)
