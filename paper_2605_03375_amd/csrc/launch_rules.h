@@ -46,12 +46,29 @@ constexpr uint32_t hold_back_pause(uint32_t items, uint32_t chip_waves, uint32_t
 // Blocks that are no whole number of slices: slices of 8 KiB if those fit (8 KiB blocks, 4096 on 8 units, restore 261 us
 // as pieces, 256 as slices; but saves on many units: 256 of 40 KiB on 64 16.8 and 19.1), pieces otherwise (16 at a time);
 // a visiting order keeps slices, of 8 KiB.
-constexpr uint32_t budget_units(bool ahead, uint32_t block_bytes, uint32_t blocks, uint32_t cu_budget, bool ordered) {
+// `short_rows`: a head-major pool whose rows are shorter than a cache line, moved directly: the longer run wins at every
+// size (rows of 64 bytes, 300 blocks of 16 KiB on 8 units: restore 32 / 51, save 39 / 57).
+constexpr uint32_t budget_units(bool ahead, uint32_t block_bytes, uint32_t blocks, uint32_t cu_budget, bool ordered,
+                                bool short_rows) {
   if (block_bytes % 8192 != 0) return ordered ? 8 : 16;
   const uint64_t items = 2ull * blocks * (block_bytes / 8192) / 2;
+  if (short_rows && block_bytes % 16384 == 0) return 16;
   if (block_bytes % 16384 != 0) return !ordered && !ahead && cu_budget > 32 && items > 1024 ? 16 : 8;
   const uint32_t one_each = cu_budget > 16 ? 16 * cu_budget : 256;
   return items > 1024 || (!ahead && (items <= one_each || cu_budget > 32)) ? 16 : 8;
+}
+
+// Whether a head-major pool goes through LDS tiles or is moved directly.  On the whole GPU it pays while a row is shorter
+// than a 128-byte line.  Under a CU budget a workgroup has one tile in flight at a time, and only rows of 16 bytes on
+// more than 16 compute units are worth that.  Through LDS / direct, us, save and restore of 16 KiB blocks:
+//   rows of 16 bytes   300 blocks on 8 units 85 / 69, 75 / 64   500 on 16  78 / 73, 73 / 64   1000 on 32  87 / 99, 83 / 90
+//                      2000 on 64  94 / 122, 89 / 139
+//   rows of 32 bytes   300 on 8  82 / 50, 75 / 44   500 on 16  78 / 57, 73 / 48   1000 on 32  87 / 69, 83 / 56
+//                      2000 on 64  94 / 79, 89 / 66
+//   rows of 64 bytes   300 on 8  81 / 38, 75 / 31   500 on 16  78 / 43, 74 / 37   1000 on 32  87 / 51, 82 / 45
+//                      2000 on 64  94 / 57, 89 / 51
+constexpr bool hnd_through_lds(uint32_t row_bytes, uint32_t cu_budget) {
+  return row_bytes < (cu_budget == 0 ? 128u : cu_budget > 16 ? 32u : 16u);
 }
 
 }  // namespace tutti

@@ -287,12 +287,8 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
       const uint64_t lds = static_cast<uint64_t>(align16(req_lds_bytes(n_req))) + static_cast<uint64_t>(tile_tokens) * pitch;
       const bool fits = tile_bytes % (L->wg_threads * 16u) == 0 && per_thread >= 1 && per_thread <= 8 &&
                         is_pow2(per_thread) && lds <= kDynLdsCap;
-      // Worth it when a row is shorter than a 128-byte line (or when asked for).  Under a CU budget a workgroup has one
-      // tile in flight at a time, and only rows of 16 bytes are worth that: through LDS / direct on 32 compute units,
-      // save and restore in us, rows of 64 bytes 88 / 52 and 82 / 51 (66 MB), 32 bytes 88 / 74 and 83 / 65, 16 bytes
-      // 53 / 58 and 49 / 55 (39 MB).
-      const uint32_t short_row = L->wg_threads == kWgThreads ? 128 : 32;
-      if (fits && (mode == 2 || row < short_row)) {
+      // Worth it where hnd_through_lds says so (or when asked for).
+      if (fits && (mode == 2 || hnd_through_lds(row, cu_budget))) {
         L->hnd_lds = true;
         L->unroll = per_thread;
         L->tile_lds = tile_tokens * pitch;
@@ -313,7 +309,8 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   // faster one (32 KiB restore: 43.8 against 45.3): it needs one owner, one id and one address per 4 KiB and reads the
   // first slices ahead of the scan.  A visiting order keeps the slices, whatever the block size.
   if (!L->hnd_lds && cu_budget && tuning().unroll == 0)
-    L->unroll = budget_units(ahead, block_bytes, table_len, cu_budget, ordered);
+    L->unroll = budget_units(ahead, block_bytes, table_len, cu_budget, ordered,
+                             pool->pool_layout == TUTTI_LAYOUT_HND && m->row_bytes < 128);
   const uint32_t slice = kPiece * L->unroll;
   uint64_t slices = m->slices_per_block;
   if (!L->hnd_lds) {

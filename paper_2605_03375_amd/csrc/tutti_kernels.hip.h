@@ -47,17 +47,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // A wave-uniform 32-bit value moved to a scalar register.
 __device__ __forceinline__ uint32_t rfl(uint32_t v) { return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(v)); }
 
-// The same if the value is known to be wave-uniform (what comes out of LDS or through vector loads is not, to the
-// compiler: kept uniform, the arithmetic behind it goes to the scalar unit and its branches are scalar ones).
-template <bool UNI>
-__device__ __forceinline__ uint32_t uni(uint32_t v) {
-  return UNI ? rfl(v) : v;
-}
-template <bool UNI>
-__device__ __forceinline__ uint64_t uni(uint64_t v) {
-  return UNI ? (static_cast<uint64_t>(rfl(static_cast<uint32_t>(v >> 32))) << 32) | rfl(static_cast<uint32_t>(v)) : v;
-}
-
 // Wave-uniform words (counts, block ids, visiting order) are fetched through the scalar (constant) path: one s_load per
 // wavefront, counted apart from the vector loads and stores in flight: it neither queues behind them nor waits for them.
 typedef const __attribute__((address_space(4))) uint32_t *const_u32_ptr;
@@ -110,12 +99,6 @@ __device__ __forceinline__ ReqLds carve_lds(unsigned char *smem, uint32_t n_req,
 }
 
 __host__ __device__ constexpr uint32_t req_lds_bytes(uint32_t n_req) { return 24u * n_req + 8u; }
-
-__device__ __forceinline__ uint64_t shfl_up_u64(uint64_t v, uint32_t delta) {
-  uint32_t lo = __shfl_up(static_cast<uint32_t>(v), delta, kWave);
-  uint32_t hi = __shfl_up(static_cast<uint32_t>(v >> 32), delta, kWave);
-  return (static_cast<uint64_t>(hi) << 32) | lo;
-}
 
 __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, uint32_t src) {
   uint32_t lo = __shfl(static_cast<uint32_t>(v), src, kWave);
@@ -556,12 +539,11 @@ __device__ __forceinline__ void lds_from_caller_extents(const tutti_extent *__re
 // Largest r in [0, n) with a[r] <= key, for a non-decreasing a with a[0] <= key.  Empty
 // requests share their offset with the next one, so the answer is never an empty request
 // when key is below the total.
-template <bool UNI = false>
 __device__ __forceinline__ uint32_t find_owner(const uint32_t *a, uint32_t n, uint32_t key) {
   uint32_t lo = 0, hi = n;
   while (hi - lo > 1) {
     const uint32_t mid = (lo + hi) >> 1;
-    if (uni<UNI>(a[mid]) <= key)
+    if (a[mid] <= key)
       lo = mid;
     else
       hi = mid;
@@ -1365,41 +1347,49 @@ struct Item {
 // ORD: the units are visited in the order a.visit lists (all K blocks, then all V blocks, each in that order);
 // a listed position that is not a block of a request that takes part is passed over.
 // u: (block, kind) unit in staging order; s: its slice, piece or tile; `report`: this thread reports what it finds out
-// of order with a unit's first part.  UNI: u and s are wave-uniform.
-template <bool UNI, bool SEP, bool ORD, bool DIRECT>
+// of order with a unit's first part.
+template <bool SEP, bool ORD, bool DIRECT>
 __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t u, uint32_t s,
                                             bool report) {
   Item d;
   d.s = s;
   report = report && s == 0 && a.status != nullptr;
   const uint32_t *off = SEP ? l.blk_off : l.table_off;
-  uint32_t r, toff;
+  uint32_t r, toff, end;
+  uint64_t stage_off;
+  // all of a request's words are asked for together: they come out of LDS one behind the other, and a workgroup that has
+  // one tile in flight waits for each (tiles of 16-byte rows on 8 compute units: 594 ns each with two waits, 550 with one)
+  const auto request = [&] {
+    d.obj_bytes = l.obj_bytes[r];
+    stage_off = l.stage_off[r];
+    toff = off[r];
+    end = off[r + 1];
+    __builtin_amdgcn_sched_barrier(0);
+  };
   if (ORD) {
     d.kind = u >= a.table_len ? 1u : 0u;
     const_u32_ptr vis = as_const(a.visit);
     const uint32_t pos = vis[rfl(u - d.kind * a.table_len)];  // wave-uniform index: one scalar load
-    if (pos >= uni<UNI>(l.table_off[n_req])) {  // beyond the blocks of the requests that take part
+    if (pos >= l.table_off[n_req]) {  // beyond the blocks of the requests that take part
       d.obj_ptr = nullptr;
       d.obj_blk = nullptr;
       d.obj_bytes = 0;
       d.tab_idx = d.n = d.j = 0;
       return d;
     }
-    r = find_owner<UNI>(l.table_off, n_req, pos);
-    toff = uni<UNI>(l.table_off[r]);
-    d.n = uni<UNI>(l.table_off[r + 1]) - toff;
+    r = find_owner(l.table_off, n_req, pos);
+    request();
+    d.n = end - toff;
     d.j = pos - toff;
   } else {
-    r = find_owner<UNI>(off, n_req, u >> 1);
-    toff = uni<UNI>(off[r]);
-    d.n = uni<UNI>(off[r + 1]) - toff;
+    r = find_owner(off, n_req, u >> 1);
+    request();
+    d.n = end - toff;
     const uint32_t v = u - 2u * toff;
     d.kind = v >= d.n ? 1u : 0u;
     d.j = v - d.kind * d.n;
   }
-  d.obj_bytes = uni<UNI>(l.obj_bytes[r]);
-  d.tab_idx = (SEP ? uni<UNI>(l.table_off[r]) : toff) + d.j;
-  const uint64_t stage_off = uni<UNI>(l.stage_off[r]);
+  d.tab_idx = (SEP ? l.table_off[r] : toff) + d.j;
   if (DIRECT) {
     // same arithmetic as the context's file offset (direct_entry_quarter), then the I/O kernel's checks
     const uint64_t file_off = (2ull * a.layer + d.kind) * d.obj_bytes + static_cast<uint64_t>(d.j) * a.block_bytes;
@@ -1416,7 +1406,7 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
   }
   d.obj_ptr = a.stage + stage_off + d.kind * d.obj_bytes;
   d.obj_blk = d.obj_ptr + static_cast<uint64_t>(d.j) * a.block_bytes;
-  if (!SEP && (stage_off > a.stage_cap || d.obj_bytes > (a.stage_cap - stage_off) / 2)) {
+  if (!SEP && ((stage_off > a.stage_cap) | (d.obj_bytes > (a.stage_cap - stage_off) / 2))) {
     // the request's objects do not fit: skip it, report once
     // (an ordered launch reports from its first workgroup instead: its list need not name the request's first block)
     if (!ORD && report && d.j == 0 && d.kind == 0) atomicOr(a.status, TUTTI_ST_STAGE_CAP);
@@ -1431,7 +1421,7 @@ template <bool SEP, bool ORD = false, bool DIRECT = false>
 __device__ __forceinline__ Item decode_item(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t it,
                                             uint32_t lane) {
   const uint32_t u = it / a.slices_per_block;
-  return decode_unit<false, SEP, ORD, DIRECT>(a, l, n_req, u, it - u * a.slices_per_block, lane == 0);
+  return decode_unit<SEP, ORD, DIRECT>(a, l, n_req, u, it - u * a.slices_per_block, lane == 0);
 }
 
 // Block id of an item through the scalar (constant) path: the index is wave-uniform, so this is
@@ -1747,7 +1737,7 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
       const uint32_t q = static_cast<uint32_t>(mine) / ppb;
       const uint32_t rest = (static_cast<uint32_t>(mine) - q * ppb) * U + lane % U;
       const uint32_t q2 = rest / ppb;
-      const Item d = decode_unit<false, SEP, false, DIRECT>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
+      const Item d = decode_unit<SEP, false, DIRECT>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
       if (d.obj_ptr != nullptr) {
         const uint32_t id = d.tab_idx < a.table_len ? a.table[d.tab_idx] : a.num_blocks;
         off = d.s * kPiece;

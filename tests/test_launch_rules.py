@@ -11,8 +11,10 @@ SOURCE = """
 extern "C" unsigned pause_of(unsigned items, unsigned chip, unsigned n_req, int file) {
   return tutti::hold_back_pause(items, chip, n_req, file != 0);
 }
-extern "C" unsigned units_of(int ahead, unsigned block_bytes, unsigned blocks, unsigned budget, int ordered) {
-  return tutti::budget_units(ahead != 0, block_bytes, blocks, budget, ordered != 0);
+extern "C" int lds_of(unsigned row, unsigned budget) { return tutti::hnd_through_lds(row, budget); }
+extern "C" unsigned units_of(int ahead, unsigned block_bytes, unsigned blocks, unsigned budget, int ordered,
+                             int short_rows) {
+  return tutti::budget_units(ahead != 0, block_bytes, blocks, budget, ordered != 0, short_rows != 0);
 }
 """
 CHIP = 8192  # wavefronts of a whole-GPU launch on 256 compute units
@@ -59,11 +61,23 @@ def test_slices_under_a_budget(rules, ahead, budget):
         for extra in (0, 16, 512, 1024):
             block = 4096 * kib4 + extra
             for blocks in (0, 1, 64, 512, 513, 4096, 1 << 20, 0xffffffff):
-                u = rules.units_of(ahead, block, blocks, budget, 1)
+                u = rules.units_of(ahead, block, blocks, budget, 1, 0)
                 assert u in (8, 16) and (u == 8 or block % 16384 == 0)
-                v = rules.units_of(ahead, block, blocks, budget, 0)
+                v = rules.units_of(ahead, block, blocks, budget, 0, 0)
                 assert v in (8, 16) and (v == 16 or block % 8192 == 0)
                 if ahead and block % 16384 == 8192:
                     assert v == 8
     for blocks in (1, 64, 256, 512):
-        assert rules.units_of(1, 32768, blocks, 32, 0) == (16 if blocks > 256 else 8)
+        assert rules.units_of(1, 32768, blocks, 32, 0, 0) == (16 if blocks > 256 else 8)
+        assert rules.units_of(ahead, 32768, blocks, budget, 0, 1) == rules.units_of(ahead, 16384, blocks, budget, 1, 1) == 16
+
+
+def test_head_major_rows_through_lds(rules):
+    """Every row below a cache line on the whole GPU, none of a line or more anywhere, and under a budget the shortest rows
+    only, on more than 16 compute units."""
+    for row in range(16, 512, 16):
+        assert rules.lds_of(row, 0) == (row < 128)
+        for budget in (1, 8, 16):
+            assert not rules.lds_of(row, budget)
+        for budget in (17, 32, 64, 256):
+            assert rules.lds_of(row, budget) == (row == 16)
