@@ -976,10 +976,14 @@ __device__ __forceinline__ IoPart io_decode(const RingArgs &g, const IoArgs &a, 
   r.src = r.dst = 0;
   r.len = 0;
   const uint32_t b = ctx / TUTTI_IOCB_SLOTS, k = ctx % TUTTI_IOCB_SLOTS;
-  const tutti_iocb *io = &g.sq[(g.first_slot + b) % g.depth];
+  const uint32_t slot = g.first_slot + b;  // below 2 * depth: the host checked first_slot < depth and n_slots <= depth
+  const tutti_iocb *io = &g.sq[slot < g.depth ? slot : slot - g.depth];
   const u32x4 hdr = *reinterpret_cast<const u32x4 *>(&io->hdr);  // iocb_idx, num_ioctx, state, done
   const u32x4 *e = reinterpret_cast<const u32x4 *>(&io->ioctx[k]);
-  const u32x4 q0 = e[0], q1 = e[1];
+  u32x4 q0 = e[0], q1 = e[1];
+  // header and context in one round trip (a context is read whether or not it is submitted: the slot holds all of them);
+  // left to itself the compiler moves the context's loads behind the header's check, which is a second one
+  asm volatile("" : "+v"(q0), "+v"(q1));
   if (hdr.z != TUTTI_IOCB_FILLED || k >= hdr.y) return r;  // nothing submitted in this slot / position
   const uint32_t opcode = q0.x & 0xffu, file_id = q0.y, len = q1.z;
   const uint64_t file_off = (static_cast<uint64_t>(q0.w) << 32) | q0.z;
@@ -1019,7 +1023,8 @@ __device__ __forceinline__ void complete_iocbs(const RingArgs g, uint32_t lane);
 // wavefront resolves its next 64 slices or pieces at once, one per lane: the three dependent loads behind each (header
 // and context together, then the descriptor) are paid once per batch, with all lanes' loads in flight together and no
 // data loads in front of them; resolved item by item they queue behind the current item's data.  On 32 compute units
-// (33.5 MB to write from 32 KiB blocks) that and the 16 KiB slices took the kernel from 49 us to 42 us.
+// (33.5 MB to write from 32 KiB blocks) that and the 16 KiB slices took the kernel from 49 us to 42 us.  On the whole GPU a
+// wavefront has one item or few, and the decode is paid in full: fill, issue and completion of 128 4 KiB blocks 9.1 us.
 // Completion is published by k_complete, enqueued right behind it on the same stream: counting finished items with
 // atomics on the IOCB header serialises on one address (measured: 1.5 ms per 4096-context layer instead of 55 us), and
 // a kernel boundary already is the "all contexts done" event.
@@ -1052,15 +1057,14 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_issue_io(cons
       // part number / parts per context without a 64-bit division (see move_pieces)
       const uint32_t q = static_cast<uint32_t>(mine) / a.parts;
       const uint32_t rest = (static_cast<uint32_t>(mine) - q * a.parts) * G + lane % G;
-      const uint32_t q2 = rest / a.parts;
+      const uint32_t q2 = PIECES ? rest / a.parts : 0;
       d = io_decode(g, a, q * G + q2, rest - q2 * a.parts, kPart);
     }
     const uint64_t live = __ballot(d.len != 0), whole = __ballot(d.len == kPart);
     if (live == 0) continue;
     d.src = or_first(d.src, live);
-    const uint64_t left = (n_items - it + n_waves - 1) / n_waves;
 #pragma unroll 1
-    for (uint32_t i = 0; i < kBatch && i < left; ++i) {
+    for (uint32_t i = 0; i < kBatch && live >> (i * G) != 0; ++i) {
       constexpr uint64_t kAll = (1ull << G) - 1;
       if ((live >> (i * G) & kAll) == 0) continue;
       move_decoded<U, G, 3>(
@@ -1773,9 +1777,8 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
     else
       obj = or_first(obj, live);
     // ---- move
-    const uint64_t left = (n_items - it + n_waves - 1) / n_waves;
 #pragma unroll 1
-    for (uint32_t i = 0; i < kBatch && i < left; ++i) {
+    for (uint32_t i = 0; i < kBatch && live >> (i * U) != 0; ++i) {
       if ((live >> (i * U) & ((1ull << U) - 1)) == 0) continue;
       const auto obj_at = [&](uint32_t k, uint32_t o) { return as_global(readlane_u64(obj, i * U + k)) + o; };
       const auto blk_at = [&](uint32_t k, uint32_t o) {
