@@ -1668,28 +1668,76 @@ const char *tutti_strerror(int code) {
 
 int tutti_last_hip_error(void) { return t_last_hip; }
 
+extern "C++" {
+namespace {
+// The smallest count over kernels of 256 threads that are launched with `lds` bytes of dynamic LDS; `*worst` carries it
+// on (negative: an error).
+template <typename... K>
+void least_resident(int *worst, uint32_t lds, K... kernels) {
+  const auto one = [&](auto kernel) {
+    int n = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, kWgThreads, lds);
+    if (e != hipSuccess) n = hip_fail(e);
+    if (*worst >= 0 && (n < 0 || n < *worst)) *worst = n;
+  };
+  (one(kernels), ...);
+}
+
+// Every kernel that a whole-GPU launch of the default shape may run.
+template <int DIR, bool HND>
+void least_resident_layer(int *worst) {
+  constexpr uint32_t few = req_lds_bytes(kWave), many = req_lds_bytes(512);
+  least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kOne>, k_layer<DIR, HND, 4, 3, kWgThreads, kFew>,
+                 k_layer<DIR, HND, 4, 3, kWgThreads, kFew, false, true>);
+  least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany>,
+                 k_layer<DIR, HND, 4, 3, kWgThreads, kMany, false, true>);
+  if constexpr (DIR == kUnpack) {
+    least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFew, true>);
+    least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, true>);
+  }
+}
+
+template <int DIR>
+void least_resident_ring(int *worst) {
+  constexpr uint32_t few = req_lds_bytes(kWave), many = req_lds_bytes(512);
+  least_resident(worst, few, k_layer_ring<DIR, 4, kWgThreads, kOne>, k_layer_ring<DIR, 4, kWgThreads, kFew>,
+                 k_layer_ring<DIR, 4, kWgThreads, kFew, true>);
+  least_resident(worst, many, k_layer_ring<DIR, 4, kWgThreads, kMany>, k_layer_ring<DIR, 4, kWgThreads, kMany, true>);
+}
+
+template <int DIR>
+void least_resident_lds(int *worst) {
+  constexpr uint32_t tile = kHndTileCap + kHndTileCap / 8;  // a full tile and its padding
+  least_resident(worst, align16(req_lds_bytes(1)) + tile, k_layer_lds<DIR, 4, kWgThreads, kFew>);
+  least_resident(worst, align16(req_lds_bytes(kWave + 1)) + tile, k_layer_lds<DIR, 4, kWgThreads, kMany>);
+}
+}  // namespace
+}  // extern "C++"
+
 int tutti_resident_wgs_per_cu(uint32_t which) {
-  // the default (unroll 4, non-temporal, 256-thread) instantiation of each data-moving kernel, with the dynamic LDS
-  // of a single-request launch (and a full 16 KiB tile + padding for the LDS-staged kernels)
-  const uint32_t lds = req_lds_bytes(1);
-  const uint32_t lds_tile = align16(lds) + kHndTileCap + kHndTileCap / 8;
-  int n = 0;
-  hipError_t e;
+  constexpr uint32_t many = req_lds_bytes(512);
+  int n = 1 << 20;
   switch (which) {
-    case 0: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kUnpack, false, 4, 3, kWgThreads, kOne>, kWgThreads, lds); break;
-    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kPack, false, 4, 3, kWgThreads, kOne>, kWgThreads, lds); break;
-    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_move<kUnpack, false, 4, 3, kWgThreads>, kWgThreads, lds); break;
-    case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_move<kPack, false, 4, 3, kWgThreads>, kWgThreads, lds); break;
-    case 4: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_ring<kUnpack, 4, kWgThreads, kOne>, kWgThreads, lds); break;
-    case 5: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_ring<kPack, 4, kWgThreads, kOne>, kWgThreads, lds); break;
-    case 6: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kUnpack, true, 4, 3, kWgThreads, kOne>, kWgThreads, lds); break;
-    case 7: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer<kPack, true, 4, 3, kWgThreads, kOne>, kWgThreads, lds); break;
-    case 8: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_lds<kUnpack, 4, kWgThreads, kFew>, kWgThreads, lds_tile); break;
-    case 9: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_layer_lds<kPack, 4, kWgThreads, kFew>, kWgThreads, lds_tile); break;
-    case 10: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_issue_io<kDefaultUnroll, kWgThreads, false>, kWgThreads, 0); break;
+    case 0: least_resident_layer<kUnpack, false>(&n); break;
+    case 1: least_resident_layer<kPack, false>(&n); break;
+    case 2:
+      least_resident(&n, many, k_move<kUnpack, false, 4, 3, kWgThreads>, k_move<kUnpack, false, 4, 3, kWgThreads, true>,
+                     k_move<kUnpack, true, 4, 3, kWgThreads>, k_move<kUnpack, true, 4, 3, kWgThreads, true>);
+      break;
+    case 3:
+      least_resident(&n, many, k_move<kPack, false, 4, 3, kWgThreads>, k_move<kPack, false, 4, 3, kWgThreads, true>,
+                     k_move<kPack, true, 4, 3, kWgThreads>, k_move<kPack, true, 4, 3, kWgThreads, true>);
+      break;
+    case 4: least_resident_ring<kUnpack>(&n); break;
+    case 5: least_resident_ring<kPack>(&n); break;
+    case 6: least_resident_layer<kUnpack, true>(&n); break;
+    case 7: least_resident_layer<kPack, true>(&n); break;
+    case 8: least_resident_lds<kUnpack>(&n); break;
+    case 9: least_resident_lds<kPack>(&n); break;
+    case 10: least_resident(&n, 0, k_issue_io<kDefaultUnroll, kWgThreads, false>, k_issue_io<kDefaultUnroll, kWgThreads, true>); break;
     default: return TUTTI_EINVAL;
   }
-  return e == hipSuccess ? n : hip_fail(e);
+  return n;
 }
 
 int tutti_cu_count(void) { return cu_count(); }

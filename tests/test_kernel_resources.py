@@ -60,3 +60,13 @@ def test_no_kernel_uses_scratch(kernels):
     bad = {n: (k[".private_segment_fixed_size"], k[".vgpr_spill_count"]) for n, k in kernels.items()
            if k[".private_segment_fixed_size"] != 0 or k[".vgpr_spill_count"] != 0}
     assert not bad, f"scratch bytes a lane, spilled vector registers: {bad}"
+
+
+def test_whole_gpu_kernels_fit_eight_times(kernels):
+    """Eight workgroups of 256 threads a compute unit are eight wavefronts a SIMD, which have 64 vector registers each:
+    every copy kernel of that workgroup size, whatever the number of requests, the blocks or the order it is for."""
+    whole = {n: k for n, k in kernels.items() if k[".max_flat_workgroup_size"] == 256 and
+             re.match(r"k_layer<|k_layer_ring<|k_move<|k_issue_io<|k_layer_lds<., [124],|k_move_lds<., [124],", n)}
+    assert len({n.split("<")[0] for n in whole}) == 6 and len(whole) > 40
+    large = {n: k[".vgpr_count"] for n, k in whole.items() if k[".vgpr_count"] > 64}
+    assert not large, large
