@@ -9,7 +9,7 @@
 // The same file builds the measurement library libtutti_bench.so when TUTTI_BENCH_BUILD is defined:
 // the same entry points, plus the launch-tuning knobs (per host thread), the baseline kernels and
 // every launch shape the knobs can select, all declared in include/tutti_bench.h.  The product
-// library holds the two launch shapes it uses and no knob.
+// library holds the three launch shapes it uses and no knob.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -239,6 +239,14 @@ bool one_request_path(const Launch &L, const MoveArgs &m, uint32_t n_req, uint64
   return 2 * wave_items < waves;
 }
 
+// Up to 64 requests on the kernels that are made for them: restores and saves of 64 blocks of 32 KiB 1 % faster than
+// through the kernels for any number, restores of 800 blocks 3 %, retrieves of 60 blocks 3 %, tiles of the whole GPU 0.7 %.
+// With a visiting order the two take the same time; pieces under a budget go 1.3 % slower through the former (1500 blocks
+// of 12.5 KiB on 32 compute units 48.4 us and 47.8), tiles under one 1 % faster or slower: those exist for any number only.
+bool few_requests(const Launch &L, const MoveArgs &m, uint32_t n_req) {
+  return n_req <= kWave && !m.visit && !(L.pieces && L.wg_threads == kBudgetWgThreads);
+}
+
 uint64_t counted_slices(const Launch &L, uint32_t bytes) {
   const uint64_t slice = kPiece * (L.unroll < 8 ? L.unroll : 8u);
   return (bytes + slice - 1) / slice;
@@ -387,7 +395,7 @@ hipError_t launch_layer_lds(const Launch &L, uint64_t entry_quarters, uint32_t l
   uint32_t n_wgs = 0;
   const Roles w = make_roles(L, entry_quarters, &n_wgs);
   const dim3 grid(n_wgs);
-  const bool many = a.n_req > kWave;
+  const bool many = a.n_req > kWave || L.wg_threads == kBudgetWgThreads;
 #define TUTTI_LDS_LAUNCH(PT, WG, REQS) \
   hipLaunchKernelGGL((k_layer_lds<DIR, PT, WG, REQS>), grid, dim3(WG), lds, s, m, q, a, w)
 #define TUTTI_LDS_CASE(PT)                                                                                        \
@@ -395,7 +403,7 @@ hipError_t launch_layer_lds(const Launch &L, uint64_t entry_quarters, uint32_t l
     if (L.wg_threads == kWgThreads) {                                                                             \
       if (many) TUTTI_LDS_LAUNCH(PT, kWgThreads, kMany); else TUTTI_LDS_LAUNCH(PT, kWgThreads, kFew);              \
     } else {                                                                                                      \
-      if (many) TUTTI_LDS_LAUNCH(PT, kBudgetWgThreads, kMany); else TUTTI_LDS_LAUNCH(PT, kBudgetWgThreads, kFew);  \
+      TUTTI_LDS_LAUNCH(PT, kBudgetWgThreads, kMany);                                                              \
     }                                                                                                             \
     break;
   switch (L.unroll) {
@@ -412,8 +420,8 @@ hipError_t launch_layer_lds(const Launch &L, uint64_t entry_quarters, uint32_t l
 }
 
 // The launch shape as template arguments: U = 16-byte accesses in flight per lane, NT = non-temporal mask,
-// WG = workgroup size.  The product library holds the two shapes plan_launch chooses by itself (whole GPU and
-// under a CU budget); the measurement build adds every shape the tuning knobs can ask for.
+// WG = workgroup size.  The product library holds the shapes that are chosen by size (whole GPU, and two under a CU
+// budget); the measurement build adds every shape the tuning knobs can ask for.
 template <int U_, int NT_, int WG_>
 struct Shape {
   static constexpr int U = U_, NT = NT_, WG = WG_;
@@ -479,13 +487,13 @@ hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStre
                               const SqeArgs &q, const LayoutArgs &a, const Roles &w) {
   const dim3 grid(n_wgs), block(S::WG);
   if constexpr (REQS != kOne) {
-    if constexpr (DIR == kUnpack) {
+    if constexpr (DIR == kUnpack && REQS == kMany) {
       if (m.visit) {  // the caller's visiting order
         hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>), grid, block, lds, s, m, q, a, w);
         return hipGetLastError();
       }
     }
-    if constexpr (has_pieces<S>) {
+    if constexpr (has_pieces<S> && (REQS == kMany || S::WG == kWgThreads)) {
       if (pieces) {
         hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, false, true>), grid, block, lds, s, m, q, a, w);
         return hipGetLastError();
@@ -506,7 +514,7 @@ hipError_t launch_layer(const Launch &L, uint64_t entry_quarters, uint32_t lds, 
     if constexpr (has_few<S>) {
       if (one_request_path<DIR>(L, m, a.n_req, move_wave_items(L, m)))
         return launch_layer_shape<S, DIR, HND, kOne>(false, n_wgs, lds, s, m, q, a, w);
-      if (a.n_req <= kWave) return launch_layer_shape<S, DIR, HND, kFew>(L.pieces, n_wgs, lds, s, m, q, a, w);
+      if (few_requests(L, m, a.n_req)) return launch_layer_shape<S, DIR, HND, kFew>(L.pieces, n_wgs, lds, s, m, q, a, w);
     }
     return launch_layer_shape<S, DIR, HND, kMany>(L.pieces, n_wgs, lds, s, m, q, a, w);
   });
@@ -517,7 +525,7 @@ hipError_t launch_ring_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStrea
                              const SqeArgs &q, const DirectArgs &d, const RingArgs &g, const RingArgs &done,
                              const FileArgs &f, const LayoutArgs &a, const Roles &w) {
   const dim3 grid(n_wgs), block(S::WG);
-  if constexpr (REQS != kOne && has_pieces<S>) {
+  if constexpr (has_pieces<S> && (REQS == kMany || (REQS == kFew && S::WG == kWgThreads))) {
     if (pieces) {
       hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG, REQS, true>), grid, block, lds, s, m, q, d, g, done, f, a, w);
       return hipGetLastError();
@@ -994,7 +1002,7 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
     if constexpr (has_few<S>) {
       if (one_request_path<DIR>(R, m, n_req, move_wave_items(R, m)))
         return launch_ring_shape<S, DIR, kOne>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
-      if (n_req <= kWave) return launch_ring_shape<S, DIR, kFew>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+      if (few_requests(R, m, n_req)) return launch_ring_shape<S, DIR, kFew>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
     }
     return launch_ring_shape<S, DIR, kMany>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
   });
@@ -1691,10 +1699,7 @@ void least_resident_layer(int *worst) {
                  k_layer<DIR, HND, 4, 3, kWgThreads, kFew, false, true>);
   least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany>,
                  k_layer<DIR, HND, 4, 3, kWgThreads, kMany, false, true>);
-  if constexpr (DIR == kUnpack) {
-    least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFew, true>);
-    least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, true>);
-  }
+  if constexpr (DIR == kUnpack) least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, true>);
 }
 
 template <int DIR>

@@ -17,9 +17,9 @@
 //   k_table_validate  debugging aid: ids in range and no id twice, by all-pairs comparison (no workspace)
 //   k_bitmap_clear, k_table_validate_bitmap   the same check in linear time with one bit per pool block
 //
-// Every workgroup first puts the per-request offsets into LDS (from the extents, or by redoing
-// the scan), then walks work items with a persistent grid-stride loop, so the grid can be any
-// size: the whole GPU, or a few compute units' worth when the caller sets a CU budget.
+// A workgroup first puts the per-request offsets into LDS (from the extents, or by redoing the scan; a fused launch of
+// one request needs neither), then walks work items with a persistent grid-stride loop, so the grid can be any size: the
+// whole GPU, or a few compute units' worth when the caller sets a CU budget.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -39,7 +39,7 @@ constexpr uint32_t kBudgetWgThreads = 1024;  // CU-budgeted launches: one 16-wav
 // Wavefronts per SIMD the register allocator must leave room for: the whole-GPU grids are sized for eight
 // 256-thread workgroups per CU being resident at once (a kernel that needs more than 64 VGPRs would hold only
 // seven, and the persistent workgroups beyond that would run after the others: a tail).  Asked for where it
-// costs no spills: 256-thread kernels with at most four 16-byte units in flight per lane.
+// costs no scratch: 256-thread kernels with at most four 16-byte units in flight per lane.
 constexpr int min_waves_per_simd(int wg_threads, int units) { return (wg_threads == 256 && units <= 4) ? 8 : 4; }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -369,8 +369,8 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
 // stores before (see hold_back).  More requests: behind the scan (600 requests, 49 MB: 20.3 us against 22.0 in front of
 // it); in the 64-bit scan (a few workgroups of a launch) not at all, it leaves no registers.
 // REQS = kFew: the host knows of at most 64 requests.  A kernel of its own, because the other scans' arguments push the
-// scalar registers over their limit, and the kernel then starts with four rounds of argument loads and spills instead
-// of one (a 256 KiB restore: 3.6 us against 4.2).
+// scalar registers over their limit, and the kernel then starts with more rounds of argument loads and spills (what that
+// gives stands at few_requests).
 constexpr int kOne = 1, kFew = 2, kMany = 3;  // requests a kernel is for: one, up to 64, any number
 
 template <int WG, int REQS, typename P>
@@ -1024,7 +1024,7 @@ __device__ __forceinline__ void complete_iocbs(const RingArgs g, uint32_t lane);
 // and context together, then the descriptor) are paid once per batch, with all lanes' loads in flight together and no
 // data loads in front of them; resolved item by item they queue behind the current item's data.  On 32 compute units
 // (33.5 MB to write from 32 KiB blocks) that and the 16 KiB slices took the kernel from 49 us to 42 us.  On the whole GPU a
-// wavefront has one item or few, and the decode is paid in full: fill, issue and completion of 128 4 KiB blocks 9.1 us.
+// wavefront has one item or few, and the decode is paid in full: fill, issue and completion of 128 4 KiB blocks 9.0 us.
 // Completion is published by k_complete, enqueued right behind it on the same stream: counting finished items with
 // atomics on the IOCB header serialises on one address (measured: 1.5 ms per 4096-context layer instead of 55 us), and
 // a kernel boundary already is the "all contexts done" event.
@@ -1951,7 +1951,8 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, PT)) void k_move_lds(con
 }
 
 // One layer's restore (DIR = kUnpack) or save (DIR = kPack) in one launch: every workgroup redoes the
-// (tiny) scan into its own LDS with its first wavefront.  The workgroups [copy_first, copy_first + copy_wgs)
+// (tiny) scan into its own LDS, with its first wavefront up to 64 requests, as a whole for more, and not at all for one
+// (move_request).  The workgroups [copy_first, copy_first + copy_wgs)
 // move the blocks; the first `sqe_wgs` workgroups of the grid also (or only) write the entries, one quarter per
 // lane, and workgroup 0 publishes extents and totals.  The copy workgroups are persistent and split the items
 // evenly, so the kernel ends when its slowest workgroup does: a workgroup with extra work in front of or behind
