@@ -12,14 +12,16 @@ namespace tutti {
 // most of the chip's `chip_waves` wavefronts an item and no wavefront more than two, by the items the requests really
 // have (the table may be longer); a launch that read nothing ahead sleeps for nothing.  Every step of the scan in front
 // delays the stores as well, so more requests wait less.
-// Restore of 32 KiB blocks, cold, us, pause 0 / 2 / 4 / 6 / 7 (items / chip_waves in brackets):
-//   1 request    320 blocks (0.63)  7.7 / 8.0 / 8.0 / 8.2 / 8.4    384 (0.75) 10.5 / 9.1 / 9.1 / 9.5 / 9.4
-//                448 (0.88)  12.1 / 12.3 / 11.4 / 10.4 / 10.4      512 (1.00) 13.9 / 13.8 / 13.9 / 13.8 / 12.6
-//                640 (1.25)  16.2 / 16.0 / 16.6 / 15.9 / 15.0      1024 (2.0) 23.7 / 23.8 / 23.8 / 23.5 / 23.5
-//   8 requests   384  9.0 / 8.8 / 9.3 / 9.1 / 9.2    448  11.8 / 11.3 / 10.1 / 10.3 / 10.4    512  13.1 / 13.3 / 13.2 / 11.3 / 11.2
-//                640  15.6 / 16.1 / 14.6 / 14.2 / 14.4    1024  23.7 / 23.7 / 23.4 / 23.4 / 23.5    2048  44.2 / 44.1 / 44.3 / 44.6 / 44.8
-//   64 requests  384  8.7 / 9.2 / 9.2 / 9.4 / 9.5    448  11.7 / 10.3 / 10.3 / 10.4 / 10.3    512  13.2 / 13.4 / 11.9 / 11.3 / 11.6
-//                640  15.8 / 14.5 / 14.2 / 14.7 / 15.0    1024  23.6 / 23.3 / 23.3 / 23.7 / 23.9    2048  43.9 / 44.1 / 44.4 / 44.8 / 45.0
+// Restore of 32 KiB blocks, cold, us, pause 0 / 2 / 4 / 6 / 7 / 8 (items / chip_waves in brackets):
+//   1 request    384 blocks (0.75)  10.5 /  9.0 /  9.1 /  9.4 /  9.3 /  9.5    448 (0.88)  12.1 / 12.3 / 11.6 / 10.4 / 10.4 / 10.6
+//                512 (1.00)         13.9 / 13.8 / 13.9 / 14.1 / 12.7 / 11.8    640 (1.25)  16.3 / 16.0 / 16.5 / 16.4 / 15.2 / 14.6
+//   8 requests   384                 9.0 /  8.8 /  9.2 /  9.0 /  9.2 /  9.4    448         11.7 / 11.2 / 10.1 / 10.3 / 10.3 / 10.1
+//                512                13.1 / 13.2 / 13.3 / 11.5 / 11.3 / 11.4    640         15.5 / 16.0 / 14.7 / 14.1 / 14.3 / 14.6
+//   64 requests  384                 8.7 /  9.1 /  9.1 /  9.3 /  9.5 /  9.7    448         11.7 / 10.2 / 10.2 / 10.4 / 10.3 / 10.5
+//                512                13.2 / 13.3 / 12.0 / 11.4 / 11.5 / 11.7    640         15.8 / 14.7 / 14.1 / 14.5 / 14.8 / 15.0
+// and 0 / 2 / 4 / 6 / 7 at 320 blocks (0.63), 1 request, 7.7 / 8.0 / 8.0 / 8.2 / 8.4, at 1024 (2.0) 23.7 / 23.8 / 23.8 /
+// 23.5 / 23.5, at 2048 (4.0), 8 requests, 44.2 / 44.1 / 44.3 / 44.6 / 44.8, 64 requests, 43.9 / 44.1 / 44.4 / 44.8 / 45.0.
+// Where the time falls off a step, the pause stands behind it.
 // `file`: a retrieve of one request reads ahead behind two more loads and starts later.  One call / in a train, pause 0 /
 // 7: 320 blocks 10.6 / 11.2 and 9.3 / 9.4, 384  12.5 / 11.8 and 11.1 / 10.3, 448  14.6 / 13.3 and 13.2 / 11.7, 640  18.3
 // / 16.8 and 16.9 / 15.8.
@@ -27,7 +29,7 @@ constexpr uint32_t hold_back_pause(uint32_t items, uint32_t chip_waves, uint32_t
   if (items > 2 * chip_waves || 32 * items <= 21 * chip_waves) return 0;
   if (file) return 7;
   const uint32_t steps = n_req > 1 ? 32u - static_cast<uint32_t>(__builtin_clz(n_req - 1)) : 0u;
-  if (32 * items > 29 * chip_waves) return 7 - steps / 3;
+  if (32 * items > 29 * chip_waves) return 8 - (steps + 1) / 2;
   if (32 * items > 25 * chip_waves) return 6 - (steps + 1) / 2;
   return steps < 4 ? 2 - steps / 2 : 0;
 }
@@ -43,6 +45,8 @@ constexpr uint32_t hold_back_pause(uint32_t items, uint32_t chip_waves, uint32_t
 //   save of 4 requests      64 on 8  14.2 / 15.4               64 on 32  6.3 / 7.0     128 on 8  32.4 / 29.2
 //                          256 on 8  64.0 / 60.9              384 on 8  95.1 / 93.8   1024 on 32  72.8 / 80.4
 //                          256 on 64  12.9 / 13.2
+// 8 KiB slices lie in neighbouring wavefronts (first_item), so a last round that is nearly empty falls to a few compute
+// units: 34 blocks, 272 slices of 8 KiB, on 8 / 16 units restore in 7.7 / 5.8 as 16 KiB and 9.7 / 7.6 as 8 KiB slices.
 // Blocks that are no whole number of slices: slices of 8 KiB if those fit (8 KiB blocks, 4096 on 8 units, restore 261 us
 // as pieces, 256 as slices; but saves on many units: 256 of 40 KiB on 64 16.8 and 19.1), pieces otherwise (16 at a time);
 // a visiting order keeps slices, of 8 KiB.
@@ -54,8 +58,12 @@ constexpr uint32_t budget_units(bool ahead, uint32_t block_bytes, uint32_t block
   const uint64_t items = 2ull * blocks * (block_bytes / 8192) / 2;
   if (short_rows && block_bytes % 16384 == 0) return 16;
   if (block_bytes % 16384 != 0) return !ordered && !ahead && cu_budget > 32 && items > 1024 ? 16 : 8;
+  if (items > 1024 || cu_budget == 0) return 16;
+  const uint64_t waves = 16ull * cu_budget, rest = 2 * items % waves;
+  const bool even = rest == 0 || 4 * rest >= 3 * waves;
+  if (ahead) return 2 * items <= waves || even ? 8 : 16;
   const uint32_t one_each = cu_budget > 16 ? 16 * cu_budget : 256;
-  return items > 1024 || (!ahead && (items <= one_each || cu_budget > 32)) ? 16 : 8;
+  return items <= one_each || cu_budget > 32 || !even ? 16 : 8;
 }
 
 // Whether a head-major pool goes through LDS tiles or is moved directly.  On the whole GPU it pays while a row is shorter

@@ -40,14 +40,14 @@ def test_stores_are_held_back_by_the_items_there_are(rules, n_req, file):
     for items in (0, 1, CHIP, 0xffffffff):
         assert rules.pause_of(items, 0, n_req, file) == 0
     for items in range(CHIP // 2, 2 * CHIP + 64, 16):
-        assert rules.pause_of(items, CHIP, n_req, file) <= 7
+        assert rules.pause_of(items, CHIP, n_req, file) <= 8
 
 
 def test_more_requests_are_held_back_less(rules):
     for items in range(0, 3 * CHIP, 64):
         pauses = [rules.pause_of(items, CHIP, n, 0) for n in range(1, 65)]
         assert pauses == sorted(pauses, reverse=True)
-    assert [rules.pause_of(CHIP, CHIP, n, 0) for n in (1, 2, 8, 64)] == [7, 7, 6, 5]
+    assert [rules.pause_of(CHIP, CHIP, n, 0) for n in (1, 2, 8, 64)] == [8, 7, 6, 5]
     assert [rules.pause_of(CHIP * 7 // 8, CHIP, n, 0) for n in (1, 2, 8, 64)] == [6, 5, 4, 3]
     assert [rules.pause_of(CHIP * 3 // 4, CHIP, n, 0) for n in (1, 2, 8, 64)] == [2, 2, 1, 0]
 
@@ -67,6 +67,7 @@ def test_slices_under_a_budget(rules, ahead, budget):
                 assert v in (8, 16) and (v == 16 or block % 8192 == 0)
                 if ahead and block % 16384 == 8192:
                     assert v == 8
+    assert [rules.units_of(1, 32768, 34, b, 0, 0) for b in (8, 16, 32, 64)] == [16, 16, 8, 8]
     for blocks in (1, 64, 256, 512):
         assert rules.units_of(1, 32768, blocks, 32, 0, 0) == (16 if blocks > 256 else 8)
         assert rules.units_of(ahead, 32768, blocks, budget, 0, 1) == rules.units_of(ahead, 16384, blocks, budget, 1, 1) == 16
