@@ -978,15 +978,27 @@ __device__ __forceinline__ IoPart io_decode(const RingArgs &g, const IoArgs &a, 
   const uint32_t b = ctx / TUTTI_IOCB_SLOTS, k = ctx % TUTTI_IOCB_SLOTS;
   const uint32_t slot = g.first_slot + b;  // below 2 * depth: the host checked first_slot < depth and n_slots <= depth
   const tutti_iocb *io = &g.sq[slot < g.depth ? slot : slot - g.depth];
-  const u32x4 hdr = *reinterpret_cast<const u32x4 *>(&io->hdr);  // iocb_idx, num_ioctx, state, done
+  const u32x4 *h = reinterpret_cast<const u32x4 *>(&io->hdr);  // iocb_idx, num_ioctx, state, done
   const u32x4 *e = reinterpret_cast<const u32x4 *>(&io->ioctx[k]);
-  u32x4 q0 = e[0], q1 = e[1];
   // Contexts of one or two parts: header and context in one round trip, whether or not the context is submitted (the slot
   // holds all of them); left to itself the compiler moves the context's loads behind the header's check (128 blocks of 4
   // KiB 9.4 us instead of 9.0).  A larger context would be read once for each of its parts, also where nothing was
-  // submitted (3 blocks of 128 KiB, cold, 10.1 us instead of 9.5).
-  if (a.parts <= 2) asm volatile("" : "+v"(q0), "+v"(q1));
+  // submitted (3 blocks of 128 KiB, cold, 10.1 us instead of 9.5): those wait for the header.
+  const bool together = a.parts <= 2;
+  u32x4 hdr, q0, q1;
+  if (together) {
+    hdr = h[0];
+    q0 = e[0];
+    q1 = e[1];
+    asm volatile("" : "+v"(hdr), "+v"(q0), "+v"(q1));
+  } else {
+    hdr = h[0];
+  }
   if (hdr.z != TUTTI_IOCB_FILLED || k >= hdr.y) return r;  // nothing submitted in this slot / position
+  if (!together) {
+    q0 = e[0];
+    q1 = e[1];
+  }
   const uint32_t opcode = q0.x & 0xffu, file_id = q0.y, len = q1.z;
   const uint64_t file_off = (static_cast<uint64_t>(q0.w) << 32) | q0.z;
   const uint64_t addr = (static_cast<uint64_t>(q1.y) << 32) | q1.x;
