@@ -1095,49 +1095,38 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_issue_io(cons
 // on a two-level tree of counters), was built and measured: 153 us per layer against 50 + 4: an agent-scope
 // release writes back the XCD's whole L2, and 2048 workgroups each pay for one.  The CQ tail is only ever
 // advanced here, so no read-modify-write atomics are needed within a stream.  A ring (or just its CQ) placed in pinned
-// host memory can be polled by the CPU while the stream runs on: ONE system-scope release stands behind the finished
-// counts and the queue entries and in front of the states and the tail, which are written through, and the states have
-// arrived before the tail is written.  Whoever sees a state sees its count, whoever sees the new tail the entries and
-// states before it.  A release writes back the XCD's L2, which in a train of layers is full of the next layer's blocks:
-// with three of them (in front of each state, behind them, in front of the tail) the completion was what a train of
-// layers waited for (retrieve of one request in a train, 32 KiB blocks: 100 / 200 / 384 / 448 blocks 5.1 / 7.9 / 12.4 /
-// 13.7 us a layer, with one 4.6 / 7.1 / 11.2 / 11.9).
+// host memory can be polled by the CPU while the stream runs on: a state and its finished count are one 8-byte store, they
+// and the queue entries are written through to system scope, and all have arrived (one wait) before the tail is written.
+// Whoever sees a state sees its count, whoever sees the new tail the entries and states before it.  Bound by its dependent
+// round trips (headers, states, tail) and, as a kernel of its own, by the launch.  There is no release: it would write back
+// the XCD's L2, which in a train of layers is full of the next layer's blocks, and costs a round trip more.  Us, with one
+// release in front of the states / without: retrieve of 16 blocks of 32 KiB 5.97 / 5.67, of 2048 46.3 / 46.0; a read of 50
+// blocks of 4 KiB a layer, 8 layers, 68.4 / 66.2; tutti_complete_io of 200 slots 3.2 / 2.4.
 __device__ __forceinline__ void complete_iocbs(const RingArgs g, uint32_t lane) {
   uint32_t *cq_entry = reinterpret_cast<uint32_t *>(g.cq + 1);
   uint32_t tail = g.cq->tail;  // every lane reads the same word
-  tutti_iocb_hdr *h = nullptr;
-  bool live = false;
   // one lane per IOCB, 64 per pass (the host checked n_slots <= depth, so the slots are distinct): the header
   // loads of a pass are in flight together, and a ballot gives each executed IOCB its place in the queue
-  uint32_t base = 0;
-  for (;;) {
+  for (uint32_t base = 0; base < g.n_slots; base += kWave) {
     const uint32_t b = base + lane;
-    uint32_t num = 0, idx = 0;
-    live = false;
+    tutti_iocb_hdr *h = nullptr;
+    u32x4 hdr = {0u, 0u, TUTTI_IOCB_FREE, 0u};  // iocb_idx, num_ioctx, state, done
     if (b < g.n_slots) {
-      h = &g.sq[(g.first_slot + b) % g.depth].hdr;
-      live = h->state == TUTTI_IOCB_FILLED;
-      num = h->num_ioctx;
-      idx = h->iocb_idx;
+      const uint32_t slot = g.first_slot + b;  // below 2 * depth, as in io_decode
+      h = &g.sq[slot < g.depth ? slot : slot - g.depth].hdr;
+      hdr = *reinterpret_cast<const u32x4 *>(h);
     }
+    const bool live = hdr.z == TUTTI_IOCB_FILLED;
     const uint64_t mask = __ballot(live);
     const uint32_t before = static_cast<uint32_t>(__popcll(mask & ((1ull << lane) - 1ull)));
     if (live) {
-      h->done = num;
-      cq_entry[(tail + before) % g.depth] = idx;
+      __hip_atomic_store(&cq_entry[(tail + before) % g.depth], hdr.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+      __hip_atomic_store(reinterpret_cast<uint64_t *>(h) + 1, (static_cast<uint64_t>(hdr.y) << 32) | TUTTI_IOCB_DONE,
+                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     tail += static_cast<uint32_t>(__popcll(mask));
-    if (g.n_slots - base <= kWave) break;  // the last pass, whose headers stay at hand
-    base += kWave;
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");  // system scope; every lane's counts and entries
-  for (uint32_t b = lane; b < base; b += kWave) {
-    tutti_iocb_hdr *e = &g.sq[(g.first_slot + b) % g.depth].hdr;
-    if (e->state == TUTTI_IOCB_FILLED)
-      __hip_atomic_store(&e->state, TUTTI_IOCB_DONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
-  if (live) __hip_atomic_store(&h->state, TUTTI_IOCB_DONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-  // the states have been written through when the wavefront's stores are done (the wavefront runs in step, so lane 0's
+  // what was written through has arrived when the wavefront's stores are done (the wavefront runs in step, so lane 0's
   // store is issued after the other lanes' wait)
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
