@@ -10,29 +10,34 @@ namespace tutti {
 // (the memory turns between reading and writing) than the same stores a little later.  So a wavefront that has read
 // ahead holds its first stores back, for the returned number of 512 clocks (0.21 us each): only if the launch gives
 // most of the chip's `chip_waves` wavefronts an item and no wavefront more than two, by the items the requests really
-// have (the table may be longer); a launch that read nothing ahead sleeps for nothing.  Every step of the scan in front
-// delays the stores as well, so more requests wait less.
-// Restore of 32 KiB blocks, cold, us, pause 0 / 2 / 4 / 6 / 7 / 8 (items / chip_waves in brackets):
-//   1 request    384 blocks (0.75)  10.5 /  9.0 /  9.1 /  9.4 /  9.3 /  9.5    448 (0.88)  12.1 / 12.3 / 11.6 / 10.4 / 10.4 / 10.6
-//                512 (1.00)         13.9 / 13.8 / 13.9 / 14.1 / 12.7 / 11.8    640 (1.25)  16.3 / 16.0 / 16.5 / 16.4 / 15.2 / 14.6
-//   8 requests   384                 9.0 /  8.8 /  9.2 /  9.0 /  9.2 /  9.4    448         11.7 / 11.2 / 10.1 / 10.3 / 10.3 / 10.1
-//                512                13.1 / 13.2 / 13.3 / 11.5 / 11.3 / 11.4    640         15.5 / 16.0 / 14.7 / 14.1 / 14.3 / 14.6
-//   64 requests  384                 8.7 /  9.1 /  9.1 /  9.3 /  9.5 /  9.7    448         11.7 / 10.2 / 10.2 / 10.4 / 10.3 / 10.5
-//                512                13.2 / 13.3 / 12.0 / 11.4 / 11.5 / 11.7    640         15.8 / 14.7 / 14.1 / 14.5 / 14.8 / 15.0
-// and 0 / 2 / 4 / 6 / 7 at 320 blocks (0.63), 1 request, 7.7 / 8.0 / 8.0 / 8.2 / 8.4, at 1024 (2.0) 23.7 / 23.8 / 23.8 /
-// 23.5 / 23.5, at 2048 (4.0), 8 requests, 44.2 / 44.1 / 44.3 / 44.6 / 44.8, 64 requests, 43.9 / 44.1 / 44.4 / 44.8 / 45.0.
+// have (the table may be longer); a launch that read nothing ahead sleeps for nothing.  Every step of the way to the first
+// store delays the stores as well: with `n_req` requests whose owner is found step by step they wait less.  The kernels
+// find it in one step and pass pause_requests(n_req).
+// Restore of 32 KiB blocks, cold, us, pause 0 / 2 / 5 / 6 / 7 / 8 / 9 (items / chip_waves in brackets):
+//   1 request    384 blocks (0.75)  10.5 /  9.1 /  9.4 /  9.5 /  9.5 /  9.5 /  9.7    448 (0.88)  12.1 / 12.3 / 10.6 / 10.4 / 10.4 / 10.6 / 10.7
+//                512 (1.00)         13.9 / 13.8 / 14.1 / 14.2 / 13.5 / 12.6 / 12.1    640 (1.25)  16.1 / 15.9 / 16.3 / 15.1 / 14.5 / 14.4 / 14.5
+//   8 requests   384                 9.8 /  8.7 /  9.3 /  9.0 /  9.0 /  9.2 /  9.5    448         11.6 / 11.9 / 10.0 / 10.1 / 10.3 / 10.4 / 10.1
+//                512                13.2 / 13.2 / 13.4 / 12.3 / 11.5 / 11.3 / 11.5    640         15.5 / 15.7 / 15.5 / 14.4 / 14.2 / 14.2 / 14.4
+//   64 requests  384                 9.4 /  8.8 /  9.2 /  9.0 /  9.1 /  9.3 /  9.5    448         11.7 / 11.8 / 10.0 / 10.2 / 10.4 / 10.2 / 10.1
+//                512                13.0 / 13.3 / 13.0 / 11.9 / 11.3 / 11.3 / 11.6    640         15.3 / 15.8 / 14.9 / 14.3 / 14.1 / 14.2 / 14.5
+// and 0 / 2 / 5 / 7 at 320 blocks (0.63), 1 request, 7.6 / 7.9 / 7.9 / 8.3, at 1024 (2.0) 23.7 / 23.8 / 23.7 / 23.5, at 2048
+// (4.0), 8 requests, 44.1 / 44.1 / 44.2 / 44.4, 64 requests 43.9 / 43.9 / 44.1 / 44.3.
 // Where the time falls off a step, the pause stands behind it.
-// `file`: a retrieve of one request reads ahead behind two more loads and starts later.  One call / in a train, pause 0 /
-// 7: 320 blocks 10.6 / 11.2 and 9.3 / 9.4, 384  12.5 / 11.8 and 11.1 / 10.3, 448  14.6 / 13.3 and 13.2 / 11.7, 640  18.3
-// / 16.8 and 16.9 / 15.8.
+// `file`: a retrieve of one request reads ahead behind two more loads and starts later.  In a train, pause 2 / 5 / 6 / 7 / 8:
+// 384 blocks 9.6 / 9.9 / 10.0 / 10.2 / 10.4, 448  12.6 / 11.1 / 11.2 / 11.2 / 11.3, 512  14.6 / 14.7 / 13.9 / 12.9 / 12.5, 640
+// 16.8 / 15.7 / 15.4 / 15.5 / 15.7; a call each the same and 1.4 more.
 constexpr uint32_t hold_back_pause(uint32_t items, uint32_t chip_waves, uint32_t n_req, bool file) {
   if (items > 2 * chip_waves || 32 * items <= 21 * chip_waves) return 0;
-  if (file) return 7;
+  if (file) return 32 * items <= 25 * chip_waves ? 2 : 32 * items <= 29 * chip_waves ? 5 : 5 * items <= 6 * chip_waves ? 8 : 6;
   const uint32_t steps = n_req > 1 ? 32u - static_cast<uint32_t>(__builtin_clz(n_req - 1)) : 0u;
-  if (32 * items > 29 * chip_waves) return 8 - (steps + 1) / 2;
+  if (32 * items > 29 * chip_waves) return (5 * items > 6 * chip_waves ? 7 : 8) - (steps + 1) / 2;
   if (32 * items > 25 * chip_waves) return 6 - (steps + 1) / 2;
   return steps < 4 ? 2 - steps / 2 : 0;
 }
+
+// The number of requests that hold_back_pause sees where one ballot finds an item's owner: only the longest scan (six
+// steps, beyond 32 requests) still delays the stores by about one step.
+constexpr uint32_t pause_requests(uint32_t n_req) { return n_req > 32 ? 2 : 1; }
 
 // Slice of a CU-budgeted copy of `blocks` blocks (K and V each), in pieces of 1 KiB.  What a compute unit moves depends on
 // the length of a wavefront's run of loads and of stores, not on the bytes in flight: a plain cold copy on 8 / 32 / 64

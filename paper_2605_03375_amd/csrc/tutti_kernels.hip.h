@@ -42,6 +42,8 @@ constexpr uint32_t kBudgetWgThreads = 1024;  // CU-budgeted launches: one 16-wav
 // costs no scratch: 256-thread kernels with at most four 16-byte units in flight per lane.
 constexpr int min_waves_per_simd(int wg_threads, int units) { return (wg_threads == 256 && units <= 4) ? 8 : 4; }
 
+constexpr int kOne = 1, kFew = 2, kMany = 3;  // requests a kernel is for: one, up to 64, any number
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // A wave-uniform 32-bit value moved to a scalar register.
@@ -371,8 +373,6 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
 // REQS = kFew: the host knows of at most 64 requests.  A kernel of its own, because the other scans' arguments push the
 // scalar registers over their limit, and the kernel then starts with more rounds of argument loads and spills (what that
 // gives stands at few_requests).
-constexpr int kOne = 1, kFew = 2, kMany = 3;  // requests a kernel is for: one, up to 64, any number
-
 template <int WG, int REQS, typename P>
 __device__ __forceinline__ void scan_extents(const ScanGeom g, const uint32_t *__restrict__ n_blocks, uint32_t n_req,
                                              ReqLds l, tutti_extent *__restrict__ ext_out,
@@ -549,6 +549,20 @@ __device__ __forceinline__ uint32_t find_owner(const uint32_t *a, uint32_t n, ui
       hi = mid;
   }
   return lo;
+}
+
+// The same for a key that all lanes of the wavefront share (and all are active): every lane compares, a ballot counts.
+// One read of LDS for up to 64 requests (FEW: there are no more) and two for more, instead of 6 to 11 that wait for each
+// other.
+template <bool FEW>
+__device__ __forceinline__ uint32_t find_owner_of_wave(const uint32_t *a, uint32_t n, uint32_t key) {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  if (FEW) return static_cast<uint32_t>(__popcll(__ballot(lane < n && a[lane] <= key))) - 1;
+  const uint32_t step = (n + kWave - 1) / kWave;  // at most TUTTI_MAX_REQ / 64
+  uint32_t at = lane * step;
+  const uint32_t first = (static_cast<uint32_t>(__popcll(__ballot(at < n && a[at] <= key))) - 1) * step;
+  at = first + lane;
+  return first + static_cast<uint32_t>(__popcll(__ballot(lane < step && at < n && a[at] <= key))) - 1;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1355,7 +1369,11 @@ struct Item {
 // a listed position that is not a block of a request that takes part is passed over.
 // u: (block, kind) unit in staging order; s: its slice, piece or tile; `report`: this thread reports what it finds out
 // of order with a unit's first part.
-template <bool SEP, bool ORD, bool DIRECT>
+// OWNER: how the request is found; kPerLane: the lanes ask for units of their own, kOfFew and kOfMany: all for the same
+// one, of at most 64 requests or of any number.
+constexpr int kPerLane = 0, kOfFew = 1, kOfMany = 2;
+
+template <bool SEP, bool ORD, bool DIRECT, int OWNER>
 __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t u, uint32_t s,
                                             bool report) {
   Item d;
@@ -1364,6 +1382,9 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
   const uint32_t *off = SEP ? l.blk_off : l.table_off;
   uint32_t r, toff, end;
   uint64_t stage_off;
+  const auto owner = [&](const uint32_t *of, uint32_t key) {
+    return OWNER == kPerLane ? find_owner(of, n_req, key) : find_owner_of_wave<OWNER == kOfFew>(of, n_req, key);
+  };
   // all of a request's words are asked for together: they come out of LDS one behind the other, and a workgroup that has
   // one tile in flight waits for each (tiles of 16-byte rows on 8 compute units: 594 ns each with two waits, 550 with one)
   const auto request = [&] {
@@ -1384,12 +1405,12 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
       d.tab_idx = d.n = d.j = 0;
       return d;
     }
-    r = find_owner(l.table_off, n_req, pos);
+    r = owner(l.table_off, pos);
     request();
     d.n = end - toff;
     d.j = pos - toff;
   } else {
-    r = find_owner(off, n_req, u >> 1);
+    r = owner(off, u >> 1);
     request();
     d.n = end - toff;
     const uint32_t v = u - 2u * toff;
@@ -1424,11 +1445,12 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
   return d;
 }
 
-template <bool SEP, bool ORD = false, bool DIRECT = false>
+template <bool SEP, int REQS, bool ORD = false, bool DIRECT = false>
 __device__ __forceinline__ Item decode_item(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t it,
                                             uint32_t lane) {
   const uint32_t u = it / a.slices_per_block;
-  return decode_unit<SEP, ORD, DIRECT>(a, l, n_req, u, it - u * a.slices_per_block, lane == 0);
+  return decode_unit<SEP, ORD, DIRECT, REQS == kMany ? kOfMany : kOfFew>(a, l, n_req, u, it - u * a.slices_per_block,
+                                                                         lane == 0);
 }
 
 // Block id of an item through the scalar (constant) path: the index is wave-uniform, so this is
@@ -1543,7 +1565,7 @@ __device__ __forceinline__ uint32_t count_units(const MoveArgs &a, const ReqLds 
   return 2u * rfl(SEP ? l.blk_off[n_req] : l.table_off[n_req]);
 }
 
-template <int DIR, bool HND, int U, int NT, int WG, bool SEP, bool ORD, bool DIRECT>
+template <int DIR, bool HND, int U, int NT, int WG, int REQS, bool SEP, bool ORD, bool DIRECT>
 __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                            uint32_t copy_wgs, const Preload<U> &pre) {
   constexpr uint32_t kSlice = kWave * 16u * U;
@@ -1553,30 +1575,33 @@ __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uin
 
   uint32_t it = first_item<WG, U>(a, wg, copy_wgs);
   if (it >= n_items) return;
-  Item cur = decode_item<SEP, ORD, DIRECT>(a, l, n_req, it, lane);
+  Item cur = decode_item<SEP, REQS, ORD, DIRECT>(a, l, n_req, it, lane);
   uint32_t id = load_block_id(a, cur);
-  bool first = true;
+  uint32_t ahead = DIR == kUnpack && pre.valid ? 1u : 0u;  // the item at hand has been read ahead
   for (;;) {
     const uint32_t nit = it + n_waves;
     const bool more = nit < n_items;
     Item nxt = cur;
     uint32_t nid = a.num_blocks;
     if (more) {
-      nxt = decode_item<SEP, ORD, DIRECT>(a, l, n_req, nit, lane);
+      nxt = decode_item<SEP, REQS, ORD, DIRECT>(a, l, n_req, nit, lane);
       nid = load_block_id(a, nxt);
     }
     // the preloaded bytes were read where the item's slice sits when the extents are the library's own; extents
     // from the caller (and the files of the direct-to-block mode) may put it elsewhere: then the slice is loaded
     // from where they say
-    const bool preloaded = DIR == kUnpack && first && pre.valid &&
+    const bool preloaded = DIR == kUnpack && ahead != 0 &&
                            ((!SEP && !ORD && !DIRECT) ||
                             cur.obj_blk + static_cast<uint64_t>(cur.s) * kSlice == pre.src);
     if (preloaded)
       store_preloaded<HND, U, NT>(a, cur, id, lane, pre);
     else
       move_one<DIR, HND, U, NT, ORD, DIRECT>(a, cur, id, lane);
-    first = false;
     if (!more) break;
+    if (DIR == kUnpack) {
+      ahead = 0;
+      asm volatile("" : "+s"(ahead));  // left to itself the compiler takes the first item out of the loop, and the loop
+    }                                  // then starts with a wait for that item's stores
     cur = nxt;
     id = nid;
     it = nit;
@@ -1744,7 +1769,7 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
       const uint32_t q = static_cast<uint32_t>(mine) / ppb;
       const uint32_t rest = (static_cast<uint32_t>(mine) - q * ppb) * U + lane % U;
       const uint32_t q2 = rest / ppb;
-      const Item d = decode_unit<SEP, false, DIRECT>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
+      const Item d = decode_unit<SEP, false, DIRECT, kPerLane>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
       if (d.obj_ptr != nullptr) {
         const uint32_t id = d.tab_idx < a.table_len ? a.table[d.tab_idx] : a.num_blocks;
         off = d.s * kPiece;
@@ -1875,7 +1900,7 @@ struct TileMove {
 // One tile per workgroup and iteration.  Not pipelined across tiles: holding the next tile's loads in
 // registers cost the eighth resident workgroup per CU (more than 64 VGPRs) and bought 0.3 us; the eight
 // workgroups of a CU cover each other's latency instead.
-template <int DIR, int PT, int WG, bool SEP>
+template <int DIR, int PT, int WG, int REQS, bool SEP>
 __device__ __forceinline__ void move_items_hnd_lds(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                                    uint32_t copy_wgs, unsigned char *tile) {
   typedef TileMove<DIR, PT, WG> TM;
@@ -1890,7 +1915,7 @@ __device__ __forceinline__ void move_items_hnd_lds(const MoveArgs a, const ReqLd
   g.r_mask = (1u << g.rs) - 1u;
 
   for (uint32_t it = wg; it < n_items; it += copy_wgs) {
-    const Item d = decode_item<SEP>(a, l, n_req, it, tid);  // workgroup-uniform; thread 0 reports
+    const Item d = decode_item<SEP, REQS>(a, l, n_req, it, tid);  // workgroup-uniform; thread 0 reports
     const uint32_t id = load_block_id(a, d);
     if (d.obj_ptr != nullptr && id < a.num_blocks) {
       u32x4 v[PT];
@@ -1941,7 +1966,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_move(const Mo
   if (PIECES)
     move_pieces<DIR, HND, U, NT, WG, true, false>(a, l, n_req, blockIdx.x, gridDim.x);
   else
-    move_items<DIR, HND, U, NT, WG, true, false, false>(a, l, n_req, blockIdx.x, gridDim.x, pre);
+    move_items<DIR, HND, U, NT, WG, kMany, true, false, false>(a, l, n_req, blockIdx.x, gridDim.x, pre);
 }
 
 template <int DIR, int PT, int WG>
@@ -1950,7 +1975,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, PT)) void k_move_lds(con
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, n_req, true);
   lds_from_caller_extents(ext, n_req, l, a.table_len, a.block_bytes, a.stage_cap, a.status);
-  move_items_hnd_lds<DIR, PT, WG, true>(a, l, n_req, blockIdx.x, gridDim.x, smem + align16(req_lds_bytes(n_req)));
+  move_items_hnd_lds<DIR, PT, WG, kMany, true>(a, l, n_req, blockIdx.x, gridDim.x, smem + align16(req_lds_bytes(n_req)));
 }
 
 // One layer's restore (DIR = kUnpack) or save (DIR = kPack) in one launch: every workgroup redoes the
@@ -2002,7 +2027,8 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
                      if (DIR == kUnpack && !ORD && !PIECES && reads_ahead(U) && copies) pre = preload_first<U, NT, WG>(m, wg, w.copy_wgs);
                    });
   if (REQS == kFew && DIR == kUnpack && pre.valid)
-    hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, a.n_req, false));
+    hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, pause_requests(a.n_req),
+                              false));
   SqeHead head;
   head.live = false;
   if (blockIdx.x < w.sqe_wgs) head = sqe_head(q, l, a.n_req, 0);
@@ -2017,7 +2043,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     if (PIECES)
       move_pieces<DIR, HND, U, NT, WG, false, false>(m, l, a.n_req, wg, w.copy_wgs);
     else
-      move_items<DIR, HND, U, NT, WG, false, ORD, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
+      move_items<DIR, HND, U, NT, WG, REQS, false, ORD, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
   }
   if (blockIdx.x < w.sqe_wgs) emit_sqes(q, l, a.n_req, 0, w.sqe_wgs, head);
 }
@@ -2121,7 +2147,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
     if (PIECES)
       move_pieces<DIR, false, U, 3, WG, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);
     else
-      move_items<DIR, false, U, 3, WG, false, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
+      move_items<DIR, false, U, 3, WG, REQS, false, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
   }
   if (bx < w.sqe_wgs) emit_iocbs(g, q, d, l, a.n_req, lead, w.sqe_wgs, head);
 }
@@ -2137,7 +2163,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, PT)) void k_layer_lds(co
   head.live = false;
   if (blockIdx.x < w.sqe_wgs) head = sqe_head(q, l, a.n_req, 0);
   if (blockIdx.x - w.copy_first < w.copy_wgs)
-    move_items_hnd_lds<DIR, PT, WG, false>(m, l, a.n_req, blockIdx.x - w.copy_first, w.copy_wgs,
+    move_items_hnd_lds<DIR, PT, WG, REQS, false>(m, l, a.n_req, blockIdx.x - w.copy_first, w.copy_wgs,
                                     smem + align16(req_lds_bytes(a.n_req)));
   if (blockIdx.x < w.sqe_wgs) emit_sqes(q, l, a.n_req, 0, w.sqe_wgs, head);
 }

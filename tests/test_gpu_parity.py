@@ -1006,6 +1006,25 @@ def test_scan_of_few_requests(orc, H, n_req):
         H.check_ring_layer(orc, c, layer=1, write=write, depth=3, first_slot=1, n_slots=2)
 
 
+@pytest.mark.parametrize("n_req", [2, 63, 64, 65, 127, 128, 129, 2047, 2048])
+def test_owner_among_mostly_empty_requests(orc, H, n_req):
+    """An item's request is the last of those that share its offset: runs of empty requests in front of, between and behind
+    the few that have blocks, which sit on both sides of the 64 probes of a search among more than 64."""
+    say("owner among", n_req, "requests")
+    step = (n_req + 63) // 64
+    n = np.zeros(n_req, np.uint32)
+    n[[r for r in (1, step - 1, step, 2 * step - 1, 63 * step - 1, 63 * step, n_req // 2, n_req - 1) if 0 <= r < n_req]] = 9
+    total = int(n.sum())
+    table = np.random.default_rng(8700 + n_req).permutation(total + 5)[:total]
+    for d, layout in ((64, 0), (16, 1)):  # slices; tiles through LDS
+        c = H.LayerCase(T=16, h=4, d=d, e=2, N=total + 5, n_blocks=n, table=table, align=4096, chunk=8192, layout=layout,
+                        name=f"owner{n_req}l{layout}")
+        H.check_everything(orc, c)
+        H.check_layer_restore(orc, c, cu_budget=2)
+    H.check_ring_layer(orc, H.LayerCase(T=16, h=4, d=64, e=2, N=total + 5, n_blocks=n, table=table, align=4096, chunk=8192),
+                       layer=0, write=True, depth=1, first_slot=0, n_slots=1)
+
+
 def test_scan_of_many_requests_wide_sums(orc, H):
     """Alignment units above 1 MiB (the padding is then summed in 64 bits), and block counts whose sum passes 2^32:
     the requests in front of the one that runs beyond the table are restored, the published extents are plain sums."""
