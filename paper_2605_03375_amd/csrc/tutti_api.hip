@@ -247,6 +247,14 @@ bool few_requests(const Launch &L, const MoveArgs &m, uint32_t n_req) {
   return n_req <= kWave && !m.visit && !(L.pieces && L.wg_threads == kBudgetWgThreads);
 }
 
+// A pack of several requests that reads its slices while it scans (preload_pack): whole slices, 3/4 of the chip's wavefronts
+// at most.
+template <int DIR>
+bool pack_ahead(const Launch &L, uint32_t n_req, uint64_t wave_items) {
+  return DIR == kPack && n_req > 1 && !L.pieces && !L.hnd_lds && L.wg_threads == kWgThreads &&
+         L.unroll == kDefaultUnroll && 4 * wave_items <= 3 * whole_gpu_waves(L);
+}
+
 uint64_t counted_slices(const Launch &L, uint32_t bytes) {
   const uint64_t slice = kPiece * (L.unroll < 8 ? L.unroll : 8u);
   return (bytes + slice - 1) / slice;
@@ -486,7 +494,7 @@ template <typename S, int DIR, bool HND, int REQS>
 hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStream_t s, const MoveArgs &m,
                               const SqeArgs &q, const LayoutArgs &a, const Roles &w) {
   const dim3 grid(n_wgs), block(S::WG);
-  if constexpr (REQS != kOne) {
+  if constexpr (REQS == kFew || REQS == kMany) {
     if constexpr (DIR == kUnpack && REQS == kMany) {
       if (m.visit) {  // the caller's visiting order
         hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>), grid, block, lds, s, m, q, a, w);
@@ -508,12 +516,22 @@ template <int DIR, bool HND>
 hipError_t launch_layer(const Launch &L, uint64_t entry_quarters, uint32_t lds, hipStream_t s, const MoveArgs &m,
                         const SqeArgs &q, const LayoutArgs &a) {
   uint32_t n_wgs = 0;
-  const Roles w = make_roles(L, entry_quarters, &n_wgs);
+  Roles w = make_roles(L, entry_quarters, &n_wgs);
   return with_shape(L, [&](auto sh) {
     using S = decltype(sh);
     if constexpr (has_few<S>) {
       if (one_request_path<DIR>(L, m, a.n_req, move_wave_items(L, m)))
         return launch_layer_shape<S, DIR, HND, kOne>(false, n_wgs, lds, s, m, q, a, w);
+      if constexpr (DIR == kPack && S::WG == kWgThreads) {
+        if (pack_ahead<DIR>(L, a.n_req, move_wave_items(L, m))) {
+          if (a.n_req <= kWave) return launch_layer_shape<S, DIR, HND, kFewAhead>(false, n_wgs, lds, s, m, q, a, w);
+          // the entry writers' scan is the longer one and reads nothing ahead: workgroups of their own
+          if (L.grid + w.sqe_wgs <= whole_gpu_wgs(L) && a.geom.align <= (1u << 20)) {
+            w.copy_first = w.sqe_wgs;
+            return launch_layer_shape<S, DIR, HND, kManyAhead>(false, L.grid + w.sqe_wgs, lds, s, m, q, a, w);
+          }
+        }
+      }
       if (few_requests(L, m, a.n_req)) return launch_layer_shape<S, DIR, HND, kFew>(L.pieces, n_wgs, lds, s, m, q, a, w);
     }
     return launch_layer_shape<S, DIR, HND, kMany>(L.pieces, n_wgs, lds, s, m, q, a, w);
@@ -1002,6 +1020,10 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
     if constexpr (has_few<S>) {
       if (one_request_path<DIR>(R, m, n_req, move_wave_items(R, m)))
         return launch_ring_shape<S, DIR, kOne>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+      if constexpr (DIR == kPack && S::WG == kWgThreads) {
+        if (n_req <= kWave && pack_ahead<DIR>(R, n_req, move_wave_items(R, m)))
+          return launch_ring_shape<S, DIR, kFewAhead>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+      }
       if (few_requests(R, m, n_req)) return launch_ring_shape<S, DIR, kFew>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
     }
     return launch_ring_shape<S, DIR, kMany>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
@@ -1700,6 +1722,10 @@ void least_resident_layer(int *worst) {
   least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany>,
                  k_layer<DIR, HND, 4, 3, kWgThreads, kMany, false, true>);
   if constexpr (DIR == kUnpack) least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, true>);
+  if constexpr (DIR == kPack) {
+    least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFewAhead>);
+    least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kManyAhead>);
+  }
 }
 
 template <int DIR>
@@ -1708,6 +1734,7 @@ void least_resident_ring(int *worst) {
   least_resident(worst, few, k_layer_ring<DIR, 4, kWgThreads, kOne>, k_layer_ring<DIR, 4, kWgThreads, kFew>,
                  k_layer_ring<DIR, 4, kWgThreads, kFew, true>);
   least_resident(worst, many, k_layer_ring<DIR, 4, kWgThreads, kMany>, k_layer_ring<DIR, 4, kWgThreads, kMany, true>);
+  if constexpr (DIR == kPack) least_resident(worst, few, k_layer_ring<DIR, 4, kWgThreads, kFewAhead>);
 }
 
 template <int DIR>

@@ -42,7 +42,10 @@ constexpr uint32_t kBudgetWgThreads = 1024;  // CU-budgeted launches: one 16-wav
 // costs no scratch: 256-thread kernels with at most four 16-byte units in flight per lane.
 constexpr int min_waves_per_simd(int wg_threads, int units) { return (wg_threads == 256 && units <= 4) ? 8 : 4; }
 
-constexpr int kOne = 1, kFew = 2, kMany = 3;  // requests a kernel is for: one, up to 64, any number
+// Requests a kernel is for: one, up to 64, any number; ...Ahead: a pack that reads ahead (preload_pack).
+constexpr int kOne = 1, kFew = 2, kMany = 3, kFewAhead = 4, kManyAhead = 5;
+constexpr bool packs_ahead(int reqs) { return reqs == kFewAhead || reqs == kManyAhead; }
+constexpr bool any_number(int reqs) { return reqs == kMany || reqs == kManyAhead; }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -253,12 +256,12 @@ __device__ __forceinline__ void wave_scan_extents(const ScanGeom g, uint32_t n, 
 // within table_len, and the host keeps 2 * table_len within 32 bits.  The others (the entry writers and the publishing
 // workgroup; align > 1 MiB, where the padding of 2048 requests may need more bits; the direct-to-block mode, whose
 // offsets wrap) carry 64-bit sums and the chunks.
-template <int WG, bool EXACT, bool SAT>
+template <int WG, bool EXACT, bool SAT, typename P>
 __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t *__restrict__ n_blocks, uint32_t n_req,
                                                 ReqLds l, tutti_extent *__restrict__ ext_out,
                                                 uint64_t *__restrict__ totals_out, uint32_t table_len,
                                                 uint32_t *__restrict__ status, const uint32_t *__restrict__ file_id,
-                                                const FileArgs files) {
+                                                const FileArgs files, P under_loads) {
   typedef typename std::conditional<EXACT, uint64_t, uint32_t>::type S;
   constexpr uint32_t kPer = TUTTI_MAX_REQ / WG, kWaves = WG / kWave;
   static_assert(3 * kWaves <= kWave, "the wavefronts' totals fit the staging-offset slots of 65 requests");
@@ -270,6 +273,7 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
                        // keeps these registers free for the bytes that a restore has in flight meanwhile
 #pragma unroll
     for (uint32_t k = 0; k < kPer; ++k) n[k] = (k < per && r0 + k < n_req) ? n_blocks[r0 + k] : 0u;
+    under_loads();
 #pragma unroll
     for (uint32_t k = 0; k < kPer; ++k) {
       blocks = add_<SAT>(blocks, static_cast<S>(n[k]));
@@ -379,19 +383,30 @@ __device__ __forceinline__ void scan_extents(const ScanGeom g, const uint32_t *_
                                              uint64_t *__restrict__ totals_out, uint32_t table_len,
                                              uint32_t *__restrict__ status, bool with_chunks,
                                              const uint32_t *__restrict__ file_id, const FileArgs files, P preload) {
-  if (REQS == kFew || n_req <= kWave) {
-    preload();
-    if (threadIdx.x < kWave) {
-      const uint32_t n = threadIdx.x < n_req ? n_blocks[threadIdx.x] : 0u;
-      const uint32_t fid = file_id && threadIdx.x < n_req ? file_id[threadIdx.x] : 0u;
+  const auto under_loads = [&] {  // a pack's: behind the loads of the counts, so that the scan need not wait for it
+    if (packs_ahead(REQS)) {
+      __builtin_amdgcn_sched_barrier(0);
+      preload();
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if (REQS == kFew || REQS == kFewAhead || (REQS == kMany && n_req <= kWave)) {
+    if (!packs_ahead(REQS)) preload();
+    uint32_t n = 0, fid = 0;
+    if (threadIdx.x < n_req) {
+      n = n_blocks[threadIdx.x];
+      if (file_id) fid = file_id[threadIdx.x];
+    }
+    under_loads();
+    if (threadIdx.x < kWave)
       wave_scan_extents(g, n, fid, n_req, threadIdx.x, l, ext_out, totals_out, table_len, status, with_chunks, file_id,
                         files);
-    }
   } else if (with_chunks || file_id || g.align > (1u << 20)) {
-    wg_scan_extents<WG, true, false>(g, n_blocks, n_req, l, ext_out, totals_out, table_len, status, file_id, files);
+    wg_scan_extents<WG, true, false>(g, n_blocks, n_req, l, ext_out, totals_out, table_len, status, file_id, files, [] {});
   } else {
-    wg_scan_extents<WG, false, true>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, nullptr, files);
-    preload();
+    wg_scan_extents<WG, false, true>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, nullptr, files,
+                                     under_loads);
+    if (!packs_ahead(REQS)) preload();
   }
   __syncthreads();
 }
@@ -1365,15 +1380,17 @@ struct Item {
 
 // SEP: the extents came from the caller (lds_from_caller_extents): items are numbered by blk_off, the table is
 // indexed by the request's own table_off, and requests that cannot be honoured already have a zero-sized object.
-// ORD: the units are visited in the order a.visit lists (all K blocks, then all V blocks, each in that order);
+// ORD: the units in staging order, or all K blocks and then all V blocks, each in the order that a.visit lists or in the
+// table's own;
 // a listed position that is not a block of a request that takes part is passed over.
 // u: (block, kind) unit in staging order; s: its slice, piece or tile; `report`: this thread reports what it finds out
 // of order with a unit's first part.
 // OWNER: how the request is found; kPerLane: the lanes ask for units of their own, kOfFew and kOfMany: all for the same
 // one, of at most 64 requests or of any number.
 constexpr int kPerLane = 0, kOfFew = 1, kOfMany = 2;
+constexpr int kStagingOrder = 0, kListOrder = 1, kTableOrder = 2;
 
-template <bool SEP, bool ORD, bool DIRECT, int OWNER>
+template <bool SEP, int ORD, bool DIRECT, int OWNER>
 __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t u, uint32_t s,
                                             bool report) {
   Item d;
@@ -1394,10 +1411,10 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
     end = off[r + 1];
     __builtin_amdgcn_sched_barrier(0);
   };
-  if (ORD) {
+  if (ORD != kStagingOrder) {
     d.kind = u >= a.table_len ? 1u : 0u;
-    const_u32_ptr vis = as_const(a.visit);
-    const uint32_t pos = vis[rfl(u - d.kind * a.table_len)];  // wave-uniform index: one scalar load
+    uint32_t pos = u - d.kind * a.table_len;
+    if (ORD == kListOrder) pos = as_const(a.visit)[rfl(pos)];  // wave-uniform index: one scalar load
     if (pos >= l.table_off[n_req]) {  // beyond the blocks of the requests that take part
       d.obj_ptr = nullptr;
       d.obj_blk = nullptr;
@@ -1424,7 +1441,8 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
     const uint64_t end = file_off + a.block_bytes;
     d.obj_ptr = a.stage;
     d.obj_blk = a.stage + stage_off + file_off;
-    if (u >= a.ctx_cap) {
+    const uint32_t ctx = ORD == kTableOrder ? 2u * toff + d.kind * d.n + d.j : u;  // the unit's place in staging order
+    if (ctx >= a.ctx_cap) {
       d.obj_ptr = nullptr;  // beyond the IOCBs the caller gave: not recorded, not executed
     } else if (stage_off == kNoFile || end > a.file_stride || end < file_off) {
       if (report) atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
@@ -1437,7 +1455,7 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
   if (!SEP && ((stage_off > a.stage_cap) | (d.obj_bytes > (a.stage_cap - stage_off) / 2))) {
     // the request's objects do not fit: skip it, report once
     // (an ordered launch reports from its first workgroup instead: its list need not name the request's first block)
-    if (!ORD && report && d.j == 0 && d.kind == 0) atomicOr(a.status, TUTTI_ST_STAGE_CAP);
+    if (ORD != kListOrder && report && d.j == 0 && d.kind == 0) atomicOr(a.status, TUTTI_ST_STAGE_CAP);
     d.obj_ptr = nullptr;
   } else if ((static_cast<uint64_t>(d.j) + 1) * a.block_bytes > d.obj_bytes) {
     d.obj_ptr = nullptr;  // the block would end beyond its object (caller-made extents only)
@@ -1445,11 +1463,11 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
   return d;
 }
 
-template <bool SEP, int REQS, bool ORD = false, bool DIRECT = false>
+template <bool SEP, int REQS, int ORD = kStagingOrder, bool DIRECT = false>
 __device__ __forceinline__ Item decode_item(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t it,
                                             uint32_t lane) {
   const uint32_t u = it / a.slices_per_block;
-  return decode_unit<SEP, ORD, DIRECT, REQS == kMany ? kOfMany : kOfFew>(a, l, n_req, u, it - u * a.slices_per_block,
+  return decode_unit<SEP, ORD, DIRECT, any_number(REQS) ? kOfMany : kOfFew>(a, l, n_req, u, it - u * a.slices_per_block,
                                                                          lane == 0);
 }
 
@@ -1460,6 +1478,15 @@ __device__ __forceinline__ uint32_t load_block_id(const MoveArgs &a, const Item 
   const uint32_t idx = __builtin_amdgcn_readfirstlane(d.tab_idx);  // uniform by construction
   const bool ok = __builtin_amdgcn_readfirstlane(d.obj_ptr != nullptr && idx < a.table_len ? 1 : 0) != 0;
   return ok ? tab[idx] : a.num_blocks;
+}
+
+// A pack's last slice of an object: zeroes behind it, up to the object's aligned size (fewer than `align` bytes).
+__device__ __forceinline__ void zero_tail(const MoveArgs &a, const Item &d, uint32_t lane) {
+  if (d.j + 1 == d.n && d.s + 1 == a.slices_per_block) {
+    const uint64_t used = static_cast<uint64_t>(d.n) * a.block_bytes;
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    for (uint64_t o = used + lane * 16ull; o < d.obj_bytes; o += kWave * 16ull) st16<0>(d.obj_ptr + o, zero);
+  }
 }
 
 // ORD: the block need not be a whole number of slices (the others are moved as pieces then).
@@ -1493,12 +1520,7 @@ __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint3
   } else if (lane == 0 && d.s == 0 && a.status) {
     atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
   }
-  if (DIR == kPack && !DIRECT && d.j + 1 == d.n && d.s + 1 == a.slices_per_block) {
-    // zero the tail of the object up to its aligned size (fewer than `align` bytes)
-    const uint64_t used = static_cast<uint64_t>(d.n) * a.block_bytes;
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-    for (uint64_t o = used + lane * 16ull; o < d.obj_bytes; o += kWave * 16ull) st16<0>(d.obj_ptr + o, zero);
-  }
+  if (DIR == kPack && !DIRECT) zero_tail(a, d, lane);
 }
 
 // Holds the stores of a wavefront that has read ahead back (hold_back_pause).
@@ -1534,6 +1556,51 @@ __device__ __forceinline__ Preload<U> preload_first(const MoveArgs &a, uint32_t 
   return p;
 }
 
+// A pack in table order (packs_ahead): the launch gives every wavefront one item at most, so the order does not matter to the
+// memory, and where an item's bytes sit follows from the table alone: they are read while the requests are being scanned,
+// instead of behind the scan, the owner and the block id: small saves are bound by that chain of dependent loads.  Cold,
+// us, in staging order / so: 32 KiB blocks, 64 in 30 requests 4.7 / 3.8, 128 in 128 7.1 / 5.4, 300 in 3 9.8 / 8.6; 1280 blocks
+// of 8 KiB in 512 requests (42 MB of traffic) 10.7 / 9.6.  With several items a wavefront, reading all K blocks first loses
+// (1000 blocks in 8 requests 24.3 / 25.5), and a table longer than the requests is read for nothing: 64 blocks with a table
+// of 380 3.96 / 4.29, of 1000 4.2 / 5.0, of 8000 4.0 / 6.1; at 3/4 of the chip both are still small.
+template <bool HND, int U, int NT, int WG>
+__device__ __forceinline__ Preload<U> preload_pack(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs) {
+  constexpr uint32_t kSlice = kWave * 16u * U;
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t it = first_item<WG, U>(a, wg, copy_wgs);
+  uint32_t kind = 0, part = 0, id = a.num_blocks;
+  if (wg < copy_wgs && it < a.items_bound) {
+    const uint32_t u = it / a.slices_per_block;
+    part = it - u * a.slices_per_block;
+    kind = u >= a.table_len ? 1u : 0u;
+    id = as_const(a.table)[u - kind * a.table_len];
+  }
+  Preload<U> p;
+  p.valid = id < a.num_blocks;
+  // every path issues the loads (of block 0 for want of another): the scanning wavefront's wait for the counts, asked for
+  // in front of them, would otherwise be one for both
+  p.src = (kind ? a.v_base : a.k_base) + static_cast<uint64_t>(p.valid ? id : 0u) * a.block_stride;
+  load_slice<HND, U, NT>(a, p.src, part * kSlice + lane * 16u, p.buf);
+  return p;
+}
+
+// What is left of it once the requests are known.
+template <int U, int NT, int WG, int REQS, bool DIRECT>
+__device__ __forceinline__ void store_pack(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t wg,
+                                           uint32_t copy_wgs, const Preload<U> &pre) {
+  constexpr uint32_t kSlice = kWave * 16u * U;
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t it = first_item<WG, U>(a, wg, copy_wgs);
+  if (it >= a.items_bound) return;
+  const Item d = decode_item<false, REQS, kTableOrder, DIRECT>(a, l, n_req, it, lane);
+  if (d.obj_ptr == nullptr) return;
+  if (pre.valid)
+    store_slice<false, U, NT>(a, d.obj_blk, d.s * kSlice + lane * 16u, pre.buf);
+  else if (lane == 0 && d.s == 0 && a.status)
+    atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
+  if (!DIRECT) zero_tail(a, d, lane);
+}
+
 // Stores of an unpack item whose slice was preloaded (whole slices only: dense staging).
 template <bool HND, int U, int NT>
 __device__ __forceinline__ void store_preloaded(const MoveArgs &a, const Item &d, uint32_t id, uint32_t lane,
@@ -1555,9 +1622,9 @@ __device__ __forceinline__ void store_preloaded(const MoveArgs &a, const Item &d
 // Number of (block, kind) units of a copy.  Staged mode: the scan (or the loader of caller-made extents) has already cut
 // the requests at table_len blocks.  Direct-to-block mode: one unit per recorded context.  The host checked that
 // the bound (2 * table_len, or the contexts the IOCBs hold) times the slices per block fits 32 bits.
-template <bool SEP, bool ORD = false, bool DIRECT = false>
+template <bool SEP, int ORD = kStagingOrder, bool DIRECT = false>
 __device__ __forceinline__ uint32_t count_units(const MoveArgs &a, const ReqLds &l, uint32_t n_req) {
-  if (ORD) return 2u * a.table_len;  // every listed position, for K and for V
+  if (ORD != kStagingOrder) return 2u * a.table_len;  // every listed position, for K and for V
   if (DIRECT) {
     const uint64_t units = 2ull * rfl(l.table_off[n_req]);
     return static_cast<uint32_t>(units < a.ctx_cap ? units : a.ctx_cap);
@@ -1565,7 +1632,7 @@ __device__ __forceinline__ uint32_t count_units(const MoveArgs &a, const ReqLds 
   return 2u * rfl(SEP ? l.blk_off[n_req] : l.table_off[n_req]);
 }
 
-template <int DIR, bool HND, int U, int NT, int WG, int REQS, bool SEP, bool ORD, bool DIRECT>
+template <int DIR, bool HND, int U, int NT, int WG, int REQS, bool SEP, int ORD, bool DIRECT>
 __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                            uint32_t copy_wgs, const Preload<U> &pre) {
   constexpr uint32_t kSlice = kWave * 16u * U;
@@ -1591,12 +1658,12 @@ __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uin
     // from the caller (and the files of the direct-to-block mode) may put it elsewhere: then the slice is loaded
     // from where they say
     const bool preloaded = DIR == kUnpack && ahead != 0 &&
-                           ((!SEP && !ORD && !DIRECT) ||
+                           ((!SEP && ORD == kStagingOrder && !DIRECT) ||
                             cur.obj_blk + static_cast<uint64_t>(cur.s) * kSlice == pre.src);
     if (preloaded)
       store_preloaded<HND, U, NT>(a, cur, id, lane, pre);
     else
-      move_one<DIR, HND, U, NT, ORD, DIRECT>(a, cur, id, lane);
+      move_one<DIR, HND, U, NT, ORD == kListOrder, DIRECT>(a, cur, id, lane);
     if (!more) break;
     if (DIR == kUnpack) {
       ahead = 0;
@@ -1753,7 +1820,7 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t n_waves = copy_wgs * (WG / kWave);
   const uint32_t ppb = a.slices_per_block;
-  const uint64_t n_pieces = static_cast<uint64_t>(count_units<SEP, false, DIRECT>(a, l, n_req)) * ppb;
+  const uint64_t n_pieces = static_cast<uint64_t>(count_units<SEP, kStagingOrder, DIRECT>(a, l, n_req)) * ppb;
   const uint32_t n_items = static_cast<uint32_t>((n_pieces + U - 1) / U);
   const uint32_t in_piece = lane * 16u;
 
@@ -1769,7 +1836,7 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
       const uint32_t q = static_cast<uint32_t>(mine) / ppb;
       const uint32_t rest = (static_cast<uint32_t>(mine) - q * ppb) * U + lane % U;
       const uint32_t q2 = rest / ppb;
-      const Item d = decode_unit<SEP, false, DIRECT, kPerLane>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
+      const Item d = decode_unit<SEP, kStagingOrder, DIRECT, kPerLane>(a, l, n_req, q * U + q2, rest - q2 * ppb, true);
       if (d.obj_ptr != nullptr) {
         const uint32_t id = d.tab_idx < a.table_len ? a.table[d.tab_idx] : a.num_blocks;
         off = d.s * kPiece;
@@ -1966,7 +2033,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_move(const Mo
   if (PIECES)
     move_pieces<DIR, HND, U, NT, WG, true, false>(a, l, n_req, blockIdx.x, gridDim.x);
   else
-    move_items<DIR, HND, U, NT, WG, kMany, true, false, false>(a, l, n_req, blockIdx.x, gridDim.x, pre);
+    move_items<DIR, HND, U, NT, WG, kMany, true, kStagingOrder, false>(a, l, n_req, blockIdx.x, gridDim.x, pre);
 }
 
 template <int DIR, int PT, int WG>
@@ -1995,6 +2062,14 @@ struct Roles {
   uint32_t copy_wgs;    // there are more passes of entries than copy workgroups)
 };
 
+// The arguments that the way to the first load needs, asked for together: left to itself the compiler loads each where it
+// is used, five or six waits one behind the other.
+__device__ __forceinline__ void args_at_hand(const MoveArgs &m, const LayoutArgs &a, const Roles &w) {
+  asm volatile("" ::"s"(m.k_base), "s"(m.v_base), "s"(m.table), "s"(m.block_stride), "s"(m.num_blocks), "s"(m.table_len),
+               "s"(m.slices_per_block), "s"(m.items_bound), "s"(m.xcd_contiguous), "s"(a.n_blocks), "s"(a.n_req),
+               "s"(w.sqe_wgs), "s"(w.copy_first), "s"(w.copy_wgs));
+}
+
 // ORD (restore only): the blocks are visited in the order m.visit lists instead of staging order; the first slices
 // cannot be preloaded then (where they sit depends on the list).
 template <int DIR, bool HND, int U, int NT, int WG, int REQS, bool ORD = false, bool PIECES = false>
@@ -2022,10 +2097,15 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     if (entries) emit_sqes(q, l, 1, 0, w.sqe_wgs, one_head);
     return;
   }
-  scan_extents<WG, REQS>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
-                   m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [&] {
-                     if (DIR == kUnpack && !ORD && !PIECES && reads_ahead(U) && copies) pre = preload_first<U, NT, WG>(m, wg, w.copy_wgs);
-                   });
+  if (packs_ahead(REQS)) args_at_hand(m, a, w);
+  scan_extents<WG, REQS>(
+      a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr, m.table_len, m.status,
+      blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [&] {
+        if (packs_ahead(REQS))
+          pre = preload_pack<HND, U, NT, WG>(m, wg, w.copy_wgs);
+        else if (DIR == kUnpack && !ORD && !PIECES && reads_ahead(U) && copies)
+          pre = preload_first<U, NT, WG>(m, wg, w.copy_wgs);
+      });
   if (REQS == kFew && DIR == kUnpack && pre.valid)
     hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, pause_requests(a.n_req),
                               false));
@@ -2040,10 +2120,12 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
         atomicOr(m.status, TUTTI_ST_STAGE_CAP);
   }
   if (copies) {
-    if (PIECES)
+    if (packs_ahead(REQS))
+      store_pack<U, NT, WG, REQS, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
+    else if (PIECES)
       move_pieces<DIR, HND, U, NT, WG, false, false>(m, l, a.n_req, wg, w.copy_wgs);
     else
-      move_items<DIR, HND, U, NT, WG, REQS, false, ORD, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
+      move_items<DIR, HND, U, NT, WG, REQS, false, ORD ? kListOrder : kStagingOrder, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
   }
   if (blockIdx.x < w.sqe_wgs) emit_sqes(q, l, a.n_req, 0, w.sqe_wgs, head);
 }
@@ -2133,21 +2215,27 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
     return;
   }
   // chunk counts only matter for the published extents; the LDS copy gets file starts instead of staging offsets
-  scan_extents<WG, REQS>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
-                   0xffffffffu, nullptr, publish, q.file_id, f, [&] {
-                     if (DIR == kUnpack && !PIECES && reads_ahead(U) && copies && a.n_req == 1)
-                       pre = preload_first_direct<U, WG>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
-                   });
+  if (packs_ahead(REQS)) args_at_hand(m, a, w);
+  scan_extents<WG, REQS>(
+      a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr, 0xffffffffu, nullptr,
+      publish, q.file_id, f, [&] {
+        if (packs_ahead(REQS))
+          pre = preload_pack<false, U, 3, WG>(m, bx - w.copy_first, w.copy_wgs);
+        else if (DIR == kUnpack && !PIECES && reads_ahead(U) && copies && a.n_req == 1)
+          pre = preload_first_direct<U, WG>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
+      });
   if (REQS == kFew && DIR == kUnpack && pre.valid)
-    hold_back(hold_back_pause(count_units<false, false, true>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, 1, true));
+    hold_back(hold_back_pause(count_units<false, kStagingOrder, true>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, 1, true));
   DirectHead head;
   head.live = false;
   if (bx < w.sqe_wgs) head = iocb_head(g, q, d, l, a.n_req, lead, w.sqe_wgs);
   if (copies) {
-    if (PIECES)
+    if (packs_ahead(REQS))
+      store_pack<U, 3, WG, REQS, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
+    else if (PIECES)
       move_pieces<DIR, false, U, 3, WG, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);
     else
-      move_items<DIR, false, U, 3, WG, REQS, false, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
+      move_items<DIR, false, U, 3, WG, REQS, false, kStagingOrder, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
   }
   if (bx < w.sqe_wgs) emit_iocbs(g, q, d, l, a.n_req, lead, w.sqe_wgs, head);
 }

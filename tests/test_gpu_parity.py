@@ -1025,6 +1025,29 @@ def test_owner_among_mostly_empty_requests(orc, H, n_req):
                        layer=0, write=True, depth=1, first_slot=0, n_slots=1)
 
 
+@pytest.mark.parametrize("n_req", [2, 64, 65, 300])
+@pytest.mark.parametrize("blocks,padding", [(1200, 0), (1200, 700), (3072, 0), (3073, 0)])
+def test_saves_that_read_ahead(orc, H, n_req, blocks, padding):
+    """Saves of several requests read their slices before the requests are scanned, up to 3/4 of the chip's 8192 wavefronts
+    (3072 blocks of one slice): both sides of that, tables longer than the requests, ids out of range in both parts of the
+    table, padded objects, a table that is cut, objects that do not fit; through the rings also too few IOCBs."""
+    say("save ahead", n_req, blocks, padding)
+    rng = np.random.default_rng(8800 + n_req + blocks)
+    n = np.ones(n_req, np.uint32)
+    n += np.bincount(rng.integers(0, n_req, size=blocks - padding - n_req), minlength=n_req).astype(np.uint32)
+    N = blocks + 5
+    table = rng.permutation(N)[:blocks].astype(np.uint32)
+    table[[7, blocks - 1]] = (N, 0xffffffff)
+    for layout, align in ((0, 4096), (1, 8192)):
+        c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=n, table=table, align=align, chunk=16384, L=2, layout=layout,
+                        name=f"ahead{n_req}b{blocks}p{padding}l{layout}")
+        H.check_layer_save(orc, c, layer=1)
+        H.check_layer_save(orc, c, layer=1, stage_cap=8192 * (blocks // 2), table_len=blocks - padding - 1)
+    c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=n, table=table, align=4096, chunk=16384, L=2)
+    for n_slots in (1, 4):
+        H.check_ring_layer(orc, c, layer=1, write=True, depth=4, first_slot=2, n_slots=n_slots)
+
+
 def test_scan_of_many_requests_wide_sums(orc, H):
     """Alignment units above 1 MiB (the padding is then summed in 64 bits), and block counts whose sum passes 2^32:
     the requests in front of the one that runs beyond the table are restored, the published extents are plain sums."""
