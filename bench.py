@@ -987,7 +987,7 @@ def hnd_rows(torch, B, w, planes, stages, dev, layers=8, reps=5):
     """Head-major pools ([h][T][d] blocks) of config 2's block size (32 KiB, 16 tokens) with (token, head) rows of
     256, 128, 64 and 32 bytes: tutti_obj_unpack / tutti_obj_pack alone, once moved 16 bytes per lane straight
     between the two orders and once through token tiles in LDS (the choice forced with the measurement library's
-    switch; the product library takes LDS for rows shorter than 128 bytes).  Random table of 2048 blocks."""
+    switch) and once as the product chooses (line tiles for rows shorter than 128 bytes).  Random table of 2048 blocks."""
     s = w.shape
     bb = s.block_tokens * s.num_kv_heads * s.head_dim * s.elt_bytes
     n_tab = int(w.block_table.size)
@@ -1010,7 +1010,7 @@ def hnd_rows(torch, B, w, planes, stages, dev, layers=8, reps=5):
             pools = [B.make_pool(k, v, **geom) for k, v in planes]
             B.tutti_obj_layout(pools[0], cfg, d_n, 1, ext, tot)
             r = {}
-            for mode, label in ((1, "direct"), (2, "lds")):
+            for mode, label in ((0, "product"), (1, "direct"), (2, "lds")):
                 B.tutti_set_hnd_mode(mode)
                 for fn, name in ((B.tutti_obj_unpack, "unpack"), (B.tutti_obj_pack, "pack")):
                     def train():
@@ -1027,7 +1027,7 @@ def hnd_rows(torch, B, w, planes, stages, dev, layers=8, reps=5):
                         torch.cuda.synchronize()
                         ts.append(a.elapsed_time(b) * 1e3 / L)
                     r[f"{label}_{name}_us"] = round(median(ts), 2)
-            r["product_choice"] = "lds" if row < 128 else "direct"
+            r["product_choice"] = "line tiles" if row < 128 else "direct"
             res[f"row_{row}B ({heads} heads x {dim})"] = r
             log(f"[bench] head-major rows of {row} B: {r}")
     finally:

@@ -190,8 +190,9 @@ int tutti_layer_restore(const tutti_pool *pool, const tutti_objcfg *cfg, const u
  * (>= the blocks of the requests within table_len) is passed over; a position listed twice is restored twice (same
  * bytes); a position not listed is not restored.  Everything else (entries, extents, totals, status bits, skip
  * rules) as tutti_layer_restore, whose results a permutation of 0..table_len-1 reproduces bit for bit.  d_visit ==
- * NULL is tutti_layer_restore itself.  A head-major pool that goes through LDS tiles keeps staging order (d_visit
- * is not read). */
+ * NULL is tutti_layer_restore itself.  A head-major pool whose (token, head) rows are shorter than 128 bytes and
+ * that is moved in tiles (T, h and the row size powers of two, and the tiles and n_req's offsets fit a compute
+ * unit's LDS; under a CU budget rows of 16 bytes on more than 16 units) keeps staging order (d_visit is not read). */
 int tutti_layer_restore_ordered(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t *d_n_blocks,
                                 uint32_t n_req, const uint32_t *d_block_table, uint32_t table_len,
                                 const uint32_t *d_file_id, uint32_t layer, const void *d_stage, uint64_t stage_cap,

@@ -68,9 +68,9 @@ int tutti_host_cost_of_restore(const tutti_pool *pool, const tutti_objcfg *cfg, 
 /* Launch tuning: wgs_per_cu persistent workgroups per compute unit for whole-GPU launches (0 = default),
  * unroll = 16-byte accesses in flight per lane (0 = default; 1, 2, 4 or 8). */
 int tutti_set_tuning(uint32_t wgs_per_cu, uint32_t unroll);
-/* Head-major pools: 0 = the library chooses (token tiles transposed in LDS when a (token, head) row is
- * shorter than 128 bytes and T, h and the row size are powers of two; else 16 bytes per lane straight
- * between the two orders), 1 = always the direct copy, 2 = through LDS whenever the shape allows. */
+/* Head-major pools: 0 = the library chooses (line tiles when a (token, head) row is shorter than 128 bytes and
+ * T, h and the row size are powers of two; else 16 bytes per lane straight between the two orders), 1 = always
+ * the latter, 2 = token tiles transposed in LDS whenever the shape allows. */
 int tutti_set_hnd_mode(uint32_t mode);
 /* How pack / unpack work items are dealt to workgroups.  0 (default): workgroup b starts at item 4b, so the
  * workgroups the dispatcher deals round-robin to the 8 XCDs take neighbouring 16 KiB; 1: each XCD takes one

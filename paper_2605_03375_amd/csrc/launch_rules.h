@@ -55,8 +55,9 @@ constexpr uint32_t pause_requests(uint32_t n_req) { return n_req > 32 ? 2 : 1; }
 // Blocks that are no whole number of slices: slices of 8 KiB if those fit (8 KiB blocks, 4096 on 8 units, restore 261 us
 // as pieces, 256 as slices; but saves on many units: 256 of 40 KiB on 64 16.8 and 19.1), pieces otherwise (16 at a time);
 // a visiting order keeps slices, of 8 KiB.
-// `short_rows`: a head-major pool whose rows are shorter than a cache line, moved directly: the longer run wins at every
-// size (rows of 64 bytes, 300 blocks of 16 KiB on 8 units: restore 32 / 51, save 39 / 57).
+// `short_rows`: a head-major pool whose rows are shorter than a cache line: the longer run wins at every size (rows of 64
+// bytes, 16 KiB blocks, as line tiles: 256 on 8 units restore 25.3 / 35.6, save 29.6 / 38.0; 192 on 32 8.2 / 11.3, 8.8 / 12.7;
+// 320 on 64 9.5 / 12.7, 9.6 / 13.9; moved directly: 300 on 8 32 / 51, 39 / 57).
 constexpr uint32_t budget_units(bool ahead, uint32_t block_bytes, uint32_t blocks, uint32_t cu_budget, bool ordered,
                                 bool short_rows) {
   if (block_bytes % 8192 != 0) return ordered ? 8 : 16;
@@ -71,8 +72,8 @@ constexpr uint32_t budget_units(bool ahead, uint32_t block_bytes, uint32_t block
   return items <= one_each || cu_budget > 32 || !even ? 16 : 8;
 }
 
-// Whether a head-major pool goes through LDS tiles or is moved directly.  On the whole GPU it pays while a row is shorter
-// than a 128-byte line.  Under a CU budget a workgroup has one tile in flight at a time, and only rows of 16 bytes on
+// Whether a head-major pool goes through LDS tiles or is moved directly, where it is not moved as line tiles
+// (as_line_tiles).  On the whole GPU it pays while a row is shorter than a 128-byte line.  Under a CU budget a workgroup has one tile in flight at a time, and only rows of 16 bytes on
 // more than 16 compute units are worth that.  Through LDS / direct, us, save and restore of 16 KiB blocks:
 //   rows of 16 bytes   300 blocks on 8 units 85 / 69, 75 / 64   500 on 16  78 / 73, 73 / 64   1000 on 32  87 / 99, 83 / 90
 //                      2000 on 64  94 / 122, 89 / 139
@@ -82,6 +83,27 @@ constexpr uint32_t budget_units(bool ahead, uint32_t block_bytes, uint32_t block
 //                      2000 on 64  94 / 57, 89 / 51
 constexpr bool hnd_through_lds(uint32_t row_bytes, uint32_t cu_budget) {
   return row_bytes < (cu_budget == 0 ? 128u : cu_budget > 16 ? 32u : 16u);
+}
+
+// Whether a head-major pool is moved as line tiles (row size, tokens and heads are powers of two): while a row is shorter
+// than a 128-byte line and the block a whole number of whole-GPU slices.  The other way for those is the object's order, in
+// which a piece of 1 KiB holds 1024 / heads bytes of every head: whole lines too for up to 8 heads, and its loads of a
+// restore need no offsets.  Us, object's order / line tiles, rows of 64 bytes, 8 heads, 16 KiB blocks: restore of 1536 on 32
+// units 57.3 / 59.3, of 256 on 8 22.4 / 22.9, of 4096 on the whole GPU 43.5 / 43.6; save of 1536 on 32 units 60.3 / 60.6, of
+// 512 21.5 / 20.9, of 384 on the whole GPU 5.5 / 5.3, of 64 in one request 3.6 / 3.4; 4 heads, rows of 16 bytes, 4 KiB blocks,
+// restore of 1536 on the whole GPU 6.5 / 6.2 (on 32 units of blocks of any size the same).
+constexpr bool as_line_tiles(uint32_t row_bytes, uint32_t block_bytes, uint32_t heads, uint32_t cu_budget, bool unpack) {
+  return row_bytes >= 16 && row_bytes < 128 && block_bytes >= 4096 &&
+         !(unpack && cu_budget != 0 && heads <= 8 && row_bytes > 16);
+}
+
+// log2 of the tokens of a line tile, from the logarithms of row size, heads and tokens: the runs of both sides about the
+// same length (never below a line, and no run is split that could stay whole where there are fewer heads or tokens).
+// 2 / 4 tokens, rows of 64 bytes, us: save of 1536 blocks of 16 KiB on 32 units 60.7 / 59.2, restore 61.8 / 60.1.
+constexpr uint32_t line_tile_shift(uint32_t row_shift, uint32_t head_shift, uint32_t token_shift) {
+  uint32_t t = (10 - row_shift) / 2;
+  if (t + head_shift < 10 - row_shift) t = 10 - row_shift - head_shift;
+  return t < token_shift ? t : token_shift;
 }
 
 }  // namespace tutti

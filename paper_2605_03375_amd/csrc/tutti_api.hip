@@ -175,6 +175,8 @@ struct Launch {
   uint32_t nontemporal;  // bit 0: loads, bit 1: stores
   bool hnd_lds;          // head-major pool moved through LDS; unroll then holds 16-byte units per thread per tile
   uint32_t tile_lds;     // bytes of LDS for the tile
+  bool lines;            // head-major pool moved as line tiles
+  bool keeps_order;      // a visiting order is not read
   bool pieces;           // blocks are no whole number of slices: moved as 1 KiB pieces
 };
 
@@ -219,7 +221,7 @@ int plan_launch(uint32_t cu_budget, uint64_t n_wave_items, Launch *out) {
   out->nontemporal = t.nontemporal & 3u;
   out->hnd_lds = false;
   out->tile_lds = 0;
-  out->pieces = false;
+  out->pieces = out->lines = out->keeps_order = false;
   out->wg_threads = cu_budget ? kBudgetWgThreads : kWgThreads;
   out->unroll = t.unroll ? t.unroll : cu_budget ? kBudgetUnroll : kDefaultUnroll;
   size_grid(cu_budget, n_wave_items, out);
@@ -261,11 +263,12 @@ uint64_t counted_slices(const Launch &L, uint32_t bytes) {
 }
 
 // Fills the kernel arguments and settles how a head-major pool is moved (L->hnd_lds, L->unroll,
-// L->tile_lds).  L must already hold the workgroup size and default unroll from plan_launch.  `ahead`: the first slices
-// are read before the requests are known (restores); `ordered`: in a caller's visiting order.
+// L->tile_lds, L->lines).  L must already hold the workgroup size and default unroll from plan_launch.  `unpack`: objects
+// to blocks; `ahead`: the first slices are read before the requests are known (restores); `ordered`: in a caller's visiting
+// order.
 int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t *d_block_table, uint32_t table_len,
                    const void *d_stage, uint64_t stage_cap, uint32_t *d_status, uint32_t n_req, uint32_t align,
-                   uint32_t cu_budget, bool ahead, bool ordered, Launch *L, MoveArgs *m) {
+                   uint32_t cu_budget, bool unpack, bool ahead, bool ordered, Launch *L, MoveArgs *m) {
   m->k_base = static_cast<unsigned char *>(pool->k_base);
   m->v_base = static_cast<unsigned char *>(pool->v_base);
   m->stage = static_cast<unsigned char *>(const_cast<void *>(d_stage));
@@ -286,15 +289,21 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   m->visit = nullptr;
   m->chip_waves = L->wg_threads == kWgThreads ? static_cast<uint32_t>(whole_gpu_waves(*L)) : 0;
 
-  L->hnd_lds = false;
+  L->hnd_lds = L->lines = false;
   L->tile_lds = 0;
   const uint32_t mode = tuning().hnd_mode;
-  if (pool->pool_layout == TUTTI_LAYOUT_HND && mode != 1) {
+  const uint32_t row = m->row_bytes, T = pool->block_tokens, h = pool->num_kv_heads;
+  const bool powers = pool->pool_layout == TUTTI_LAYOUT_HND && is_pow2(row) && is_pow2(T) && is_pow2(h);
+  // (more blocks than line tiles can number go through LDS, whose tiles are larger)
+  bool lines = powers && mode == 0 && as_line_tiles(row, block_bytes, h, cu_budget, unpack) &&
+               2ull * table_len * counted_slices(*L, block_bytes) <= 0xffffffffull;
+  // where the rule for LDS holds the launch keeps staging order, whatever list of positions it is given
+  L->keeps_order = false;
+  if (powers && mode != 1) {
     // through LDS: T, h and the row size powers of two, one token of all heads within the tile cap,
     // the tile a whole number (1, 2, 4 or 8) of 16-byte units per thread, and LDS to hold it
-    const uint32_t row = m->row_bytes, T = pool->block_tokens, h = pool->num_kv_heads;
     const uint64_t group = static_cast<uint64_t>(h) * row;
-    if (is_pow2(row) && is_pow2(T) && is_pow2(h) && row >= 16 && group <= kHndTileCap) {
+    if (row >= 16 && group <= kHndTileCap) {
       uint32_t tile_tokens = static_cast<uint32_t>(kHndTileCap / group);
       if (tile_tokens > T) tile_tokens = T;
       const uint32_t tile_bytes = tile_tokens * static_cast<uint32_t>(group);
@@ -303,8 +312,8 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
       const uint64_t lds = static_cast<uint64_t>(align16(req_lds_bytes(n_req))) + static_cast<uint64_t>(tile_tokens) * pitch;
       const bool fits = tile_bytes % (L->wg_threads * 16u) == 0 && per_thread >= 1 && per_thread <= 8 &&
                         is_pow2(per_thread) && lds <= kDynLdsCap;
-      // Worth it where hnd_through_lds says so (or when asked for).
-      if (fits && (mode == 2 || hnd_through_lds(row, cu_budget))) {
+      L->keeps_order = fits && (mode == 2 || hnd_through_lds(row, cu_budget));
+      if (L->keeps_order && !lines) {
         L->hnd_lds = true;
         L->unroll = per_thread;
         L->tile_lds = tile_tokens * pitch;
@@ -317,6 +326,8 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
       }
     }
   }
+  const bool visits = ordered && !L->keeps_order;
+  lines = lines && !visits;
   // Slices of `unroll` pieces where they fill the blocks exactly, single pieces (dealt out in groups of `unroll`, across
   // blocks) where they do not.  Measured, save / restore in us, slices (the last one short) -> pieces: blocks of 1 KiB
   // 32.0 -> 30.7 / 31.0 -> 30.2 (164 MB of traffic), 3 KiB 70.7 -> 66.3 / 65.9 -> 61.9 (369 MB), 5 KiB 76.9 -> 73.7 /
@@ -325,13 +336,20 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   // faster one (32 KiB restore: 43.8 against 45.3): it needs one owner, one id and one address per 4 KiB and reads the
   // first slices ahead of the scan.  A visiting order keeps the slices, whatever the block size.
   if (!L->hnd_lds && cu_budget && tuning().unroll == 0)
-    L->unroll = budget_units(ahead, block_bytes, table_len, cu_budget, ordered,
+    L->unroll = budget_units(ahead, block_bytes, table_len, cu_budget, visits,
                              pool->pool_layout == TUTTI_LAYOUT_HND && m->row_bytes < 128);
   const uint32_t slice = kPiece * L->unroll;
   uint64_t slices = m->slices_per_block;
   if (!L->hnd_lds) {
     slices = (static_cast<uint64_t>(block_bytes) + slice - 1) / slice;
-    L->pieces = block_bytes % slice != 0 && !ordered;
+    L->pieces = block_bytes % slice != 0 && !visits;
+    if (lines && !L->pieces) {
+      L->lines = true;
+      m->row_shift = log2u(row);
+      m->head_shift = log2u(h);
+      m->token_shift = log2u(T);
+      m->tile_shift = line_tile_shift(m->row_shift, m->head_shift, m->token_shift);
+    }
     m->slices_per_block = static_cast<uint32_t>(
         L->pieces ? (static_cast<uint64_t>(block_bytes) + kPiece - 1) / kPiece : slices);
   }
@@ -474,12 +492,12 @@ template <typename S>
 constexpr bool has_pieces = S::WG == kWgThreads || S::U == kBudgetUnroll;
 #endif
 
-template <int DIR, bool HND>
+template <int DIR, int HND>
 hipError_t launch_move(const Launch &L, uint32_t lds, hipStream_t s, const MoveArgs &m, const tutti_extent *ext,
                        uint32_t n_req) {
   return with_shape(L, [&](auto sh) {
     using S = decltype(sh);
-    if constexpr (has_pieces<S>) {
+    if constexpr (has_pieces<S> && HND != kLines) {
       if (L.pieces) {
         hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG, true>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req);
         return hipGetLastError();
@@ -490,11 +508,11 @@ hipError_t launch_move(const Launch &L, uint32_t lds, hipStream_t s, const MoveA
   });
 }
 
-template <typename S, int DIR, bool HND, int REQS>
+template <typename S, int DIR, int HND, int REQS>
 hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStream_t s, const MoveArgs &m,
                               const SqeArgs &q, const LayoutArgs &a, const Roles &w) {
   const dim3 grid(n_wgs), block(S::WG);
-  if constexpr (REQS == kFew || REQS == kMany) {
+  if constexpr ((REQS == kFew || REQS == kMany) && HND != kLines) {
     if constexpr (DIR == kUnpack && REQS == kMany) {
       if (m.visit) {  // the caller's visiting order
         hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>), grid, block, lds, s, m, q, a, w);
@@ -512,7 +530,7 @@ hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStre
   return hipGetLastError();
 }
 
-template <int DIR, bool HND>
+template <int DIR, int HND>
 hipError_t launch_layer(const Launch &L, uint64_t entry_quarters, uint32_t lds, hipStream_t s, const MoveArgs &m,
                         const SqeArgs &q, const LayoutArgs &a) {
   uint32_t n_wgs = 0;
@@ -574,7 +592,7 @@ int move_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const tutti_exte
   if (rc) return rc;
   MoveArgs m;
   rc = fill_move_args(pool, bb, d_block_table, table_len, d_stage, stage_cap, d_status, n_req, cfg->align, cu_budget,
-                      DIR == kUnpack && bb % cfg->align == 0, false, &L, &m);
+                      DIR == kUnpack, DIR == kUnpack && bb % cfg->align == 0, false, &L, &m);
   if (rc) return rc;
   size_grid(cu_budget, move_wave_items(L, m), &L);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -583,8 +601,9 @@ int move_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const tutti_exte
     e = launch_move_lds<DIR>(L, align16(req_lds_bytes(n_req)) + L.tile_lds, s, m, d_extents, n_req);
   } else {
     const uint32_t lds = req_lds_bytes(n_req);
-    e = (pool->pool_layout == TUTTI_LAYOUT_HND) ? launch_move<DIR, true>(L, lds, s, m, d_extents, n_req)
-                                                 : launch_move<DIR, false>(L, lds, s, m, d_extents, n_req);
+    e = L.lines                                   ? launch_move<DIR, kLines>(L, lds, s, m, d_extents, n_req)
+        : pool->pool_layout == TUTTI_LAYOUT_HND ? launch_move<DIR, kHnd>(L, lds, s, m, d_extents, n_req)
+                                                : launch_move<DIR, kNhd>(L, lds, s, m, d_extents, n_req);
   }
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
 }
@@ -678,9 +697,9 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
   if (rc) return rc;
   MoveArgs m;
   rc = fill_move_args(pool, bb, d_block_table, table_len, d_stage, stage_cap, d_status, n_req, cfg->align, cu_budget,
-                      DIR == kUnpack && bb % cfg->align == 0, d_visit != nullptr, &L, &m);
+                      DIR == kUnpack, DIR == kUnpack && bb % cfg->align == 0, d_visit != nullptr, &L, &m);
   if (rc) return rc;
-  if (!L.hnd_lds) m.visit = d_visit;  // the tiles of the through-LDS path keep staging order
+  if (!L.keeps_order) m.visit = d_visit;
   size_grid(cu_budget, move_wave_items(L, m), &L);
   // one lane per 16-byte quarter of an entry; no more entries than the capacity, nor than the table can give
   // (every request has at most obj/chunk + 1 chunks per object, and obj < blocks*block_bytes + align <= ... + chunk)
@@ -699,8 +718,9 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
     e = launch_layer_lds<DIR>(L, entry_quarters, align16(req_lds_bytes(n_req)) + L.tile_lds, s, m, q, a);
   } else {
     const uint32_t lds = req_lds_bytes(n_req);
-    e = (pool->pool_layout == TUTTI_LAYOUT_HND) ? launch_layer<DIR, true>(L, entry_quarters, lds, s, m, q, a)
-                                                 : launch_layer<DIR, false>(L, entry_quarters, lds, s, m, q, a);
+    e = L.lines                                   ? launch_layer<DIR, kLines>(L, entry_quarters, lds, s, m, q, a)
+        : pool->pool_layout == TUTTI_LAYOUT_HND ? launch_layer<DIR, kHnd>(L, entry_quarters, lds, s, m, q, a)
+                                                : launch_layer<DIR, kNhd>(L, entry_quarters, lds, s, m, q, a);
   }
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
 }
@@ -985,7 +1005,7 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
   raw.pool_layout = TUTTI_LAYOUT_NHD;
   MoveArgs m;
   rc = fill_move_args(&raw, bb, d_block_table, table_len, store->base, 0, d_status, n_req, cfg->align, cu_budget,
-                      DIR == kUnpack && n_req == 1, false, &L, &m);
+                      DIR == kUnpack, DIR == kUnpack && n_req == 1, false, &L, &m);
   if (rc) return rc;
   m.dense = 0;
   m.layer = layer;
@@ -1714,7 +1734,7 @@ void least_resident(int *worst, uint32_t lds, K... kernels) {
 }
 
 // Every kernel that a whole-GPU launch of the default shape may run.
-template <int DIR, bool HND>
+template <int DIR, int HND>
 void least_resident_layer(int *worst) {
   constexpr uint32_t few = req_lds_bytes(kWave), many = req_lds_bytes(512);
   least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kOne>, k_layer<DIR, HND, 4, 3, kWgThreads, kFew>,

@@ -1215,8 +1215,9 @@ struct MoveArgs {
   uint32_t row_bytes;
   uint32_t block_tokens;
   uint32_t num_kv_heads;
-  // head-major pools moved through LDS (T, h and the row size are powers of two there):
-  // a tile is 2^tile_shift tokens x all heads; slices_per_block then counts tiles
+  // head-major pools moved as line tiles or through LDS (T, h and the row size are powers of two there): a tile is
+  // 2^tile_shift tokens x as many heads as make up 1 KiB (tile_offsets), or x all heads; through LDS slices_per_block counts
+  // tiles
   uint32_t row_shift;    // log2(row_bytes)
   uint32_t head_shift;   // log2(num_kv_heads)
   uint32_t token_shift;  // log2(block_tokens)
@@ -1286,6 +1287,13 @@ __device__ __forceinline__ uint32_t hnd_offset(uint32_t o, uint32_t row_bytes, u
   return (i * T + t) * row_bytes + w;
 }
 
+// How a lane's 16-byte units lie on one side of a copy: one behind the other, found row by row in a head-major block, or
+// as line tiles (LineTile).
+constexpr int kNhd = 0, kHnd = 1, kLines = 2;                              // pools
+constexpr int kLinear = 0, kRows = 1, kTileObj = 2, kTilePool = 3;         // sides
+constexpr int pool_side(int hnd) { return hnd == kLines ? kTilePool : hnd == kHnd ? kRows : kLinear; }
+constexpr int obj_side(int hnd) { return hnd == kLines ? kTileObj : kLinear; }
+
 // The offsets in the block of a lane's 16-byte units, whose canonical offsets o, o + 1 KiB, o + 2 KiB, ... lie a piece
 // apart: as they are, or (head-major) with the row and head of the first unit found by division and those of the others
 // by addition.  Divided out for 16 units at a time they stand beside 64 data registers, and the kernel spills.
@@ -1339,29 +1347,62 @@ __device__ __forceinline__ void head_offsets(const MoveArgs &a, uint32_t o0, uin
     __builtin_amdgcn_sched_barrier(0);
   }
 }
-template <bool HND, int U, int NT>
-__device__ __forceinline__ void load_slice(const MoveArgs &a, const unsigned char *blk, uint32_t o0, u32x4 (&buf)[U]) {
-  if (HND) {
-    uint32_t at[U];
-    head_offsets(a, o0, at);
+
+// Line tiles: a head-major pool whose (token, head) rows are shorter than a 128-byte line, without a detour through LDS.
+// What bounds such a copy is the lines that a wavefront instruction touches in part, above all with stores: in the object's
+// order it stores one row to every head.  So an instruction takes a tile of 2^tile_shift tokens by as many heads as make up
+// 1 KiB, and the lanes are dealt out so that it touches whole lines on both sides: runs of 2^tile_shift rows in the block,
+// of the tile's heads in the object (rows of 64 / 32 / 16 bytes: 256 and 256, 128 and 256, 128 and 128 bytes).  The tiles
+// of a block are numbered in the object's order, a slice is U of them; row size, heads and tokens are powers of two.  A
+// lane's place in a tile is the same for every tile; what depends on the tile is wave-uniform.
+// Graph replay, us, through LDS (or, under a budget, direct where that was faster) / so, blocks of 16 KiB, 4 requests:
+//   rows of 64 bytes   restore of 4096 blocks 45.8 / 43.5 (a token-major pool: 43.2), 384 6.2 / 5.5, 64 in one request 3.8 /
+//                      3.5; save 49.0 / 47.7, 6.3 / 5.3, 4.0 / 3.5; on 32 compute units, 1536 blocks: restore 69 / 59, save 80 / 59
+//   rows of 32 bytes   restore of 4096 45.9 / 43.7, save 49.3 / 48.0; on 32 units, 1536: 95 / 62, 111 / 63
+//   rows of 16 bytes   restore of 4096 45.9 / 44.3, save 49.2 / 48.1; on 32 units, 1536: 144 / 70, 152 / 74
+template <bool POOL, int U>
+__device__ __forceinline__ void tile_offsets(const MoveArgs &a, uint32_t o0, uint32_t (&at)[U]) {
+  const uint32_t lane = threadIdx.x & (kWave - 1), first = rfl(o0 / kPiece);
+  const uint32_t rs = a.row_shift, hs = a.head_shift, ts = a.token_shift, tg = a.tile_shift, hg = 10u - rs - tg;
+  // lane -> 16-byte unit of a row, token, head, the block's order
+  const uint32_t w = lane & ((1u << (rs - 4)) - 1u), t = lane >> (rs - 4) & ((1u << tg) - 1u), i = lane >> (rs - 4 + tg);
+  const uint32_t mine = (POOL ? (i << ts) + t : (t << hs) + i) << rs | w << 4;
 #pragma unroll
-    for (int k = 0; k < U; ++k) buf[k] = ld16<NT>(blk + at[k]);
-  } else {
+  for (int k = 0; k < U; ++k) {
+    const uint32_t q = first + k, heads = q & ((1u << (hs - hg)) - 1u), tokens = q >> (hs - hg);
+    at[k] = mine + ((POOL ? (heads << (hg + ts)) + (tokens << tg) : (tokens << (tg + hs)) + (heads << hg)) << rs);
+  }
+  if (U > 4) __builtin_amdgcn_sched_barrier(0);  // a run of stores with arithmetic in between moves less
+}
+template <int SIDE, int U, int NT>
+__device__ __forceinline__ void load_slice(const MoveArgs &a, const unsigned char *blk, uint32_t o0, u32x4 (&buf)[U]) {
+  if (SIDE == kLinear) {
 #pragma unroll
     for (int k = 0; k < U; ++k) buf[k] = ld16<NT>(blk + (o0 + k * kPiece));
+  } else {
+    uint32_t at[U];
+    if (SIDE == kRows)
+      head_offsets(a, o0, at);
+    else
+      tile_offsets<SIDE == kTilePool>(a, o0, at);
+#pragma unroll
+    for (int k = 0; k < U; ++k) buf[k] = ld16<NT>(blk + at[k]);
   }
 }
-template <bool HND, int U, int NT>
+template <int SIDE, int U, int NT>
 __device__ __forceinline__ void store_slice(const MoveArgs &a, unsigned char *blk, uint32_t o0, const u32x4 (&buf)[U]) {
-  if (HND) {
-    if (U > 4) __builtin_amdgcn_sched_barrier(0);  // the loads first: the offsets are worked out under them
-    uint32_t at[U];
-    head_offsets(a, o0, at);
-#pragma unroll
-    for (int k = 0; k < U; ++k) st16<NT>(blk + at[k], buf[k]);
-  } else {
+  if (SIDE == kLinear) {
 #pragma unroll
     for (int k = 0; k < U; ++k) st16<NT>(blk + (o0 + k * kPiece), buf[k]);
+  } else {
+    if (U > 4) __builtin_amdgcn_sched_barrier(0);  // the loads first: the offsets are worked out under them
+    uint32_t at[U];
+    if (SIDE == kRows)
+      head_offsets(a, o0, at);
+    else
+      tile_offsets<SIDE == kTilePool>(a, o0, at);
+#pragma unroll
+    for (int k = 0; k < U; ++k) st16<NT>(blk + at[k], buf[k]);
   }
 }
 
@@ -1490,7 +1531,7 @@ __device__ __forceinline__ void zero_tail(const MoveArgs &a, const Item &d, uint
 }
 
 // ORD: the block need not be a whole number of slices (the others are moved as pieces then).
-template <int DIR, bool HND, int U, int NT, bool ORD, bool DIRECT>
+template <int DIR, int HND, int U, int NT, bool ORD, bool DIRECT>
 __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint32_t id, uint32_t lane) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   if (d.obj_ptr == nullptr) return;
@@ -1502,8 +1543,8 @@ __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint3
     if (!ORD || in_blk + kSlice <= a.block_bytes) {
       // whole slice inside the block: U independent loads in flight, then U stores
       u32x4 buf[U];
-      load_slice<HND && DIR == kPack, U, NT>(a, DIR == kPack ? blk_ptr : obj_blk, o0, buf);
-      store_slice<HND && DIR == kUnpack, U, NT>(a, DIR == kPack ? obj_blk : blk_ptr, o0, buf);
+      load_slice<DIR == kPack ? pool_side(HND) : obj_side(HND), U, NT>(a, DIR == kPack ? blk_ptr : obj_blk, o0, buf);
+      store_slice<DIR == kPack ? obj_side(HND) : pool_side(HND), U, NT>(a, DIR == kPack ? obj_blk : blk_ptr, o0, buf);
     } else {
       // ragged last slice of a block: one guarded 16-byte move at a time
       for (int k = 0; k < U; ++k) {
@@ -1540,18 +1581,19 @@ struct Preload {
   bool valid;
 };
 
-template <int U, int NT, int WG>
+template <int HND, int U, int NT, int WG>
 __device__ __forceinline__ Preload<U> preload_first(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t it = first_item<WG, U>(a, wg, copy_wgs);
+  const uint64_t at = static_cast<uint64_t>(it) * kSlice;
+  // a slice of line tiles lies anywhere in its block (a power of two, and dense staging has no gap between blocks)
+  const uint32_t in_blk = HND == kLines ? static_cast<uint32_t>(at) & (a.block_bytes - 1) : 0u;
   Preload<U> p;
-  p.valid = a.dense != 0 && it < a.items_bound && (static_cast<uint64_t>(it) + 1) * kSlice <= a.stage_cap;
-  p.src = a.stage + static_cast<uint64_t>(it) * kSlice;
+  p.valid = a.dense != 0 && it < a.items_bound && at - in_blk + (HND == kLines ? a.block_bytes : kSlice) <= a.stage_cap;
+  p.src = a.stage + at;
   if (p.valid) {
-    const unsigned char *src = p.src + lane * 16u;
-#pragma unroll
-    for (int k = 0; k < U; ++k) p.buf[k] = ld16<NT>(src + k * (kWave * 16u));
+    load_slice<obj_side(HND), U, NT>(a, p.src - in_blk, in_blk + lane * 16u, p.buf);
   }
   return p;
 }
@@ -1563,7 +1605,7 @@ __device__ __forceinline__ Preload<U> preload_first(const MoveArgs &a, uint32_t 
 // of 8 KiB in 512 requests (42 MB of traffic) 10.7 / 9.6.  With several items a wavefront, reading all K blocks first loses
 // (1000 blocks in 8 requests 24.3 / 25.5), and a table longer than the requests is read for nothing: 64 blocks with a table
 // of 380 3.96 / 4.29, of 1000 4.2 / 5.0, of 8000 4.0 / 6.1; at 3/4 of the chip both are still small.
-template <bool HND, int U, int NT, int WG>
+template <int HND, int U, int NT, int WG>
 __device__ __forceinline__ Preload<U> preload_pack(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -1580,12 +1622,12 @@ __device__ __forceinline__ Preload<U> preload_pack(const MoveArgs &a, uint32_t w
   // every path issues the loads (of block 0 for want of another): the scanning wavefront's wait for the counts, asked for
   // in front of them, would otherwise be one for both
   p.src = (kind ? a.v_base : a.k_base) + static_cast<uint64_t>(p.valid ? id : 0u) * a.block_stride;
-  load_slice<HND, U, NT>(a, p.src, part * kSlice + lane * 16u, p.buf);
+  load_slice<pool_side(HND), U, NT>(a, p.src, part * kSlice + lane * 16u, p.buf);
   return p;
 }
 
 // What is left of it once the requests are known.
-template <int U, int NT, int WG, int REQS, bool DIRECT>
+template <int HND, int U, int NT, int WG, int REQS, bool DIRECT>
 __device__ __forceinline__ void store_pack(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t wg,
                                            uint32_t copy_wgs, const Preload<U> &pre) {
   constexpr uint32_t kSlice = kWave * 16u * U;
@@ -1595,21 +1637,21 @@ __device__ __forceinline__ void store_pack(const MoveArgs &a, const ReqLds &l, u
   const Item d = decode_item<false, REQS, kTableOrder, DIRECT>(a, l, n_req, it, lane);
   if (d.obj_ptr == nullptr) return;
   if (pre.valid)
-    store_slice<false, U, NT>(a, d.obj_blk, d.s * kSlice + lane * 16u, pre.buf);
+    store_slice<obj_side(HND), U, NT>(a, d.obj_blk, d.s * kSlice + lane * 16u, pre.buf);
   else if (lane == 0 && d.s == 0 && a.status)
     atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
   if (!DIRECT) zero_tail(a, d, lane);
 }
 
 // Stores of an unpack item whose slice was preloaded (whole slices only: dense staging).
-template <bool HND, int U, int NT>
+template <int HND, int U, int NT>
 __device__ __forceinline__ void store_preloaded(const MoveArgs &a, const Item &d, uint32_t id, uint32_t lane,
                                                 const Preload<U> &p) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   if (d.obj_ptr == nullptr) return;
   if (id < a.num_blocks) {
     unsigned char *blk_ptr = (d.kind ? a.v_base : a.k_base) + static_cast<uint64_t>(id) * a.block_stride;
-    store_slice<HND, U, NT>(a, blk_ptr, d.s * kSlice + lane * 16u, p.buf);
+    store_slice<pool_side(HND), U, NT>(a, blk_ptr, d.s * kSlice + lane * 16u, p.buf);
   } else if (lane == 0 && d.s == 0 && a.status) {
     atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
   }
@@ -1632,7 +1674,7 @@ __device__ __forceinline__ uint32_t count_units(const MoveArgs &a, const ReqLds 
   return 2u * rfl(SEP ? l.blk_off[n_req] : l.table_off[n_req]);
 }
 
-template <int DIR, bool HND, int U, int NT, int WG, int REQS, bool SEP, int ORD, bool DIRECT>
+template <int DIR, int HND, int U, int NT, int WG, int REQS, bool SEP, int ORD, bool DIRECT>
 __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                            uint32_t copy_wgs, const Preload<U> &pre) {
   constexpr uint32_t kSlice = kWave * 16u * U;
@@ -1755,7 +1797,7 @@ __device__ __forceinline__ OneReq one_request(const MoveArgs &m, const LayoutArg
 
 // The copy loop of one request whose blocks are a whole number of slices; the next item's block id is requested before
 // the current item's loads and stores are issued.
-template <int DIR, bool HND, int U, int NT, int WG, bool DIRECT>
+template <int DIR, int HND, int U, int NT, int WG, bool DIRECT>
 __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q, uint32_t wg, uint32_t copy_wgs,
                                              const Preload<U> &pre) {
   constexpr uint32_t kSlice = U * kPiece;
@@ -1787,11 +1829,11 @@ __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q,
       unsigned char *obj = q.base + at;
       const uint32_t o0 = part * kSlice + lane * 16u;
       if (DIR == kUnpack && first) {
-        store_slice<HND, U, NT>(a, blk, o0, pre.buf);
+        store_slice<pool_side(HND), U, NT>(a, blk, o0, pre.buf);
       } else {
         u32x4 buf[U];
-        load_slice<HND && DIR == kPack, U, NT>(a, DIR == kPack ? blk : obj, o0, buf);
-        store_slice<HND && DIR == kUnpack, U, NT>(a, DIR == kPack ? obj : blk, o0, buf);
+        load_slice<DIR == kPack ? pool_side(HND) : obj_side(HND), U, NT>(a, DIR == kPack ? blk : obj, o0, buf);
+        store_slice<DIR == kPack ? obj_side(HND) : pool_side(HND), U, NT>(a, DIR == kPack ? obj : blk, o0, buf);
       }
     } else if (lane == 0 && part == 0 && a.status) {
       atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
@@ -1813,7 +1855,7 @@ __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q,
 // The copy loop for blocks that are no whole number of slices.  A wavefront decodes its next 64 pieces at once, one per
 // lane (owner by binary search, block id, both addresses), so that the table loads of 64/U items are in flight together
 // and an item costs a few lane reads; then it moves them item by item.
-template <int DIR, bool HND, int U, int NT, int WG, bool SEP, bool DIRECT>
+template <int DIR, int HND, int U, int NT, int WG, bool SEP, bool DIRECT>
 __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                             uint32_t copy_wgs) {
   constexpr uint32_t kBatch = kWave / U;  // items decoded at once
@@ -1892,6 +1934,8 @@ __device__ __forceinline__ void move_pieces(const MoveArgs a, const ReqLds l, ui
 // Head-major pools with short rows.  A block is stored [h][T][row]; the object wants [T][h][row].
 // Moving 16 bytes per lane straight between the two orders touches the pool in row-sized pieces,
 // which is fine while a row fills whole 128-byte lines and poor below that (partial-line writes).
+// Line tiles (tile_offsets) are the faster way round that; this one stays for tables with more blocks than they can number
+// and for the measurement build.
 // Here a workgroup stages one tile (2^tile_shift tokens x all heads) in LDS instead: the object
 // side is read or written as one contiguous run, the pool side as h runs of tile_tokens*row bytes,
 // and the transpose happens in LDS.  Tokens are padded by one row in LDS so that the lanes of a
@@ -2021,14 +2065,14 @@ __global__ __launch_bounds__(WG) void k_sqe(const SqeArgs a, const ScanGeom g,
 }
 
 // PIECES: the blocks are no whole number of slices (here and below).
-template <int DIR, bool HND, int U, int NT, int WG, bool PIECES = false>
+template <int DIR, int HND, int U, int NT, int WG, bool PIECES = false>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_move(const MoveArgs a, const tutti_extent *__restrict__ ext,
                                                       uint32_t n_req) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, n_req, true);
   Preload<U> pre;
   pre.valid = false;
-  if (DIR == kUnpack && !PIECES && reads_ahead(U)) pre = preload_first<U, NT, WG>(a, blockIdx.x, gridDim.x);
+  if (DIR == kUnpack && !PIECES && reads_ahead(U)) pre = preload_first<HND, U, NT, WG>(a, blockIdx.x, gridDim.x);
   lds_from_caller_extents(ext, n_req, l, a.table_len, a.block_bytes, a.stage_cap, a.status);
   if (PIECES)
     move_pieces<DIR, HND, U, NT, WG, true, false>(a, l, n_req, blockIdx.x, gridDim.x);
@@ -2072,7 +2116,7 @@ __device__ __forceinline__ void args_at_hand(const MoveArgs &m, const LayoutArgs
 
 // ORD (restore only): the blocks are visited in the order m.visit lists instead of staging order; the first slices
 // cannot be preloaded then (where they sit depends on the list).
-template <int DIR, bool HND, int U, int NT, int WG, int REQS, bool ORD = false, bool PIECES = false>
+template <int DIR, int HND, int U, int NT, int WG, int REQS, bool ORD = false, bool PIECES = false>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const MoveArgs m, const SqeArgs q_, const LayoutArgs a_, const Roles w) {
   extern __shared__ __align__(16) unsigned char smem[];
   SqeArgs q = q_;  // (as in k_layer_ring)
@@ -2087,7 +2131,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
   pre.valid = false;
   const bool publish = blockIdx.x == 0;  // also an entry-writing workgroup: there is at least one
   if constexpr (REQS == kOne) {
-    if (DIR == kUnpack && reads_ahead(U) && copies) pre = preload_first<U, NT, WG>(m, wg, w.copy_wgs);
+    if (DIR == kUnpack && reads_ahead(U) && copies) pre = preload_first<HND, U, NT, WG>(m, wg, w.copy_wgs);
     const bool entries = blockIdx.x < w.sqe_wgs;
     const OneReq one = one_request(m, a, l, publish, entries, nullptr, FileArgs{0, 0, 0});
     SqeHead one_head;
@@ -2104,7 +2148,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
         if (packs_ahead(REQS))
           pre = preload_pack<HND, U, NT, WG>(m, wg, w.copy_wgs);
         else if (DIR == kUnpack && !ORD && !PIECES && reads_ahead(U) && copies)
-          pre = preload_first<U, NT, WG>(m, wg, w.copy_wgs);
+          pre = preload_first<HND, U, NT, WG>(m, wg, w.copy_wgs);
       });
   if (REQS == kFew && DIR == kUnpack && pre.valid)
     hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, pause_requests(a.n_req),
@@ -2121,7 +2165,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
   }
   if (copies) {
     if (packs_ahead(REQS))
-      store_pack<U, NT, WG, REQS, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
+      store_pack<HND, U, NT, WG, REQS, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
     else if (PIECES)
       move_pieces<DIR, HND, U, NT, WG, false, false>(m, l, a.n_req, wg, w.copy_wgs);
     else
@@ -2210,7 +2254,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
     DirectHead one_head;
     one_head.live = false;
     if (entries) one_head = iocb_head(g, q, d, l, 1, lead, w.sqe_wgs);
-    if (copies) move_request<DIR, false, U, 3, WG, true>(m, one, bx - w.copy_first, w.copy_wgs, pre);
+    if (copies) move_request<DIR, kNhd, U, 3, WG, true>(m, one, bx - w.copy_first, w.copy_wgs, pre);
     if (entries) emit_iocbs(g, q, d, l, 1, lead, w.sqe_wgs, one_head);
     return;
   }
@@ -2220,7 +2264,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
       a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr, 0xffffffffu, nullptr,
       publish, q.file_id, f, [&] {
         if (packs_ahead(REQS))
-          pre = preload_pack<false, U, 3, WG>(m, bx - w.copy_first, w.copy_wgs);
+          pre = preload_pack<kNhd, U, 3, WG>(m, bx - w.copy_first, w.copy_wgs);
         else if (DIR == kUnpack && !PIECES && reads_ahead(U) && copies && a.n_req == 1)
           pre = preload_first_direct<U, WG>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
       });
@@ -2231,11 +2275,11 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
   if (bx < w.sqe_wgs) head = iocb_head(g, q, d, l, a.n_req, lead, w.sqe_wgs);
   if (copies) {
     if (packs_ahead(REQS))
-      store_pack<U, 3, WG, REQS, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
+      store_pack<kNhd, U, 3, WG, REQS, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
     else if (PIECES)
-      move_pieces<DIR, false, U, 3, WG, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);
+      move_pieces<DIR, kNhd, U, 3, WG, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);
     else
-      move_items<DIR, false, U, 3, WG, REQS, false, kStagingOrder, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
+      move_items<DIR, kNhd, U, 3, WG, REQS, false, kStagingOrder, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
   }
   if (bx < w.sqe_wgs) emit_iocbs(g, q, d, l, a.n_req, lead, w.sqe_wgs, head);
 }

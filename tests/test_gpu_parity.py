@@ -119,6 +119,39 @@ def test_head_major_paths(orc, H, request, shape, mode):
     H.check_everything(orc, c, cu_budget=3)
 
 
+LINE_TILE_SHAPES = [
+    # T, h, d, e, N, n_blocks, align: rows of 16, 32 and 64 bytes; one slice a block to many, few tokens, few heads
+    (16, 16, 16, 1, 200, [37, 0, 60], 4096),     # 4 KiB blocks: one slice
+    (1, 256, 16, 1, 64, [5, 9], 4096),           # a single token
+    (256, 1, 16, 1, 64, [5, 9], 4096),           # a single head
+    (4, 64, 32, 1, 150, [21, 40], 4096),
+    (2, 128, 64, 1, 150, [70, 11], 16384),
+    (16, 16, 32, 2, 300, [110, 1, 7], 4096),
+    (32, 4, 64, 1, 128, [50, 2], 16384),         # 8 KiB blocks in padded objects
+    (64, 64, 16, 2, 40, [9, 12], 65536),          # 128 KiB blocks
+]
+
+
+@pytest.mark.parametrize("shape", LINE_TILE_SHAPES, ids=lambda s: f"T{s[0]}h{s[1]}row{s[2] * s[3]}")
+def test_head_major_line_tiles(orc, H, shape):
+    """Head-major blocks with rows below a line, whole GPU and budgets, one request and several, and a staging buffer that
+    ends inside a block that is read ahead."""
+    T, h, d, e, N, nb, align = shape
+    say("line tiles", shape)
+    rng = np.random.default_rng(700 + T + h)
+    n = sum(nb)
+    c = H.LayerCase(T=T, h=h, d=d, e=e, N=N, n_blocks=nb, table=rng.permutation(N)[:n], chunk=2 << 20, L=2, align=align,
+                    layout=1, seed=h, name=f"tiles{shape}")
+    for budget in (0, 3, 32):
+        H.check_everything(orc, c, cu_budget=budget)
+    one = H.LayerCase(T=T, h=h, d=d, e=e, N=N, n_blocks=[n], table=rng.permutation(N)[:n], chunk=2 << 20, L=2, align=align,
+                      layout=1, seed=h, name=f"tiles1{shape}")
+    H.check_everything(orc, one)
+    o_ext, _ = orc.obj_layout(c.orc_pool(orc), c.orc_cfg(orc), c.n_blocks)
+    for cap in (int(o_ext["stage_off"][len(nb) - 1]) + 4096 + 16, 16):
+        H.check_layer_restore(orc, c, stage_cap=cap, seed=41)
+
+
 def test_head_major_lds_edge_cases(orc, H):
     """Bad ids, a small staging buffer and the 2048-request limit through the LDS-staged path."""
     say("hnd lds edges")

@@ -12,6 +12,12 @@ extern "C" unsigned pause_of(unsigned items, unsigned chip, unsigned n_req, int 
   return tutti::hold_back_pause(items, chip, n_req, file != 0);
 }
 extern "C" int lds_of(unsigned row, unsigned budget) { return tutti::hnd_through_lds(row, budget); }
+extern "C" int tiles_of(unsigned row, unsigned block_bytes, unsigned heads, unsigned budget, int unpack) {
+  return tutti::as_line_tiles(row, block_bytes, heads, budget, unpack != 0);
+}
+extern "C" unsigned tile_shift_of(unsigned row_shift, unsigned head_shift, unsigned token_shift) {
+  return tutti::line_tile_shift(row_shift, head_shift, token_shift);
+}
 extern "C" unsigned units_of(int ahead, unsigned block_bytes, unsigned blocks, unsigned budget, int ordered,
                              int short_rows) {
   return tutti::budget_units(ahead != 0, block_bytes, blocks, budget, ordered != 0, short_rows != 0);
@@ -82,3 +88,36 @@ def test_head_major_rows_through_lds(rules):
             assert not rules.lds_of(row, budget)
         for budget in (17, 32, 64, 256):
             assert rules.lds_of(row, budget) == (row == 16)
+
+
+def test_line_tiles_cover_the_block(rules):
+    """Every shape that the rule takes: the tiles are whole, deal out every 16 bytes of the block once on both sides, and
+    touch whole lines on both wherever tokens and heads are enough for it."""
+    taken = 0
+    for rs in range(4, 7):
+        for hs in range(0, 8):
+            for ts in range(0, 9):
+                if not rules.tiles_of(1 << rs, 1 << (rs + hs + ts), 1 << hs, 0, 1):
+                    assert rs + hs + ts < 12
+                    continue
+                taken += 1
+                tg = rules.tile_shift_of(rs, hs, ts)
+                hg = 10 - rs - tg
+                assert 0 <= tg <= ts and 0 <= hg <= hs
+                assert tg + rs >= 7 or tg == ts
+                assert hg + rs >= 7 or hg == hs
+                if ts + hs + rs > 14:
+                    continue
+                pool, obj = set(), set()
+                for q in range(1 << (rs + hs + ts - 10)):
+                    heads, tokens = q & ((1 << (hs - hg)) - 1), q >> (hs - hg)
+                    for lane in range(64):
+                        w, t = lane & ((1 << (rs - 4)) - 1), lane >> (rs - 4) & ((1 << tg) - 1)
+                        i = lane >> (rs - 4 + tg)
+                        i, t = (heads << hg) + i, (tokens << tg) + t
+                        pool.add((((i << ts) + t) << rs) + 16 * w)
+                        obj.add((((t << hs) + i) << rs) + 16 * w)
+                assert pool == obj == set(range(0, 1 << (rs + hs + ts), 16))
+    assert taken > 80
+    assert not rules.tiles_of(128, 32768, 16, 0, 0) and not rules.tiles_of(64, 16384, 8, 32, 1)
+    assert rules.tiles_of(64, 16384, 8, 32, 0) and rules.tiles_of(64, 16384, 16, 32, 1)
