@@ -1,4 +1,4 @@
-"""ctypes binding of libtutti (include/tutti.h): argument marshalling only.
+"""Python binding of libtutti (include/tutti.h): argument marshalling only.
 
 Every function has the name and argument order of its C entry point; device pointers may be
 given as torch tensors (their data_ptr() is taken) or as integers.  `stream=None` means
@@ -10,6 +10,9 @@ exports the same entry points plus the measurement aids of include/tutti_bench.h
 knobs, every launch shape).  The wrappers of the measurement aids always call the latter;
 `use_bench_library(True)` also routes the ordinary entry points through it, so that an experiment can run the
 product's kernels in another launch shape.  Nothing but bench.py and the tests of those aids does that.
+
+The wrappers are ctypes calls.  Those of the per-layer entry points are called through an extension module
+(csrc/fast_call.cpp), which reads ordinary arguments itself and hands everything else to the wrapper.
 """
 import ctypes as C
 import os
@@ -229,6 +232,7 @@ def product_lib():
     global _LIB
     if _LIB is None:
         _LIB = _load(LIB_PATH, False)
+        _bind_fast_calls()
     return _LIB
 
 
@@ -244,6 +248,8 @@ def use_bench_library(on=True):
     """Route the ordinary entry points through libtutti_bench.so (experiments with the tuning knobs) or back."""
     global _USE_BENCH
     _USE_BENCH = bool(on)
+    if _fast_call is not None:
+        _fast_call.enable(False)   # back to the product library: at the next call that asks for the current stream
 
 
 def lib():
@@ -254,7 +260,7 @@ def lib():
 
 
 # A short prefix's restore is over in 3 us on the GPU, so what a call costs on this side is what a train of layers runs
-# at.  Pointers therefore travel as plain integers (argtypes makes them void *; wrapping each of nine in a c_void_p took
+# at (hence the extension module).  Pointers therefore travel as plain integers (argtypes makes them void *; wrapping each of nine in a c_void_p took
 # 2 us of a call) and the current stream is asked for its handle alone (without building a Stream object: 1 us).
 # tutti_layer_restore of a 256 KiB prefix, from Python: 8.6 us a call before, 5.7 now.
 def _p(x):
@@ -281,7 +287,10 @@ def _stream(stream):
             _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
                 lambda device: torch.cuda.current_stream(device).cuda_stream)
             _torch_cuda = torch.cuda
-        return _raw_stream(_torch_cuda.current_device())
+        handle = _raw_stream(_torch_cuda.current_device())
+        if _fast_call is not None and not _USE_BENCH:
+            _fast_call.enable(True)   # the device has been initialised in this process
+        return handle
     if hasattr(stream, "cuda_stream"):
         return stream.cuda_stream
     return int(stream)
@@ -703,3 +712,45 @@ def tutti_host_cost_of_restore(pool, cfg, d_n_blocks, n_req, d_block_table, tabl
                                                   _p(d_sqe), sqe_cap, cu_budget, _p(d_status), _stream(stream),
                                                   n_calls, C.byref(ns)))
     return ns.value
+
+
+# The entry points whose ordinary calls the extension module makes (its callables stand in the wrappers' places).
+_FAST_NAMES = ["tutti_layer_restore", "tutti_layer_save", "tutti_obj_layout", "tutti_obj_pack", "tutti_obj_unpack",
+               "tutti_sqe_build", "tutti_iocb_fill_direct", "tutti_issue_io", "tutti_issue_io_chained",
+               "tutti_retrieve_layer", "tutti_store_layer", "tutti_retrieve_layer_issue", "tutti_store_layer_issue",
+               "tutti_retrieve_layer_chained", "tutti_store_layer_chained", "tutti_complete_io"]
+_fast_call = None
+
+
+def _wrap_fast(module, name, slow):
+    """The extension module's callable for an entry point and its ctypes wrapper."""
+    code = slow.__code__
+    return module.wrap(name, slow, code.co_varnames[:code.co_argcount], slow.__defaults__)
+
+
+def _install_fast_calls():
+    global _fast_call
+    try:
+        import torch  # noqa: F401  (the module is linked against it)
+        from . import _fast_call as module
+    except ImportError:
+        return        # not built: the ctypes wrappers make the same calls
+    _fast_call = module
+    for name in _FAST_NAMES:
+        globals()[name] = _wrap_fast(module, name, globals()[name])
+
+
+def _bind_fast_calls():
+    if _fast_call is None:
+        return
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return
+    _fast_call.setup((tutti_pool, tutti_objcfg, tutti_ring, tutti_filestore), torch.Tensor, torch._C._cuda_getDevice, raw,
+                     _check)
+    for name in _FAST_NAMES:
+        _fast_call.bind(globals()[name], C.cast(getattr(_LIB, name), C.c_void_p).value)
+
+
+_install_fast_calls()

@@ -1,0 +1,298 @@
+// Python callables for the per-layer entry points of tutti.h: what the ctypes wrappers of binding.py do for the arguments
+// that a serving loop passes, without building a ctypes argument list on every call.
+//
+// A train of layers of a short prefix runs at the pace of its calls: restore of 256 KiB, one call, 5.8 us through ctypes, of
+// which 3.6 are the launch.  Bound by the launch now; tensors are unpacked in C++ (data_ptr() as a method costs 50 ns each,
+// and a call has up to nine of them).
+//
+// Whatever is out of the ordinary (another type, an error while an argument is read, a library or a device that has not
+// been used yet) goes to the ctypes wrapper with the very same arguments, which accepts or refuses it.
+#include <Python.h>
+#include <ATen/PythonTorchFunctionTLS.h>
+#include <pthread.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <atomic>
+#include <cstddef>
+#include <cstdint>
+#include <cstring>
+#include <type_traits>
+#include <utility>
+
+#include "tutti.h"
+
+namespace {
+
+enum Kind : uint8_t { kPointer, kStruct, kInt };
+constexpr size_t kMaxArgs = 24;
+
+// What the module has been told: classes of the C records, torch's functions, binding.py's error check.
+PyObject *g_records[4];  // tutti_pool, tutti_objcfg, tutti_ring, tutti_filestore
+PyObject *g_tensor_type, *g_get_device, *g_raw_stream, *g_check;
+std::atomic<bool> g_ready{false};  // the product library is the one in use, and torch has initialised the device here
+
+// The ctypes class that an argument of this C type is an instance of; -1: it is no record.
+template <typename A>
+constexpr int record_of() {
+  using T = std::remove_cv_t<std::remove_pointer_t<A>>;
+  return std::is_same_v<T, tutti_pool> ? 0 : std::is_same_v<T, tutti_objcfg> ? 1 : std::is_same_v<T, tutti_ring> ? 2
+         : std::is_same_v<T, tutti_filestore> ? 3 : -1;
+}
+
+// Arguments as 64-bit words; the last one is the stream.
+struct Entry {
+  const char *name;
+  size_t n;
+  Kind kind[kMaxArgs];
+  int8_t record[kMaxArgs];
+  int (*invoke)(void *fn, const uint64_t *word);
+};
+
+template <typename A>
+A from_word(uint64_t w) {
+  if constexpr (std::is_pointer_v<A>)
+    return reinterpret_cast<A>(static_cast<uintptr_t>(w));
+  else
+    return static_cast<A>(w);
+}
+
+template <typename... A, size_t... I>
+int invoke_words(void *fn, const uint64_t *word, std::index_sequence<I...>) {
+  return reinterpret_cast<int (*)(A...)>(fn)(from_word<A>(word[I])...);
+}
+
+template <typename... A>
+Entry entry(const char *name, int (*)(A...)) {
+  static_assert(sizeof...(A) <= kMaxArgs);
+  Entry e{name, sizeof...(A), {}, {}, nullptr};
+  size_t i = 0;
+  ((e.kind[i] = record_of<A>() >= 0 ? kStruct : std::is_pointer_v<A> ? kPointer : kInt, e.record[i] = record_of<A>(), ++i), ...);
+  e.invoke = [](void *fn, const uint64_t *word) { return invoke_words<A...>(fn, word, std::index_sequence_for<A...>{}); };
+  return e;
+}
+
+// (the functions are named for their types alone: their addresses come from the library that binding.py has loaded)
+#define ENTRY(f) entry(#f, static_cast<decltype(&f)>(nullptr))
+const Entry kEntries[] = {
+    ENTRY(tutti_layer_restore),          ENTRY(tutti_layer_save),           ENTRY(tutti_obj_layout),
+    ENTRY(tutti_obj_pack),               ENTRY(tutti_obj_unpack),           ENTRY(tutti_sqe_build),
+    ENTRY(tutti_iocb_fill_direct),       ENTRY(tutti_issue_io),             ENTRY(tutti_issue_io_chained),
+    ENTRY(tutti_retrieve_layer),         ENTRY(tutti_store_layer),          ENTRY(tutti_retrieve_layer_issue),
+    ENTRY(tutti_store_layer_issue),      ENTRY(tutti_retrieve_layer_chained), ENTRY(tutti_store_layer_chained),
+    ENTRY(tutti_complete_io),
+};
+#undef ENTRY
+
+struct Call {
+  PyObject_HEAD
+  vectorcallfunc vectorcall;
+  const Entry *entry;
+  void *fn;
+  PyObject *name, *slow;
+  PyObject *names;                // argument names in order, interned
+  uint64_t defaults[kMaxArgs];    // words of the arguments from `required` on
+  size_t required;
+};
+
+// The word of one argument.  false: not an ordinary one (no Python error is set then).
+bool pointer_word(PyObject *x, uint64_t *out) {
+  if (reinterpret_cast<PyObject *>(Py_TYPE(x)) == g_tensor_type) {
+    try {
+      *out = reinterpret_cast<uintptr_t>(THPVariable_Unpack(x).data_ptr());
+      return true;
+    } catch (...) {
+      return false;
+    }
+  }
+  if (x == Py_None) {
+    *out = 0;
+    return true;
+  }
+  if (!PyLong_CheckExact(x)) return false;
+  *out = PyLong_AsUnsignedLongLongMask(x);
+  return true;
+}
+
+bool stream_word(uint64_t *out) {  // torch's current stream
+  PyObject *dev = PyObject_CallNoArgs(g_get_device);
+  PyObject *raw = dev ? PyObject_CallOneArg(g_raw_stream, dev) : nullptr;
+  Py_XDECREF(dev);
+  const bool ok = raw && PyLong_CheckExact(raw);
+  if (ok) *out = PyLong_AsUnsignedLongLongMask(raw);
+  Py_XDECREF(raw);
+  if (!ok) PyErr_Clear();
+  return ok;
+}
+
+struct Views {
+  Py_buffer view[4];
+  int n = 0;
+  ~Views() {
+    while (n > 0) PyBuffer_Release(&view[--n]);
+  }
+};
+
+bool read_words(const Call *c, PyObject *const *args, size_t n_pos, PyObject *kwnames, uint64_t *word, Views *views) {
+  const Entry &e = *c->entry;
+  PyObject *given[kMaxArgs] = {};
+  if (n_pos > e.n) return false;
+  for (size_t i = 0; i < n_pos; ++i) given[i] = args[i];
+  const Py_ssize_t n_kw = kwnames ? PyTuple_GET_SIZE(kwnames) : 0;
+  for (Py_ssize_t k = 0; k < n_kw; ++k) {
+    size_t i = n_pos;
+    while (i < e.n && PyTuple_GET_ITEM(c->names, i) != PyTuple_GET_ITEM(kwnames, k)) ++i;
+    if (i == e.n || given[i]) return false;
+    given[i] = args[n_pos + k];
+  }
+  for (size_t i = 0; i + 1 < e.n; ++i) {
+    PyObject *x = given[i];
+    if (!x) {
+      if (i < c->required) return false;
+      word[i] = c->defaults[i];
+    } else if (e.kind[i] == kInt) {
+      if (!PyLong_CheckExact(x)) return false;
+      word[i] = PyLong_AsUnsignedLongLongMask(x);
+    } else if (e.kind[i] == kPointer) {
+      if (!pointer_word(x, &word[i])) return false;
+    } else {
+      if (reinterpret_cast<PyObject *>(Py_TYPE(x)) != g_records[e.record[i]] || views->n == 4) return false;
+      if (PyObject_GetBuffer(x, &views->view[views->n], PyBUF_SIMPLE) != 0) {
+        PyErr_Clear();
+        return false;
+      }
+      word[i] = reinterpret_cast<uintptr_t>(views->view[views->n++].buf);
+    }
+  }
+  PyObject *s = given[e.n - 1];
+  if (!s || s == Py_None) return stream_word(&word[e.n - 1]);
+  if (!PyLong_CheckExact(s)) return false;
+  word[e.n - 1] = PyLong_AsUnsignedLongLongMask(s);
+  return true;
+}
+
+PyObject *call(PyObject *self, PyObject *const *args, size_t nargsf, PyObject *kwnames) {
+  Call *c = reinterpret_cast<Call *>(self);
+  if (g_ready.load(std::memory_order_relaxed) && c->fn && !at::impl::torch_function_mode_enabled()) {
+    uint64_t word[kMaxArgs];
+    Views views;
+    if (read_words(c, args, PyVectorcall_NARGS(nargsf), kwnames, word, &views)) {
+      int rc;
+      Py_BEGIN_ALLOW_THREADS
+      rc = c->entry->invoke(c->fn, word);
+      Py_END_ALLOW_THREADS
+      PyObject *code = PyLong_FromLong(rc);
+      if (rc == TUTTI_OK || !code) return code;
+      PyObject *r = PyObject_CallFunctionObjArgs(g_check, c->name, code, nullptr);
+      Py_DECREF(code);
+      return r;
+    }
+  }
+  return PyObject_Vectorcall(c->slow, args, nargsf, kwnames);
+}
+
+void call_dealloc(PyObject *self) {
+  Call *c = reinterpret_cast<Call *>(self);
+  Py_XDECREF(c->name);
+  Py_XDECREF(c->slow);
+  Py_XDECREF(c->names);
+  Py_TYPE(self)->tp_free(self);
+}
+
+// What is asked of it (its name, module, doc string, signature) is the wrapper's; it is pickled by that name.
+PyObject *call_getattro(PyObject *self, PyObject *name) {
+  Call *c = reinterpret_cast<Call *>(self);
+  if (PyUnicode_Check(name)) {
+    if (PyUnicode_CompareWithASCIIString(name, "__wrapped__") == 0) return Py_NewRef(c->slow);
+    for (const char *own : {"__class__", "__reduce__", "__reduce_ex__"})
+      if (PyUnicode_CompareWithASCIIString(name, own) == 0) return PyObject_GenericGetAttr(self, name);
+  }
+  return PyObject_GetAttr(c->slow, name);
+}
+
+PyObject *call_reduce(PyObject *self, PyObject *) { return Py_NewRef(reinterpret_cast<Call *>(self)->name); }
+PyMethodDef kCallMethods[] = {{"__reduce__", call_reduce, METH_NOARGS, nullptr}, {nullptr, nullptr, 0, nullptr}};
+
+PyTypeObject CallType = {PyVarObject_HEAD_INIT(nullptr, 0)};
+
+// wrap(name, slow, names, defaults): the callable of an entry point.  `names`: its arguments' names in order, `defaults`: the
+// last ones' defaults (None or 0), the stream's included.
+PyObject *wrap(PyObject *, PyObject *args) {
+  const char *name;
+  PyObject *slow, *names, *defaults;
+  if (!PyArg_ParseTuple(args, "sOO!O!", &name, &slow, &PyTuple_Type, &names, &PyTuple_Type, &defaults)) return nullptr;
+  const Entry *e = nullptr;
+  for (const Entry &x : kEntries)
+    if (strcmp(x.name, name) == 0) e = &x;
+  const size_t n = static_cast<size_t>(PyTuple_GET_SIZE(names)), n_def = static_cast<size_t>(PyTuple_GET_SIZE(defaults));
+  if (!e || e->n != n || n_def < 1 || n_def > n) {
+    PyErr_Format(PyExc_ValueError, "%s: not an entry point of these arguments", name);
+    return nullptr;
+  }
+  Call *c = PyObject_New(Call, &CallType);
+  if (!c) return nullptr;
+  c->vectorcall = call;
+  c->entry = e;
+  c->fn = nullptr;
+  c->name = PyUnicode_InternFromString(name);
+  c->slow = Py_NewRef(slow);
+  c->names = Py_NewRef(names);
+  c->required = n - n_def;
+  for (size_t i = c->required; i < n; ++i) {
+    PyObject *d = PyTuple_GET_ITEM(defaults, i - c->required);
+    c->defaults[i] = PyLong_Check(d) ? PyLong_AsUnsignedLongLongMask(d) : 0;
+  }
+  return reinterpret_cast<PyObject *>(c);
+}
+
+// bind(callable, address): where the library has the entry point.
+PyObject *bind(PyObject *, PyObject *args) {
+  PyObject *o;
+  unsigned long long at;
+  if (!PyArg_ParseTuple(args, "O!K", &CallType, &o, &at)) return nullptr;
+  reinterpret_cast<Call *>(o)->fn = reinterpret_cast<void *>(static_cast<uintptr_t>(at));
+  Py_RETURN_NONE;
+}
+
+// setup(records, tensor type, function: current device, function: its current stream's handle, function: error check)
+PyObject *setup(PyObject *, PyObject *args) {
+  PyObject *r[4], *o[4];
+  if (!PyArg_ParseTuple(args, "(OOOO)OOOO", &r[0], &r[1], &r[2], &r[3], &o[0], &o[1], &o[2], &o[3])) return nullptr;
+  for (int i = 0; i < 4; ++i) Py_XSETREF(g_records[i], Py_NewRef(r[i]));
+  PyObject **const to[4] = {&g_tensor_type, &g_get_device, &g_raw_stream, &g_check};
+  for (int i = 0; i < 4; ++i) Py_XSETREF(*to[i], Py_NewRef(o[i]));
+  Py_RETURN_NONE;
+}
+
+// enable(on): from here on the ordinary arguments are (are not) read here.
+PyObject *enable(PyObject *, PyObject *on) {
+  const int v = PyObject_IsTrue(on);
+  if (v < 0) return nullptr;
+  g_ready.store(v != 0 && g_check != nullptr, std::memory_order_relaxed);
+  Py_RETURN_NONE;
+}
+
+// A forked child has no device: torch says so when it is asked by way of the wrappers.
+void in_child() { g_ready.store(false, std::memory_order_relaxed); }
+
+PyMethodDef kMethods[] = {{"wrap", wrap, METH_VARARGS, nullptr},
+                          {"bind", bind, METH_VARARGS, nullptr},
+                          {"setup", setup, METH_VARARGS, nullptr},
+                          {"enable", enable, METH_O, nullptr},
+                          {nullptr, nullptr, 0, nullptr}};
+PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_fast_call", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__fast_call(void) {
+  CallType.tp_name = "paper_2605_03375_amd._fast_call.Call";
+  CallType.tp_basicsize = sizeof(Call);
+  CallType.tp_dealloc = call_dealloc;
+  CallType.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_VECTORCALL;
+  CallType.tp_vectorcall_offset = offsetof(Call, vectorcall);
+  CallType.tp_call = PyVectorcall_Call;
+  CallType.tp_getattro = call_getattro;
+  CallType.tp_methods = kCallMethods;
+  if (PyType_Ready(&CallType) != 0) return nullptr;
+  pthread_atfork(nullptr, nullptr, in_child);
+  return PyModule_Create(&kModule);
+}
