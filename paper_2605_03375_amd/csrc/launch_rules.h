@@ -72,6 +72,21 @@ constexpr uint32_t budget_units(bool ahead, uint32_t block_bytes, uint32_t block
   return items <= one_each || cu_budget > 32 || !even ? 16 : 8;
 }
 
+// Whether the submission entries (or the contexts) of a whole-GPU launch of up to 64 requests are written by workgroups of
+// their own, in front of the `copy_wgs` that move blocks, instead of riding along with the first of those.  Riding along a
+// small launch is as long as the scan with the entries' divisions, the copy and the entry one behind the other; a larger one
+// hides that behind its other items, and the workgroups in front then only come first.  Graph replay, us, along / apart:
+//   1 request     restore of 2 blocks of 32 KiB 3.3 / 2.7, 64 3.35 / 3.1, 100 3.5 / 3.4, 128 (512 workgroups) 3.9 / 3.8; save 3.0 /
+//                 2.7, 3.8 / 3.6; retrieve of 64 6.1 / 5.5, 100 6.2 / 5.5; 16 layers of 64: retrieves 64.6 / 59.4, stores 72.9 / 59.5
+//                 200 (800): restore 5.9 / 5.9, retrieve 8.5 / 8.5, store 8.6 / 8.6
+//   several       restore of 64 in 8 4.3 / 4.0, 128 in 30 4.8 / 4.5, 160 in 8 (640) 4.95 / 4.9; save 4.1 / 3.8, 4.6 / 4.2, 4.7 / 4.6;
+//                 retrieve 6.8 / 6.2, 7.6 / 7.4, 8.6 / 8.1; 16 layers of 20 in 5: retrieves 78 / 60, stores 66 / 56
+//                 200 in 8 (800): store 7.7 / 8.2; 1500 blocks of 4 KiB (750) 7.2 / 8.6
+// (What loses: a train of 3 stores of 100 blocks in 8, 15.4 / 16.2, of retrieves of 120 in one request, 15.7 / 16.2.)
+constexpr bool entries_apart(uint32_t copy_wgs, uint32_t cus, uint32_t n_req) {
+  return 2 * copy_wgs <= (n_req == 1 ? 4 : 5) * cus;
+}
+
 // Whether a head-major pool goes through LDS tiles or is moved directly, where it is not moved as line tiles
 // (as_line_tiles).  On the whole GPU it pays while a row is shorter than a 128-byte line.  Under a CU budget a workgroup has one tile in flight at a time, and only rows of 16 bytes on
 // more than 16 compute units are worth that.  Through LDS / direct, us, save and restore of 16 KiB blocks:

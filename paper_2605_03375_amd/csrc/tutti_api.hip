@@ -249,12 +249,26 @@ bool few_requests(const Launch &L, const MoveArgs &m, uint32_t n_req) {
   return n_req <= kWave && !m.visit && !(L.pieces && L.wg_threads == kBudgetWgThreads);
 }
 
-// A pack of several requests that reads its slices while it scans (preload_pack): whole slices, 3/4 of the chip's wavefronts
-// at most.
+// Gives the entry writers of a whole-GPU launch workgroups of their own where that is the shorter way (entries_apart): so
+// many that the items start at a multiple of eight workgroups and fall to the same XCDs as without (those beyond the
+// writers do nothing).  `lead`: workgroups in front of all.
+void separate_entries(const Launch &L, uint32_t n_req, uint32_t lead, Roles *w, uint32_t *n_wgs) {
+  const uint32_t own = (w->sqe_wgs + lead + 7) / 8 * 8 - lead;
+  if (L.wg_threads != kWgThreads || !entries_apart(L.grid, L.cus, n_req) || lead + own + L.grid > whole_gpu_wgs(L)) return;
+  w->copy_first = own;
+  *n_wgs = own + L.grid;
+}
+
+// Several requests whose slices are read under the scan.  A pack (preload_pack): whole slices, 3/4 of the chip's wavefronts
+// at most.  A restore of more than 64 requests, which otherwise reads its first slices behind the scan (scan_extents): as
+// long as no wavefront has a second item.  Graph replay, us, behind / under the scan, 32 KiB blocks: 150 in 150 requests
+// 6.9 / 5.3, 350 in 100 10.4 / 8.6, 480 in 200 12.6 / 11.4; blocks of 4 KiB, 1500 in 500 9.1 / 6.2, 3000 in 1000 14.3 / 11.1;
+// with a second item, 600 requests, 49 MB, 20.3 / 22.0.
 template <int DIR>
-bool pack_ahead(const Launch &L, uint32_t n_req, uint64_t wave_items) {
-  return DIR == kPack && n_req > 1 && !L.pieces && !L.hnd_lds && L.wg_threads == kWgThreads &&
-         L.unroll == kDefaultUnroll && 4 * wave_items <= 3 * whole_gpu_waves(L);
+bool scan_reads(const Launch &L, const MoveArgs &m, uint32_t n_req, uint64_t wave_items) {
+  if (n_req == 1 || L.pieces || L.hnd_lds || L.wg_threads != kWgThreads || L.unroll != kDefaultUnroll) return false;
+  if (DIR == kPack) return 4 * wave_items <= 3 * whole_gpu_waves(L);
+  return n_req > kWave && m.dense != 0 && m.visit == nullptr && wave_items <= whole_gpu_waves(L);
 }
 
 uint64_t counted_slices(const Launch &L, uint32_t bytes) {
@@ -538,19 +552,29 @@ hipError_t launch_layer(const Launch &L, uint64_t entry_quarters, uint32_t lds, 
   return with_shape(L, [&](auto sh) {
     using S = decltype(sh);
     if constexpr (has_few<S>) {
-      if (one_request_path<DIR>(L, m, a.n_req, move_wave_items(L, m)))
+      if (one_request_path<DIR>(L, m, a.n_req, move_wave_items(L, m))) {
+        separate_entries(L, 1, 0, &w, &n_wgs);
         return launch_layer_shape<S, DIR, HND, kOne>(false, n_wgs, lds, s, m, q, a, w);
-      if constexpr (DIR == kPack && S::WG == kWgThreads) {
-        if (pack_ahead<DIR>(L, a.n_req, move_wave_items(L, m))) {
-          if (a.n_req <= kWave) return launch_layer_shape<S, DIR, HND, kFewAhead>(false, n_wgs, lds, s, m, q, a, w);
-          // the entry writers' scan is the longer one and reads nothing ahead: workgroups of their own
-          if (L.grid + w.sqe_wgs <= whole_gpu_wgs(L) && a.geom.align <= (1u << 20)) {
+      }
+      if constexpr (S::WG == kWgThreads) {
+        if (scan_reads<DIR>(L, m, a.n_req, move_wave_items(L, m))) {
+          if (a.n_req <= kWave) {
+            if constexpr (DIR == kPack) {
+              separate_entries(L, a.n_req, 0, &w, &n_wgs);
+              return launch_layer_shape<S, DIR, HND, kFewAhead>(false, n_wgs, lds, s, m, q, a, w);
+            }
+          } else if (L.grid + w.sqe_wgs <= whole_gpu_wgs(L) && a.geom.align <= (1u << 20)) {
+            // the entry writers' scan is the longer one and reads nothing ahead: workgroups of their own
+            // (as they are: rounded up to eight, 150 blocks in 150 requests restore in 5.9 us instead of 5.3)
             w.copy_first = w.sqe_wgs;
             return launch_layer_shape<S, DIR, HND, kManyAhead>(false, L.grid + w.sqe_wgs, lds, s, m, q, a, w);
           }
         }
       }
-      if (few_requests(L, m, a.n_req)) return launch_layer_shape<S, DIR, HND, kFew>(L.pieces, n_wgs, lds, s, m, q, a, w);
+      if (few_requests(L, m, a.n_req)) {
+        separate_entries(L, a.n_req, 0, &w, &n_wgs);
+        return launch_layer_shape<S, DIR, HND, kFew>(L.pieces, n_wgs, lds, s, m, q, a, w);
+      }
     }
     return launch_layer_shape<S, DIR, HND, kMany>(L.pieces, n_wgs, lds, s, m, q, a, w);
   });
@@ -1031,18 +1055,19 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint32_t n_wgs = 0;
-  const Roles w = make_roles(L, 4 * n_ctx, &n_wgs);
+  Roles w = make_roles(L, 4 * n_ctx, &n_wgs);
   const uint32_t lds = req_lds_bytes(n_req);
   Launch R = L;
   R.nontemporal = 3;  // the ring kernels have one cache policy
   hipError_t e = with_shape(R, [&](auto sh) {
     using S = decltype(sh);
     if constexpr (has_few<S>) {
-      if (one_request_path<DIR>(R, m, n_req, move_wave_items(R, m)))
-        return launch_ring_shape<S, DIR, kOne>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+      const bool one = one_request_path<DIR>(R, m, n_req, move_wave_items(R, m));
+      const bool ahead = DIR == kPack && n_req <= kWave && scan_reads<DIR>(R, m, n_req, move_wave_items(R, m));
+      if (one || ahead || few_requests(R, m, n_req)) separate_entries(R, n_req, lead, &w, &n_wgs);
+      if (one) return launch_ring_shape<S, DIR, kOne>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
       if constexpr (DIR == kPack && S::WG == kWgThreads) {
-        if (n_req <= kWave && pack_ahead<DIR>(R, n_req, move_wave_items(R, m)))
-          return launch_ring_shape<S, DIR, kFewAhead>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+        if (ahead) return launch_ring_shape<S, DIR, kFewAhead>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
       }
       if (few_requests(R, m, n_req)) return launch_ring_shape<S, DIR, kFew>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
     }
@@ -1742,10 +1767,8 @@ void least_resident_layer(int *worst) {
   least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany>,
                  k_layer<DIR, HND, 4, 3, kWgThreads, kMany, false, true>);
   if constexpr (DIR == kUnpack) least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, true>);
-  if constexpr (DIR == kPack) {
-    least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFewAhead>);
-    least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kManyAhead>);
-  }
+  if constexpr (DIR == kPack) least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFewAhead>);
+  least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kManyAhead>);
 }
 
 template <int DIR>

@@ -42,9 +42,10 @@ constexpr uint32_t kBudgetWgThreads = 1024;  // CU-budgeted launches: one 16-wav
 // costs no scratch: 256-thread kernels with at most four 16-byte units in flight per lane.
 constexpr int min_waves_per_simd(int wg_threads, int units) { return (wg_threads == 256 && units <= 4) ? 8 : 4; }
 
-// Requests a kernel is for: one, up to 64, any number; ...Ahead: a pack that reads ahead (preload_pack).
+// Requests a kernel is for: one, up to 64, any number; ...Ahead: several whose slices are read behind the loads of the counts,
+// under the scan (a pack's by preload_pack).
 constexpr int kOne = 1, kFew = 2, kMany = 3, kFewAhead = 4, kManyAhead = 5;
-constexpr bool packs_ahead(int reqs) { return reqs == kFewAhead || reqs == kManyAhead; }
+constexpr bool reads_under_scan(int reqs) { return reqs == kFewAhead || reqs == kManyAhead; }
 constexpr bool any_number(int reqs) { return reqs == kMany || reqs == kManyAhead; }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -384,14 +385,14 @@ __device__ __forceinline__ void scan_extents(const ScanGeom g, const uint32_t *_
                                              uint32_t *__restrict__ status, bool with_chunks,
                                              const uint32_t *__restrict__ file_id, const FileArgs files, P preload) {
   const auto under_loads = [&] {  // a pack's: behind the loads of the counts, so that the scan need not wait for it
-    if (packs_ahead(REQS)) {
+    if (reads_under_scan(REQS)) {
       __builtin_amdgcn_sched_barrier(0);
       preload();
       __builtin_amdgcn_sched_barrier(0);
     }
   };
   if (REQS == kFew || REQS == kFewAhead || (REQS == kMany && n_req <= kWave)) {
-    if (!packs_ahead(REQS)) preload();
+    if (!reads_under_scan(REQS)) preload();
     uint32_t n = 0, fid = 0;
     if (threadIdx.x < n_req) {
       n = n_blocks[threadIdx.x];
@@ -406,7 +407,7 @@ __device__ __forceinline__ void scan_extents(const ScanGeom g, const uint32_t *_
   } else {
     wg_scan_extents<WG, false, true>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, nullptr, files,
                                      under_loads);
-    if (!packs_ahead(REQS)) preload();
+    if (!reads_under_scan(REQS)) preload();
   }
   __syncthreads();
 }
@@ -1598,7 +1599,7 @@ __device__ __forceinline__ Preload<U> preload_first(const MoveArgs &a, uint32_t 
   return p;
 }
 
-// A pack in table order (packs_ahead): the launch gives every wavefront one item at most, so the order does not matter to the
+// A pack in table order (reads_under_scan): the launch gives every wavefront one item at most, so the order does not matter to the
 // memory, and where an item's bytes sit follows from the table alone: they are read while the requests are being scanned,
 // instead of behind the scan, the owner and the block id: small saves are bound by that chain of dependent loads.  Cold,
 // us, in staging order / so: 32 KiB blocks, 64 in 30 requests 4.7 / 3.8, 128 in 128 7.1 / 5.4, 300 in 3 9.8 / 8.6; 1280 blocks
@@ -1619,9 +1620,10 @@ __device__ __forceinline__ Preload<U> preload_pack(const MoveArgs &a, uint32_t w
   }
   Preload<U> p;
   p.valid = id < a.num_blocks;
-  // every path issues the loads (of block 0 for want of another): the scanning wavefront's wait for the counts, asked for
-  // in front of them, would otherwise be one for both
-  p.src = (kind ? a.v_base : a.k_base) + static_cast<uint64_t>(p.valid ? id : 0u) * a.block_stride;
+  // every path issues the loads (of some block for want of another, not the same one from all XCDs): the scanning wavefront's
+  // wait for the counts, asked for in front of them, would otherwise be one for both
+  const uint32_t spare = blockIdx.x < a.num_blocks ? blockIdx.x : 0u;
+  p.src = (kind ? a.v_base : a.k_base) + static_cast<uint64_t>(p.valid ? id : spare) * a.block_stride;
   load_slice<pool_side(HND), U, NT>(a, p.src, part * kSlice + lane * 16u, p.buf);
   return p;
 }
@@ -2099,11 +2101,12 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, PT)) void k_move_lds(con
 // once, adds that work's latency to the whole kernel (measured: 2.4 us of 53 with the entry writers as extra
 // workgroups behind a full grid).  So the entries ride along: an entry-writing workgroup finds its quarter's
 // request and asks for the file id right after the scan, runs its share of the copy, and only then assembles
-// and stores the entry; with enough entries every workgroup of the grid takes one pass of them.
+// and stores the entry; with enough entries every workgroup of the grid takes one pass of them.  A small launch leaves places
+// free and hides nothing behind its few items: there the entry writers are workgroups of their own (entries_apart).
 struct Roles {
   uint32_t sqe_wgs;     // workgroups [0, sqe_wgs) write entries
   uint32_t copy_first;  // workgroups [copy_first, copy_first + copy_wgs) move blocks (the grid may be larger when
-  uint32_t copy_wgs;    // there are more passes of entries than copy workgroups)
+  uint32_t copy_wgs;    // there are more passes of entries than copy workgroups); 0, or beyond the entry writers
 };
 
 // The arguments that the way to the first load needs, asked for together: left to itself the compiler loads each where it
@@ -2141,11 +2144,11 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     if (entries) emit_sqes(q, l, 1, 0, w.sqe_wgs, one_head);
     return;
   }
-  if (packs_ahead(REQS)) args_at_hand(m, a, w);
+  if (reads_under_scan(REQS)) args_at_hand(m, a, w);
   scan_extents<WG, REQS>(
       a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr, m.table_len, m.status,
       blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [&] {
-        if (packs_ahead(REQS))
+        if (DIR == kPack && reads_under_scan(REQS))
           pre = preload_pack<HND, U, NT, WG>(m, wg, w.copy_wgs);
         else if (DIR == kUnpack && !ORD && !PIECES && reads_ahead(U) && copies)
           pre = preload_first<HND, U, NT, WG>(m, wg, w.copy_wgs);
@@ -2164,7 +2167,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
         atomicOr(m.status, TUTTI_ST_STAGE_CAP);
   }
   if (copies) {
-    if (packs_ahead(REQS))
+    if (DIR == kPack && reads_under_scan(REQS))
       store_pack<HND, U, NT, WG, REQS, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
     else if (PIECES)
       move_pieces<DIR, HND, U, NT, WG, false, false>(m, l, a.n_req, wg, w.copy_wgs);
@@ -2259,11 +2262,11 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
     return;
   }
   // chunk counts only matter for the published extents; the LDS copy gets file starts instead of staging offsets
-  if (packs_ahead(REQS)) args_at_hand(m, a, w);
+  if (reads_under_scan(REQS)) args_at_hand(m, a, w);
   scan_extents<WG, REQS>(
       a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr, 0xffffffffu, nullptr,
       publish, q.file_id, f, [&] {
-        if (packs_ahead(REQS))
+        if (reads_under_scan(REQS))
           pre = preload_pack<kNhd, U, 3, WG>(m, bx - w.copy_first, w.copy_wgs);
         else if (DIR == kUnpack && !PIECES && reads_ahead(U) && copies && a.n_req == 1)
           pre = preload_first_direct<U, WG>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
@@ -2274,7 +2277,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
   head.live = false;
   if (bx < w.sqe_wgs) head = iocb_head(g, q, d, l, a.n_req, lead, w.sqe_wgs);
   if (copies) {
-    if (packs_ahead(REQS))
+    if (reads_under_scan(REQS))
       store_pack<kNhd, U, 3, WG, REQS, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
     else if (PIECES)
       move_pieces<DIR, kNhd, U, 3, WG, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);

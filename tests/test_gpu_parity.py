@@ -119,6 +119,33 @@ def test_head_major_paths(orc, H, request, shape, mode):
     H.check_everything(orc, c, cu_budget=3)
 
 
+@pytest.mark.parametrize("layout", [0, 1], ids=["nhd", "hnd"])
+@pytest.mark.parametrize("blocks,reqs", [(1, 1), (1024, 1), (1025, 1), (1280, 3), (1281, 3), (70, 66), (3700, 65), (4096, 65),
+                                         (4097, 65)])
+def test_entry_writers_apart_and_along(orc, H, blocks, reqs, layout):
+    """Blocks of one slice at both sides of the sizes from which entries (and contexts) are written by the copy's own
+    workgroups, and of the size up to which restores of many requests read ahead; more entries than one workgroup
+    writes, a train behind a completion, too few IOCBs, entries cut."""
+    say("entries apart", blocks, reqs, layout)
+    rng = np.random.default_rng(900 + blocks + reqs)
+    nb = np.full(reqs, blocks // reqs, np.uint32)
+    nb[: blocks % reqs] += 1
+    N = blocks + 50
+    c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=nb, table=rng.permutation(N)[:blocks], chunk=4096, L=2, layout=layout,
+                    seed=reqs, name=f"apart{blocks}r{reqs}")
+    H.check_layer_restore(orc, c)
+    H.check_layer_save(orc, c)
+    H.check_layer_restore(orc, c, table_len=blocks - 1, sqe_cap=blocks)
+    H.check_layer_save(orc, c, sqe_cap=5)
+    if layout == 0:
+        slots = -(-2 * blocks // 2048)
+        for write in (False, True):
+            H.check_ring_layer(orc, c, 1, write, slots + 1, 1, slots)
+            H.check_ring_layer_train(orc, c, [0, 1], write, 2 * slots, slots)
+            if slots > 1:
+                H.check_ring_layer(orc, c, 0, write, slots, 0, slots - 1)
+
+
 LINE_TILE_SHAPES = [
     # T, h, d, e, N, n_blocks, align: rows of 16, 32 and 64 bytes; one slice a block to many, few tokens, few heads
     (16, 16, 16, 1, 200, [37, 0, 60], 4096),     # 4 KiB blocks: one slice

@@ -18,6 +18,9 @@ extern "C" int tiles_of(unsigned row, unsigned block_bytes, unsigned heads, unsi
 extern "C" unsigned tile_shift_of(unsigned row_shift, unsigned head_shift, unsigned token_shift) {
   return tutti::line_tile_shift(row_shift, head_shift, token_shift);
 }
+extern "C" int apart_of(unsigned copy_wgs, unsigned cus, unsigned n_req) {
+  return tutti::entries_apart(copy_wgs, cus, n_req);
+}
 extern "C" unsigned units_of(int ahead, unsigned block_bytes, unsigned blocks, unsigned budget, int ordered,
                              int short_rows) {
   return tutti::budget_units(ahead != 0, block_bytes, blocks, budget, ordered != 0, short_rows != 0);
@@ -121,3 +124,10 @@ def test_line_tiles_cover_the_block(rules):
     assert taken > 80
     assert not rules.tiles_of(128, 32768, 16, 0, 0) and not rules.tiles_of(64, 16384, 8, 32, 1)
     assert rules.tiles_of(64, 16384, 8, 32, 0) and rules.tiles_of(64, 16384, 16, 32, 1)
+
+
+def test_entries_apart_from_small_launches_only(rules):
+    for cus in (1, 8, 256):
+        for n_req, last in ((1, 2 * cus), (2, 5 * cus // 2), (64, 5 * cus // 2)):
+            assert rules.apart_of(1, cus, n_req) and rules.apart_of(last, cus, n_req)
+            assert not rules.apart_of(last + 1, cus, n_req) and not rules.apart_of(8 * cus, cus, n_req)
