@@ -100,15 +100,21 @@ constexpr bool hnd_through_lds(uint32_t row_bytes, uint32_t cu_budget) {
   return row_bytes < (cu_budget == 0 ? 128u : cu_budget > 16 ? 32u : 16u);
 }
 
-// Whether a head-major pool is moved as line tiles (row size, tokens and heads are powers of two): while a row is shorter
-// than a 128-byte line and the block a whole number of whole-GPU slices.  The other way for those is the object's order, in
+// Whether a head-major pool is moved as line tiles (row size, tokens and heads are powers of two).  While a row is shorter
+// than a 128-byte line and the block a whole number of whole-GPU slices they are: the other way is the object's order, in
 // which a piece of 1 KiB holds 1024 / heads bytes of every head: whole lines too for up to 8 heads, and its loads of a
 // restore need no offsets.  Us, object's order / line tiles, rows of 64 bytes, 8 heads, 16 KiB blocks: restore of 1536 on 32
 // units 57.3 / 59.3, of 256 on 8 22.4 / 22.9, of 4096 on the whole GPU 43.5 / 43.6; save of 1536 on 32 units 60.3 / 60.6, of
 // 512 21.5 / 20.9, of 384 on the whole GPU 5.5 / 5.3, of 64 in one request 3.6 / 3.4; 4 heads, rows of 16 bytes, 4 KiB blocks,
 // restore of 1536 on the whole GPU 6.5 / 6.2 (on 32 units of blocks of any size the same).
-constexpr bool as_line_tiles(uint32_t row_bytes, uint32_t block_bytes, uint32_t heads, uint32_t cu_budget, bool unpack) {
-  return row_bytes >= 16 && row_bytes < 128 && block_bytes >= 4096 &&
+// Rows of a line or more, up to 512 bytes, are whole lines in the object's order as well, but there each offset takes two
+// divisions: `half_empty`, whole-GPU launches with items for half of the chip's wavefronts at most, where that shows.  Rows of
+// 256 bytes, 8 heads: save of 16 blocks of 32 KiB 3.16 / 2.89, 64 3.71 / 3.53, 64 in 33 requests 4.22 / 4.04; restore 2.96 /
+// 2.89, 3.33 / 3.27, 4.38 / 4.33; beyond, save of 384 in 8 10.25 / 10.5, 2048 47.6 / 47.5, restore 9.0 / 8.9, 43.5 / 43.9.
+constexpr bool as_line_tiles(uint32_t row_bytes, uint32_t block_bytes, uint32_t heads, uint32_t cu_budget, bool unpack,
+                             bool half_empty) {
+  if (row_bytes >= 128) return cu_budget == 0 && half_empty && row_bytes <= 512 && block_bytes >= 4096;
+  return row_bytes >= 16 && block_bytes >= 4096 &&
          !(unpack && cu_budget != 0 && heads <= 8 && row_bytes > 16);
 }
 

@@ -309,7 +309,8 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   const uint32_t row = m->row_bytes, T = pool->block_tokens, h = pool->num_kv_heads;
   const bool powers = pool->pool_layout == TUTTI_LAYOUT_HND && is_pow2(row) && is_pow2(T) && is_pow2(h);
   // (more blocks than line tiles can number go through LDS, whose tiles are larger)
-  bool lines = powers && mode == 0 && as_line_tiles(row, block_bytes, h, cu_budget, unpack) &&
+  const bool half_empty = 4ull * table_len * counted_slices(*L, block_bytes) <= whole_gpu_waves(*L);
+  bool lines = powers && mode == 0 && as_line_tiles(row, block_bytes, h, cu_budget, unpack, half_empty) &&
                2ull * table_len * counted_slices(*L, block_bytes) <= 0xffffffffull;
   // where the rule for LDS holds the launch keeps staging order, whatever list of positions it is given
   L->keeps_order = false;

@@ -156,13 +156,18 @@ LINE_TILE_SHAPES = [
     (16, 16, 32, 2, 300, [110, 1, 7], 4096),
     (32, 4, 64, 1, 128, [50, 2], 16384),         # 8 KiB blocks in padded objects
     (64, 64, 16, 2, 40, [9, 12], 65536),          # 128 KiB blocks
+    (16, 8, 128, 2, 600, [200, 57], 4096),       # rows of 256 bytes: slices for one block more than half of the chip's
+    (16, 8, 128, 2, 600, [200, 56], 4096),       # wavefronts, and for just half
+    (4, 2, 256, 2, 90, [31, 0, 18], 4096),       # rows of 512 bytes, one slice
+    (1, 8, 256, 2, 90, [31, 0, 18], 8192),
+    (32, 1, 128, 1, 90, [31, 0, 18], 4096),
 ]
 
 
 @pytest.mark.parametrize("shape", LINE_TILE_SHAPES, ids=lambda s: f"T{s[0]}h{s[1]}row{s[2] * s[3]}")
 def test_head_major_line_tiles(orc, H, shape):
-    """Head-major blocks with rows below a line, whole GPU and budgets, one request and several, and a staging buffer that
-    ends inside a block that is read ahead."""
+    """Head-major blocks with rows below a line (and longer ones in small launches), whole GPU and budgets, one request and
+    several, and a staging buffer that ends inside a block that is read ahead."""
     T, h, d, e, N, nb, align = shape
     say("line tiles", shape)
     rng = np.random.default_rng(700 + T + h)

@@ -12,8 +12,8 @@ extern "C" unsigned pause_of(unsigned items, unsigned chip, unsigned n_req, int 
   return tutti::hold_back_pause(items, chip, n_req, file != 0);
 }
 extern "C" int lds_of(unsigned row, unsigned budget) { return tutti::hnd_through_lds(row, budget); }
-extern "C" int tiles_of(unsigned row, unsigned block_bytes, unsigned heads, unsigned budget, int unpack) {
-  return tutti::as_line_tiles(row, block_bytes, heads, budget, unpack != 0);
+extern "C" int tiles_of(unsigned row, unsigned block_bytes, unsigned heads, unsigned budget, int unpack, int half_empty) {
+  return tutti::as_line_tiles(row, block_bytes, heads, budget, unpack != 0, half_empty != 0);
 }
 extern "C" unsigned tile_shift_of(unsigned row_shift, unsigned head_shift, unsigned token_shift) {
   return tutti::line_tile_shift(row_shift, head_shift, token_shift);
@@ -97,10 +97,10 @@ def test_line_tiles_cover_the_block(rules):
     """Every shape that the rule takes: the tiles are whole, deal out every 16 bytes of the block once on both sides, and
     touch whole lines on both wherever tokens and heads are enough for it."""
     taken = 0
-    for rs in range(4, 7):
+    for rs in range(4, 10):
         for hs in range(0, 8):
             for ts in range(0, 9):
-                if not rules.tiles_of(1 << rs, 1 << (rs + hs + ts), 1 << hs, 0, 1):
+                if not rules.tiles_of(1 << rs, 1 << (rs + hs + ts), 1 << hs, 0, 1, 1):
                     assert rs + hs + ts < 12
                     continue
                 taken += 1
@@ -122,8 +122,9 @@ def test_line_tiles_cover_the_block(rules):
                         obj.add((((t << hs) + i) << rs) + 16 * w)
                 assert pool == obj == set(range(0, 1 << (rs + hs + ts), 16))
     assert taken > 80
-    assert not rules.tiles_of(128, 32768, 16, 0, 0) and not rules.tiles_of(64, 16384, 8, 32, 1)
-    assert rules.tiles_of(64, 16384, 8, 32, 0) and rules.tiles_of(64, 16384, 16, 32, 1)
+    assert not rules.tiles_of(128, 32768, 16, 0, 0, 0) and not rules.tiles_of(64, 16384, 8, 32, 1, 0)
+    assert not rules.tiles_of(1024, 32768, 16, 0, 0, 1) and not rules.tiles_of(256, 32768, 16, 8, 0, 1)
+    assert rules.tiles_of(64, 16384, 8, 32, 0, 0) and rules.tiles_of(64, 16384, 16, 32, 1, 0)
 
 
 def test_entries_apart_from_small_launches_only(rules):
