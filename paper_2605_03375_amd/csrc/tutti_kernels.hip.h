@@ -85,6 +85,9 @@ __device__ __forceinline__ void st16(unsigned char *p, u32x4 v) {
 // blk_off[r] is the number of blocks of the requests before r that the call moves: the copy loops number their
 // work items by it.  When the library computed the extents itself it is the table offset (same array); a copy
 // kernel that was handed extents keeps it in the sqe_base array, which it has no other use for.
+// The direct-to-block mode has no use for sqe_base and keeps `wraps` there: not 0 if the requests' blocks sum to 2^32 or
+// more.  table_off, which is not cut at the table's length in that mode, then starts again from 0 somewhere and is not in
+// order.
 // ------------------------------------------------------------------------------------------
 struct ReqLds {
   uint64_t *stage_off;
@@ -92,6 +95,8 @@ struct ReqLds {
   uint32_t *table_off;
   uint32_t *sqe_base;
   uint32_t *blk_off;
+  __device__ __forceinline__ uint32_t &wraps() const { return sqe_base[0]; }
+  bool unordered;  // the same, in a register: set behind the scan for more than 64 requests
 };
 
 __device__ __forceinline__ ReqLds carve_lds(unsigned char *smem, uint32_t n_req, bool caller_extents = false) {
@@ -101,6 +106,7 @@ __device__ __forceinline__ ReqLds carve_lds(unsigned char *smem, uint32_t n_req,
   l.table_off = reinterpret_cast<uint32_t *>(l.obj_bytes + n_req);
   l.sqe_base = l.table_off + n_req + 1;
   l.blk_off = caller_extents ? l.sqe_base : l.table_off;
+  l.unordered = false;
   return l;
 }
 
@@ -234,6 +240,7 @@ __device__ __forceinline__ void wave_scan_extents(const ScanGeom g, uint32_t n, 
     if (r + 1 == n_req) {
       l.table_off[n_req] = beyond_mask != 0 ? cut_total : static_cast<uint32_t>(inc_tab);
       l.sqe_base[n_req] = static_cast<uint32_t>(inc_sqe);
+      if (file_id) l.wraps() = inc_tab > 0xffffffffu ? 1u : 0u;
       if (totals_out) {
         totals_out[0] = inc_stage;
         totals_out[1] = inc_sqe;
@@ -341,7 +348,7 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
     if (EXACT) {
       const uint64_t n_chunks = obj_chunks(g, obj);
       const uint32_t sqe_base = static_cast<uint32_t>(2 * c);
-      l.sqe_base[r] = sqe_base;
+      if (!file_id) l.sqe_base[r] = sqe_base;
       if (ext_out) {
         tutti_extent e;
         e.stage_off = stage_off;
@@ -361,6 +368,7 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
     if (!cut) l.table_off[n_req] = static_cast<uint32_t>(t_all);
     if (EXACT) {
       l.sqe_base[n_req] = static_cast<uint32_t>(2 * c_all);
+      if (file_id) l.wraps() = t_all > 0xffffffffu ? 1u : 0u;
       if (totals_out) {
         totals_out[0] = 2 * (static_cast<uint64_t>(t_all) * g.block_bytes + p_all);
         totals_out[1] = 2 * c_all;
@@ -570,10 +578,29 @@ __device__ __forceinline__ uint32_t find_owner(const uint32_t *a, uint32_t n, ui
 // The same for a key that all lanes of the wavefront share (and all are active): every lane compares, a ballot counts.
 // One read of LDS for up to 64 requests (FEW: there are no more) and two for more, instead of 6 to 11 that wait for each
 // other.
-template <bool FEW>
-__device__ __forceinline__ uint32_t find_owner_of_wave(const uint32_t *a, uint32_t n, uint32_t key) {
+// For offsets that may be out of order (the direct-to-block mode's, ReqLds::wraps) it makes find_owner's choice: a position
+// may belong to several requests then, and the recorded contexts name that one.  Up to 64 requests need no flag for it: where
+// the lanes that compare true are the first ones, without a gap, there is one place only where a search can end, and where
+// they are not the same search runs over the ballot's bits.
+template <bool FEW, bool DIRECT>
+__device__ __forceinline__ uint32_t find_owner_of_wave(const ReqLds &l, const uint32_t *a, uint32_t n, uint32_t key) {
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  if (FEW) return static_cast<uint32_t>(__popcll(__ballot(lane < n && a[lane] <= key))) - 1;
+  if (FEW) {
+    const uint64_t below = __ballot(lane < n && a[lane] <= key);
+    if (DIRECT && __builtin_expect((below & (below + 1)) != 0, 0)) {
+      uint32_t lo = 0, hi = n;
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if ((below >> mid & 1) != 0)
+          lo = mid;
+        else
+          hi = mid;
+      }
+      return lo;
+    }
+    return static_cast<uint32_t>(__popcll(below)) - 1;
+  }
+  if (DIRECT && __builtin_expect(l.unordered, 0)) return find_owner(a, n, key);
   const uint32_t step = (n + kWave - 1) / kWave;  // at most TUTTI_MAX_REQ / 64
   uint32_t at = lane * step;
   const uint32_t first = (static_cast<uint32_t>(__popcll(__ballot(at < n && a[at] <= key))) - 1) * step;
@@ -1442,7 +1469,8 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
   uint32_t r, toff, end;
   uint64_t stage_off;
   const auto owner = [&](const uint32_t *of, uint32_t key) {
-    return OWNER == kPerLane ? find_owner(of, n_req, key) : find_owner_of_wave<OWNER == kOfFew>(of, n_req, key);
+    return OWNER == kPerLane ? find_owner(of, n_req, key)
+                             : find_owner_of_wave<OWNER == kOfFew, DIRECT>(l, of, n_req, key);
   };
   // all of a request's words are asked for together: they come out of LDS one behind the other, and a workgroup that has
   // one tile in flight waits for each (tiles of 16-byte rows on 8 compute units: 594 ns each with two waits, 550 with one)
@@ -1570,6 +1598,19 @@ __device__ __forceinline__ void hold_back(uint32_t pause) {
   for (uint32_t i = 0; i < pause; ++i) __builtin_amdgcn_s_sleep(8);
 }
 
+// Number of (block, kind) units of a copy.  Staged mode: the scan (or the loader of caller-made extents) has already cut
+// the requests at table_len blocks.  Direct-to-block mode: one unit per recorded context.  The host checked that
+// the bound (2 * table_len, or the contexts the IOCBs hold) times the slices per block fits 32 bits.
+template <bool SEP, int ORD = kStagingOrder, bool DIRECT = false>
+__device__ __forceinline__ uint32_t count_units(const MoveArgs &a, const ReqLds &l, uint32_t n_req) {
+  if (ORD != kStagingOrder) return 2u * a.table_len;  // every listed position, for K and for V
+  if (DIRECT) {
+    const uint64_t units = 2ull * rfl(l.table_off[n_req]);
+    return static_cast<uint32_t>(units < a.ctx_cap ? units : a.ctx_cap);
+  }
+  return 2u * rfl(SEP ? l.blk_off[n_req] : l.table_off[n_req]);
+}
+
 // First item of a wavefront in an unpack from dense staging: its source bytes do not depend on the extents,
 // so their loads can be in flight while the workgroup is still fetching or scanning the extents.  (Slices of up to 8 KiB:
 // 16 loads in flight need the registers, and such launches have many items a wavefront.)
@@ -1628,6 +1669,28 @@ __device__ __forceinline__ Preload<U> preload_pack(const MoveArgs &a, uint32_t w
   return p;
 }
 
+// The pack of a ring call whose offsets are out of order (ReqLds::wraps), instead of store_pack: table order is not the
+// contexts' order then.  A block at a time: such counts are a caller's mistake, and the code has to be small rather than fast
+// (as a second whole copy loop in the kernel it cost ordinary calls 0.2 us).
+__device__ __forceinline__ void pack_unordered(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t first_wave,
+                                               uint32_t n_waves) {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t units = count_units<false, kStagingOrder, true>(a, l, n_req);
+#pragma unroll 1
+  for (uint32_t u = first_wave; u < units; u += n_waves) {
+    const Item d = decode_unit<false, kStagingOrder, true, kPerLane>(a, l, n_req, u, 0, lane == 0);
+    const uint32_t id = load_block_id(a, d);
+    if (d.obj_ptr == nullptr) continue;
+    if (id < a.num_blocks) {
+      const unsigned char *blk = (d.kind ? a.v_base : a.k_base) + static_cast<uint64_t>(id) * a.block_stride;
+#pragma unroll 1
+      for (uint32_t o = lane * 16u; o < a.block_bytes; o += kPiece) st16<3>(d.obj_blk + o, ld16<3>(blk + o));
+    } else if (lane == 0 && a.status) {
+      atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
+    }
+  }
+}
+
 // What is left of it once the requests are known.
 template <int HND, int U, int NT, int WG, int REQS, bool DIRECT>
 __device__ __forceinline__ void store_pack(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t wg,
@@ -1663,19 +1726,6 @@ __device__ __forceinline__ void store_preloaded(const MoveArgs &a, const Item &d
 // grid may hold other workgroups with other work).
 // Software-pipelined by one item: the next item is decoded and its block id requested before the
 // current item's loads and stores are issued.
-// Number of (block, kind) units of a copy.  Staged mode: the scan (or the loader of caller-made extents) has already cut
-// the requests at table_len blocks.  Direct-to-block mode: one unit per recorded context.  The host checked that
-// the bound (2 * table_len, or the contexts the IOCBs hold) times the slices per block fits 32 bits.
-template <bool SEP, int ORD = kStagingOrder, bool DIRECT = false>
-__device__ __forceinline__ uint32_t count_units(const MoveArgs &a, const ReqLds &l, uint32_t n_req) {
-  if (ORD != kStagingOrder) return 2u * a.table_len;  // every listed position, for K and for V
-  if (DIRECT) {
-    const uint64_t units = 2ull * rfl(l.table_off[n_req]);
-    return static_cast<uint32_t>(units < a.ctx_cap ? units : a.ctx_cap);
-  }
-  return 2u * rfl(SEP ? l.blk_off[n_req] : l.table_off[n_req]);
-}
-
 template <int DIR, int HND, int U, int NT, int WG, int REQS, bool SEP, int ORD, bool DIRECT>
 __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                            uint32_t copy_wgs, const Preload<U> &pre) {
@@ -2244,7 +2294,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
     return;
   }
   const uint32_t bx = blockIdx.x - lead;
-  const ReqLds l = carve_lds(smem, a.n_req);
+  ReqLds l = carve_lds(smem, a.n_req);
   const bool copies = bx - w.copy_first < w.copy_wgs;
   Preload<U> pre;
   pre.valid = false;
@@ -2273,11 +2323,14 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
       });
   if (REQS == kFew && DIR == kUnpack && pre.valid)
     hold_back(hold_back_pause(count_units<false, kStagingOrder, true>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, 1, true));
+  if (any_number(REQS)) l.unordered = rfl(l.wraps()) != 0;
   DirectHead head;
   head.live = false;
   if (bx < w.sqe_wgs) head = iocb_head(g, q, d, l, a.n_req, lead, w.sqe_wgs);
   if (copies) {
-    if (reads_under_scan(REQS))
+    if (reads_under_scan(REQS) && __builtin_expect(rfl(l.wraps()) != 0, 0))
+      pack_unordered(m, l, a.n_req, (bx - w.copy_first) * (WG / kWave) + rfl(threadIdx.x / kWave), w.copy_wgs * (WG / kWave));
+    else if (reads_under_scan(REQS))
       store_pack<kNhd, U, 3, WG, REQS, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
     else if (PIECES)
       move_pieces<DIR, kNhd, U, 3, WG, false, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs);

@@ -1113,6 +1113,54 @@ def test_saves_that_read_ahead(orc, H, n_req, blocks, padding):
         H.check_ring_layer(orc, c, layer=1, write=True, depth=4, first_slot=2, n_slots=n_slots)
 
 
+@pytest.mark.parametrize("cu_budget", [0, 4])
+@pytest.mark.parametrize("write", [True, False], ids=["store", "retrieve"])
+@pytest.mark.parametrize("counts", [{0: 3, 1: 0xfffffffe, 2: 2}, {0: 3, 1: 0xfffffffe, 2: 4}, {0: 2, 33: 0xfffffffd, 63: 3},
+                                    {0: 3, 69: 0xfffffffe}, {0: 3, 1: 0xfffffffe, 69: 2}, {3: 5, 150: 0xfffffffc, 151: 4, 299: 1}],
+                         ids=str)
+def test_ring_call_with_offsets_that_wrap(H, counts, write, cu_budget):
+    """Counts whose sum passes 2^32: the table offsets start again from 0, so that a position has several requests to belong
+    to.  The copy takes the one that the recorded contexts name: executing them gives the same file store and planes."""
+    n_req = max(counts) + 1
+    say("ring wraps", counts, write, cu_budget)
+    n = np.zeros(n_req, np.uint32)
+    for r, x in counts.items():
+        n[r] = x
+    bb, N, L, n_slots, addr = 4096, 40, 2, 1, 0x7f00_0000_1000
+    c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=np.zeros(n_req, np.uint32), table=np.random.default_rng(5).permutation(N)[:16],
+                    L=L, chunk=4096, name="ring_wraps")
+    c.d_n_blocks = torch.from_numpy(n.view(np.int32)).to(H.DEV)
+    stride = 2 * L * 5 * bb
+    store = torch.randint(0, 256, (n_req * stride,), dtype=torch.uint8, device=H.DEV)
+    if not write:                  # every request's file holds the same: two writers of one block write the same bytes
+        store.view(n_req, -1, bb)[:] = torch.randint(0, 256, (bb,), dtype=torch.uint8, device=H.DEV)
+    results = []
+    sq_bytes, cq_bytes = B.ring_bytes(n_slots)
+    sq = torch.zeros(sq_bytes, dtype=torch.uint8, device=H.DEV)
+    cq = torch.zeros(cq_bytes, dtype=torch.uint8, device=H.DEV)
+    ring = B.make_ring(sq, cq, n_slots)
+    B.tutti_ring_init(ring)
+    ext = torch.zeros(32 * n_req, dtype=torch.uint8, device=H.DEV)
+    tot = torch.zeros(2, dtype=torch.int64, device=H.DEV)
+    for from_contexts in (False, True):
+        k2, v2, files, st = c.k_dev.clone(), c.v_dev.clone(), store.clone(), H.new_status()
+        pool, fs = c.gpu_pool(k2, v2), B.make_filestore(files, stride, 1000, n_req)
+        if from_contexts:
+            sgl = torch.zeros(2 * N * 16, dtype=torch.uint8, device=H.DEV)
+            B.tutti_sgl_table_build(pool, k2.data_ptr(), v2.data_ptr(), 5, sgl, 2 * N, st)
+            B.tutti_issue_io(ring, 0, n_slots, sgl, 2 * N, addr, fs, bb, cu_budget, st)
+        else:
+            issue = B.tutti_store_layer_issue if write else B.tutti_retrieve_layer_issue
+            issue(ring, 0, n_slots, pool, c.gpu_cfg(), c.d_n_blocks, n_req, c.d_table, 16, c.d_file_id, 1, addr, 5, fs, ext, tot,
+                  cu_budget, st)
+        torch.cuda.synchronize()
+        results.append((k2, v2, files))
+    header = sq[:64].cpu().numpy().view(np.uint32)
+    assert header[1] == 2 * (int(n.sum(dtype=np.uint64)) % (1 << 32)) > 0
+    assert not all(torch.equal(x, y) for x, y in zip(results[0], (c.k_dev, c.v_dev, store)))
+    assert all(torch.equal(x, y) for x, y in zip(*results))
+
+
 def test_scan_of_many_requests_wide_sums(orc, H):
     """Alignment units above 1 MiB (the padding is then summed in 64 bits), and block counts whose sum passes 2^32:
     the requests in front of the one that runs beyond the table are restored, the published extents are plain sums."""
