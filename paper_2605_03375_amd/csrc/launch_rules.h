@@ -87,6 +87,13 @@ constexpr bool entries_apart(uint32_t copy_wgs, uint32_t cus, uint32_t n_req) {
   return 2 * copy_wgs <= (n_req == 1 ? 4 : 5) * cus;
 }
 
+// Items (slices of the table's blocks) up to which a save of several requests reads them all without a look at the requests'
+// counts (PackItem).  What lies behind the requests' blocks in the table is then read for nothing: with all of it, a quarter of
+// the chip's wavefronts (128 blocks of 32 KiB, 8 MiB) is the most at which that costs no more than it gains.  Graph replay, us,
+// 2 blocks in 2 requests with a table of 96 / 128 / 160 / 200: in staging order 3.6 / 3.6 / 3.8 / 3.8, read at once 3.2 / 3.4 /
+// 3.9 / 4.8, counted first 3.1 / 3.3 / 3.1 / 3.6.
+constexpr uint32_t pack_at_once(uint32_t chip_waves) { return chip_waves / 4; }
+
 // Whether a head-major pool goes through LDS tiles or is moved directly, where it is not moved as line tiles
 // (as_line_tiles).  On the whole GPU it pays while a row is shorter than a 128-byte line.  Under a CU budget a workgroup has one tile in flight at a time, and only rows of 16 bytes on
 // more than 16 compute units are worth that.  Through LDS / direct, us, save and restore of 16 KiB blocks:

@@ -559,15 +559,22 @@ hipError_t launch_layer(const Launch &L, uint64_t entry_quarters, uint32_t lds, 
       }
       if constexpr (S::WG == kWgThreads) {
         if (scan_reads<DIR>(L, m, a.n_req, move_wave_items(L, m))) {
+          [[maybe_unused]] const bool count_first = move_wave_items(L, m) > pack_at_once(m.chip_waves);
           if (a.n_req <= kWave) {
             if constexpr (DIR == kPack) {
               separate_entries(L, a.n_req, 0, &w, &n_wgs);
+              if (count_first)
+                return launch_layer_shape<S, DIR, HND, kFewCounted>(false, n_wgs, lds, s, m, q, a, w);
               return launch_layer_shape<S, DIR, HND, kFewAhead>(false, n_wgs, lds, s, m, q, a, w);
             }
           } else if (L.grid + w.sqe_wgs <= whole_gpu_wgs(L) && a.geom.align <= (1u << 20)) {
             // the entry writers' scan is the longer one and reads nothing ahead: workgroups of their own
             // (as they are: rounded up to eight, 150 blocks in 150 requests restore in 5.9 us instead of 5.3)
             w.copy_first = w.sqe_wgs;
+            if constexpr (DIR == kPack) {
+              if (count_first)
+                return launch_layer_shape<S, DIR, HND, kManyCounted>(false, L.grid + w.sqe_wgs, lds, s, m, q, a, w);
+            }
             return launch_layer_shape<S, DIR, HND, kManyAhead>(false, L.grid + w.sqe_wgs, lds, s, m, q, a, w);
           }
         }
@@ -1068,6 +1075,8 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
       if (one || ahead || few_requests(R, m, n_req)) separate_entries(R, n_req, lead, &w, &n_wgs);
       if (one) return launch_ring_shape<S, DIR, kOne>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
       if constexpr (DIR == kPack && S::WG == kWgThreads) {
+        if (ahead && move_wave_items(R, m) > pack_at_once(m.chip_waves))
+          return launch_ring_shape<S, DIR, kFewCounted>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
         if (ahead) return launch_ring_shape<S, DIR, kFewAhead>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
       }
       if (few_requests(R, m, n_req)) return launch_ring_shape<S, DIR, kFew>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
@@ -1768,8 +1777,10 @@ void least_resident_layer(int *worst) {
   least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany>,
                  k_layer<DIR, HND, 4, 3, kWgThreads, kMany, false, true>);
   if constexpr (DIR == kUnpack) least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, true>);
-  if constexpr (DIR == kPack) least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFewAhead>);
+  if constexpr (DIR == kPack)
+    least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFewAhead>, k_layer<DIR, HND, 4, 3, kWgThreads, kFewCounted>);
   least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kManyAhead>);
+  if constexpr (DIR == kPack) least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kManyCounted>);
 }
 
 template <int DIR>
@@ -1778,7 +1789,8 @@ void least_resident_ring(int *worst) {
   least_resident(worst, few, k_layer_ring<DIR, 4, kWgThreads, kOne>, k_layer_ring<DIR, 4, kWgThreads, kFew>,
                  k_layer_ring<DIR, 4, kWgThreads, kFew, true>);
   least_resident(worst, many, k_layer_ring<DIR, 4, kWgThreads, kMany>, k_layer_ring<DIR, 4, kWgThreads, kMany, true>);
-  if constexpr (DIR == kPack) least_resident(worst, few, k_layer_ring<DIR, 4, kWgThreads, kFewAhead>);
+  if constexpr (DIR == kPack)
+    least_resident(worst, few, k_layer_ring<DIR, 4, kWgThreads, kFewAhead>, k_layer_ring<DIR, 4, kWgThreads, kFewCounted>);
 }
 
 template <int DIR>

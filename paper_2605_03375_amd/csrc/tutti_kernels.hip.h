@@ -44,9 +44,11 @@ constexpr int min_waves_per_simd(int wg_threads, int units) { return (wg_threads
 
 // Requests a kernel is for: one, up to 64, any number; ...Ahead: several whose slices are read behind the loads of the counts,
 // under the scan (a pack's by preload_pack).
-constexpr int kOne = 1, kFew = 2, kMany = 3, kFewAhead = 4, kManyAhead = 5;
-constexpr bool reads_under_scan(int reqs) { return reqs == kFewAhead || reqs == kManyAhead; }
-constexpr bool any_number(int reqs) { return reqs == kMany || reqs == kManyAhead; }
+// ...Counted: a pack whose slices are read when the counts have been summed.
+constexpr int kOne = 1, kFew = 2, kMany = 3, kFewAhead = 4, kManyAhead = 5, kFewCounted = 6, kManyCounted = 7;
+constexpr bool counts_first(int reqs) { return reqs == kFewCounted || reqs == kManyCounted; }
+constexpr bool reads_under_scan(int reqs) { return reqs == kFewAhead || reqs == kManyAhead || counts_first(reqs); }
+constexpr bool any_number(int reqs) { return reqs == kMany || reqs == kManyAhead || reqs == kManyCounted; }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -152,6 +154,12 @@ __device__ __forceinline__ S wave_scan(S v, uint32_t active = kWave) {
   if (active <= 32) return v;
   v = add_<SAT>(v, dpp_or_0<0x143, 0xc>(v));  // row_bcast:31 into rows 2 and 3
   return v;
+}
+
+// The wavefront's sum of a count per lane (0 in the lanes from n_req on), 2^32 - 1 if it is that or more.
+__device__ __forceinline__ uint32_t sum_of_counts(uint32_t n, uint32_t n_req) {
+  const uint32_t sums = wave_scan<true>(n, n_req);
+  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(sums), static_cast<int>(n_req - 1)));
 }
 
 // The file store of the direct-to-block mode: file f at base + (f - first_file_id)*file_stride.
@@ -264,12 +272,14 @@ __device__ __forceinline__ void wave_scan_extents(const ScanGeom g, uint32_t n, 
 // within table_len, and the host keeps 2 * table_len within 32 bits.  The others (the entry writers and the publishing
 // workgroup; align > 1 MiB, where the padding of 2048 requests may need more bits; the direct-to-block mode, whose
 // offsets wrap) carry 64-bit sums and the chunks.
-template <int WG, bool EXACT, bool SAT, typename P>
+// KEEP: the counts stay in LDS (in sqe_base, which such a workgroup has no use for) instead of being read again, because the
+// bytes that `counted` requests are on their way by then, and loads arrive in order.
+template <int WG, bool EXACT, bool SAT, bool KEEP, typename P, typename C>
 __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t *__restrict__ n_blocks, uint32_t n_req,
                                                 ReqLds l, tutti_extent *__restrict__ ext_out,
                                                 uint64_t *__restrict__ totals_out, uint32_t table_len,
                                                 uint32_t *__restrict__ status, const uint32_t *__restrict__ file_id,
-                                                const FileArgs files, P under_loads) {
+                                                const FileArgs files, P preload, C counted) {
   typedef typename std::conditional<EXACT, uint64_t, uint32_t>::type S;
   constexpr uint32_t kPer = TUTTI_MAX_REQ / WG, kWaves = WG / kWave;
   static_assert(3 * kWaves <= kWave, "the wavefronts' totals fit the staging-offset slots of 65 requests");
@@ -281,11 +291,14 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
                        // keeps these registers free for the bytes that a restore has in flight meanwhile
 #pragma unroll
     for (uint32_t k = 0; k < kPer; ++k) n[k] = (k < per && r0 + k < n_req) ? n_blocks[r0 + k] : 0u;
-    under_loads();
+    __builtin_amdgcn_sched_barrier(0);
+    preload();
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (uint32_t k = 0; k < kPer; ++k) {
       blocks = add_<SAT>(blocks, static_cast<S>(n[k]));
       pads += obj_pad(g, n[k]);
+      if (KEEP && k < per && r0 + k < n_req) l.sqe_base[r0 + k] = n[k];
     }
   }
   if (EXACT) {
@@ -321,6 +334,7 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
       c += pc;
     }
   }
+  if (KEEP) counted(static_cast<uint32_t>(t_all));
   __syncthreads();
   const bool cut = !file_id && t_all > table_len;  // the same in every thread
   uint32_t cut_total = 0;
@@ -328,7 +342,7 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
     S x = t;
 #pragma unroll 1
     for (uint32_t k = 0; k < per && r0 + k < n_req; ++k) {  // exactly one request starts within the table and ends beyond it
-      const S next = add_<SAT>(x, static_cast<S>(n_blocks[r0 + k]));
+      const S next = add_<SAT>(x, static_cast<S>(KEEP ? l.sqe_base[r0 + k] : n_blocks[r0 + k]));
       if (x <= table_len && next > table_len) l.table_off[n_req] = static_cast<uint32_t>(x);
       x = next;
     }
@@ -337,7 +351,7 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
   }
 #pragma unroll 1
   for (uint32_t k = 0; k < per && r0 + k < n_req; ++k) {
-    const uint32_t r = r0 + k, n = n_blocks[r];
+    const uint32_t r = r0 + k, n = KEEP ? l.sqe_base[r] : n_blocks[r];
     const uint32_t pad = obj_pad(g, n);
     const uint64_t obj = static_cast<uint64_t>(n) * g.block_bytes + pad;
     const uint64_t stage_off = 2 * (static_cast<uint64_t>(t) * g.block_bytes + p);
@@ -386,35 +400,43 @@ __device__ __forceinline__ void wg_scan_extents(const ScanGeom g, const uint32_t
 // REQS = kFew: the host knows of at most 64 requests.  A kernel of its own, because the other scans' arguments push the
 // scalar registers over their limit, and the kernel then starts with more rounds of argument loads and spills (what that
 // gives stands at few_requests).
-template <int WG, int REQS, typename P>
+// Kernels that read under the scan: `preload` is called behind the loads of the counts, so that the scan need not wait for it,
+// and, where they count first, `counted` with the requests' blocks (2^32 - 1 if there are more) once they are summed.  In the
+// 64-bit scan neither is called.
+template <int WG, int REQS, typename P, typename C>
 __device__ __forceinline__ void scan_extents(const ScanGeom g, const uint32_t *__restrict__ n_blocks, uint32_t n_req,
                                              ReqLds l, tutti_extent *__restrict__ ext_out,
                                              uint64_t *__restrict__ totals_out, uint32_t table_len,
                                              uint32_t *__restrict__ status, bool with_chunks,
-                                             const uint32_t *__restrict__ file_id, const FileArgs files, P preload) {
-  const auto under_loads = [&] {  // a pack's: behind the loads of the counts, so that the scan need not wait for it
+                                             const uint32_t *__restrict__ file_id, const FileArgs files, P preload,
+                                             C counted) {
+  if (REQS == kFew || REQS == kFewAhead || REQS == kFewCounted || (REQS == kMany && n_req <= kWave)) {
+    if (!reads_under_scan(REQS)) preload();
+    uint32_t n = 0, fid = 0;
+    // (to sum the counts every wavefront needs them, the same few words as the one before it: the cache has them)
+    const uint32_t r = REQS == kFewCounted ? threadIdx.x & (kWave - 1) : threadIdx.x;
+    if (r < n_req) {
+      n = n_blocks[r];
+      if (file_id) fid = file_id[r];
+    }
     if (reads_under_scan(REQS)) {
       __builtin_amdgcn_sched_barrier(0);
       preload();
       __builtin_amdgcn_sched_barrier(0);
     }
-  };
-  if (REQS == kFew || REQS == kFewAhead || (REQS == kMany && n_req <= kWave)) {
-    if (!reads_under_scan(REQS)) preload();
-    uint32_t n = 0, fid = 0;
-    if (threadIdx.x < n_req) {
-      n = n_blocks[threadIdx.x];
-      if (file_id) fid = file_id[threadIdx.x];
-    }
-    under_loads();
+    if (counts_first(REQS)) counted(sum_of_counts(n, n_req));
     if (threadIdx.x < kWave)
       wave_scan_extents(g, n, fid, n_req, threadIdx.x, l, ext_out, totals_out, table_len, status, with_chunks, file_id,
                         files);
   } else if (with_chunks || file_id || g.align > (1u << 20)) {
-    wg_scan_extents<WG, true, false>(g, n_blocks, n_req, l, ext_out, totals_out, table_len, status, file_id, files, [] {});
+    wg_scan_extents<WG, true, false, false>(g, n_blocks, n_req, l, ext_out, totals_out, table_len, status, file_id, files,
+                                           [] {}, [](uint32_t) {});
   } else {
-    wg_scan_extents<WG, false, true>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, nullptr, files,
-                                     under_loads);
+    wg_scan_extents<WG, false, true, counts_first(REQS)>(g, n_blocks, n_req, l, nullptr, nullptr, table_len, status, nullptr, files,
+                                           [&] {
+                                             if (reads_under_scan(REQS)) preload();
+                                           },
+                                           counted);
     if (!reads_under_scan(REQS)) preload();
   }
   __syncthreads();
@@ -1450,14 +1472,14 @@ struct Item {
 // SEP: the extents came from the caller (lds_from_caller_extents): items are numbered by blk_off, the table is
 // indexed by the request's own table_off, and requests that cannot be honoured already have a zero-sized object.
 // ORD: the units in staging order, or all K blocks and then all V blocks, each in the order that a.visit lists or in the
-// table's own;
+// table's own, or the K and the V block of every table position in turn;
 // a listed position that is not a block of a request that takes part is passed over.
 // u: (block, kind) unit in staging order; s: its slice, piece or tile; `report`: this thread reports what it finds out
 // of order with a unit's first part.
 // OWNER: how the request is found; kPerLane: the lanes ask for units of their own, kOfFew and kOfMany: all for the same
 // one, of at most 64 requests or of any number.
 constexpr int kPerLane = 0, kOfFew = 1, kOfMany = 2;
-constexpr int kStagingOrder = 0, kListOrder = 1, kTableOrder = 2;
+constexpr int kStagingOrder = 0, kListOrder = 1, kTableOrder = 2, kPairOrder = 3;
 
 template <bool SEP, int ORD, bool DIRECT, int OWNER>
 __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t u, uint32_t s,
@@ -1482,8 +1504,8 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
     __builtin_amdgcn_sched_barrier(0);
   };
   if (ORD != kStagingOrder) {
-    d.kind = u >= a.table_len ? 1u : 0u;
-    uint32_t pos = u - d.kind * a.table_len;
+    d.kind = ORD == kPairOrder ? u & 1u : u >= a.table_len ? 1u : 0u;
+    uint32_t pos = ORD == kPairOrder ? u >> 1 : u - d.kind * a.table_len;
     if (ORD == kListOrder) pos = as_const(a.visit)[rfl(pos)];  // wave-uniform index: one scalar load
     if (pos >= l.table_off[n_req]) {  // beyond the blocks of the requests that take part
       d.obj_ptr = nullptr;
@@ -1511,7 +1533,7 @@ __device__ __forceinline__ Item decode_unit(const MoveArgs &a, const ReqLds &l, 
     const uint64_t end = file_off + a.block_bytes;
     d.obj_ptr = a.stage;
     d.obj_blk = a.stage + stage_off + file_off;
-    const uint32_t ctx = ORD == kTableOrder ? 2u * toff + d.kind * d.n + d.j : u;  // the unit's place in staging order
+    const uint32_t ctx = ORD != kStagingOrder ? 2u * toff + d.kind * d.n + d.j : u;  // the unit's place in staging order
     if (ctx >= a.ctx_cap) {
       d.obj_ptr = nullptr;  // beyond the IOCBs the caller gave: not recorded, not executed
     } else if (stage_off == kNoFile || end > a.file_stride || end < file_off) {
@@ -1640,32 +1662,50 @@ __device__ __forceinline__ Preload<U> preload_first(const MoveArgs &a, uint32_t 
   return p;
 }
 
-// A pack in table order (reads_under_scan): the launch gives every wavefront one item at most, so the order does not matter to the
-// memory, and where an item's bytes sit follows from the table alone: they are read while the requests are being scanned,
-// instead of behind the scan, the owner and the block id: small saves are bound by that chain of dependent loads.  Cold,
-// us, in staging order / so: 32 KiB blocks, 64 in 30 requests 4.7 / 3.8, 128 in 128 7.1 / 5.4, 300 in 3 9.8 / 8.6; 1280 blocks
-// of 8 KiB in 512 requests (42 MB of traffic) 10.7 / 9.6.  With several items a wavefront, reading all K blocks first loses
-// (1000 blocks in 8 requests 24.3 / 25.5), and a table longer than the requests is read for nothing: 64 blocks with a table
-// of 380 3.96 / 4.29, of 1000 4.2 / 5.0, of 8000 4.0 / 6.1; at 3/4 of the chip both are still small.
-template <int HND, int U, int NT, int WG>
-__device__ __forceinline__ Preload<U> preload_pack(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs) {
+// A pack in table order (reads_under_scan): the launch gives every wavefront one item at most, so the order does not matter to
+// the memory, and where an item's bytes sit follows from the table alone: they are read while the requests are being scanned,
+// instead of behind the scan, the owner and the block id: small saves are bound by that chain of dependent loads.  In a table
+// longer than the requests' blocks some are read for nothing; tables of more than pack_at_once items are therefore read when the
+// sum of the counts has said that the position is one of the requests' (and K and V of a position side by side: what there is
+// to do then lies in the first workgroups).  The item's block id is asked for behind the counts: in front of them saves of 72
+// to 150 blocks took 0.3 us longer.
+// Graph replay, 32 KiB blocks, us, in staging order / read at once whatever the table's length / so: 64 blocks in 30 requests
+// 5.4 / 3.8 / 3.8, with a table of 384 blocks 5.2 / 6.7 / 4.5; 150 in 8 6.2 / 5.1 / 5.1, table of 384 6.6 / 8.1 / 5.9; 2 in 2, table of
+// 384 3.7 / 6.1 / 3.7; 128 in 128 6.9 / 5.4 / 5.4, table of 384 6.8 / 8.0 / 6.1; 300 in 200 10.4 / 8.0 / 9.1; 1280 of 8 KiB in 512
+// 11.0 / 9.5 / 10.4.  (Of more than 64 requests, the first quarter of the chip's items read at once and the others counted: waits
+// on both in one kernel made the short tables 0.3 us slower.)  With several items a wavefront, reading all K blocks first
+// loses (1000 blocks in 8 requests 24.3 / 25.5).
+constexpr int pack_order(int reqs) { return counts_first(reqs) ? kPairOrder : kTableOrder; }
+
+template <int U, int WG, int REQS>
+struct PackItem {
+  uint32_t kind, pos, part;  // pos: in the table
+  uint32_t id;               // num_blocks: no such item
+  PackItem() = default;
+  __device__ __forceinline__ PackItem(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs)
+      : kind(0), pos(0), part(0), id(a.num_blocks) {
+    const uint32_t it = first_item<WG, U>(a, wg, copy_wgs);
+    if (wg < copy_wgs && it < a.items_bound) {
+      const uint32_t u = it / a.slices_per_block;
+      part = it - u * a.slices_per_block;
+      kind = pack_order(REQS) == kPairOrder ? u & 1u : u >= a.table_len ? 1u : 0u;
+      pos = pack_order(REQS) == kPairOrder ? u >> 1 : u - kind * a.table_len;
+      id = as_const(a.table)[pos];
+    }
+  }
+};
+
+template <int HND, int U, int NT, int WG, int REQS>
+__device__ __forceinline__ Preload<U> preload_pack(const MoveArgs &a, const PackItem<U, WG, REQS> &f) {
   constexpr uint32_t kSlice = kWave * 16u * U;
   const uint32_t lane = threadIdx.x & (kWave - 1);
-  const uint32_t it = first_item<WG, U>(a, wg, copy_wgs);
-  uint32_t kind = 0, part = 0, id = a.num_blocks;
-  if (wg < copy_wgs && it < a.items_bound) {
-    const uint32_t u = it / a.slices_per_block;
-    part = it - u * a.slices_per_block;
-    kind = u >= a.table_len ? 1u : 0u;
-    id = as_const(a.table)[u - kind * a.table_len];
-  }
   Preload<U> p;
-  p.valid = id < a.num_blocks;
-  // every path issues the loads (of some block for want of another, not the same one from all XCDs): the scanning wavefront's
-  // wait for the counts, asked for in front of them, would otherwise be one for both
+  p.valid = f.id < a.num_blocks;
+  // every path issues the loads (of some block for want of another, not the same one from all XCDs): the wait for the counts,
+  // asked for in front of them, would otherwise be one for both
   const uint32_t spare = blockIdx.x < a.num_blocks ? blockIdx.x : 0u;
-  p.src = (kind ? a.v_base : a.k_base) + static_cast<uint64_t>(p.valid ? id : spare) * a.block_stride;
-  load_slice<pool_side(HND), U, NT>(a, p.src, part * kSlice + lane * 16u, p.buf);
+  p.src = (f.kind ? a.v_base : a.k_base) + static_cast<uint64_t>(p.valid ? f.id : spare) * a.block_stride;
+  load_slice<pool_side(HND), U, NT>(a, p.src, f.part * kSlice + lane * 16u, p.buf);
   return p;
 }
 
@@ -1699,7 +1739,7 @@ __device__ __forceinline__ void store_pack(const MoveArgs &a, const ReqLds &l, u
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t it = first_item<WG, U>(a, wg, copy_wgs);
   if (it >= a.items_bound) return;
-  const Item d = decode_item<false, REQS, kTableOrder, DIRECT>(a, l, n_req, it, lane);
+  const Item d = decode_item<false, REQS, pack_order(REQS), DIRECT>(a, l, n_req, it, lane);
   if (d.obj_ptr == nullptr) return;
   if (pre.valid)
     store_slice<obj_side(HND), U, NT>(a, d.obj_blk, d.s * kSlice + lane * 16u, pre.buf);
@@ -2104,7 +2144,7 @@ __global__ __launch_bounds__(kWgThreads) void k_layout(const LayoutArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, a.n_req);
   scan_extents<kWgThreads, kMany>(a.geom, a.n_blocks, a.n_req, l, a.extents, a.totals, 0xffffffffu, nullptr, true, nullptr,
-                           FileArgs{0, 0, 0}, [] {});
+                           FileArgs{0, 0, 0}, [] {}, [](uint32_t) {});
 }
 
 template <int WG>
@@ -2195,13 +2235,19 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     return;
   }
   if (reads_under_scan(REQS)) args_at_hand(m, a, w);
+  PackItem<U, WG, REQS> first;
   scan_extents<WG, REQS>(
       a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr, m.table_len, m.status,
       blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [&] {
-        if (DIR == kPack && reads_under_scan(REQS))
-          pre = preload_pack<HND, U, NT, WG>(m, wg, w.copy_wgs);
-        else if (DIR == kUnpack && !ORD && !PIECES && reads_ahead(U) && copies)
+        if (DIR == kPack && reads_under_scan(REQS)) {
+          first = PackItem<U, WG, REQS>(m, wg, w.copy_wgs);
+          if (!counts_first(REQS)) pre = preload_pack<HND, U, NT>(m, first);
+        } else if (DIR == kUnpack && !ORD && !PIECES && reads_ahead(U) && copies) {
           pre = preload_first<HND, U, NT, WG>(m, wg, w.copy_wgs);
+        }
+      },
+      [&](uint32_t blocks) {
+        if (DIR == kPack && first.pos < blocks) pre = preload_pack<HND, U, NT>(m, first);
       });
   if (REQS == kFew && DIR == kUnpack && pre.valid)
     hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, pause_requests(a.n_req),
@@ -2313,13 +2359,19 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
   }
   // chunk counts only matter for the published extents; the LDS copy gets file starts instead of staging offsets
   if (reads_under_scan(REQS)) args_at_hand(m, a, w);
+  PackItem<U, WG, REQS> first;
   scan_extents<WG, REQS>(
       a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr, 0xffffffffu, nullptr,
       publish, q.file_id, f, [&] {
-        if (reads_under_scan(REQS))
-          pre = preload_pack<kNhd, U, 3, WG>(m, bx - w.copy_first, w.copy_wgs);
-        else if (DIR == kUnpack && !PIECES && reads_ahead(U) && copies && a.n_req == 1)
+        if (DIR == kPack && reads_under_scan(REQS)) {
+          first = PackItem<U, WG, REQS>(m, bx - w.copy_first, w.copy_wgs);
+          if (!counts_first(REQS)) pre = preload_pack<kNhd, U, 3>(m, first);
+        } else if (DIR == kUnpack && !PIECES && reads_ahead(U) && copies && a.n_req == 1) {
           pre = preload_first_direct<U, WG>(m, a.n_blocks, q.file_id, f, bx - w.copy_first, w.copy_wgs);
+        }
+      },
+      [&](uint32_t blocks) {
+        if (DIR == kPack && first.pos < blocks) pre = preload_pack<kNhd, U, 3>(m, first);
       });
   if (REQS == kFew && DIR == kUnpack && pre.valid)
     hold_back(hold_back_pause(count_units<false, kStagingOrder, true>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, 1, true));
@@ -2346,7 +2398,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, PT)) void k_layer_lds(co
   const ReqLds l = carve_lds(smem, a.n_req);
   const bool publish = blockIdx.x == 0;  // also an entry-writing workgroup: there is at least one
   scan_extents<WG, REQS>(a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr,
-                   m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [] {});
+                   m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [] {}, [](uint32_t) {});
   SqeHead head;
   head.live = false;
   if (blockIdx.x < w.sqe_wgs) head = sqe_head(q, l, a.n_req, 0);

@@ -1113,12 +1113,75 @@ def test_saves_that_read_ahead(orc, H, n_req, blocks, padding):
         H.check_ring_layer(orc, c, layer=1, write=True, depth=4, first_slot=2, n_slots=n_slots)
 
 
+@pytest.mark.parametrize("n_req", [2, 33, 64, 65, 300])
+@pytest.mark.parametrize("blocks,padding", [(1024, 0), (1025, 0), (1024, 600), (1500, 1000), (3072, 2700)])
+def test_saves_with_tables_longer_than_the_requests(orc, H, n_req, blocks, padding):
+    """Both sides of the table's length (a quarter of the chip's 8192 wavefronts, 1024 blocks of one slice) from which a save of
+    several requests counts their blocks before it reads: ids out of range in front of and behind the last request's blocks,
+    tables that are cut, padded objects, requests without blocks; through the rings also too few IOCBs."""
+    say("save counted", n_req, blocks, padding)
+    rng = np.random.default_rng(8850 + n_req + blocks)
+    n = np.bincount(rng.integers(n_req // 3, n_req, size=blocks - padding), minlength=n_req).astype(np.uint32)
+    N = blocks + 5
+    table = rng.permutation(N)[:blocks].astype(np.uint32)
+    table[[7, blocks - padding - 1, blocks - 1]] = (N, 0xffffffff, N)
+    for layout, align in ((0, 4096), (1, 8192)):
+        c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=n, table=table, align=align, chunk=16384, L=2, layout=layout,
+                        name=f"counted{n_req}b{blocks}p{padding}l{layout}")
+        H.check_layer_save(orc, c, layer=1)
+        H.check_layer_save(orc, c, layer=1, table_len=blocks - padding - 1)
+        H.check_layer_save(orc, c, layer=1, stage_cap=8192 * ((blocks - padding) // 2))
+    c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=n, table=table, align=4096, chunk=16384, L=2)
+    for n_slots in (1, 4):
+        H.check_ring_layer(orc, c, layer=1, write=True, depth=4, first_slot=2, n_slots=n_slots)
+
+
+def test_a_long_table_is_not_read_for_nothing(H):
+    """A save of a few blocks takes about as long with a table of 384 entries as with its own: reading all that the table names
+    (24 MiB, other blocks each time) would nearly double it."""
+    say("save long table")
+    n_calls, N = 16, 16 * 384
+    n = torch.tensor([2, 3, 1, 2], dtype=torch.int32, device=H.DEV)
+    fid = torch.arange(4, dtype=torch.int32, device=H.DEV)
+    tables = torch.from_numpy(np.random.default_rng(77).permutation(N).astype(np.int32)).to(H.DEV).view(n_calls, 384)
+    k, v = (torch.zeros(N << 15, dtype=torch.uint8, device=H.DEV) for _ in range(2))
+    pool = B.make_pool(k, v, num_blocks=N, block_tokens=16, num_kv_heads=8, head_dim=128, elt_bytes=2)
+    cfg = B.make_cfg(4096, 1 << 20, 1)
+    stage = torch.zeros(2 * 8 << 15, dtype=torch.uint8, device=H.DEV)
+    ext = torch.zeros(32 * 4, dtype=torch.uint8, device=H.DEV)
+    tot = torch.zeros(2, dtype=torch.int64, device=H.DEV)
+    sqe = torch.zeros(64 * 8, dtype=torch.uint8, device=H.DEV)
+    st = H.new_status()
+    graphs, times = {}, {8: [], 384: []}
+    for length in times:
+        def train():
+            for t in tables:
+                B.tutti_layer_save(pool, cfg, n, 4, t, length, fid, 0, stage, stage.numel(), 0, 1, ext, tot, sqe, 8, 0, st)
+        train()
+        torch.cuda.synchronize()
+        graphs[length] = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graphs[length]):
+            train()
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for _ in range(9):
+        for length, g in graphs.items():
+            g.replay()
+            a.record()
+            g.replay()
+            b.record()
+            torch.cuda.synchronize()
+            times[length].append(a.elapsed_time(b))
+    assert int(st.item()) == 0
+    assert np.median(times[384]) < 1.5 * np.median(times[8]), times
+
+
 @pytest.mark.parametrize("cu_budget", [0, 4])
 @pytest.mark.parametrize("write", [True, False], ids=["store", "retrieve"])
 @pytest.mark.parametrize("counts", [{0: 3, 1: 0xfffffffe, 2: 2}, {0: 3, 1: 0xfffffffe, 2: 4}, {0: 2, 33: 0xfffffffd, 63: 3},
                                     {0: 3, 69: 0xfffffffe}, {0: 3, 1: 0xfffffffe, 69: 2}, {3: 5, 150: 0xfffffffc, 151: 4, 299: 1}],
                          ids=str)
-def test_ring_call_with_offsets_that_wrap(H, counts, write, cu_budget):
+@pytest.mark.parametrize("positions", [16, 1100])   # a store reads the shorter table at once, the longer one counted
+def test_ring_call_with_offsets_that_wrap(H, counts, write, cu_budget, positions):
     """Counts whose sum passes 2^32: the table offsets start again from 0, so that a position has several requests to belong
     to.  The copy takes the one that the recorded contexts name: executing them gives the same file store and planes."""
     n_req = max(counts) + 1
@@ -1126,8 +1189,8 @@ def test_ring_call_with_offsets_that_wrap(H, counts, write, cu_budget):
     n = np.zeros(n_req, np.uint32)
     for r, x in counts.items():
         n[r] = x
-    bb, N, L, n_slots, addr = 4096, 40, 2, 1, 0x7f00_0000_1000
-    c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=np.zeros(n_req, np.uint32), table=np.random.default_rng(5).permutation(N)[:16],
+    bb, N, L, n_slots, addr = 4096, positions + 24, 2, 1, 0x7f00_0000_1000
+    c = H.LayerCase(T=16, h=2, d=64, e=2, N=N, n_blocks=np.zeros(n_req, np.uint32), table=np.random.default_rng(5).permutation(N)[:positions],
                     L=L, chunk=4096, name="ring_wraps")
     c.d_n_blocks = torch.from_numpy(n.view(np.int32)).to(H.DEV)
     stride = 2 * L * 5 * bb
@@ -1151,7 +1214,7 @@ def test_ring_call_with_offsets_that_wrap(H, counts, write, cu_budget):
             B.tutti_issue_io(ring, 0, n_slots, sgl, 2 * N, addr, fs, bb, cu_budget, st)
         else:
             issue = B.tutti_store_layer_issue if write else B.tutti_retrieve_layer_issue
-            issue(ring, 0, n_slots, pool, c.gpu_cfg(), c.d_n_blocks, n_req, c.d_table, 16, c.d_file_id, 1, addr, 5, fs, ext, tot,
+            issue(ring, 0, n_slots, pool, c.gpu_cfg(), c.d_n_blocks, n_req, c.d_table, positions, c.d_file_id, 1, addr, 5, fs, ext, tot,
                   cu_budget, st)
         torch.cuda.synchronize()
         results.append((k2, v2, files))
