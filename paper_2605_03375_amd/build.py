@@ -4,7 +4,9 @@ hipcc cross-compiles without a GPU.  `python -m paper_2605_03375_amd.build` or `
 """
 import importlib.util
 import os
+import shutil
 import subprocess
+import sys
 import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -38,15 +40,25 @@ def _build(out: str, defines, force: bool, verbose: bool) -> str:
     return out
 
 
-def build_fast_call(force: bool = True, verbose: bool = False) -> str:
-    """The extension module that binding.py calls the per-layer entry points through: paper_2605_03375_amd/_fast_call.so."""
+def build_fast_call(force: bool = True, verbose: bool = False):
+    """The extension module that binding.py calls the per-layer entry points through, or None where PyTorch, Python's headers
+    or a C++ compiler are missing: binding.py makes the same calls through ctypes then, and libtutti needs none of them."""
+    spec = importlib.util.find_spec("torch")
+    include = sysconfig.get_paths()["include"]
+    cxx = os.environ.get("CXX", "g++")
+    missing = [what for what, there in (("PyTorch", spec is not None), (f"{include}/Python.h",
+                                        os.path.exists(os.path.join(include, "Python.h"))),
+                                        (cxx, shutil.which(cxx.split()[0]) is not None)) if not there]
+    if missing:
+        print(f"no extension module for Python calls: {', '.join(missing)} not found", file=sys.stderr)
+        return None
+    torch = list(spec.submodule_search_locations)[0]
     if not force and os.path.exists(FAST_CALL):
         if os.path.getmtime(FAST_CALL) >= max(os.path.getmtime(p) for p in FAST_CALL_DEPS):
             return FAST_CALL
-    torch = list(importlib.util.find_spec("torch").submodule_search_locations)[0]
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
+    cmd = [*cxx.split(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
            "-Wno-missing-field-initializers", f"-I{os.path.join(ROOT, 'include')}",
-           f"-I{sysconfig.get_paths()['include']}", "-isystem", os.path.join(torch, "include"),
+           f"-I{include}", "-isystem", os.path.join(torch, "include"),
            "-isystem", os.path.join(torch, "include", "torch", "csrc", "api", "include"), FAST_CALL_DEPS[0],
            "-o", FAST_CALL, f"-L{os.path.join(torch, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
     if verbose:
@@ -57,8 +69,9 @@ def build_fast_call(force: bool = True, verbose: bool = False) -> str:
 
 def build_lib(force: bool = True, verbose: bool = False) -> str:
     """The product library: paper_2605_03375_amd/libtutti.so, and the extension module beside it."""
+    lib = _build(LIB, [], force, verbose)
     build_fast_call(force, verbose)
-    return _build(LIB, [], force, verbose)
+    return lib
 
 
 def build_bench_lib(force: bool = True, verbose: bool = False) -> str:

@@ -122,3 +122,17 @@ def test_codes_and_identity(module):
         assert f.__name__ == name and f.__module__ == B.__name__ and pickle.loads(pickle.dumps(f)) is f
     with pytest.raises(ValueError):
         module.wrap("tutti_complete_io", print, ("a", "b"), (None,))
+
+
+@pytest.mark.parametrize("missing", ["torch", "headers", "compiler"])
+def test_the_library_is_built_without_what_the_module_needs(monkeypatch, tmp_path, missing):
+    ran = []
+    monkeypatch.setattr(build.subprocess, "run", lambda cmd, **k: ran.append(cmd))
+    if missing == "torch":
+        monkeypatch.setattr(build.importlib.util, "find_spec", lambda name: None)
+    elif missing == "headers":
+        monkeypatch.setattr(build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    else:
+        monkeypatch.setenv("CXX", str(tmp_path / "no-such-compiler"))
+    assert build.build_lib(force=True) == build.LIB
+    assert [cmd[cmd.index("-o") + 1] for cmd in ran] == [build.LIB]
