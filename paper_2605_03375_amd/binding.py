@@ -260,8 +260,9 @@ def lib():
 
 
 # A short prefix's restore is over in 3 us on the GPU, so what a call costs on this side is what a train of layers runs
-# at (hence the extension module).  Pointers therefore travel as plain integers (argtypes makes them void *; wrapping each of nine in a c_void_p took
-# 2 us of a call) and the current stream is asked for its handle alone (without building a Stream object: 1 us).
+# at (hence the extension module).  Pointers therefore travel as plain integers (argtypes makes them void *; wrapping each of
+# nine in a c_void_p took 2 us of a call) and the current stream is asked for its handle alone (without building a Stream
+# object: 1 us).
 # tutti_layer_restore of a 256 KiB prefix, from Python: 8.6 us a call before, 5.7 now.
 def _p(x):
     """Device (or host) pointer of a tensor / array / int / None, as an integer or None."""
@@ -728,16 +729,26 @@ def _wrap_fast(module, name, slow):
     return module.wrap(name, slow, code.co_varnames[:code.co_argcount], slow.__defaults__)
 
 
+def _form(argtypes):
+    """Argument types of an entry point as the extension module writes them (fast_call.cpp, Entry::form)."""
+    words = {C.c_void_p: "p", C.c_uint32: "i", C.c_uint64: "l"}
+    words.update({C.POINTER(t): str(i) for i, t in enumerate((tutti_pool, tutti_objcfg, tutti_ring, tutti_filestore))})
+    return "".join(words.get(t, "?") for t in argtypes)
+
+
 def _install_fast_calls():
     global _fast_call
     try:
-        import torch  # noqa: F401  (the module is linked against it)
+        import torch
         from . import _fast_call as module
-    except ImportError:
+        # one that was built for another PyTorch, or for other entry points than these, makes no calls
+        if module.BUILT_FOR != f"[torch {torch.__version__}]":
+            return
+        wrapped = {name: _wrap_fast(module, name, globals()[name]) for name in _FAST_NAMES}
+    except (ImportError, AttributeError, ValueError):
         return        # not built: the ctypes wrappers make the same calls
     _fast_call = module
-    for name in _FAST_NAMES:
-        globals()[name] = _wrap_fast(module, name, globals()[name])
+    globals().update(wrapped)
 
 
 def _bind_fast_calls():
@@ -750,7 +761,9 @@ def _bind_fast_calls():
     _fast_call.setup((tutti_pool, tutti_objcfg, tutti_ring, tutti_filestore), torch.Tensor, torch._C._cuda_getDevice, raw,
                      _check)
     for name in _FAST_NAMES:
-        _fast_call.bind(globals()[name], C.cast(getattr(_LIB, name), C.c_void_p).value)
+        fn = getattr(_LIB, name)
+        same = _fast_call.form(name) == _form(fn.argtypes)   # else the call stays with the ctypes wrapper
+        _fast_call.bind(globals()[name], C.cast(fn, C.c_void_p).value if same else 0)
 
 
 _install_fast_calls()

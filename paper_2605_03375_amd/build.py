@@ -4,6 +4,7 @@ hipcc cross-compiles without a GPU.  `python -m paper_2605_03375_amd.build` or `
 """
 import importlib.util
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -14,7 +15,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libtutti.so")
 BENCH_LIB = os.path.join(HERE, "libtutti_bench.so")  # the same sources with the measurement aids compiled in
-FAST_CALL = os.path.join(HERE, "_fast_call.so")      # Python callables of the per-layer entry points (host code only)
+# Python callables of the per-layer entry points (host code only); the name says which Python it is for
+FAST_CALL = os.path.join(HERE, "_fast_call" + sysconfig.get_config_var("EXT_SUFFIX"))
 FAST_CALL_DEPS = [os.path.join(CSRC, "fast_call.cpp"), os.path.join(ROOT, "include", "tutti.h")]
 SOURCES = [os.path.join(CSRC, "tutti_api.hip"), os.path.join(CSRC, "tutti_host.cpp")]
 DEPS = SOURCES + [os.path.join(CSRC, "tutti_kernels.hip.h"), os.path.join(CSRC, "launch_rules.h"),
@@ -40,6 +42,14 @@ def _build(out: str, defines, force: bool, verbose: bool) -> str:
     return out
 
 
+def _fast_call_is_current(mark: str) -> bool:
+    """Newer than its sources, and built for the PyTorch that is installed (fast_call.cpp leaves the mark)."""
+    if not os.path.exists(FAST_CALL) or os.path.getmtime(FAST_CALL) < max(os.path.getmtime(p) for p in FAST_CALL_DEPS):
+        return False
+    with open(FAST_CALL, "rb") as f:
+        return b"[torch " + mark.encode() + b"]" in f.read()
+
+
 def build_fast_call(force: bool = True, verbose: bool = False):
     """The extension module that binding.py calls the per-layer entry points through, or None where PyTorch, Python's headers
     or a C++ compiler are missing: binding.py makes the same calls through ctypes then, and libtutti needs none of them."""
@@ -53,11 +63,12 @@ def build_fast_call(force: bool = True, verbose: bool = False):
         print(f"no extension module for Python calls: {', '.join(missing)} not found", file=sys.stderr)
         return None
     torch = list(spec.submodule_search_locations)[0]
-    if not force and os.path.exists(FAST_CALL):
-        if os.path.getmtime(FAST_CALL) >= max(os.path.getmtime(p) for p in FAST_CALL_DEPS):
-            return FAST_CALL
+    with open(os.path.join(torch, "version.py")) as f:
+        version = re.search(r"__version__ *= *['\"]([^'\"]+)", f.read()).group(1)
+    if not force and _fast_call_is_current(version):
+        return FAST_CALL
     cmd = [*cxx.split(), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
-           "-Wno-missing-field-initializers", f"-I{os.path.join(ROOT, 'include')}",
+           "-Wno-missing-field-initializers", f'-DBUILT_FOR_TORCH="{version}"', f"-I{os.path.join(ROOT, 'include')}",
            f"-I{include}", "-isystem", os.path.join(torch, "include"),
            "-isystem", os.path.join(torch, "include", "torch", "csrc", "api", "include"), FAST_CALL_DEPS[0],
            "-o", FAST_CALL, f"-L{os.path.join(torch, 'lib')}", "-ltorch_python", "-ltorch_cpu", "-lc10"]

@@ -21,6 +21,10 @@
 
 #include "tutti.h"
 
+#ifndef BUILT_FOR_TORCH
+#error "BUILT_FOR_TORCH: the version of the PyTorch whose headers these are, as a string"
+#endif
+
 namespace {
 
 enum Kind : uint8_t { kPointer, kStruct, kInt };
@@ -45,6 +49,7 @@ struct Entry {
   size_t n;
   Kind kind[kMaxArgs];
   int8_t record[kMaxArgs];
+  char form[kMaxArgs + 1];  // what binding.py compares with the ctypes declaration: 0 to 3 a record, p a pointer, i / l 32 / 64 bits
   int (*invoke)(void *fn, const uint64_t *word);
 };
 
@@ -64,9 +69,12 @@ int invoke_words(void *fn, const uint64_t *word, std::index_sequence<I...>) {
 template <typename... A>
 Entry entry(const char *name, int (*)(A...)) {
   static_assert(sizeof...(A) <= kMaxArgs);
-  Entry e{name, sizeof...(A), {}, {}, nullptr};
+  Entry e{name, sizeof...(A), {}, {}, {}, nullptr};
   size_t i = 0;
-  ((e.kind[i] = record_of<A>() >= 0 ? kStruct : std::is_pointer_v<A> ? kPointer : kInt, e.record[i] = record_of<A>(), ++i), ...);
+  ((e.kind[i] = record_of<A>() >= 0 ? kStruct : std::is_pointer_v<A> ? kPointer : kInt, e.record[i] = record_of<A>(),
+    e.form[i] = record_of<A>() >= 0 ? static_cast<char>('0' + record_of<A>())
+                : std::is_pointer_v<A> ? 'p' : sizeof(A) == 4 ? 'i' : sizeof(A) == 8 ? 'l' : '?',
+    ++i), ...);
   e.invoke = [](void *fn, const uint64_t *word) { return invoke_words<A...>(fn, word, std::index_sequence_for<A...>{}); };
   return e;
 }
@@ -244,6 +252,14 @@ PyObject *wrap(PyObject *, PyObject *args) {
   return reinterpret_cast<PyObject *>(c);
 }
 
+// form(name): the entry point's arguments as this module was built for them, one letter each (Entry::form).
+PyObject *form(PyObject *, PyObject *name) {
+  if (PyUnicode_Check(name))
+    for (const Entry &x : kEntries)
+      if (PyUnicode_CompareWithASCIIString(name, x.name) == 0) return PyUnicode_FromString(x.form);
+  Py_RETURN_NONE;
+}
+
 // bind(callable, address): where the library has the entry point.
 PyObject *bind(PyObject *, PyObject *args) {
   PyObject *o;
@@ -271,10 +287,13 @@ PyObject *enable(PyObject *, PyObject *on) {
   Py_RETURN_NONE;
 }
 
+const char kBuiltFor[] = "[torch " BUILT_FOR_TORCH "]";  // also what build.py looks for in the file
+
 // A forked child has no device: torch says so when it is asked by way of the wrappers.
 void in_child() { g_ready.store(false, std::memory_order_relaxed); }
 
 PyMethodDef kMethods[] = {{"wrap", wrap, METH_VARARGS, nullptr},
+                          {"form", form, METH_O, nullptr},
                           {"bind", bind, METH_VARARGS, nullptr},
                           {"setup", setup, METH_VARARGS, nullptr},
                           {"enable", enable, METH_O, nullptr},
@@ -294,5 +313,7 @@ PyMODINIT_FUNC PyInit__fast_call(void) {
   CallType.tp_methods = kCallMethods;
   if (PyType_Ready(&CallType) != 0) return nullptr;
   pthread_atfork(nullptr, nullptr, in_child);
-  return PyModule_Create(&kModule);
+  PyObject *module = PyModule_Create(&kModule);
+  if (module && PyModule_AddStringConstant(module, "BUILT_FOR", kBuiltFor) != 0) Py_CLEAR(module);
+  return module;
 }

@@ -2,11 +2,13 @@
 words that reach the C function, and what it leaves to the ctypes wrapper."""
 import ctypes as C
 import pickle
+import types as pytypes
 
 import numpy as np
 import pytest
 import torch
 
+import paper_2605_03375_amd as package
 from paper_2605_03375_amd import binding as B
 from paper_2605_03375_amd import build
 
@@ -122,6 +124,35 @@ def test_codes_and_identity(module):
         assert f.__name__ == name and f.__module__ == B.__name__ and pickle.loads(pickle.dumps(f)) is f
     with pytest.raises(ValueError):
         module.wrap("tutti_complete_io", print, ("a", "b"), (None,))
+
+
+def _bad_wrap(*a):
+    raise ValueError("not an entry point of these arguments")
+
+
+@pytest.mark.parametrize("found", [{}, {"BUILT_FOR": "[torch 0.1]", "wrap": lambda *a: print},
+                                   {"BUILT_FOR": f"[torch {torch.__version__}]", "wrap": _bad_wrap}],
+                         ids=["of an older build", "for another torch", "for other arguments"])
+def test_a_module_of_another_build_is_left_alone(monkeypatch, found):
+    monkeypatch.setattr(package, "_fast_call", pytypes.SimpleNamespace(**found), raising=False)
+    monkeypatch.setattr(B, "_fast_call", None)
+    before = {name: getattr(B, name) for name in B._FAST_NAMES}
+    B._install_fast_calls()
+    assert B._fast_call is None and all(getattr(B, name) is f for name, f in before.items())
+
+
+def test_entry_points_that_changed_are_not_bound(module, monkeypatch):
+    """The module's idea of an entry point's arguments is compared with the ctypes declaration."""
+    lib = B.product_lib()
+    for name in B._FAST_NAMES:
+        assert module.form(name) == B._form(getattr(lib, name).argtypes) and "?" not in module.form(name)
+    assert module.form("tutti_cu_count") is None
+    bound = {}
+    monkeypatch.setattr(B, "_fast_call", pytypes.SimpleNamespace(
+        setup=lambda *a: None, form=lambda name: module.form(name).replace("il", "li", name == "tutti_issue_io"),
+        bind=lambda call, at: bound.__setitem__(call.__name__, at)))
+    B._bind_fast_calls()
+    assert [name for name, at in bound.items() if at == 0] == ["tutti_issue_io"] and len(bound) == len(B._FAST_NAMES)
 
 
 @pytest.mark.parametrize("missing", ["torch", "headers", "compiler"])
