@@ -1768,19 +1768,29 @@ void least_resident(int *worst, uint32_t lds, K... kernels) {
   (one(kernels), ...);
 }
 
-// Every kernel that a whole-GPU launch of the default shape may run.
+// Every kernel that a whole-GPU launch of the default shape may run (line tiles: whole slices in staging order only).
 template <int DIR, int HND>
 void least_resident_layer(int *worst) {
   constexpr uint32_t few = req_lds_bytes(kWave), many = req_lds_bytes(512);
-  least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kOne>, k_layer<DIR, HND, 4, 3, kWgThreads, kFew>,
-                 k_layer<DIR, HND, 4, 3, kWgThreads, kFew, false, true>);
-  least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany>,
-                 k_layer<DIR, HND, 4, 3, kWgThreads, kMany, false, true>);
-  if constexpr (DIR == kUnpack) least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, true>);
-  if constexpr (DIR == kPack)
+  least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kOne>, k_layer<DIR, HND, 4, 3, kWgThreads, kFew>);
+  least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany>, k_layer<DIR, HND, 4, 3, kWgThreads, kManyAhead>);
+  if constexpr (HND != kLines) {
+    least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFew, false, true>);
+    least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, false, true>);
+    if constexpr (DIR == kUnpack) least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, true>);
+  }
+  if constexpr (DIR == kPack) {
     least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFewAhead>, k_layer<DIR, HND, 4, 3, kWgThreads, kFewCounted>);
-  least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kManyAhead>);
-  if constexpr (DIR == kPack) least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kManyCounted>);
+    least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kManyCounted>);
+  }
+}
+
+template <int DIR>
+void least_resident_move(int *worst) {
+  constexpr uint32_t many = req_lds_bytes(512);
+  least_resident(worst, many, k_move<DIR, kNhd, 4, 3, kWgThreads>, k_move<DIR, kNhd, 4, 3, kWgThreads, true>,
+                 k_move<DIR, kHnd, 4, 3, kWgThreads>, k_move<DIR, kHnd, 4, 3, kWgThreads, true>,
+                 k_move<DIR, kLines, 4, 3, kWgThreads>);
 }
 
 template <int DIR>
@@ -1803,23 +1813,22 @@ void least_resident_lds(int *worst) {
 }  // extern "C++"
 
 int tutti_resident_wgs_per_cu(uint32_t which) {
-  constexpr uint32_t many = req_lds_bytes(512);
   int n = 1 << 20;
   switch (which) {
-    case 0: least_resident_layer<kUnpack, false>(&n); break;
-    case 1: least_resident_layer<kPack, false>(&n); break;
-    case 2:
-      least_resident(&n, many, k_move<kUnpack, false, 4, 3, kWgThreads>, k_move<kUnpack, false, 4, 3, kWgThreads, true>,
-                     k_move<kUnpack, true, 4, 3, kWgThreads>, k_move<kUnpack, true, 4, 3, kWgThreads, true>);
-      break;
-    case 3:
-      least_resident(&n, many, k_move<kPack, false, 4, 3, kWgThreads>, k_move<kPack, false, 4, 3, kWgThreads, true>,
-                     k_move<kPack, true, 4, 3, kWgThreads>, k_move<kPack, true, 4, 3, kWgThreads, true>);
-      break;
+    case 0: least_resident_layer<kUnpack, kNhd>(&n); break;
+    case 1: least_resident_layer<kPack, kNhd>(&n); break;
+    case 2: least_resident_move<kUnpack>(&n); break;
+    case 3: least_resident_move<kPack>(&n); break;
     case 4: least_resident_ring<kUnpack>(&n); break;
     case 5: least_resident_ring<kPack>(&n); break;
-    case 6: least_resident_layer<kUnpack, true>(&n); break;
-    case 7: least_resident_layer<kPack, true>(&n); break;
+    case 6:
+      least_resident_layer<kUnpack, kHnd>(&n);
+      least_resident_layer<kUnpack, kLines>(&n);
+      break;
+    case 7:
+      least_resident_layer<kPack, kHnd>(&n);
+      least_resident_layer<kPack, kLines>(&n);
+      break;
     case 8: least_resident_lds<kUnpack>(&n); break;
     case 9: least_resident_lds<kPack>(&n); break;
     case 10: least_resident(&n, 0, k_issue_io<kDefaultUnroll, kWgThreads, false>, k_issue_io<kDefaultUnroll, kWgThreads, true>); break;

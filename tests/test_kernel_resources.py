@@ -4,6 +4,7 @@ compute unit, which is what those launches' grids are sized for."""
 import re
 import struct
 import subprocess
+import sys
 
 import msgpack
 import pytest
@@ -44,14 +45,18 @@ def _metadata(elf):
     raise AssertionError("no kernel metadata")
 
 
+def _short_names(mangled):
+    """Kernel names without namespace and arguments."""
+    names = subprocess.run(["c++filt"], input="\n".join(mangled), capture_output=True, text=True, check=True).stdout
+    return [re.sub(r"\((tutti::|unsigned).*", "", n).replace("void ", "").replace("tutti::", "")
+            for n in names.split("\n")[:len(mangled)]]
+
+
 @pytest.fixture(scope="module")
 def kernels():
     with open(B.LIB_PATH, "rb") as f:
         found = _metadata(_code_object(f.read()))["amdhsa.kernels"]
-    names = subprocess.run(["c++filt"], input="\n".join(k[".name"] for k in found), capture_output=True, text=True,
-                           check=True).stdout.split("\n")
-    return {re.sub(r"\((tutti::|unsigned).*", "", n).replace("void ", "").replace("tutti::", ""): k
-            for n, k in zip(names, found)}
+    return dict(zip(_short_names([k[".name"] for k in found]), found))
 
 
 def test_no_kernel_uses_scratch(kernels):
@@ -70,3 +75,39 @@ def test_whole_gpu_kernels_fit_eight_times(kernels):
     assert len({n.split("<")[0] for n in whole}) == 6 and len(whole) > 40
     large = {n: k[".vgpr_count"] for n, k in whole.items() if k[".vgpr_count"] > 64}
     assert not large, large
+
+
+# Stands in for the two HIP calls by which kernels become known and are asked about, so that the query runs without a GPU.
+RECORDER = """
+#include <cstdio>
+#include <map>
+static std::map<const void *, const char *> names;
+extern "C" void __hipRegisterFunction(void **, const void *host, char *, const char *name, unsigned, void *, void *, void *,
+                                      void *, int *) { names[host] = name; }
+extern "C" int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *host, int, size_t) {
+  std::puts(names.at(host));
+  std::fflush(stdout);
+  *n = 8;
+  return 0;
+}
+"""
+ASK = """
+import ctypes, sys
+ctypes.CDLL(sys.argv[1], ctypes.RTLD_GLOBAL)
+lib = ctypes.CDLL(sys.argv[2])
+for which in sys.argv[3:]:
+    assert lib.tutti_resident_wgs_per_cu(int(which)) == 8
+"""
+
+
+@pytest.mark.parametrize("which,kernel", [((2, 3), "k_move<"), ((4, 5), "k_layer_ring<"), ((0, 1, 6, 7), "k_layer<"),
+                                          ((10,), "k_issue_io<")], ids=lambda x: x if isinstance(x, str) else "")
+def test_residency_query_asks_about_every_kernel(kernels, tmp_path, which, kernel):
+    """tutti_resident_wgs_per_cu is the least over all kernels that a whole-GPU call of that kind may run."""
+    source, stub = tmp_path / "recorder.cpp", tmp_path / "recorder.so"
+    source.write_text(RECORDER)
+    subprocess.run(["g++", "-shared", "-fPIC", str(source), "-o", str(stub)], check=True)
+    out = subprocess.run([sys.executable, "-c", ASK, str(stub), B.LIB_PATH, *map(str, which)], capture_output=True, text=True,
+                         check=True).stdout
+    there = {n for n, k in kernels.items() if n.startswith(kernel) and k[".max_flat_workgroup_size"] == 256}
+    assert set(_short_names(out.split())) == there and len(there) >= 2
