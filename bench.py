@@ -16,7 +16,8 @@ Prints ONE JSON line on stdout; progress goes to stderr.
 Further legs of the same line (all on by default; --quick leaves them out): the save, the copy kernels alone,
 copy ceilings and the scattered-copy floor, entries built per second, configs 3 and 4 at their real pool sizes,
 config 5 (CU budgets and a CU-masked I/O domain beside two GEMMs) with the slack table it yields, the ring
-path, and a sweep of the prefix length from 1K to 128K tokens (eager launches and a HIP-graph replay).
+path, and a sweep of the prefix length from 1K to 128K tokens (eager launches and a HIP-graph replay).  Legs that the
+line has no room for (LINE_LIMIT) go to stderr, one JSON line each, and are named in legs_on_stderr.
 """
 import argparse
 import dataclasses
@@ -36,6 +37,20 @@ HBM_PEAK_GBPS = 8000.0  # MI355X published HBM3E peak
 
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
+
+
+LINE_LIMIT = 12000  # characters: of a longer line what keeps the end of a run's output may keep a part
+
+
+def split_line(out, limit=LINE_LIMIT):
+    """The result line, and the legs that it has no room for: the longest ones, until the others fit."""
+    line, rest = dict(out), {}
+    legs = sorted((k for k, v in out.items() if isinstance(v, dict) and k != "config"), key=lambda k: len(json.dumps(out[k])))
+    while legs and len(json.dumps(line)) > limit:
+        name = legs.pop()
+        rest[name] = line.pop(name)
+        line["legs_on_stderr"] = list(rest)
+    return line, rest
 
 
 def median(xs):
@@ -435,7 +450,10 @@ def main():
     if cpu2 is not None:
         out["cpu_baseline"] = cpu2
         out["cpu_baseline"]["other_configs"] = cpu_baseline_others(W)
-    print(json.dumps(out), flush=True)
+    line, rest = split_line(out)
+    for name, leg in rest.items():
+        log(json.dumps({name: leg}))
+    print(json.dumps(line), flush=True)
 
 
 def placed_planes(torch, n_layers, plane_bytes, dev, reserve_bytes, place=True, stage_bytes=0, stage_rotation=0):
