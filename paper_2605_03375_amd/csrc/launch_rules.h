@@ -10,16 +10,25 @@ namespace tutti {
 // (the memory turns between reading and writing) than the same stores a little later.  So a wavefront that has read
 // ahead holds its first stores back, for the returned number of 512 clocks (0.21 us each): only if the launch gives
 // most of the chip's `chip_waves` wavefronts an item and no wavefront more than two, by the items the requests really
-// have (the table may be longer); a launch that read nothing ahead sleeps for nothing.  Every step of the way to the first
-// store delays the stores as well: with `n_req` requests whose owner is found step by step they wait less.  The kernels
-// find it in one step and pass pause_requests(n_req).
-// Restore of 32 KiB blocks, cold, us, pause 0 / 2 / 5 / 6 / 7 / 8 / 9 (items / chip_waves in brackets):
-//   1 request    384 blocks (0.75)  10.5 /  9.1 /  9.4 /  9.5 /  9.5 /  9.5 /  9.7    448 (0.88)  12.1 / 12.3 / 10.6 / 10.4 / 10.4 / 10.6 / 10.7
-//                512 (1.00)         13.9 / 13.8 / 14.1 / 14.2 / 13.5 / 12.6 / 12.1    640 (1.25)  16.1 / 15.9 / 16.3 / 15.1 / 14.5 / 14.4 / 14.5
-//   8 requests   384                 9.8 /  8.7 /  9.3 /  9.0 /  9.0 /  9.2 /  9.5    448         11.6 / 11.9 / 10.0 / 10.1 / 10.3 / 10.4 / 10.1
-//                512                13.2 / 13.2 / 13.4 / 12.3 / 11.5 / 11.3 / 11.5    640         15.5 / 15.7 / 15.5 / 14.4 / 14.2 / 14.2 / 14.4
-//   64 requests  384                 9.4 /  8.8 /  9.2 /  9.0 /  9.1 /  9.3 /  9.5    448         11.7 / 11.8 / 10.0 / 10.2 / 10.4 / 10.2 / 10.1
-//                512                13.0 / 13.3 / 13.0 / 11.9 / 11.3 / 11.3 / 11.6    640         15.3 / 15.8 / 14.9 / 14.3 / 14.1 / 14.2 / 14.5
+// have (the table may be longer); a launch that read nothing ahead sleeps for nothing.  Only the longest scan (six steps,
+// beyond 32 requests) delays the stores by itself, by about one step.
+// Restore of 32 KiB blocks, graph replay of 16 layers, us, pause 0 / 2 / 5 / 6 / 7 / 8 / 9 / 10 (items / chip_waves in brackets):
+//   1 request    384 blocks (0.75)  10.5 /  9.3 /  9.3 /  9.6 /  9.5 /  9.4 /  9.6 /  9.8
+//                448 (0.88)         12.2 / 12.4 / 10.5 / 10.2 / 10.3 / 10.4 / 10.7 / 10.6
+//                464 (0.91)         12.8 / 13.1 / 13.2 / 13.0 / 11.8 / 11.1 / 11.0 / 11.2
+//                512 (1.00)         13.8 / 14.0 / 14.4 / 14.2 / 13.5 / 12.2 / 11.6 / 11.6
+//                560 (1.09)         15.4 / 15.0 / 15.4 / 15.1 / 13.6 / 12.9 / 12.9 / 13.0
+//                640 (1.25)         17.0 / 16.7 / 17.1 / 16.3 / 15.0 / 14.8 / 14.9 / 15.2
+//   8 requests   384                10.4 /  9.1 /  9.6 /  9.6 /  9.6 /  9.7 / 10.0 / 10.1
+//                448                12.6 / 12.7 / 10.6 / 10.4 / 10.5 / 10.8 / 10.9 / 10.8
+//                464                13.1 / 13.3 / 13.3 / 12.2 / 11.2 / 11.0 / 11.1 / 11.1
+//                512                13.9 / 14.2 / 14.4 / 13.7 / 12.6 / 11.9 / 11.6 / 11.7
+//                640                17.1 / 17.0 / 17.1 / 15.6 / 15.2 / 15.0 / 15.1 / 15.4
+//   64 requests  384                10.1 /  9.1 /  9.7 /  9.6 /  9.6 /  9.7 / 10.0 / 10.2
+//                448                12.6 / 12.6 / 10.5 / 10.4 / 10.9 / 10.7 / 10.8 / 10.9
+//                464                13.0 / 13.3 / 13.2 / 12.0 / 11.2 / 11.2 / 11.3 / 11.3
+//                512                14.2 / 14.5 / 14.4 / 13.2 / 12.0 / 11.6 / 11.9 / 12.0
+//                640                17.0 / 17.1 / 16.4 / 15.4 / 15.1 / 15.1 / 15.3 / 15.6
 // and 0 / 2 / 5 / 7 at 320 blocks (0.63), 1 request, 7.6 / 7.9 / 7.9 / 8.3, at 1024 (2.0) 23.7 / 23.8 / 23.7 / 23.5, at 2048
 // (4.0), 8 requests, 44.1 / 44.1 / 44.2 / 44.4, 64 requests 43.9 / 43.9 / 44.1 / 44.3.
 // Where the time falls off a step, the pause stands behind it.
@@ -29,15 +38,10 @@ namespace tutti {
 constexpr uint32_t hold_back_pause(uint32_t items, uint32_t chip_waves, uint32_t n_req, bool file) {
   if (items > 2 * chip_waves || 32 * items <= 21 * chip_waves) return 0;
   if (file) return 32 * items <= 25 * chip_waves ? 2 : 32 * items <= 29 * chip_waves ? 5 : 5 * items <= 6 * chip_waves ? 8 : 6;
-  const uint32_t steps = n_req > 1 ? 32u - static_cast<uint32_t>(__builtin_clz(n_req - 1)) : 0u;
-  if (32 * items > 29 * chip_waves) return (5 * items > 6 * chip_waves ? 7 : 8) - (steps + 1) / 2;
-  if (32 * items > 25 * chip_waves) return 6 - (steps + 1) / 2;
-  return steps < 4 ? 2 - steps / 2 : 0;
+  if (32 * items <= 25 * chip_waves) return 2;
+  if (32 * items <= 28 * chip_waves) return 6;
+  return n_req <= 32 && 10 * items <= 11 * chip_waves ? 9 : 8;
 }
-
-// The number of requests that hold_back_pause sees where one ballot finds an item's owner: only the longest scan (six
-// steps, beyond 32 requests) still delays the stores by about one step.
-constexpr uint32_t pause_requests(uint32_t n_req) { return n_req > 32 ? 2 : 1; }
 
 // Slice of a CU-budgeted copy of `blocks` blocks (K and V each), in pieces of 1 KiB.  What a compute unit moves depends on
 // the length of a wavefront's run of loads and of stores, not on the bytes in flight: a plain cold copy on 8 / 32 / 64
@@ -95,8 +99,9 @@ constexpr bool entries_apart(uint32_t copy_wgs, uint32_t cus, uint32_t n_req) {
 constexpr uint32_t pack_at_once(uint32_t chip_waves) { return chip_waves / 4; }
 
 // Whether a head-major pool goes through LDS tiles or is moved directly, where it is not moved as line tiles
-// (as_line_tiles).  On the whole GPU it pays while a row is shorter than a 128-byte line.  Under a CU budget a workgroup has one tile in flight at a time, and only rows of 16 bytes on
-// more than 16 compute units are worth that.  Through LDS / direct, us, save and restore of 16 KiB blocks:
+// (as_line_tiles); where this holds an ordered restore keeps staging order.  On the whole GPU it pays while a row is shorter
+// than a 128-byte line.  Under a CU budget a workgroup has one tile in flight at a time, and only rows of 16 bytes on more
+// than 16 compute units are worth that.  Through LDS / direct, us, save and restore of 16 KiB blocks:
 //   rows of 16 bytes   300 blocks on 8 units 85 / 69, 75 / 64   500 on 16  78 / 73, 73 / 64   1000 on 32  87 / 99, 83 / 90
 //                      2000 on 64  94 / 122, 89 / 139
 //   rows of 32 bytes   300 on 8  82 / 50, 75 / 44   500 on 16  78 / 57, 73 / 48   1000 on 32  87 / 69, 83 / 56

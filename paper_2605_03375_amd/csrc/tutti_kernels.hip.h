@@ -4,7 +4,8 @@
 //   k_layout        one workgroup: extents of all requests by a prefix scan
 //   k_sqe           submission entries from extents, four lanes per 64-byte entry
 //   k_move          pack / unpack between paged blocks and objects, extents given
-//   k_move_lds      the same for head-major pools with short rows: token tile transposed in LDS
+//   k_move_lds      the same for head-major pools with short rows and more blocks than k_move's line tiles can number
+//                   (and for the measurement build): token tile transposed in LDS
 //   k_layer         one layer's restore (or save) in one launch: scan + entries + unpack (or pack)
 //   k_layer_lds     the same with the LDS-staged transpose
 //   k_sgl_table     direct-to-block mode: the pool's mapping table, one 16-byte descriptor per block
@@ -2250,8 +2251,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
         if (DIR == kPack && first.pos < blocks) pre = preload_pack<HND, U, NT>(m, first);
       });
   if (REQS == kFew && DIR == kUnpack && pre.valid)
-    hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, pause_requests(a.n_req),
-                              false));
+    hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, a.n_req, false));
   SqeHead head;
   head.live = false;
   if (blockIdx.x < w.sqe_wgs) head = sqe_head(q, l, a.n_req, 0);

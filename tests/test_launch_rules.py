@@ -49,16 +49,19 @@ def test_stores_are_held_back_by_the_items_there_are(rules, n_req, file):
     for items in (0, 1, CHIP, 0xffffffff):
         assert rules.pause_of(items, 0, n_req, file) == 0
     for items in range(CHIP // 2, 2 * CHIP + 64, 16):
-        assert rules.pause_of(items, CHIP, n_req, file) <= 8
+        assert rules.pause_of(items, CHIP, n_req, file) <= 9
 
 
 def test_more_requests_are_held_back_less(rules):
     for items in range(0, 3 * CHIP, 64):
         pauses = [rules.pause_of(items, CHIP, n, 0) for n in range(1, 65)]
         assert pauses == sorted(pauses, reverse=True)
-    assert [rules.pause_of(CHIP, CHIP, n, 0) for n in (1, 2, 8, 64)] == [8, 7, 6, 5]
-    assert [rules.pause_of(CHIP * 7 // 8, CHIP, n, 0) for n in (1, 2, 8, 64)] == [6, 5, 4, 3]
-    assert [rules.pause_of(CHIP * 3 // 4, CHIP, n, 0) for n in (1, 2, 8, 64)] == [2, 2, 1, 0]
+    # behind the step that the time falls off at each size
+    assert [rules.pause_of(CHIP, CHIP, n, 0) for n in (1, 2, 8, 32, 33, 64)] == [9, 9, 9, 9, 8, 8]
+    assert [rules.pause_of(CHIP * 29 // 32, CHIP, n, 0) for n in (1, 2, 8, 64)] == [9, 9, 9, 8]
+    assert [rules.pause_of(CHIP * 7 // 8, CHIP, n, 0) for n in (1, 2, 8, 64)] == [6, 6, 6, 6]
+    assert [rules.pause_of(CHIP * 3 // 4, CHIP, n, 0) for n in (1, 2, 8, 64)] == [2, 2, 2, 2]
+    assert [rules.pause_of(CHIP * 5 // 4, CHIP, n, 0) for n in (1, 2, 8, 64)] == [8, 8, 8, 8]
 
 
 @pytest.mark.parametrize("ahead", [0, 1])
