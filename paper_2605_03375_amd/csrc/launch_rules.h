@@ -76,6 +76,10 @@ constexpr uint32_t budget_units(bool ahead, uint32_t block_bytes, uint32_t block
   return items <= one_each || cu_budget > 32 || !even ? 16 : 8;
 }
 
+// The launch shapes that have kernels for blocks that are no whole number of slices (pieces): under a budget the one that
+// budget_units asks for then.  In any other shape the kernel of whole slices would read and write beyond the blocks.
+constexpr bool pieces_shape(bool whole_gpu, uint32_t units) { return whole_gpu || units == 16; }
+
 // Whether the submission entries (or the contexts) of a whole-GPU launch of up to 64 requests are written by workgroups of
 // their own, in front of the `copy_wgs` that move blocks, instead of riding along with the first of those.  Riding along a
 // small launch is as long as the scan with the entries' divisions, the copy and the entry one behind the other; a larger one

@@ -504,7 +504,7 @@ template <typename S>
 constexpr bool has_pieces = true;
 #else
 template <typename S>
-constexpr bool has_pieces = S::WG == kWgThreads || S::U == kBudgetUnroll;
+constexpr bool has_pieces = pieces_shape(S::WG == kWgThreads, S::U);
 #endif
 
 template <int DIR, int HND>
@@ -512,11 +512,12 @@ hipError_t launch_move(const Launch &L, uint32_t lds, hipStream_t s, const MoveA
                        uint32_t n_req) {
   return with_shape(L, [&](auto sh) {
     using S = decltype(sh);
-    if constexpr (has_pieces<S> && HND != kLines) {
-      if (L.pieces) {
+    if (L.pieces) {  // never through the kernel of whole slices
+      if constexpr (has_pieces<S> && HND != kLines) {
         hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG, true>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req);
         return hipGetLastError();
       }
+      return hipErrorInvalidValue;
     }
     hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req);
     return hipGetLastError();
@@ -541,6 +542,7 @@ hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStre
       }
     }
   }
+  if (pieces) return hipErrorInvalidValue;  // never through the kernel of whole slices
   hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS>), grid, block, lds, s, m, q, a, w);
   return hipGetLastError();
 }
@@ -599,6 +601,7 @@ hipError_t launch_ring_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStrea
       return hipGetLastError();
     }
   }
+  if (pieces) return hipErrorInvalidValue;  // never through the kernel of whole slices
   hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG, REQS>), grid, block, lds, s, m, q, d, g, done, f, a, w);
   return hipGetLastError();
 }

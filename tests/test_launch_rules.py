@@ -25,6 +25,7 @@ extern "C" unsigned units_of(int ahead, unsigned block_bytes, unsigned blocks, u
                              int short_rows) {
   return tutti::budget_units(ahead != 0, block_bytes, blocks, budget, ordered != 0, short_rows != 0);
 }
+extern "C" int pieces_of(int whole_gpu, unsigned units) { return tutti::pieces_shape(whole_gpu != 0, units); }
 """
 CHIP = 8192  # wavefronts of a whole-GPU launch on 256 compute units
 
@@ -83,6 +84,21 @@ def test_slices_under_a_budget(rules, ahead, budget):
     for blocks in (1, 64, 256, 512):
         assert rules.units_of(1, 32768, blocks, 32, 0, 0) == (16 if blocks > 256 else 8)
         assert rules.units_of(ahead, 32768, blocks, budget, 0, 1) == rules.units_of(ahead, 16384, blocks, budget, 1, 1) == 16
+
+
+@pytest.mark.parametrize("ahead,short_rows", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("budget", [1, 16, 32, 256])
+def test_ragged_blocks_have_a_kernel(rules, ahead, short_rows, budget):
+    """Where the slices that the rule asks for do not fill the blocks, the shape is one that moves pieces."""
+    ragged = 0
+    for block in [16 * k for k in range(1, 1100)] + [1024 * k for k in range(18, 256)]:
+        for blocks in (1, 64, 513, 4096, 1 << 20):
+            units = rules.units_of(ahead, block, blocks, budget, 0, short_rows)
+            if block % (units * 1024) != 0:
+                ragged += 1
+                assert rules.pieces_of(0, units)
+        assert rules.pieces_of(1, 4)
+    assert ragged > 1000 and not rules.pieces_of(0, 8)
 
 
 def test_head_major_rows_through_lds(rules):
