@@ -95,12 +95,29 @@ constexpr bool entries_apart(uint32_t copy_wgs, uint32_t cus, uint32_t n_req) {
   return 2 * copy_wgs <= (n_req == 1 ? 4 : 5) * cus;
 }
 
-// Items (slices of the table's blocks) up to which a save of several requests reads them all without a look at the requests'
-// counts (PackItem).  What lies behind the requests' blocks in the table is then read for nothing: with all of it, a quarter of
-// the chip's wavefronts (128 blocks of 32 KiB, 8 MiB) is the most at which that costs no more than it gains.  Graph replay, us,
-// 2 blocks in 2 requests with a table of 96 / 128 / 160 / 200: in staging order 3.6 / 3.6 / 3.8 / 3.8, read at once 3.2 / 3.4 /
-// 3.9 / 4.8, counted first 3.1 / 3.3 / 3.1 / 3.6.
-constexpr uint32_t pack_at_once(uint32_t chip_waves) { return chip_waves / 4; }
+// Whether a save of several requests reads its `items` (slices of the table's blocks) at once, or when it has counted the
+// requests' blocks (PackItem).  What lies behind the requests' blocks in the table is read for nothing then: with all of it, a
+// quarter of the chip's wavefronts (128 blocks of 32 KiB, 8 MiB) is the most at which that costs no more than it gains.  Graph
+// replay, us, 2 blocks in 2 requests with a table of 96 / 128 / 160 / 200: in staging order 3.6 / 3.6 / 3.8 / 3.8, read at once
+// 3.2 / 3.4 / 3.9 / 4.8, counted first 3.1 / 3.3 / 3.1 / 3.6.
+// Up to 64 requests counting costs nothing.  For more it takes a barrier, and the stores then start among the reads; a table of
+// up to 8 blocks a request (saves behind a decode step) is taken to be theirs, a longer one for a fixed capacity.  Beyond 1024
+// requests reading the counts again behind the data is the longer way.  At once / counted first:
+//   all owned   8 KiB blocks, 1280 in 512 9.7 / 10.8, 1024 in 256 7.2 / 8.4, 1024 in 128 7.2 / 8.3; 32 KiB, 300 in 200 8.2 / 9.3;
+//               4 KiB, 3000 in 1000 12.2 / 12.9, in 250 11.2 / 11.8, in 2000 22.6 / 18.7
+//   half owned  7.9 / 7.6, 6.6 / 6.5, 6.4 / 6.0; 7.9 / 6.3; 10.7 / 9.8, 9.1 / 6.7, 20.1 / 16.8
+//   few owned   7.3 / 5.1, 6.0 / 4.4, 5.9 / 4.3; 6.1 / 4.4; 9.8 / 7.5, 7.0 / 4.7, 18.4 / 15.7
+constexpr bool pack_at_once(uint64_t items, uint32_t chip_waves, uint32_t n_req, uint32_t table_len) {
+  return 4 * items <= chip_waves || (n_req > 64 && n_req <= 1024 && table_len <= 8 * n_req);
+}
+
+// The same pause as hold_back_pause for a save of more than 64 requests that has read its slices at once, by the items the
+// requests have: more than half of the chip's wavefronts.  Us, graph replay and eager calls on warm data, pause 0 / 1 / 2 / 3:
+//   1280 of 8 KiB in 512   8.7 8.5 / 8.5 8.3 / 8.5 8.3 / 8.7 8.5    350 of 32 KiB in 100   10.2 9.7 / 10.1 9.3 / 9.8 9.3 / 9.8 9.1
+//   3000 of 4 KiB in 1000  12.0 11.3 / 11.9 11.3 / 11.8 11.2 / 11.6 10.9    1500 of 8 KiB in 300  10.1 9.6 / 10.5 10.1 / 9.9 9.4 / 10.1 9.6
+//   300 of 32 KiB in 200   7.2 7.2 / 7.2 7.1 / 7.3 7.1 / 7.6 7.3
+// and with half of the chip's, 1024 of 8 KiB in 256, 6.3 6.3 / 6.5 6.4 / 6.8 6.6; 150 of 32 KiB in 70 5.5 5.3 / 5.7 5.5 / 5.9 5.7.
+constexpr uint32_t pack_pause(uint32_t items, uint32_t chip_waves) { return 2 * items > chip_waves ? 2 : 0; }
 
 // Whether a head-major pool goes through LDS tiles or is moved directly, where it is not moved as line tiles
 // (as_line_tiles); where this holds an ordered restore keeps staging order.  On the whole GPU it pays while a row is shorter

@@ -561,7 +561,8 @@ hipError_t launch_layer(const Launch &L, uint64_t entry_quarters, uint32_t lds, 
       }
       if constexpr (S::WG == kWgThreads) {
         if (scan_reads<DIR>(L, m, a.n_req, move_wave_items(L, m))) {
-          [[maybe_unused]] const bool count_first = move_wave_items(L, m) > pack_at_once(m.chip_waves);
+          [[maybe_unused]] const bool count_first =
+              !pack_at_once(move_wave_items(L, m), m.chip_waves, a.n_req, m.table_len);
           if (a.n_req <= kWave) {
             if constexpr (DIR == kPack) {
               separate_entries(L, a.n_req, 0, &w, &n_wgs);
@@ -1078,7 +1079,7 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
       if (one || ahead || few_requests(R, m, n_req)) separate_entries(R, n_req, lead, &w, &n_wgs);
       if (one) return launch_ring_shape<S, DIR, kOne>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
       if constexpr (DIR == kPack && S::WG == kWgThreads) {
-        if (ahead && move_wave_items(R, m) > pack_at_once(m.chip_waves))
+        if (ahead && !pack_at_once(move_wave_items(R, m), m.chip_waves, n_req, m.table_len))
           return launch_ring_shape<S, DIR, kFewCounted>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
         if (ahead) return launch_ring_shape<S, DIR, kFewAhead>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
       }

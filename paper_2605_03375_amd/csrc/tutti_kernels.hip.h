@@ -1666,16 +1666,16 @@ __device__ __forceinline__ Preload<U> preload_first(const MoveArgs &a, uint32_t 
 // A pack in table order (reads_under_scan): the launch gives every wavefront one item at most, so the order does not matter to
 // the memory, and where an item's bytes sit follows from the table alone: they are read while the requests are being scanned,
 // instead of behind the scan, the owner and the block id: small saves are bound by that chain of dependent loads.  In a table
-// longer than the requests' blocks some are read for nothing; tables of more than pack_at_once items are therefore read when the
-// sum of the counts has said that the position is one of the requests' (and K and V of a position side by side: what there is
-// to do then lies in the first workgroups).  The item's block id is asked for behind the counts: in front of them saves of 72
-// to 150 blocks took 0.3 us longer.
+// longer than the requests' blocks some are read for nothing; where pack_at_once says no they are therefore read when the sum of
+// the counts has said that the position is one of the requests' (and K and V of a position side by side: what there is to do
+// then lies in the first workgroups).  The item's block id is asked for behind the counts: in front of them saves of 72 to 150
+// blocks took 0.3 us longer.
 // Graph replay, 32 KiB blocks, us, in staging order / read at once whatever the table's length / so: 64 blocks in 30 requests
 // 5.4 / 3.8 / 3.8, with a table of 384 blocks 5.2 / 6.7 / 4.5; 150 in 8 6.2 / 5.1 / 5.1, table of 384 6.6 / 8.1 / 5.9; 2 in 2, table of
-// 384 3.7 / 6.1 / 3.7; 128 in 128 6.9 / 5.4 / 5.4, table of 384 6.8 / 8.0 / 6.1; 300 in 200 10.4 / 8.0 / 9.1; 1280 of 8 KiB in 512
-// 11.0 / 9.5 / 10.4.  (Of more than 64 requests, the first quarter of the chip's items read at once and the others counted: waits
-// on both in one kernel made the short tables 0.3 us slower.)  With several items a wavefront, reading all K blocks first
-// loses (1000 blocks in 8 requests 24.3 / 25.5).
+// 384 3.7 / 6.1 / 3.7; 128 in 128 6.9 / 5.4 / 5.4; 300 in 200 10.4 / 8.0 / 8.2; 1280 of 8 KiB in 512 11.0 / 9.7 / 9.7.  (Of more than
+// 64 requests, the first quarter of the chip's items read at once and the others counted: waits on both in one kernel made the
+// short tables 0.3 us slower.)  With several items a wavefront, reading all K blocks first loses (1000 blocks in 8 requests
+// 24.3 / 25.5).
 constexpr int pack_order(int reqs) { return counts_first(reqs) ? kPairOrder : kTableOrder; }
 
 template <int U, int WG, int REQS>
@@ -2263,6 +2263,8 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
         atomicOr(m.status, TUTTI_ST_STAGE_CAP);
   }
   if (copies) {
+    if (DIR == kPack && REQS == kManyAhead)
+      hold_back(pack_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves));
     if (DIR == kPack && reads_under_scan(REQS))
       store_pack<HND, U, NT, WG, REQS, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
     else if (PIECES)

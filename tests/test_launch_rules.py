@@ -25,6 +25,9 @@ extern "C" unsigned units_of(int ahead, unsigned block_bytes, unsigned blocks, u
                              int short_rows) {
   return tutti::budget_units(ahead != 0, block_bytes, blocks, budget, ordered != 0, short_rows != 0);
 }
+extern "C" int at_once_of(unsigned long long items, unsigned chip, unsigned n_req, unsigned table_len) {
+  return tutti::pack_at_once(items, chip, n_req, table_len);
+}
 extern "C" int pieces_of(int whole_gpu, unsigned units) { return tutti::pieces_shape(whole_gpu != 0, units); }
 """
 CHIP = 8192  # wavefronts of a whole-GPU launch on 256 compute units
@@ -151,3 +154,13 @@ def test_entries_apart_from_small_launches_only(rules):
         for n_req, last in ((1, 2 * cus), (2, 5 * cus // 2), (64, 5 * cus // 2)):
             assert rules.apart_of(1, cus, n_req) and rules.apart_of(last, cus, n_req)
             assert not rules.apart_of(last + 1, cus, n_req) and not rules.apart_of(8 * cus, cus, n_req)
+
+
+def test_long_tables_are_counted_first(rules):
+    """Up to 64 requests beyond a quarter of the chip; of more, tables of more than 8 blocks a request."""
+    rules.at_once_of.argtypes = [ctypes.c_ulonglong] + [ctypes.c_uint] * 3
+    for n_req, longest in ((2, 0), (64, 0), (65, 520), (512, 4096), (1024, 8192), (1025, 0), (2048, 0)):
+        for table in (1, 8, 520, 521, 4096, 4097, 8192, 8193, 0xffffffff):
+            assert rules.at_once_of(CHIP // 4, CHIP, n_req, table)
+            assert rules.at_once_of(CHIP // 4 + 1, CHIP, n_req, table) == (table <= longest)
+            assert rules.at_once_of(1 << 33, CHIP, n_req, table) == (table <= longest)
