@@ -205,8 +205,9 @@ def check_sqe(orc, c, ext, o_ext, o_tot, layer=0, stage_addr=0x7F1200000000, sgl
 
 
 def check_layer_restore(orc, c, layer=0, cu_budget=0, stage_addr=0x7F1200000000, sgl_id=7, seed=5, sqe_cap=None,
-                        stage_cap=None, table_len=None, visit=None):
-    """visit: table positions in visiting order (numpy): both sides run their ordered restore on the same list."""
+                        stage_cap=None, table_len=None, visit=None, unread=False):
+    """visit: table positions in visiting order (numpy): both sides run their ordered restore on the same list, or the
+    oracle its plain one where the pool keeps staging order whatever the list says (unread)."""
     tl = c.table.size if table_len is None else table_len
     o_ext0, o_tot0 = orc.obj_layout(c.orc_pool(orc), c.orc_cfg(orc), c.n_blocks)
     nbytes = max(int(o_tot0[0]), 16)
@@ -237,10 +238,10 @@ def check_layer_restore(orc, c, layer=0, cu_budget=0, stage_addr=0x7F1200000000,
                                       c.d_file_id, layer, stage, scap, stage_addr, sgl_id, ext, tot, sqe, cap, d_visit,
                                       cu_budget, st)
         torch.cuda.synchronize()
-        o_ext, o_tot, o_sqe, o_st = orc.layer_restore_ordered(c.orc_pool(orc, ok, ov), c.orc_cfg(orc), c.n_blocks,
-                                                              c.table, c.file_id, layer, stage.cpu().numpy(),
-                                                              stage_addr, sgl_id, cap, visit, stage_cap=scap,
-                                                              table_len=tl)
+        o_args = (c.orc_pool(orc, ok, ov), c.orc_cfg(orc), c.n_blocks, c.table, c.file_id, layer, stage.cpu().numpy(),
+                  stage_addr, sgl_id, cap)
+        o_restore = orc.layer_restore if unread else lambda *a, **k: orc.layer_restore_ordered(*a, visit, **k)
+        o_ext, o_tot, o_sqe, o_st = o_restore(*o_args, stage_cap=scap, table_len=tl)
     assert ext.cpu().numpy()[: 32 * c.n_req].tobytes() == o_ext.tobytes()
     assert np.array_equal(tot.cpu().numpy().view(np.uint64), o_tot)
     n_written = min(n_sqe, cap)

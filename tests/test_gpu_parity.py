@@ -184,9 +184,14 @@ def test_head_major_line_tiles(orc, H, shape):
         H.check_layer_restore(orc, c, stage_cap=cap, seed=41)
 
 
-def test_head_major_lds_edge_cases(orc, H):
-    """Bad ids, a small staging buffer and the 2048-request limit through the LDS-staged path."""
-    say("hnd lds edges")
+@pytest.mark.parametrize("mode", [0, 2], ids=["auto", "lds"])
+def test_head_major_lds_edge_cases(orc, H, request, mode):
+    """Bad ids, a small staging buffer and the 2048-request limit, as line tiles and through the LDS-staged path (a knob of
+    the measurement library)."""
+    say("hnd lds edges, mode", mode)
+    if mode:
+        request.getfixturevalue("knobs")
+        B.tutti_set_hnd_mode(mode)
     table = np.array([3, 999, 5, 16, 7, 1], np.uint32)
     c = H.LayerCase(T=16, h=32, d=32, e=2, N=16, n_blocks=[4, 2], table=table, layout=1, name="hnd_bad_ids")
     ext, tot, o_ext, o_tot = H.check_layout(orc, c)
@@ -1071,21 +1076,31 @@ def test_scan_of_few_requests(orc, H, n_req):
         H.check_ring_layer(orc, c, layer=1, write=write, depth=3, first_slot=1, n_slots=2)
 
 
+@pytest.mark.parametrize("mode", [0, 2], ids=["auto", "lds"])
 @pytest.mark.parametrize("n_req", [2, 63, 64, 65, 127, 128, 129, 2047, 2048])
-def test_owner_among_mostly_empty_requests(orc, H, n_req):
+def test_owner_among_mostly_empty_requests(orc, H, request, n_req, mode):
     """An item's request is the last of those that share its offset: runs of empty requests in front of, between and behind
-    the few that have blocks, which sit on both sides of the 64 probes of a search among more than 64."""
-    say("owner among", n_req, "requests")
+    the few that have blocks, which sit on both sides of the 64 probes of a search among more than 64.  Slices, line tiles
+    (4 KiB blocks, rows of 32 bytes), or LDS tiles where the requests' offsets leave LDS for one (the measurement library)."""
+    say("owner among", n_req, "requests, mode", mode)
+    if mode:
+        request.getfixturevalue("knobs")
+        B.tutti_set_hnd_mode(mode)
     step = (n_req + 63) // 64
     n = np.zeros(n_req, np.uint32)
     n[[r for r in (1, step - 1, step, 2 * step - 1, 63 * step - 1, 63 * step, n_req // 2, n_req - 1) if 0 <= r < n_req]] = 9
     total = int(n.sum())
     table = np.random.default_rng(8700 + n_req).permutation(total + 5)[:total]
-    for d, layout in ((64, 0), (16, 1)):  # slices; tiles through LDS
-        c = H.LayerCase(T=16, h=4, d=d, e=2, N=total + 5, n_blocks=n, table=table, align=4096, chunk=8192, layout=layout,
+    for h, d, layout in ((4, 64, 0), (8, 16, 1)):
+        if mode and layout == 0:
+            continue
+        c = H.LayerCase(T=16, h=h, d=d, e=2, N=total + 5, n_blocks=n, table=table, align=4096, chunk=8192, layout=layout,
                         name=f"owner{n_req}l{layout}")
+        assert c.T * c.h * c.d * c.e >= 4096
         H.check_everything(orc, c)
         H.check_layer_restore(orc, c, cu_budget=2)
+    if mode:
+        return
     H.check_ring_layer(orc, H.LayerCase(T=16, h=4, d=64, e=2, N=total + 5, n_blocks=n, table=table, align=4096, chunk=8192),
                        layer=0, write=True, depth=1, first_slot=0, n_slots=1)
 
@@ -1756,8 +1771,19 @@ ORDERED_SHAPES = [
     (16, 8, 128, 2, 300, [40, 0, 7, 25, 1], 0, 0),     # 32 KiB blocks: eight whole slices each
     (16, 8, 128, 2, 300, [40, 0, 7, 25, 1], 1, 0),     # head-major, rows of 256 bytes: moved row by row, in order
     (16, 5, 40, 2, 200, [7, 0, 33, 1, 2], 0, 48),      # 6400-byte blocks: a ragged last slice, padded objects, stride
-    (16, 2, 16, 2, 128, [9, 30, 2], 1, 0),             # head-major through LDS tiles: the order is not used
+    (16, 2, 16, 2, 128, [9, 30, 2], 1, 0),             # head-major, 1 KiB blocks: row by row, in order
+    (16, 8, 16, 2, 128, [9, 30, 2], 1, 0),             # head-major, 4 KiB blocks of short rows: line tiles on the whole
+    (16, 16, 32, 2, 128, [9, 30, 2], 1, 0),            # GPU, where the list is not read; 16 KiB blocks
 ]
+
+
+def keeps_staging_order(c, budget):
+    """Whether an ordered restore of this case does not read its list: short head-major rows in tiles of 4 KiB and more (powers
+    of two all); under a CU budget rows of 16 bytes only, in tiles of 16 KiB and more on more than 16 compute units."""
+    row, T, h = c.d * c.e, c.T, c.h
+    if c.layout != 1 or any(x & (x - 1) for x in (row, T, h)) or not 16 <= row < (128 if budget == 0 else 32 if budget > 16 else 16):
+        return False
+    return min(T * h * row, 16384) >= (4096 if budget == 0 else 16384)
 
 
 @pytest.mark.parametrize("shape", ORDERED_SHAPES, ids=lambda s: f"T{s[0]}h{s[1]}d{s[2]}L{s[6]}")
@@ -1771,7 +1797,6 @@ def test_layer_restore_in_a_given_order(orc, H, shape):
     n = int(np.sum(nb))
     c = H.LayerCase(T=T, h=h, d=d, e=e, N=N, n_blocks=nb, table=rng.permutation(N)[:n], chunk=8192, L=3,
                     layout=layout, pad=pad, name="ordered")
-    through_lds = layout == 1 and d * e < 128
     # the device's own order for this table, checked against the oracle's, then used by both
     work = torch.zeros(B.tutti_table_order_work_bytes(N), dtype=torch.uint8, device=H.DEV)
     d_visit = torch.zeros(n, dtype=torch.int32, device=H.DEV)
@@ -1783,33 +1808,35 @@ def test_layer_restore_in_a_given_order(orc, H, shape):
     for k, visit in enumerate(perms):
         for budget in (0, 3):
             H.check_layer_restore(orc, c, layer=k % 3, cu_budget=budget, visit=visit, seed=20 + k)
-    if through_lds:
-        return            # lists that are not permutations mean something only where the list is read
     # lists that are not permutations: out of range, twice, missing
     odd = by_id.copy()
     odd[0] = n
     odd[1] = 0xFFFFFFFF
     odd[2] = odd[3]
     odd[n - 1] = odd[n - 2]
-    H.check_layer_restore(orc, c, visit=odd, seed=31)
-    H.check_layer_restore(orc, c, visit=np.zeros(n, np.uint32), seed=32)
+    for budget in (0, 3):
+        unread = keeps_staging_order(c, budget)
+        assert unread == (budget == 0 and layout == 1 and d * e < 128 and T * h * d * e >= 4096)
+        H.check_layer_restore(orc, c, visit=odd, seed=31, cu_budget=budget, unread=unread)
+        H.check_layer_restore(orc, c, visit=np.zeros(n, np.uint32), seed=32, cu_budget=budget, unread=unread)
+    unread = keeps_staging_order(c, 0)
     # a table shorter than the requests claim: the list still has table_len entries, some now beyond the live blocks
     for tl in (n - 1, int(nb[0]), int(nb[0]) - 1, 0):
-        H.check_layer_restore(orc, c, table_len=tl, visit=rng.permutation(n).astype(np.uint32), seed=33)
+        H.check_layer_restore(orc, c, table_len=tl, visit=rng.permutation(n).astype(np.uint32), seed=33, unread=unread)
     # staging and entry capacities too small, with the first block of the request that does not fit not listed
     o_ext, _ = orc.obj_layout(c.orc_pool(orc), c.orc_cfg(orc), c.n_blocks)
     last = c.n_req - 1
     cap = int(o_ext["stage_off"][last]) + 16
-    H.check_layer_restore(orc, c, stage_cap=cap, sqe_cap=3, visit=by_id, seed=34)
+    H.check_layer_restore(orc, c, stage_cap=cap, sqe_cap=3, visit=by_id, seed=34, unread=unread)
     skip_first = by_id.copy()
     skip_first[skip_first == int(o_ext["table_off"][last])] = 0
-    H.check_layer_restore(orc, c, stage_cap=cap, visit=skip_first, seed=35)
+    H.check_layer_restore(orc, c, stage_cap=cap, visit=skip_first, seed=35, unread=unread)
     # ids out of range in the table
     bad = c.table.copy()
     bad[[1, n // 2]] = [N, 0xFFFFFFFF]
     cb = H.LayerCase(T=T, h=h, d=d, e=e, N=N, n_blocks=nb, table=bad, chunk=8192, L=3, layout=layout, pad=pad,
                      name="ordered_bad_ids")
-    H.check_layer_restore(orc, cb, visit=by_id, seed=36)
+    H.check_layer_restore(orc, cb, visit=by_id, seed=36, unread=unread)
     # no list: the plain restore
     st = H.new_status()
     k2, v2 = c.k_dev.clone(), c.v_dev.clone()
