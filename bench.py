@@ -397,6 +397,8 @@ def main():
         out["copy_ceiling"]["us_per_copy_between_two_regions"] = round(median(ts), 2)
     if not args.no_corun:
         out["per_cu_limits"] = per_cu_limits(torch, B, dev)
+        # the size of a budgeted write-behind flush of 512 blocks: what 32 compute units copy of it when they do nothing else
+        out["per_cu_limits_32MiB"] = per_cu_limits(torch, B, dev, nbytes=32 << 20, budgets=(32,), n_buf=16)
         out["corun"] = {
             "note": "config 5: the restore of config 2 on one stream beside a bf16 GEMM looping on another, each "
                     "timed while the other outlasts it; budget = cu_budget argument, domain = a CU-masked stream "

@@ -44,9 +44,9 @@ constexpr uint32_t hold_back_pause(uint32_t items, uint32_t chip_waves, uint32_t
 }
 
 // Slice of a CU-budgeted copy of `blocks` blocks (K and V each), in pieces of 1 KiB.  What a compute unit moves depends on
-// the length of a wavefront's run of loads and of stores, not on the bytes in flight: a plain cold copy on 8 / 32 / 64
-// compute units (1024 threads each) reaches 62 / 52 / 44 GB/s per unit with 8 KiB runs, with one item in flight as with
-// two, and 72 / 64 / 56 with 16 KiB.  But a longer run also ends later: up to about 1024 items, in a working set that the
+// the length of a wavefront's run of loads and of stores, not on the bytes in flight: a plain cold copy of 256 MiB on 8 / 32 /
+// 64 compute units (1024 threads each) reaches 61 / 52 / 45 GB/s per unit with 8 KiB runs, with one item in flight as with
+// two, and 75 / 63 / 56 with 16 KiB (of 32 MiB 61 / 51 / 43 and 75 / 60 / 49).  But a longer run also ends later: up to about 1024 items, in a working set that the
 // last-level cache holds, 8 KiB are the better where the launch reads its first slices ahead (`ahead`), and without that
 // unless every wavefront gets one item at most or the compute units are many.  16 / 8 KiB, us, 32 KiB blocks:
 //   restore of 4 requests   64 blocks on 32 units 6.5 / 5.1    128 on 64  7.9 / 5.7    128 on 8  31.0 / 30.4

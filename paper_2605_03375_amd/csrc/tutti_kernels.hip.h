@@ -2542,6 +2542,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_copy(unsigned
       u32x4 buf[U];
 #pragma unroll
       for (int k = 0; k < U; ++k) buf[k] = ld16<NT>(src + o0 + k * (kWave * 16ull));
+      if (U > 4) __builtin_amdgcn_sched_barrier(0);  // one run of loads, one of stores, as in load_slice and store_slice
 #pragma unroll
       for (int k = 0; k < U; ++k) st16<NT>(dst + o0 + k * (kWave * 16ull), buf[k]);
     } else {
