@@ -46,9 +46,10 @@ constexpr uint32_t hold_back_pause(uint32_t items, uint32_t chip_waves, uint32_t
 // Slice of a CU-budgeted copy of `blocks` blocks (K and V each), in pieces of 1 KiB.  What a compute unit moves depends on
 // the length of a wavefront's run of loads and of stores, not on the bytes in flight: a plain cold copy of 256 MiB on 8 / 32 /
 // 64 compute units (1024 threads each) reaches 61 / 52 / 45 GB/s per unit with 8 KiB runs, with one item in flight as with
-// two, and 75 / 63 / 56 with 16 KiB (of 32 MiB 61 / 51 / 43 and 75 / 60 / 49).  But a longer run also ends later: up to about 1024 items, in a working set that the
-// last-level cache holds, 8 KiB are the better where the launch reads its first slices ahead (`ahead`), and without that
-// unless every wavefront gets one item at most or the compute units are many.  16 / 8 KiB, us, 32 KiB blocks:
+// two, and 75 / 63 / 56 with 16 KiB (of 32 MiB 61 / 51 / 43 and 75 / 60 / 49).  But a longer run also ends later: up to about
+// 1024 items, in a working set that the last-level cache holds, 8 KiB are the better where the launch reads its first slices
+// ahead (`ahead`), and without that unless every wavefront gets one item at most or the compute units are many.  16 / 8 KiB,
+// us, 32 KiB blocks:
 //   restore of 4 requests   64 blocks on 32 units 6.5 / 5.1    128 on 64  7.9 / 5.7    128 on 8  31.0 / 30.4
 //                          256 on 32  20.2 / 20.5             384 on 8  90.9 / 92.4   1024 on 32  71.5 / 79.4
 //   save of 4 requests      64 on 8  14.2 / 15.4               64 on 32  6.3 / 7.0     128 on 8  32.4 / 29.2
@@ -114,7 +115,8 @@ constexpr bool pack_at_once(uint64_t items, uint32_t chip_waves, uint32_t n_req,
 // The same pause as hold_back_pause for a save of more than 64 requests that has read its slices at once, by the items the
 // requests have: more than half of the chip's wavefronts.  Us, graph replay and eager calls on warm data, pause 0 / 1 / 2 / 3:
 //   1280 of 8 KiB in 512   8.7 8.5 / 8.5 8.3 / 8.5 8.3 / 8.7 8.5    350 of 32 KiB in 100   10.2 9.7 / 10.1 9.3 / 9.8 9.3 / 9.8 9.1
-//   3000 of 4 KiB in 1000  12.0 11.3 / 11.9 11.3 / 11.8 11.2 / 11.6 10.9    1500 of 8 KiB in 300  10.1 9.6 / 10.5 10.1 / 9.9 9.4 / 10.1 9.6
+//   3000 of 4 KiB in 1000  12.0 11.3 / 11.9 11.3 / 11.8 11.2 / 11.6 10.9
+//   1500 of 8 KiB in 300   10.1 9.6 / 10.5 10.1 / 9.9 9.4 / 10.1 9.6
 //   300 of 32 KiB in 200   7.2 7.2 / 7.2 7.1 / 7.3 7.1 / 7.6 7.3
 // and with half of the chip's, 1024 of 8 KiB in 256, 6.3 6.3 / 6.5 6.4 / 6.8 6.6; 150 of 32 KiB in 70 5.5 5.3 / 5.7 5.5 / 5.9 5.7.
 constexpr uint32_t pack_pause(uint32_t items, uint32_t chip_waves) { return 2 * items > chip_waves ? 2 : 0; }
