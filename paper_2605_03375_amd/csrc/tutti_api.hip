@@ -392,10 +392,10 @@ hipError_t launch_move_lds(const Launch &L, uint32_t lds, hipStream_t s, const M
   case PT:                                                                                                        \
     if (L.wg_threads == kWgThreads)                                                                               \
       hipLaunchKernelGGL((k_move_lds<DIR, PT, kWgThreads>), dim3(L.grid), dim3(kWgThreads), lds, s, m, ext,        \
-                         n_req);                                                                                  \
+                         n_req, L.grid);                                                                                  \
     else                                                                                                          \
       hipLaunchKernelGGL((k_move_lds<DIR, PT, kBudgetWgThreads>), dim3(L.grid), dim3(kBudgetWgThreads), lds, s,    \
-                         m, ext, n_req);                                                                          \
+                         m, ext, n_req, L.grid);                                                                          \
     break;
   switch (L.unroll) {
     TUTTI_LDS_CASE(1)
@@ -514,12 +514,12 @@ hipError_t launch_move(const Launch &L, uint32_t lds, hipStream_t s, const MoveA
     using S = decltype(sh);
     if (L.pieces) {  // never through the kernel of whole slices
       if constexpr (has_pieces<S> && HND != kLines) {
-        hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG, true>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req);
+        hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG, true>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req, L.grid);
         return hipGetLastError();
       }
       return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req);
+    hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req, L.grid);
     return hipGetLastError();
   });
 }
@@ -697,10 +697,10 @@ int tutti_sqe_build(const tutti_pool *pool, const tutti_objcfg *cfg, const tutti
   const ScanGeom geom{bb, cfg->align, cfg->chunk_bytes};
   if (E.wg_threads == kWgThreads)
     hipLaunchKernelGGL(k_sqe<kWgThreads>, dim3(E.grid), dim3(kWgThreads), req_lds_bytes(n_req),
-                       static_cast<hipStream_t>(stream), q, geom, d_extents, n_req);
+                       static_cast<hipStream_t>(stream), q, geom, d_extents, n_req, E.grid);
   else
     hipLaunchKernelGGL(k_sqe<kBudgetWgThreads>, dim3(E.grid), dim3(kBudgetWgThreads), req_lds_bytes(n_req),
-                       static_cast<hipStream_t>(stream), q, geom, d_extents, n_req);
+                       static_cast<hipStream_t>(stream), q, geom, d_extents, n_req, E.grid);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
 }
@@ -821,7 +821,7 @@ int tutti_sgl_table_build(const tutti_pool *pool, uint64_t k_addr, uint64_t v_ad
   uint64_t need = (2ull * pool->num_blocks + kWgThreads - 1) / kWgThreads;
   const uint64_t lim = static_cast<uint64_t>(cus) * 8;
   const uint32_t grid = static_cast<uint32_t>(need < lim ? need : lim);
-  hipLaunchKernelGGL(k_sgl_table, dim3(grid), dim3(kWgThreads), 0, static_cast<hipStream_t>(stream), a);
+  hipLaunchKernelGGL(k_sgl_table, dim3(grid), dim3(kWgThreads), 0, static_cast<hipStream_t>(stream), a, grid);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
 }
@@ -851,10 +851,10 @@ int tutti_sqe_build_direct(const tutti_pool *pool, const tutti_objcfg *cfg, cons
   const ScanGeom geom{bb, cfg->align, cfg->chunk_bytes};
   if (E.wg_threads == kWgThreads)
     hipLaunchKernelGGL(k_sqe_direct<kWgThreads>, dim3(E.grid), dim3(kWgThreads), req_lds_bytes(n_req),
-                       static_cast<hipStream_t>(stream), q, d, geom, d_extents, n_req);
+                       static_cast<hipStream_t>(stream), q, d, geom, d_extents, n_req, E.grid);
   else
     hipLaunchKernelGGL(k_sqe_direct<kBudgetWgThreads>, dim3(E.grid), dim3(kBudgetWgThreads), req_lds_bytes(n_req),
-                       static_cast<hipStream_t>(stream), q, d, geom, d_extents, n_req);
+                       static_cast<hipStream_t>(stream), q, d, geom, d_extents, n_req, E.grid);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
 }
@@ -918,10 +918,10 @@ int tutti_iocb_fill_direct(const tutti_ring *ring, uint32_t first_slot, uint32_t
   const ScanGeom geom{bb, cfg->align, cfg->chunk_bytes};
   if (E.wg_threads == kWgThreads)
     hipLaunchKernelGGL(k_iocb_fill<kWgThreads>, dim3(E.grid), dim3(kWgThreads), req_lds_bytes(n_req),
-                       static_cast<hipStream_t>(stream), g, q, d, geom, d_extents, n_req);
+                       static_cast<hipStream_t>(stream), g, q, d, geom, d_extents, n_req, E.grid);
   else
     hipLaunchKernelGGL(k_iocb_fill<kBudgetWgThreads>, dim3(E.grid), dim3(kBudgetWgThreads), req_lds_bytes(n_req),
-                       static_cast<hipStream_t>(stream), g, q, d, geom, d_extents, n_req);
+                       static_cast<hipStream_t>(stream), g, q, d, geom, d_extents, n_req, E.grid);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
 }
@@ -975,7 +975,7 @@ int issue_io_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slots
   RingArgs g{ring->d_sq, static_cast<tutti_cq_hdr *>(ring->d_cq), ring->depth, first_slot, n_slots};
   const dim3 grid(L.grid + lead);
 #define TUTTI_ISSUE(U, WG, PIECES) \
-  hipLaunchKernelGGL((k_issue_io<U, WG, PIECES>), grid, dim3(WG), 0, s, g, gd, a)
+  hipLaunchKernelGGL((k_issue_io<U, WG, PIECES>), grid, dim3(WG), 0, s, g, gd, a, grid.x)
   if (L.wg_threads == kWgThreads) {
     if (pieces) TUTTI_ISSUE(kDefaultUnroll, kWgThreads, true); else TUTTI_ISSUE(kDefaultUnroll, kWgThreads, false);
   } else {
@@ -1176,7 +1176,7 @@ int tutti_wait_cqe(const tutti_ring *ring, uint32_t slot, uint32_t *d_flag, void
   if (rc) return rc;
   if (!d_flag) return TUTTI_EINVAL;
   hipLaunchKernelGGL(k_cq_check, dim3(1), dim3(kWave), 0, static_cast<hipStream_t>(stream), ring->d_sq, ring->depth, slot,
-                     1u, d_flag);
+                     1u, d_flag, 1u);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
 }
@@ -1187,9 +1187,9 @@ int tutti_wait_cqe_range(const tutti_ring *ring, uint32_t first_slot, uint32_t n
   if (rc) return rc;
   if (n_slots > 0 && !d_flags) return TUTTI_EINVAL;
   if (n_slots == 0) return TUTTI_OK;
-  const uint32_t grid = (n_slots + kWgThreads - 1) / kWgThreads;
-  hipLaunchKernelGGL(k_cq_check, dim3(grid < 64u ? grid : 64u), dim3(kWgThreads), 0, static_cast<hipStream_t>(stream),
-                     ring->d_sq, ring->depth, first_slot, n_slots, d_flags);
+  const uint32_t need = (n_slots + kWgThreads - 1) / kWgThreads, grid = need < 64u ? need : 64u;
+  hipLaunchKernelGGL(k_cq_check, dim3(grid), dim3(kWgThreads), 0, static_cast<hipStream_t>(stream), ring->d_sq, ring->depth,
+                     first_slot, n_slots, d_flags, grid);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
 }

@@ -512,7 +512,13 @@ __device__ __forceinline__ bool lds_from_extents(const tutti_extent *__restrict_
       if (r + 1 < n_req) bad = bad || l.sqe_base[r + 1] != nx_sqe[k] || l.table_off[r + 1] != nx_tab[k];
     }
   }
-  const bool any_bad = __syncthreads_or(bad ? 1 : 0) != 0;
+  __shared__ uint32_t bad_waves[WG / kWave];
+  const bool bad_wave = __ballot(bad) != 0;
+  if (lane == 0) bad_waves[threadIdx.x / kWave] = bad_wave ? 1u : 0u;
+  __syncthreads();
+  bool any_bad = false;
+#pragma unroll
+  for (uint32_t w = 0; w < WG / kWave; ++w) any_bad = any_bad || bad_waves[w] != 0;
   if (any_bad && blockIdx.x == 0 && threadIdx.x == 0 && status) atomicOr(status, TUTTI_ST_BAD_EXTENT);
   return !any_bad;
 }
@@ -528,10 +534,11 @@ __device__ __forceinline__ bool lds_from_extents(const tutti_extent *__restrict_
 //   - blocks that would end beyond their object are skipped by the copy loop (TUTTI_ST_BAD_EXTENT).
 // All threads stage the raw fields, then the first wavefront scans n_blocks (64 requests per pass) into
 // blk_off[], the numbering of the work items.  Workgroup 0 reports.
+template <int WG>
 __device__ __forceinline__ void lds_from_caller_extents(const tutti_extent *__restrict__ ext, uint32_t n_req, ReqLds l,
                                                         uint32_t table_len, uint32_t block_bytes, uint64_t stage_cap,
                                                         uint32_t *__restrict__ status) {
-  for (uint32_t r = threadIdx.x; r < n_req; r += blockDim.x) {
+  for (uint32_t r = threadIdx.x; r < n_req; r += WG) {
     const tutti_extent e = ext[r];
     l.stage_off[r] = e.stage_off;
     l.obj_bytes[r] = e.obj_bytes;
@@ -691,11 +698,12 @@ struct SqeHead {
   bool live;     // the lane has a first quarter
 };
 
+template <int WG>
 __device__ __forceinline__ SqeHead sqe_head(const SqeArgs a, const ReqLds l, uint32_t n_req, uint32_t first_wg) {
   const uint32_t n_sqe = l.sqe_base[n_req];
   const uint32_t n_write = n_sqe < a.sqe_cap ? n_sqe : a.sqe_cap;
   SqeHead h;
-  h.q = static_cast<uint64_t>(blockIdx.x - first_wg) * blockDim.x + threadIdx.x;
+  h.q = static_cast<uint64_t>(blockIdx.x - first_wg) * WG + threadIdx.x;
   h.live = h.q < 4ull * n_write;
   h.r = 0;
   h.fid = 0;
@@ -706,6 +714,7 @@ __device__ __forceinline__ SqeHead sqe_head(const SqeArgs a, const ReqLds l, uin
   return h;
 }
 
+template <int WG>
 __device__ __forceinline__ void emit_sqes(const SqeArgs a, const ReqLds l, uint32_t n_req, uint32_t first_wg,
                                           uint32_t n_wgs, const SqeHead h) {
   const uint32_t n_sqe = l.sqe_base[n_req];
@@ -714,7 +723,7 @@ __device__ __forceinline__ void emit_sqes(const SqeArgs a, const ReqLds l, uint3
   if (n_sqe > a.sqe_cap && wg == 0 && threadIdx.x == 0 && a.status) atomicOr(a.status, TUTTI_ST_SQE_CAP);
   if (!h.live) return;
   const uint64_t n_quarters = 4ull * n_write;
-  const uint64_t stride = static_cast<uint64_t>(n_wgs) * blockDim.x;
+  const uint64_t stride = static_cast<uint64_t>(n_wgs) * WG;
   u32x4 *out = reinterpret_cast<u32x4 *>(a.sqe);
   const uint32_t part = static_cast<uint32_t>(h.q & 3);  // the stride is a multiple of 4: the same quarter every pass
   out[h.q] = sqe_quarter(a, l, h.r, static_cast<uint32_t>(h.q >> 2), part, h.fid);
@@ -741,13 +750,13 @@ struct SglArgs {
   uint32_t cap;
 };
 
-__global__ __launch_bounds__(kWgThreads) void k_sgl_table(const SglArgs a) {
+__global__ __launch_bounds__(kWgThreads) void k_sgl_table(const SglArgs a, uint32_t n_wgs) {
   const uint64_t n = 2ull * a.num_blocks;
   if (n > a.cap && blockIdx.x == 0 && threadIdx.x == 0 && a.status) atomicOr(a.status, TUTTI_ST_SQE_CAP);
   const uint64_t n_write = n < a.cap ? n : a.cap;
-  const uint64_t stride = static_cast<uint64_t>(gridDim.x) * blockDim.x;
+  const uint64_t stride = static_cast<uint64_t>(n_wgs) * kWgThreads;
   u32x4 *out = reinterpret_cast<u32x4 *>(a.table);
-  for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n_write; i += stride) {
+  for (uint64_t i = static_cast<uint64_t>(blockIdx.x) * kWgThreads + threadIdx.x; i < n_write; i += stride) {
     const bool v_plane = i >= a.num_blocks;
     const uint64_t b = v_plane ? i - a.num_blocks : i;
     const uint64_t addr = (v_plane ? a.v_addr : a.k_addr) + b * a.block_stride;
@@ -840,10 +849,11 @@ struct DirectHead {
   bool live;
 };
 
+template <int WG>
 __device__ __forceinline__ DirectHead direct_head(const SqeArgs a, const DirectArgs d, const ReqLds l, uint32_t n_req,
                                                   uint64_t n_write, uint32_t first_wg, uint32_t n_wgs) {
   const uint64_t n_quarters = 4ull * n_write;
-  const uint64_t per_pass = blockDim.x;  // quarters one workgroup writes per pass: 4 KiB for 256 threads
+  constexpr uint64_t per_pass = WG;  // quarters one workgroup writes per pass: 4 KiB for 256 threads
   const uint64_t passes = (n_quarters + per_pass * n_wgs - 1) / (per_pass * n_wgs);
   const uint64_t begin = static_cast<uint64_t>(blockIdx.x - first_wg) * passes * per_pass;
   DirectHead h;
@@ -858,11 +868,11 @@ __device__ __forceinline__ DirectHead direct_head(const SqeArgs a, const DirectA
   return h;
 }
 
-template <typename Dst>
+template <int WG, typename Dst>
 __device__ __forceinline__ void emit_direct_entries(const SqeArgs a, const DirectArgs d, const ReqLds l, uint32_t n_req,
                                                     const DirectHead h, Dst dst) {
   if (!h.live) return;
-  const uint64_t per_pass = blockDim.x;
+  constexpr uint64_t per_pass = WG;
   uint64_t q = h.q;
   uint32_t i = static_cast<uint32_t>(q >> 2);
   const uint32_t part = static_cast<uint32_t>(q & 3);  // per_pass is a multiple of 4: the same quarter every pass
@@ -884,20 +894,22 @@ __device__ __forceinline__ void emit_direct_entries(const SqeArgs a, const Direc
   }
 }
 
-__device__ __forceinline__ void emit_direct_sqes(const SqeArgs a, const DirectArgs d, const ReqLds l, uint32_t n_req) {
+template <int WG>
+__device__ __forceinline__ void emit_direct_sqes(const SqeArgs a, const DirectArgs d, const ReqLds l, uint32_t n_req,
+                                                 uint32_t n_wgs) {
   const uint64_t n_sqe = 2ull * l.table_off[n_req];
   const uint64_t n_write = n_sqe < a.sqe_cap ? n_sqe : a.sqe_cap;
   if (n_sqe > a.sqe_cap && blockIdx.x == 0 && threadIdx.x == 0 && a.status) atomicOr(a.status, TUTTI_ST_SQE_CAP);
   tutti_sqe *out = a.sqe;
-  emit_direct_entries(a, d, l, n_req, direct_head(a, d, l, n_req, n_write, 0, gridDim.x),
-                      [out](uint32_t i) { return out + i; });
+  emit_direct_entries<WG>(a, d, l, n_req, direct_head<WG>(a, d, l, n_req, n_write, 0, n_wgs),
+                          [out](uint32_t i) { return out + i; });
 }
 
 // ------------------------------------------------------------------------------------------
 // Rings.  An SQ slot is an IOCB: 64-byte header + 2048 contexts.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kWgThreads) void k_ring_init(tutti_iocb *sq, tutti_cq_hdr *cq, uint32_t depth) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  const uint32_t i = blockIdx.x * kWgThreads + threadIdx.x;
   if (i < depth) {
     u32x4 *h = reinterpret_cast<u32x4 *>(&sq[i].hdr);
     const u32x4 zero = {0u, 0u, 0u, 0u};
@@ -927,19 +939,21 @@ __device__ __forceinline__ uint64_t iocb_fill_count(const RingArgs &g, const Req
   return n_ctx < cap ? n_ctx : cap;
 }
 
+template <int WG>
 __device__ __forceinline__ DirectHead iocb_head(const RingArgs g, const SqeArgs a, const DirectArgs d, const ReqLds l,
                                                 uint32_t n_req, uint32_t first_wg, uint32_t n_wgs) {
-  return direct_head(a, d, l, n_req, iocb_fill_count(g, l, n_req), first_wg, n_wgs);
+  return direct_head<WG>(a, d, l, n_req, iocb_fill_count(g, l, n_req), first_wg, n_wgs);
 }
 
+template <int WG>
 __device__ __forceinline__ void emit_iocbs(const RingArgs g, const SqeArgs a, const DirectArgs d, const ReqLds l,
                                            uint32_t n_req, uint32_t first_wg, uint32_t n_wgs, const DirectHead h) {
   const uint64_t n_ctx = 2ull * l.table_off[n_req];
   const uint64_t cap = static_cast<uint64_t>(g.n_slots) * TUTTI_IOCB_SLOTS;
   const uint64_t n_fill = iocb_fill_count(g, l, n_req);
-  const uint64_t tid = static_cast<uint64_t>(blockIdx.x - first_wg) * blockDim.x + threadIdx.x;
+  const uint64_t tid = static_cast<uint64_t>(blockIdx.x - first_wg) * WG + threadIdx.x;
   if (n_ctx > cap && tid == 0 && a.status) atomicOr(a.status, TUTTI_ST_SQE_CAP);
-  const uint64_t stride = static_cast<uint64_t>(n_wgs) * blockDim.x;
+  const uint64_t stride = static_cast<uint64_t>(n_wgs) * WG;
   for (uint64_t b = tid; b < g.n_slots; b += stride) {  // one thread per IOCB header
     const uint64_t lo = b * TUTTI_IOCB_SLOTS;
     uint64_t cnt = n_fill > lo ? n_fill - lo : 0;
@@ -952,7 +966,7 @@ __device__ __forceinline__ void emit_iocbs(const RingArgs g, const SqeArgs a, co
     hd->opcode = a.opcode;
   }
   const RingArgs ring = g;
-  emit_direct_entries(a, d, l, n_req, h, [ring](uint32_t i) {
+  emit_direct_entries<WG>(a, d, l, n_req, h, [ring](uint32_t i) {
     return &ring.sq[(ring.first_slot + i / TUTTI_IOCB_SLOTS) % ring.depth].ioctx[i % TUTTI_IOCB_SLOTS];
   });
 }
@@ -960,11 +974,11 @@ __device__ __forceinline__ void emit_iocbs(const RingArgs g, const SqeArgs a, co
 template <int WG>
 __global__ __launch_bounds__(WG) void k_iocb_fill(const RingArgs g, const SqeArgs a, const DirectArgs d,
                                                            const ScanGeom geom, const tutti_extent *__restrict__ ext,
-                                                           uint32_t n_req) {
+                                                           uint32_t n_req, uint32_t n_wgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, n_req);
   if (!lds_from_extents<WG>(ext, n_req, l, geom, a.status)) return;
-  emit_iocbs(g, a, d, l, n_req, 0, gridDim.x, iocb_head(g, a, d, l, n_req, 0, gridDim.x));
+  emit_iocbs<WG>(g, a, d, l, n_req, 0, n_wgs, iocb_head<WG>(g, a, d, l, n_req, 0, n_wgs));
 }
 
 constexpr uint32_t kPiece = kWave * 16u;  // what one wavefront instruction of 16 bytes per lane covers: 1 KiB
@@ -1126,7 +1140,7 @@ __device__ __forceinline__ void complete_iocbs(const RingArgs g, uint32_t lane);
 // workgroup more, in front, whose first wavefront completes them and leaves (see k_layer_ring).
 template <int U, int WG, bool PIECES>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_issue_io(const RingArgs g, const RingArgs done,
-                                                                             const IoArgs a) {
+                                                                             const IoArgs a, uint32_t grid) {
   constexpr uint32_t G = PIECES ? U : 1, kBatch = kWave / G;  // parts of an item, items decoded at once
   constexpr uint32_t kPart = PIECES ? kPiece : U * kPiece;
   const uint32_t lane = threadIdx.x & (kWave - 1);
@@ -1135,7 +1149,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_issue_io(cons
     if (threadIdx.x < kWave) complete_iocbs(done, threadIdx.x);
     return;
   }
-  const uint32_t wgs = gridDim.x - lead, wg = blockIdx.x - lead, wave = rfl(threadIdx.x / kWave);
+  const uint32_t wgs = grid - lead, wg = blockIdx.x - lead, wave = rfl(threadIdx.x / kWave);
   const uint32_t n_waves = wgs * (WG / kWave);
   const uint64_t n_parts = static_cast<uint64_t>(g.n_slots) * TUTTI_IOCB_SLOTS * a.parts;
   const uint32_t n_items = static_cast<uint32_t>((n_parts + G - 1) / G);  // the host checked this fits 32 bits
@@ -1222,8 +1236,8 @@ __global__ __launch_bounds__(kWave) void k_complete(const RingArgs g) {
 
 // wait_cqe for n slots from `slot` on (wrapping at depth): flag[i] <- 1 if IOCB (slot + i) % depth is DONE, else 0.
 __global__ __launch_bounds__(kWgThreads) void k_cq_check(const tutti_iocb *sq, uint32_t depth, uint32_t slot, uint32_t n,
-                                                          uint32_t *flag) {
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+                                                          uint32_t *flag, uint32_t n_wgs) {
+  for (uint32_t i = blockIdx.x * kWgThreads + threadIdx.x; i < n; i += n_wgs * kWgThreads) {
     const uint32_t st =
         __hip_atomic_load(&sq[(slot + i) % depth].hdr.state, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
     flag[i] = st == TUTTI_IOCB_DONE ? 1u : 0u;
@@ -1232,11 +1246,12 @@ __global__ __launch_bounds__(kWgThreads) void k_cq_check(const tutti_iocb *sq, u
 
 template <int WG>
 __global__ __launch_bounds__(WG) void k_sqe_direct(const SqeArgs a, const DirectArgs d, const ScanGeom geom,
-                                                            const tutti_extent *__restrict__ ext, uint32_t n_req) {
+                                                            const tutti_extent *__restrict__ ext, uint32_t n_req,
+                                                            uint32_t n_wgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, n_req);
   if (!lds_from_extents<WG>(ext, n_req, l, geom, a.status)) return;
-  emit_direct_sqes(a, d, l, n_req);
+  emit_direct_sqes<WG>(a, d, l, n_req, n_wgs);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -2150,36 +2165,36 @@ __global__ __launch_bounds__(kWgThreads) void k_layout(const LayoutArgs a) {
 
 template <int WG>
 __global__ __launch_bounds__(WG) void k_sqe(const SqeArgs a, const ScanGeom g,
-                                                     const tutti_extent *__restrict__ ext, uint32_t n_req) {
+                                                     const tutti_extent *__restrict__ ext, uint32_t n_req, uint32_t n_wgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, n_req);
   if (!lds_from_extents<WG>(ext, n_req, l, g, a.status)) return;
-  emit_sqes(a, l, n_req, 0, gridDim.x, sqe_head(a, l, n_req, 0));
+  emit_sqes<WG>(a, l, n_req, 0, n_wgs, sqe_head<WG>(a, l, n_req, 0));
 }
 
 // PIECES: the blocks are no whole number of slices (here and below).
 template <int DIR, int HND, int U, int NT, int WG, bool PIECES = false>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_move(const MoveArgs a, const tutti_extent *__restrict__ ext,
-                                                      uint32_t n_req) {
+                                                      uint32_t n_req, uint32_t n_wgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, n_req, true);
   Preload<U> pre;
   pre.valid = false;
-  if (DIR == kUnpack && !PIECES && reads_ahead(U)) pre = preload_first<HND, U, NT, WG>(a, blockIdx.x, gridDim.x);
-  lds_from_caller_extents(ext, n_req, l, a.table_len, a.block_bytes, a.stage_cap, a.status);
+  if (DIR == kUnpack && !PIECES && reads_ahead(U)) pre = preload_first<HND, U, NT, WG>(a, blockIdx.x, n_wgs);
+  lds_from_caller_extents<WG>(ext, n_req, l, a.table_len, a.block_bytes, a.stage_cap, a.status);
   if (PIECES)
-    move_pieces<DIR, HND, U, NT, WG, true, false>(a, l, n_req, blockIdx.x, gridDim.x);
+    move_pieces<DIR, HND, U, NT, WG, true, false>(a, l, n_req, blockIdx.x, n_wgs);
   else
-    move_items<DIR, HND, U, NT, WG, kMany, true, kStagingOrder, false>(a, l, n_req, blockIdx.x, gridDim.x, pre);
+    move_items<DIR, HND, U, NT, WG, kMany, true, kStagingOrder, false>(a, l, n_req, blockIdx.x, n_wgs, pre);
 }
 
 template <int DIR, int PT, int WG>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, PT)) void k_move_lds(const MoveArgs a, const tutti_extent *__restrict__ ext,
-                                                  uint32_t n_req) {
+                                                  uint32_t n_req, uint32_t n_wgs) {
   extern __shared__ __align__(16) unsigned char smem[];
   const ReqLds l = carve_lds(smem, n_req, true);
-  lds_from_caller_extents(ext, n_req, l, a.table_len, a.block_bytes, a.stage_cap, a.status);
-  move_items_hnd_lds<DIR, PT, WG, kMany, true>(a, l, n_req, blockIdx.x, gridDim.x, smem + align16(req_lds_bytes(n_req)));
+  lds_from_caller_extents<WG>(ext, n_req, l, a.table_len, a.block_bytes, a.stage_cap, a.status);
+  move_items_hnd_lds<DIR, PT, WG, kMany, true>(a, l, n_req, blockIdx.x, n_wgs, smem + align16(req_lds_bytes(n_req)));
 }
 
 // One layer's restore (DIR = kUnpack) or save (DIR = kPack) in one launch: every workgroup redoes the
@@ -2230,9 +2245,9 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     const OneReq one = one_request(m, a, l, publish, entries, nullptr, FileArgs{0, 0, 0});
     SqeHead one_head;
     one_head.live = false;
-    if (entries) one_head = sqe_head(q, l, 1, 0);
+    if (entries) one_head = sqe_head<WG>(q, l, 1, 0);
     if (copies) move_request<DIR, HND, U, NT, WG, false>(m, one, wg, w.copy_wgs, pre);
-    if (entries) emit_sqes(q, l, 1, 0, w.sqe_wgs, one_head);
+    if (entries) emit_sqes<WG>(q, l, 1, 0, w.sqe_wgs, one_head);
     return;
   }
   if (reads_under_scan(REQS)) args_at_hand(m, a, w);
@@ -2254,7 +2269,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, a.n_req, false));
   SqeHead head;
   head.live = false;
-  if (blockIdx.x < w.sqe_wgs) head = sqe_head(q, l, a.n_req, 0);
+  if (blockIdx.x < w.sqe_wgs) head = sqe_head<WG>(q, l, a.n_req, 0);
   if (ORD && wg == 0 && m.status) {
     // requests whose objects do not fit the staging buffer are skipped by every item: report them here, once
     for (uint32_t r = threadIdx.x; r < a.n_req; r += WG)
@@ -2272,7 +2287,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     else
       move_items<DIR, HND, U, NT, WG, REQS, false, ORD ? kListOrder : kStagingOrder, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
   }
-  if (blockIdx.x < w.sqe_wgs) emit_sqes(q, l, a.n_req, 0, w.sqe_wgs, head);
+  if (blockIdx.x < w.sqe_wgs) emit_sqes<WG>(q, l, a.n_req, 0, w.sqe_wgs, head);
 }
 
 // First item of a wavefront in a retrieve of ONE request: its file bytes sit at
@@ -2354,9 +2369,9 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
     const OneReq one = one_request(m, a, l, publish, entries, q.file_id, f);
     DirectHead one_head;
     one_head.live = false;
-    if (entries) one_head = iocb_head(g, q, d, l, 1, lead, w.sqe_wgs);
+    if (entries) one_head = iocb_head<WG>(g, q, d, l, 1, lead, w.sqe_wgs);
     if (copies) move_request<DIR, kNhd, U, 3, WG, true>(m, one, bx - w.copy_first, w.copy_wgs, pre);
-    if (entries) emit_iocbs(g, q, d, l, 1, lead, w.sqe_wgs, one_head);
+    if (entries) emit_iocbs<WG>(g, q, d, l, 1, lead, w.sqe_wgs, one_head);
     return;
   }
   // chunk counts only matter for the published extents; the LDS copy gets file starts instead of staging offsets
@@ -2380,7 +2395,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
   if (any_number(REQS)) l.unordered = rfl(l.wraps()) != 0;
   DirectHead head;
   head.live = false;
-  if (bx < w.sqe_wgs) head = iocb_head(g, q, d, l, a.n_req, lead, w.sqe_wgs);
+  if (bx < w.sqe_wgs) head = iocb_head<WG>(g, q, d, l, a.n_req, lead, w.sqe_wgs);
   if (copies) {
     if (reads_under_scan(REQS) && __builtin_expect(rfl(l.wraps()) != 0, 0))
       pack_unordered(m, l, a.n_req, (bx - w.copy_first) * (WG / kWave) + rfl(threadIdx.x / kWave), w.copy_wgs * (WG / kWave));
@@ -2391,7 +2406,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
     else
       move_items<DIR, kNhd, U, 3, WG, REQS, false, kStagingOrder, true>(m, l, a.n_req, bx - w.copy_first, w.copy_wgs, pre);
   }
-  if (bx < w.sqe_wgs) emit_iocbs(g, q, d, l, a.n_req, lead, w.sqe_wgs, head);
+  if (bx < w.sqe_wgs) emit_iocbs<WG>(g, q, d, l, a.n_req, lead, w.sqe_wgs, head);
 }
 
 template <int DIR, int PT, int WG, int REQS>
@@ -2403,11 +2418,11 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, PT)) void k_layer_lds(co
                    m.table_len, m.status, blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [] {}, [](uint32_t) {});
   SqeHead head;
   head.live = false;
-  if (blockIdx.x < w.sqe_wgs) head = sqe_head(q, l, a.n_req, 0);
+  if (blockIdx.x < w.sqe_wgs) head = sqe_head<WG>(q, l, a.n_req, 0);
   if (blockIdx.x - w.copy_first < w.copy_wgs)
     move_items_hnd_lds<DIR, PT, WG, REQS, false>(m, l, a.n_req, blockIdx.x - w.copy_first, w.copy_wgs,
                                     smem + align16(req_lds_bytes(a.n_req)));
-  if (blockIdx.x < w.sqe_wgs) emit_sqes(q, l, a.n_req, 0, w.sqe_wgs, head);
+  if (blockIdx.x < w.sqe_wgs) emit_sqes<WG>(q, l, a.n_req, 0, w.sqe_wgs, head);
 }
 
 // The preconditions of an unpack on its table, checked without any workspace: every id below num_blocks, no id
