@@ -81,6 +81,39 @@ constexpr uint32_t budget_units(bool ahead, uint32_t block_bytes, uint32_t block
 // budget_units asks for then.  In any other shape the kernel of whole slices would read and write beyond the blocks.
 constexpr bool pieces_shape(bool whole_gpu, uint32_t units) { return whole_gpu || units == 16; }
 
+// Blocks that are no whole number of 4 KiB slices, token-major, of a fused launch on the whole GPU: pieces (move_pieces), or equal
+// slices of whole 128-byte lines, as few as there can be (cut_slice; 0: none).  Slices read ahead, and save one request's or a few
+// requests' blocks without a scan, like those of other blocks; pieces need a search and a table load in each lane first, but put
+// several blocks into an item and fill its accesses.  So it goes by the items (cuts_blocks): up to one for each of the chip's
+// wavefronts, twice that for a save of one request, which reads behind a single load, and half of it for a restore of blocks that
+// are a whole number of pieces.  A slice of up to 2 KiB uses half of its accesses or less: only where a wavefront would do nothing
+// else.  Graph replay, us, pieces / slices, by payload:
+//                              0.5 MiB        2            4            8           12           16           32          128
+//   12.5 KiB  restore of 1   3.86 / 2.85  4.20 / 3.29  4.45 / 3.81  5.79 / 4.86  7.09 / 6.29  8.40 / 8.28  14.0 / 14.1  46.5 / 46.8
+//   blocks    of 8 requests  4.15 / 3.48  4.46 / 3.96  4.81 / 4.37  6.17 / 5.57  7.49 / 6.91  8.81 / 8.25  14.2 / 14.2  46.2 / 45.9
+//             of 200                                                7.89 / 7.53  8.60 / 7.99  10.2 / 9.7   15.2 / 15.6  46.7 / 46.2
+//             save of 1      3.88 / 2.85  4.36 / 3.34  4.63 / 3.83  5.88 / 4.71  7.18 / 6.20  8.56 / 7.58  14.0 / 13.4  48.7 / 47.6
+//             of 8           4.31 / 3.46  4.55 / 3.63  4.91 / 3.87  6.08 / 4.48  7.60 / 5.48  8.86 / 7.25  14.5 / 14.5  48.6 / 48.8
+//             of 200                                                8.26 / 5.63  9.05 / 6.05  10.5 / 7.3   16.2 / 16.0  50.6 / 50.3
+//   10 KiB    restore of 1   3.70 / 2.90  4.04 / 3.31  4.27 / 3.80  5.16 / 5.05  6.66 / 6.80  8.11 / 8.24  13.9 / 13.8  45.4 / 47.0
+//             save of 8      4.16 / 3.30  4.49 / 3.62  4.72 / 3.93  5.59 / 4.44  7.19 / 5.70  8.31 / 8.20  14.0 / 14.1  47.3 / 48.6
+//   1 KiB     restore of 1   3.64 / 2.77  3.79 / 3.14  4.06 / 4.31  5.19 / 6.26
+//             of 200         6.37 / 5.64  6.45 / 5.78  6.56 / 5.97  7.62 / 7.97
+//             save of 8      4.11 / 3.45  4.18 / 3.73  4.62 / 4.41  5.61 / 6.25
+constexpr uint32_t cut_slice(uint32_t block_bytes) {
+  if (block_bytes % 128 != 0 || block_bytes < 1024 || block_bytes > (512u << 10)) return 0;
+  const uint32_t lines = block_bytes / 128, least = lines / 32 + (lines % 32 != 0 ? 1 : 0);
+  for (uint32_t n = least; n == least || n < 2 * least; ++n)
+    if (lines % n == 0) return 128 * (lines / n);
+  return 0;
+}
+constexpr bool cuts_blocks(bool unpack, uint32_t n_req, uint32_t block_bytes, uint32_t slice, uint64_t items,
+                           uint32_t chip_waves) {
+  if (slice <= 2048) return (unpack ? 4 : 2) * items <= chip_waves;
+  if (unpack) return (block_bytes % 1024 == 0 ? 2 : 1) * items <= chip_waves;
+  return items <= (n_req == 1 ? 2ull : 1ull) * chip_waves;
+}
+
 // Whether the submission entries (or the contexts) of a whole-GPU launch of up to 64 requests are written by workgroups of
 // their own, in front of the `copy_wgs` that move blocks, instead of riding along with the first of those.  Riding along a
 // small launch is as long as the scan with the entries' divisions, the copy and the entry one behind the other; a larger one

@@ -175,9 +175,11 @@ struct Launch {
   uint32_t nontemporal;  // bit 0: loads, bit 1: stores
   bool hnd_lds;          // head-major pool moved through LDS; unroll then holds 16-byte units per thread per tile
   uint32_t tile_lds;     // bytes of LDS for the tile
+  bool head_major;       // [h][T][row] with more than one head and more than one token: otherwise that is the objects' order
   bool lines;            // head-major pool moved as line tiles
   bool keeps_order;      // a visiting order is not read
   bool pieces;           // blocks are no whole number of slices: moved as 1 KiB pieces
+  bool cut;              // the same, cut into equal slices of fewer bytes
 };
 
 constexpr uint32_t kHndTileCap = 16384;      // largest tile staged in LDS: 8 workgroups per CU keep their tiles resident
@@ -221,7 +223,7 @@ int plan_launch(uint32_t cu_budget, uint64_t n_wave_items, Launch *out) {
   out->nontemporal = t.nontemporal & 3u;
   out->hnd_lds = false;
   out->tile_lds = 0;
-  out->pieces = out->lines = out->keeps_order = false;
+  out->pieces = out->cut = out->head_major = out->lines = out->keeps_order = false;
   out->wg_threads = cu_budget ? kBudgetWgThreads : kWgThreads;
   out->unroll = t.unroll ? t.unroll : cu_budget ? kBudgetUnroll : kDefaultUnroll;
   size_grid(cu_budget, n_wave_items, out);
@@ -279,10 +281,10 @@ uint64_t counted_slices(const Launch &L, uint32_t bytes) {
 // Fills the kernel arguments and settles how a head-major pool is moved (L->hnd_lds, L->unroll,
 // L->tile_lds, L->lines).  L must already hold the workgroup size and default unroll from plan_launch.  `unpack`: objects
 // to blocks; `ahead`: the first slices are read before the requests are known (restores); `ordered`: in a caller's visiting
-// order.
+// order; `cuts`: the caller has kernels for cut slices.
 int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t *d_block_table, uint32_t table_len,
                    const void *d_stage, uint64_t stage_cap, uint32_t *d_status, uint32_t n_req, uint32_t align,
-                   uint32_t cu_budget, bool unpack, bool ahead, bool ordered, Launch *L, MoveArgs *m) {
+                   uint32_t cu_budget, bool unpack, bool ahead, bool ordered, bool cuts, Launch *L, MoveArgs *m) {
   m->k_base = static_cast<unsigned char *>(pool->k_base);
   m->v_base = static_cast<unsigned char *>(pool->v_base);
   m->stage = static_cast<unsigned char *>(const_cast<void *>(d_stage));
@@ -303,14 +305,17 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   m->visit = nullptr;
   m->chip_waves = L->wg_threads == kWgThreads ? static_cast<uint32_t>(whole_gpu_waves(*L)) : 0;
 
+  m->slice_bytes = 0;
+
   L->hnd_lds = L->lines = false;
   L->tile_lds = 0;
   const uint32_t mode = tuning().hnd_mode;
   const uint32_t row = m->row_bytes, T = pool->block_tokens, h = pool->num_kv_heads;
+  L->head_major = pool->pool_layout == TUTTI_LAYOUT_HND && ((T > 1 && h > 1) || mode != 0);
   const bool powers = pool->pool_layout == TUTTI_LAYOUT_HND && is_pow2(row) && is_pow2(T) && is_pow2(h);
   // (more blocks than line tiles can number go through LDS, whose tiles are larger)
   const bool half_empty = 4ull * table_len * counted_slices(*L, block_bytes) <= whole_gpu_waves(*L);
-  bool lines = powers && mode == 0 && as_line_tiles(row, block_bytes, h, cu_budget, unpack, half_empty) &&
+  bool lines = L->head_major && powers && mode == 0 && as_line_tiles(row, block_bytes, h, cu_budget, unpack, half_empty) &&
                2ull * table_len * counted_slices(*L, block_bytes) <= 0xffffffffull;
   // where the rule for LDS holds the launch keeps staging order, whatever list of positions it is given
   L->keeps_order = false;
@@ -328,7 +333,7 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
       const bool fits = tile_bytes % (L->wg_threads * 16u) == 0 && per_thread >= 1 && per_thread <= 8 &&
                         is_pow2(per_thread) && lds <= kDynLdsCap;
       L->keeps_order = fits && (mode == 2 || hnd_through_lds(row, cu_budget));
-      if (L->keeps_order && !lines) {
+      if (L->head_major && L->keeps_order && !lines) {
         L->hnd_lds = true;
         L->unroll = per_thread;
         L->tile_lds = tile_tokens * pitch;
@@ -352,12 +357,22 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   // first slices ahead of the scan.  A visiting order keeps the slices, whatever the block size.
   if (!L->hnd_lds && cu_budget && tuning().unroll == 0)
     L->unroll = budget_units(ahead, block_bytes, table_len, cu_budget, visits,
-                             pool->pool_layout == TUTTI_LAYOUT_HND && m->row_bytes < 128);
+                             L->head_major && m->row_bytes < 128);
   const uint32_t slice = kPiece * L->unroll;
   uint64_t slices = m->slices_per_block;
   if (!L->hnd_lds) {
     slices = (static_cast<uint64_t>(block_bytes) + slice - 1) / slice;
     L->pieces = block_bytes % slice != 0 && !visits;
+    if (L->pieces && cuts && !L->head_major && cu_budget == 0 && L->unroll == kDefaultUnroll && L->nontemporal == 3) {
+      const uint32_t bytes = cut_slice(block_bytes);
+      if (bytes != 0 &&
+          cuts_blocks(unpack, n_req, block_bytes, bytes, 2ull * table_len * (block_bytes / bytes), m->chip_waves)) {
+        L->pieces = false;
+        L->cut = true;
+        m->slice_bytes = bytes;
+        slices = block_bytes / bytes;
+      }
+    }
     if (lines && !L->pieces) {
       L->lines = true;
       m->row_shift = log2u(row);
@@ -374,7 +389,7 @@ int fill_move_args(const tutti_pool *pool, uint32_t block_bytes, const uint32_t 
   m->items_bound = static_cast<uint32_t>(2u * table_len * slices);
   m->xcd_contiguous = tuning().xcd_contiguous;
   // dense staging: no padding anywhere and no ragged slice, so the staging offset of an item is item * slice
-  m->dense = (!L->hnd_lds && block_bytes % align == 0 && block_bytes % slice == 0) ? 1u : 0u;
+  m->dense = (!L->hnd_lds && block_bytes % align == 0 && (L->cut || block_bytes % slice == 0)) ? 1u : 0u;
   return TUTTI_OK;
 }
 
@@ -507,13 +522,25 @@ template <typename S>
 constexpr bool has_pieces = pieces_shape(S::WG == kWgThreads, S::U);
 #endif
 
+// Line tiles and cut slices are moved by kernels of whole slices in staging order; those of cut slices exist in the whole-GPU
+// shape only (fill_move_args asks for them in no other).
+constexpr bool any_blocks(int hnd) { return hnd == kNhd || hnd == kHnd; }
+
+template <int HND, typename F>
+hipError_t with_shape_for(const Launch &L, F &&f) {
+  if constexpr (HND == kCut)
+    return f(Shape<kDefaultUnroll, 3, kWgThreads>{});
+  else
+    return with_shape(L, f);
+}
+
 template <int DIR, int HND>
 hipError_t launch_move(const Launch &L, uint32_t lds, hipStream_t s, const MoveArgs &m, const tutti_extent *ext,
                        uint32_t n_req) {
   return with_shape(L, [&](auto sh) {
     using S = decltype(sh);
     if (L.pieces) {  // never through the kernel of whole slices
-      if constexpr (has_pieces<S> && HND != kLines) {
+      if constexpr (has_pieces<S> && any_blocks(HND)) {
         hipLaunchKernelGGL((k_move<DIR, HND, S::U, S::NT, S::WG, true>), dim3(L.grid), dim3(S::WG), lds, s, m, ext, n_req, L.grid);
         return hipGetLastError();
       }
@@ -528,7 +555,7 @@ template <typename S, int DIR, int HND, int REQS>
 hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStream_t s, const MoveArgs &m,
                               const SqeArgs &q, const LayoutArgs &a, const Roles &w) {
   const dim3 grid(n_wgs), block(S::WG);
-  if constexpr ((REQS == kFew || REQS == kMany) && HND != kLines) {
+  if constexpr ((REQS == kFew || REQS == kMany) && any_blocks(HND)) {
     if constexpr (DIR == kUnpack && REQS == kMany) {
       if (m.visit) {  // the caller's visiting order
         hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>), grid, block, lds, s, m, q, a, w);
@@ -552,7 +579,7 @@ hipError_t launch_layer(const Launch &L, uint64_t entry_quarters, uint32_t lds, 
                         const SqeArgs &q, const LayoutArgs &a) {
   uint32_t n_wgs = 0;
   Roles w = make_roles(L, entry_quarters, &n_wgs);
-  return with_shape(L, [&](auto sh) {
+  return with_shape_for<HND>(L, [&](auto sh) {
     using S = decltype(sh);
     if constexpr (has_few<S>) {
       if (one_request_path<DIR>(L, m, a.n_req, move_wave_items(L, m))) {
@@ -628,7 +655,7 @@ int move_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const tutti_exte
   if (rc) return rc;
   MoveArgs m;
   rc = fill_move_args(pool, bb, d_block_table, table_len, d_stage, stage_cap, d_status, n_req, cfg->align, cu_budget,
-                      DIR == kUnpack, DIR == kUnpack && bb % cfg->align == 0, false, &L, &m);
+                      DIR == kUnpack, DIR == kUnpack && bb % cfg->align == 0, false, false, &L, &m);
   if (rc) return rc;
   size_grid(cu_budget, move_wave_items(L, m), &L);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -638,7 +665,7 @@ int move_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const tutti_exte
   } else {
     const uint32_t lds = req_lds_bytes(n_req);
     e = L.lines                                   ? launch_move<DIR, kLines>(L, lds, s, m, d_extents, n_req)
-        : pool->pool_layout == TUTTI_LAYOUT_HND ? launch_move<DIR, kHnd>(L, lds, s, m, d_extents, n_req)
+        : L.head_major                            ? launch_move<DIR, kHnd>(L, lds, s, m, d_extents, n_req)
                                                 : launch_move<DIR, kNhd>(L, lds, s, m, d_extents, n_req);
   }
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
@@ -733,7 +760,8 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
   if (rc) return rc;
   MoveArgs m;
   rc = fill_move_args(pool, bb, d_block_table, table_len, d_stage, stage_cap, d_status, n_req, cfg->align, cu_budget,
-                      DIR == kUnpack, DIR == kUnpack && bb % cfg->align == 0, d_visit != nullptr, &L, &m);
+                      DIR == kUnpack, DIR == kUnpack && bb % cfg->align == 0, d_visit != nullptr,
+                      true, &L, &m);
   if (rc) return rc;
   if (!L.keeps_order) m.visit = d_visit;
   size_grid(cu_budget, move_wave_items(L, m), &L);
@@ -755,7 +783,8 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
   } else {
     const uint32_t lds = req_lds_bytes(n_req);
     e = L.lines                                   ? launch_layer<DIR, kLines>(L, entry_quarters, lds, s, m, q, a)
-        : pool->pool_layout == TUTTI_LAYOUT_HND ? launch_layer<DIR, kHnd>(L, entry_quarters, lds, s, m, q, a)
+        : L.cut                                   ? launch_layer<DIR, kCut>(L, entry_quarters, lds, s, m, q, a)
+        : L.head_major                            ? launch_layer<DIR, kHnd>(L, entry_quarters, lds, s, m, q, a)
                                                 : launch_layer<DIR, kNhd>(L, entry_quarters, lds, s, m, q, a);
   }
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
@@ -1041,7 +1070,7 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
   raw.pool_layout = TUTTI_LAYOUT_NHD;
   MoveArgs m;
   rc = fill_move_args(&raw, bb, d_block_table, table_len, store->base, 0, d_status, n_req, cfg->align, cu_budget,
-                      DIR == kUnpack, DIR == kUnpack && n_req == 1, false, &L, &m);
+                      DIR == kUnpack, DIR == kUnpack && n_req == 1, false, false, &L, &m);
   if (rc) return rc;
   m.dense = 0;
   m.layer = layer;
@@ -1772,13 +1801,13 @@ void least_resident(int *worst, uint32_t lds, K... kernels) {
   (one(kernels), ...);
 }
 
-// Every kernel that a whole-GPU launch of the default shape may run (line tiles: whole slices in staging order only).
+// Every kernel that a whole-GPU launch of the default shape may run (line tiles and cut slices: whole slices in staging order only).
 template <int DIR, int HND>
 void least_resident_layer(int *worst) {
   constexpr uint32_t few = req_lds_bytes(kWave), many = req_lds_bytes(512);
   least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kOne>, k_layer<DIR, HND, 4, 3, kWgThreads, kFew>);
   least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany>, k_layer<DIR, HND, 4, 3, kWgThreads, kManyAhead>);
-  if constexpr (HND != kLines) {
+  if constexpr (any_blocks(HND)) {
     least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFew, false, true>);
     least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, false, true>);
     if constexpr (DIR == kUnpack) least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany, true>);
@@ -1819,8 +1848,14 @@ void least_resident_lds(int *worst) {
 int tutti_resident_wgs_per_cu(uint32_t which) {
   int n = 1 << 20;
   switch (which) {
-    case 0: least_resident_layer<kUnpack, kNhd>(&n); break;
-    case 1: least_resident_layer<kPack, kNhd>(&n); break;
+    case 0:
+      least_resident_layer<kUnpack, kNhd>(&n);
+      least_resident_layer<kUnpack, kCut>(&n);
+      break;
+    case 1:
+      least_resident_layer<kPack, kNhd>(&n);
+      least_resident_layer<kPack, kCut>(&n);
+      break;
     case 2: least_resident_move<kUnpack>(&n); break;
     case 3: least_resident_move<kPack>(&n); break;
     case 4: least_resident_ring<kUnpack>(&n); break;

@@ -1263,7 +1263,8 @@ __global__ __launch_bounds__(WG) void k_sqe_direct(const SqeArgs a, const Direct
 // Blocks that are no whole number of slices are cut into pieces instead: 1 KiB, what one wavefront instruction covers
 // (the last of a block may be shorter), and an item is U consecutive pieces, which may belong to different blocks.
 // A block of 12.5 KiB is 13 pieces instead of four slices of which the last moves 512 of its 4096 bytes; four blocks
-// of 1 KiB are one item instead of four.
+// of 1 KiB are one item instead of four.  (Where a launch is bound by how soon its first bytes move rather than by how many
+// are on their way, such blocks are cut into equal slices all the same: cuts_blocks.)
 // ------------------------------------------------------------------------------------------
 struct MoveArgs {
   unsigned char *k_base;
@@ -1289,6 +1290,7 @@ struct MoveArgs {
   uint32_t token_shift;  // log2(block_tokens)
   uint32_t tile_shift;   // log2(tokens per tile)
   uint32_t lds_pitch;    // bytes between consecutive tokens of the tile in LDS: h*row_bytes + row_bytes
+  uint32_t slice_bytes;  // kCut: what a slice of a block moves
   // dense staging: blocks are whole alignment units and whole slices, so item `it` of an unpack reads the
   // staging bytes [it*slice, (it+1)*slice) whatever the extents are; items_bound = 2 * table_len * slices
   uint32_t dense;
@@ -1355,10 +1357,26 @@ __device__ __forceinline__ uint32_t hnd_offset(uint32_t o, uint32_t row_bytes, u
 
 // How a lane's 16-byte units lie on one side of a copy: one behind the other, found row by row in a head-major block, or
 // as line tiles (LineTile).
-constexpr int kNhd = 0, kHnd = 1, kLines = 2;                              // pools
-constexpr int kLinear = 0, kRows = 1, kTileObj = 2, kTilePool = 3;         // sides
-constexpr int pool_side(int hnd) { return hnd == kLines ? kTilePool : hnd == kHnd ? kRows : kLinear; }
-constexpr int obj_side(int hnd) { return hnd == kLines ? kTileObj : kLinear; }
+// kCut: token-major blocks that are no whole number of U KiB, cut into equal slices of fewer bytes (cut_slice, which has the
+// figures); what a slice leaves of the U KiB that a wavefront's accesses cover, the bounds check of a buffer access drops.
+constexpr int kNhd = 0, kHnd = 1, kLines = 2, kCut = 3;                     // pools
+constexpr int kLinear = 0, kRows = 1, kTileObj = 2, kTilePool = 3, kShort = 4;  // sides
+constexpr int pool_side(int hnd) { return hnd == kLines ? kTilePool : hnd == kHnd ? kRows : hnd == kCut ? kShort : kLinear; }
+constexpr int obj_side(int hnd) { return hnd == kLines ? kTileObj : hnd == kCut ? kShort : kLinear; }
+template <int HND, int U>
+__device__ __forceinline__ uint32_t slice_bytes(const MoveArgs &a) {
+  return HND == kCut ? a.slice_bytes : U * kPiece;
+}
+
+// Buffer accesses to the `bytes` bytes from p on (the same in every lane): beyond them a load gives zeroes and a store does
+// nothing, decided by the memory pipe for each lane, with no branch and no address to clamp.
+constexpr int kRawBuffer = 0x00027000;  // descriptor word 3: untyped 32-bit elements
+constexpr int kNonTemporal = 2;         // cache policy of a buffer access
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t bounded(const unsigned char *p, uint32_t bytes) {
+  const uint64_t at = reinterpret_cast<uint64_t>(p);
+  const uint64_t base = static_cast<uint64_t>(rfl(static_cast<uint32_t>(at >> 32))) << 32 | rfl(static_cast<uint32_t>(at));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void *>(base), 0, static_cast<int>(bytes), kRawBuffer);
+}
 
 // The offsets in the block of a lane's 16-byte units, whose canonical offsets o, o + 1 KiB, o + 2 KiB, ... lie a piece
 // apart: as they are, or (head-major) with the row and head of the first unit found by division and those of the others
@@ -1445,6 +1463,12 @@ __device__ __forceinline__ void load_slice(const MoveArgs &a, const unsigned cha
   if (SIDE == kLinear) {
 #pragma unroll
     for (int k = 0; k < U; ++k) buf[k] = ld16<NT>(blk + (o0 + k * kPiece));
+  } else if (SIDE == kShort) {
+    const uint32_t mine = (threadIdx.x & (kWave - 1)) * 16u;
+    const __amdgpu_buffer_rsrc_t s = bounded(blk + (o0 - mine), a.slice_bytes);
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      buf[k] = __builtin_amdgcn_raw_buffer_load_b128(s, static_cast<int>(mine + k * kPiece), 0, kNonTemporal);
   } else {
     uint32_t at[U];
     if (SIDE == kRows)
@@ -1460,6 +1484,12 @@ __device__ __forceinline__ void store_slice(const MoveArgs &a, unsigned char *bl
   if (SIDE == kLinear) {
 #pragma unroll
     for (int k = 0; k < U; ++k) st16<NT>(blk + (o0 + k * kPiece), buf[k]);
+  } else if (SIDE == kShort) {
+    const uint32_t mine = (threadIdx.x & (kWave - 1)) * 16u;
+    const __amdgpu_buffer_rsrc_t s = bounded(blk + (o0 - mine), a.slice_bytes);
+#pragma unroll
+    for (int k = 0; k < U; ++k)
+      __builtin_amdgcn_raw_buffer_store_b128(buf[k], s, static_cast<int>(mine + k * kPiece), 0, kNonTemporal);
   } else {
     if (U > 4) __builtin_amdgcn_sched_barrier(0);  // the loads first: the offsets are worked out under them
     uint32_t at[U];
@@ -1600,14 +1630,14 @@ __device__ __forceinline__ void zero_tail(const MoveArgs &a, const Item &d, uint
 // ORD: the block need not be a whole number of slices (the others are moved as pieces then).
 template <int DIR, int HND, int U, int NT, bool ORD, bool DIRECT>
 __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint32_t id, uint32_t lane) {
-  constexpr uint32_t kSlice = kWave * 16u * U;
+  const uint32_t slice = slice_bytes<HND, U>(a);
   if (d.obj_ptr == nullptr) return;
-  const uint32_t in_blk = d.s * kSlice;  // first byte of the slice inside the block
+  const uint32_t in_blk = d.s * slice;  // first byte of the slice inside the block
   if (id < a.num_blocks) {
     unsigned char *blk_ptr = (d.kind ? a.v_base : a.k_base) + static_cast<uint64_t>(id) * a.block_stride;
     unsigned char *obj_blk = d.obj_blk;
     const uint32_t o0 = in_blk + lane * 16u;  // this lane's first 16 bytes, canonical offset in the block
-    if (!ORD || in_blk + kSlice <= a.block_bytes) {
+    if (!ORD || in_blk + slice <= a.block_bytes) {
       // whole slice inside the block: U independent loads in flight, then U stores
       u32x4 buf[U];
       load_slice<DIR == kPack ? pool_side(HND) : obj_side(HND), U, NT>(a, DIR == kPack ? blk_ptr : obj_blk, o0, buf);
@@ -1663,14 +1693,14 @@ struct Preload {
 
 template <int HND, int U, int NT, int WG>
 __device__ __forceinline__ Preload<U> preload_first(const MoveArgs &a, uint32_t wg, uint32_t copy_wgs) {
-  constexpr uint32_t kSlice = kWave * 16u * U;
+  const uint32_t slice = slice_bytes<HND, U>(a);
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t it = first_item<WG, U>(a, wg, copy_wgs);
-  const uint64_t at = static_cast<uint64_t>(it) * kSlice;
+  const uint64_t at = static_cast<uint64_t>(it) * slice;
   // a slice of line tiles lies anywhere in its block (a power of two, and dense staging has no gap between blocks)
   const uint32_t in_blk = HND == kLines ? static_cast<uint32_t>(at) & (a.block_bytes - 1) : 0u;
   Preload<U> p;
-  p.valid = a.dense != 0 && it < a.items_bound && at - in_blk + (HND == kLines ? a.block_bytes : kSlice) <= a.stage_cap;
+  p.valid = a.dense != 0 && it < a.items_bound && at - in_blk + (HND == kLines ? a.block_bytes : slice) <= a.stage_cap;
   p.src = a.stage + at;
   if (p.valid) {
     load_slice<obj_side(HND), U, NT>(a, p.src - in_blk, in_blk + lane * 16u, p.buf);
@@ -1713,7 +1743,7 @@ struct PackItem {
 
 template <int HND, int U, int NT, int WG, int REQS>
 __device__ __forceinline__ Preload<U> preload_pack(const MoveArgs &a, const PackItem<U, WG, REQS> &f) {
-  constexpr uint32_t kSlice = kWave * 16u * U;
+  const uint32_t slice = slice_bytes<HND, U>(a);
   const uint32_t lane = threadIdx.x & (kWave - 1);
   Preload<U> p;
   p.valid = f.id < a.num_blocks;
@@ -1721,7 +1751,7 @@ __device__ __forceinline__ Preload<U> preload_pack(const MoveArgs &a, const Pack
   // asked for in front of them, would otherwise be one for both
   const uint32_t spare = blockIdx.x < a.num_blocks ? blockIdx.x : 0u;
   p.src = (f.kind ? a.v_base : a.k_base) + static_cast<uint64_t>(p.valid ? f.id : spare) * a.block_stride;
-  load_slice<pool_side(HND), U, NT>(a, p.src, f.part * kSlice + lane * 16u, p.buf);
+  load_slice<pool_side(HND), U, NT>(a, p.src, f.part * slice + lane * 16u, p.buf);
   return p;
 }
 
@@ -1751,14 +1781,14 @@ __device__ __forceinline__ void pack_unordered(const MoveArgs &a, const ReqLds &
 template <int HND, int U, int NT, int WG, int REQS, bool DIRECT>
 __device__ __forceinline__ void store_pack(const MoveArgs &a, const ReqLds &l, uint32_t n_req, uint32_t wg,
                                            uint32_t copy_wgs, const Preload<U> &pre) {
-  constexpr uint32_t kSlice = kWave * 16u * U;
+  const uint32_t slice = slice_bytes<HND, U>(a);
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t it = first_item<WG, U>(a, wg, copy_wgs);
   if (it >= a.items_bound) return;
   const Item d = decode_item<false, REQS, pack_order(REQS), DIRECT>(a, l, n_req, it, lane);
   if (d.obj_ptr == nullptr) return;
   if (pre.valid)
-    store_slice<obj_side(HND), U, NT>(a, d.obj_blk, d.s * kSlice + lane * 16u, pre.buf);
+    store_slice<obj_side(HND), U, NT>(a, d.obj_blk, d.s * slice + lane * 16u, pre.buf);
   else if (lane == 0 && d.s == 0 && a.status)
     atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
   if (!DIRECT) zero_tail(a, d, lane);
@@ -1768,11 +1798,11 @@ __device__ __forceinline__ void store_pack(const MoveArgs &a, const ReqLds &l, u
 template <int HND, int U, int NT>
 __device__ __forceinline__ void store_preloaded(const MoveArgs &a, const Item &d, uint32_t id, uint32_t lane,
                                                 const Preload<U> &p) {
-  constexpr uint32_t kSlice = kWave * 16u * U;
+  const uint32_t slice = slice_bytes<HND, U>(a);
   if (d.obj_ptr == nullptr) return;
   if (id < a.num_blocks) {
     unsigned char *blk_ptr = (d.kind ? a.v_base : a.k_base) + static_cast<uint64_t>(id) * a.block_stride;
-    store_slice<pool_side(HND), U, NT>(a, blk_ptr, d.s * kSlice + lane * 16u, p.buf);
+    store_slice<pool_side(HND), U, NT>(a, blk_ptr, d.s * slice + lane * 16u, p.buf);
   } else if (lane == 0 && d.s == 0 && a.status) {
     atomicOr(a.status, TUTTI_ST_BAD_BLOCK);
   }
@@ -1785,7 +1815,7 @@ __device__ __forceinline__ void store_preloaded(const MoveArgs &a, const Item &d
 template <int DIR, int HND, int U, int NT, int WG, int REQS, bool SEP, int ORD, bool DIRECT>
 __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uint32_t n_req, uint32_t wg,
                                            uint32_t copy_wgs, const Preload<U> &pre) {
-  constexpr uint32_t kSlice = kWave * 16u * U;
+  const uint32_t slice = slice_bytes<HND, U>(a);
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t n_waves = copy_wgs * (WG / kWave);
   const uint32_t n_items = count_units<SEP, ORD, DIRECT>(a, l, n_req) * a.slices_per_block;
@@ -1809,7 +1839,7 @@ __device__ __forceinline__ void move_items(const MoveArgs a, const ReqLds l, uin
     // from where they say
     const bool preloaded = DIR == kUnpack && ahead != 0 &&
                            ((!SEP && ORD == kStagingOrder && !DIRECT) ||
-                            cur.obj_blk + static_cast<uint64_t>(cur.s) * kSlice == pre.src);
+                            cur.obj_blk + static_cast<uint64_t>(cur.s) * slice == pre.src);
     if (preloaded)
       store_preloaded<HND, U, NT>(a, cur, id, lane, pre);
     else
@@ -1908,7 +1938,7 @@ __device__ __forceinline__ OneReq one_request(const MoveArgs &m, const LayoutArg
 template <int DIR, int HND, int U, int NT, int WG, bool DIRECT>
 __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q, uint32_t wg, uint32_t copy_wgs,
                                              const Preload<U> &pre) {
-  constexpr uint32_t kSlice = U * kPiece;
+  const uint32_t slice = slice_bytes<HND, U>(a);
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t n_waves = copy_wgs * (WG / kWave);
   const uint32_t S = a.slices_per_block;
@@ -1935,7 +1965,7 @@ __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q,
     if (fits && id < a.num_blocks) {
       unsigned char *blk = (kind ? a.v_base : a.k_base) + static_cast<uint64_t>(id) * a.block_stride;
       unsigned char *obj = q.base + at;
-      const uint32_t o0 = part * kSlice + lane * 16u;
+      const uint32_t o0 = part * slice + lane * 16u;
       if (DIR == kUnpack && first) {
         store_slice<pool_side(HND), U, NT>(a, blk, o0, pre.buf);
       } else {

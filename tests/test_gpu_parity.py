@@ -1315,6 +1315,42 @@ def test_blocks_moved_as_pieces(orc, H, T, h, d, e):
             H.check_rings(orc, c, 1, opcode, depth=3, first_slot=1, n_slots=2, cu_budget=budget)
 
 
+@pytest.mark.parametrize("n_req", [1, 2, 64, 65, 300])
+@pytest.mark.parametrize("T,h,d,e,layout", [(16, 1, 64, 1, 0), (16, 1, 64, 1, 1), (17, 1, 64, 2, 0), (32, 5, 80, 1, 0),
+                                            (16, 5, 80, 2, 0), (1, 31, 128, 1, 1)])
+def test_blocks_cut_into_slices_of_their_own_size(orc, H, T, h, d, e, layout, n_req):
+    """Token-major blocks (and head-major ones of one head or one token, which are the same) of 1 to 12.5 KiB: one slice of the
+    block's size or several, that fill their accesses or leave lanes out, with padded and dense objects; launches of a few
+    items, of as many as the last that is cut and one more; a table longer than the blocks, a skipped id, capacities that are
+    short, strided planes."""
+    bb = T * h * d * e
+    slices = {1024: 1, 2176: 1, 12800: 4, 3968: 1}[bb]
+    say("cut blocks of", bb, "bytes in", n_req, "requests")
+    rng = np.random.default_rng(8700 + bb + n_req)
+    limits = [8192 // k // (2 * slices) for k in ((4, 2) if bb == 1024 else (2, 1))]
+    for blocks in sorted({n_req, 301, *limits, limits[-1] + 1}):
+        if blocks < n_req:
+            continue
+        n = np.full(n_req, blocks // n_req, np.uint32)
+        n[n_req // 2] += blocks - int(n.sum())
+        N = blocks + 9
+        table = rng.permutation(N).astype(np.uint32)
+        if blocks > 1:
+            table[blocks // 2] = N
+        for align in (4096, 128):
+            c = H.LayerCase(T=T, h=h, d=d, e=e, N=N, n_blocks=n, table=table, align=align, chunk=8192, L=2, layout=layout, pad=48,
+                            name=f"cut{bb}n{n_req}b{blocks}a{align}")
+            H.check_layer_restore(orc, c, layer=1, table_len=blocks)
+            H.check_layer_save(orc, c, layer=1, table_len=blocks)
+            if blocks == 301:
+                H.check_layer_save(orc, c)
+                H.check_layer_restore(orc, c)
+                H.check_layer_save(orc, c, table_len=blocks - 1)
+                H.check_layer_restore(orc, c, table_len=blocks - 1)
+                H.check_layer_save(orc, c, table_len=blocks, stage_cap=2 * blocks * bb - 16)
+                H.check_layer_restore(orc, c, table_len=blocks, stage_cap=2 * blocks * bb - 16)
+
+
 @pytest.mark.parametrize("T,h,d,e,layout", [(16, 1, 128, 2, 0), (16, 2, 128, 2, 0), (16, 5, 80, 2, 0), (16, 4, 128, 2, 0),
                                             (16, 6, 128, 2, 0), (16, 5, 128, 2, 0), (16, 16, 32, 1, 1), (16, 32, 32, 1, 1),
                                             (16, 8, 64, 1, 1), (16, 16, 64, 1, 1), (16, 24, 64, 1, 1), (8, 32, 64, 2, 1),

@@ -28,6 +28,10 @@ extern "C" unsigned units_of(int ahead, unsigned block_bytes, unsigned blocks, u
 extern "C" int at_once_of(unsigned long long items, unsigned chip, unsigned n_req, unsigned table_len) {
   return tutti::pack_at_once(items, chip, n_req, table_len);
 }
+extern "C" unsigned cut_of(unsigned block_bytes) { return tutti::cut_slice(block_bytes); }
+extern "C" int cuts_of(int unpack, unsigned n_req, unsigned block, unsigned slice, unsigned long long items, unsigned chip) {
+  return tutti::cuts_blocks(unpack != 0, n_req, block, slice, items, chip);
+}
 extern "C" int pieces_of(int whole_gpu, unsigned units) { return tutti::pieces_shape(whole_gpu != 0, units); }
 """
 CHIP = 8192  # wavefronts of a whole-GPU launch on 256 compute units
@@ -164,3 +168,32 @@ def test_long_tables_are_counted_first(rules):
             assert rules.at_once_of(CHIP // 4, CHIP, n_req, table)
             assert rules.at_once_of(CHIP // 4 + 1, CHIP, n_req, table) == (table <= longest)
             assert rules.at_once_of(1 << 33, CHIP, n_req, table) == (table <= longest)
+
+
+def test_cut_slices_fill_the_block(rules):
+    """Whole lines, at most the 4 KiB of a wavefront's accesses, as few as can be and none left over; none for blocks without
+    such slices."""
+    cut = 0
+    for block in [*range(16, 1 << 16, 16), *range(1 << 16, 1 << 20, 128), 0xfffffff0, 0xffffff80]:
+        b = rules.cut_of(block)
+        if b:
+            cut += 1
+            assert block % b == 0 and b % 128 == 0 and b <= 4096
+            assert b == block or b > 1024
+            assert not [n for n in range(-(-block // 4096), block // b) if block % (128 * n) == 0]
+        else:
+            assert block % 128 or not 1024 <= block <= 512 << 10 or \
+                not [n for n in range(-(-block // 4096), 2 * -(-block // 4096)) if block % (128 * n) == 0]
+    assert cut > 1000
+    assert [rules.cut_of(b) for b in (1024, 2560, 6400, 12800, 15360, 30720)] == [1024, 2560, 3200, 3200, 3840, 3840]
+
+
+def test_blocks_are_cut_up_to_a_slice_a_wavefront(rules):
+    rules.cuts_of.argtypes = [ctypes.c_int] + [ctypes.c_uint] * 3 + [ctypes.c_ulonglong, ctypes.c_uint]
+    for unpack, n_req, block, most in ((0, 1, 12800, 2 * CHIP), (0, 2, 12800, CHIP), (0, 300, 2176, CHIP), (1, 1, 6400, CHIP),
+                                       (1, 65, 12800, CHIP), (1, 65, 15360, CHIP // 2), (0, 1, 2048, CHIP // 2),
+                                       (0, 65, 1024, CHIP // 2), (1, 1, 1024, CHIP // 4), (1, 2, 2048, CHIP // 4)):
+        slice_ = rules.cut_of(block)
+        assert rules.cuts_of(unpack, n_req, block, slice_, 0, CHIP) and rules.cuts_of(unpack, n_req, block, slice_, most, CHIP)
+        assert not rules.cuts_of(unpack, n_req, block, slice_, most + 1, CHIP)
+        assert not rules.cuts_of(unpack, n_req, block, slice_, 1 << 33, CHIP)
