@@ -20,6 +20,7 @@ FAST_CALL = os.path.join(HERE, "_fast_call" + sysconfig.get_config_var("EXT_SUFF
 FAST_CALL_DEPS = [os.path.join(CSRC, "fast_call.cpp"), os.path.join(ROOT, "include", "tutti.h")]
 SOURCES = [os.path.join(CSRC, "tutti_api.hip"), os.path.join(CSRC, "tutti_host.cpp")]
 DEPS = SOURCES + [os.path.join(CSRC, "tutti_kernels.hip.h"), os.path.join(CSRC, "launch_rules.h"),
+                  os.path.join(CSRC, "layer_call.h"),
                   os.path.join(ROOT, "include", "tutti.h"),
                   os.path.join(ROOT, "include", "tutti_bench.h")]
 

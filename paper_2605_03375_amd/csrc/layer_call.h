@@ -1,0 +1,171 @@
+// The arguments of a fused launch in 112 bytes.  Plain C++, so that it can be tested without a GPU.
+#pragma once
+
+#include <stdint.h>
+
+namespace tutti {
+
+// The runtime copies the arguments of every launch into memory from malloc, which it gives back when the kernel has
+// ended.  Up to 112 bytes that is one of malloc's smallest chunks, kept in lists of their own size; a larger one is
+// merged with its neighbours and cut out again.  A train of launches of an otherwise empty kernel, us each, by bytes of
+// arguments (the first train after a start takes 2.5 to 2.8 with any):
+//   32  2.64   64  2.80   96  2.85   104  2.88   112  2.88   120  3.45   128  3.6   160  3.65   264  3.7   384  3.8
+// So a fused launch hands over bit fields (its arguments as separate words are 260 bytes), and the kernel takes them apart
+// with some thirty scalar instructions.  Calls from Python, us, words / fields: restore of 256 KiB 4.2 / 3.4, a train of 32 of
+// 4 MiB 131 / 113 and 139 / 116; the kernels by themselves (graph replay of 60 kinds of call) take the same time within 0.2 %,
+// the smallest 0.03 us more.
+//
+// What a field leaves out is what it cannot hold: addresses lie below 2^47 (the host checks the ones that are used), planes,
+// staging, entries, strides and block sizes are multiples of 16, a chunk is a multiple of the alignment, which is a power of two.
+constexpr uint32_t kLayerCallWords = 14;
+struct LayerCall {
+  uint64_t w[kLayerCallWords];
+};
+static_assert(sizeof(LayerCall) <= 112, "one of malloc's smallest chunks");
+
+struct LayerFields {
+  uint64_t k_base, v_base, stage, sqe;                             // addresses, multiples of 16
+  uint64_t table, n_blocks, extents, totals, file_id, status;      // addresses
+  uint64_t block_stride;                                           // multiple of 16; taken as signed
+  uint64_t stage_cap;                                              // rounded down to 16; 2^47 - 16 where it is more
+  uint64_t stage_addr;                                             // multiple of 16
+  uint32_t num_blocks, table_len, block_bytes, chunk_bytes, sqe_cap, sgl_id, layer, n_req, align;
+  uint32_t sqe_wgs, copy_wgs, copy_first;                          // copy_first: 0, sqe_wgs, or that rounded up to 8
+  uint32_t chip_waves;                                             // rounded down to 128; 127 * 128 where it is more
+  uint32_t dense, xcd_contiguous;                                  // 0 or 1
+  uint32_t size_a, size_b, left_out;                               // of a block (BlockSizes), or of its slices
+};
+
+// Tokens, heads and row size of a head-major block: two of them, in 14 bits each, and which one is left out, the block having
+// the size that it has.  With the row in units of 16 bytes the three make up at most 2^28, so no two are above 2^14.
+struct BlockSizes {
+  uint32_t tokens, heads, row_bytes;
+};
+constexpr uint32_t kMostSize = 1u << 14;
+constexpr void put_sizes(LayerFields &f, BlockSizes s) {
+  const uint32_t row = s.row_bytes / 16;
+  f.left_out = s.tokens <= kMostSize && row <= kMostSize ? 0u : s.heads <= kMostSize && row <= kMostSize ? 1u : 2u;
+  f.size_a = f.left_out == 1 ? s.heads : s.tokens;
+  f.size_b = f.left_out == 2 ? s.heads : row;
+}
+constexpr uint32_t log2_of(uint32_t power) { return 31u - static_cast<uint32_t>(__builtin_clz(power)); }
+// `powers`: all three are powers of two.
+constexpr BlockSizes get_sizes(const LayerFields &f, bool powers) {
+  const uint32_t units = f.block_bytes / 16;
+  const uint32_t third = powers ? units >> (log2_of(f.size_a) + log2_of(f.size_b)) : units / (f.size_a * f.size_b);
+  if (f.left_out == 0) return BlockSizes{f.size_a, third, 16 * f.size_b};
+  if (f.left_out == 1) return BlockSizes{third, f.size_a, 16 * f.size_b};
+  return BlockSizes{f.size_a, f.size_b, 16 * third};
+}
+
+namespace layer_call {
+struct Bits {
+  uint32_t at, n;
+};
+// What the way to the first load needs lies in words of its own.
+constexpr Bits kKBase{0, 44}, kCopyWgs{44, 12}, kAlign{56, 5}, kDense{61, 1}, kFirst{62, 2};
+constexpr Bits kVBase{64, 44}, kSqeWgs{108, 12}, kChip{120, 7}, kXcd{127, 1};
+constexpr Bits kStage{128, 44}, kReqs{172, 12}, kLeftOut{184, 2};
+constexpr Bits kStride{192, 44}, kLayer{236, 16};
+constexpr Bits kNumBlocks{256, 32}, kTableLen{288, 31};
+constexpr Bits kBlockBytes{320, 28}, kSizeA{348, 14}, kSizeB{362, 14}, kSglLow{376, 8};
+constexpr Bits kTable{384, 47}, kNBlocks{431, 47}, kExtents{478, 47}, kTotals{525, 47}, kFileId{572, 47}, kStatus{619, 47};
+constexpr Bits kSqe{666, 43}, kStageCap{709, 43}, kStageAddr{752, 60}, kSqeCap{812, 32}, kChunk{844, 28}, kSglHigh{872, 24};
+static_assert(kSglHigh.at + kSglHigh.n == 64 * kLayerCallWords, "the last field ends the last word");
+
+constexpr uint64_t kBelow(uint32_t n) { return n == 64 ? ~0ull : (1ull << n) - 1; }
+constexpr uint64_t get(const LayerCall &c, Bits f) {
+  const uint32_t i = f.at / 64, s = f.at % 64;
+  uint64_t v = c.w[i] >> s;
+  if (s + f.n > 64) v |= c.w[i + 1] << (64 - s);
+  return v & kBelow(f.n);
+}
+constexpr uint32_t get32(const LayerCall &c, Bits f) { return static_cast<uint32_t>(get(c, f)); }
+constexpr void put(LayerCall &c, Bits f, uint64_t v) {
+  const uint32_t i = f.at / 64, s = f.at % 64;
+  v &= kBelow(f.n);
+  c.w[i] |= v << s;
+  if (s + f.n > 64) c.w[i + 1] |= v >> (64 - s);
+}
+}  // namespace layer_call
+
+constexpr uint64_t kAddressEnd = 1ull << 47;  // user addresses, of the host and of the GPU alike, lie below
+constexpr uint32_t kMostWgs = 4088;           // workgroups of a launch that the fields hold
+
+constexpr LayerCall pack(const LayerFields &f) {
+  using namespace layer_call;
+  LayerCall c{};
+  put(c, kKBase, f.k_base >> 4);
+  put(c, kVBase, f.v_base >> 4);
+  put(c, kStage, f.stage >> 4);
+  put(c, kSqe, f.sqe >> 4);
+  put(c, kTable, f.table);
+  put(c, kNBlocks, f.n_blocks);
+  put(c, kExtents, f.extents);
+  put(c, kTotals, f.totals);
+  put(c, kFileId, f.file_id);
+  put(c, kStatus, f.status);
+  put(c, kStride, f.block_stride >> 4);
+  put(c, kStageCap, (f.stage_cap < kAddressEnd ? f.stage_cap : kAddressEnd - 16) >> 4);
+  put(c, kStageAddr, f.stage_addr >> 4);
+  put(c, kNumBlocks, f.num_blocks);
+  put(c, kTableLen, f.table_len);
+  put(c, kBlockBytes, f.block_bytes >> 4);
+  put(c, kChunk, f.chunk_bytes >> 4);
+  put(c, kSqeCap, f.sqe_cap);
+  put(c, kSglLow, f.sgl_id);
+  put(c, kSglHigh, f.sgl_id >> 8);
+  put(c, kLayer, f.layer);
+  put(c, kReqs, f.n_req);
+  put(c, kAlign, log2_of(f.align));
+  put(c, kSqeWgs, f.sqe_wgs);
+  put(c, kCopyWgs, f.copy_wgs);
+  put(c, kFirst, f.copy_first == 0 ? 0 : f.copy_first == f.sqe_wgs ? 1 : 2);
+  put(c, kChip, f.chip_waves / 128 < 127 ? f.chip_waves / 128 : 127);
+  put(c, kDense, f.dense);
+  put(c, kXcd, f.xcd_contiguous);
+  put(c, kSizeA, f.size_a - 1);
+  put(c, kSizeB, f.size_b - 1);
+  put(c, kLeftOut, f.left_out);
+  return c;
+}
+
+constexpr LayerFields unpack(const LayerCall &c) {
+  using namespace layer_call;
+  LayerFields f{};
+  f.k_base = get(c, kKBase) << 4;
+  f.v_base = get(c, kVBase) << 4;
+  f.stage = get(c, kStage) << 4;
+  f.sqe = get(c, kSqe) << 4;
+  f.table = get(c, kTable);
+  f.n_blocks = get(c, kNBlocks);
+  f.extents = get(c, kExtents);
+  f.totals = get(c, kTotals);
+  f.file_id = get(c, kFileId);
+  f.status = get(c, kStatus);
+  f.block_stride = static_cast<uint64_t>(static_cast<int64_t>(get(c, kStride) << 20) >> 16);
+  f.stage_cap = get(c, kStageCap) << 4;
+  f.stage_addr = get(c, kStageAddr) << 4;
+  f.num_blocks = get32(c, kNumBlocks);
+  f.table_len = get32(c, kTableLen);
+  f.block_bytes = get32(c, kBlockBytes) << 4;
+  f.chunk_bytes = get32(c, kChunk) << 4;
+  f.sqe_cap = get32(c, kSqeCap);
+  f.sgl_id = get32(c, kSglHigh) << 8 | get32(c, kSglLow);
+  f.layer = get32(c, kLayer);
+  f.n_req = get32(c, kReqs);
+  f.align = 1u << get32(c, kAlign);
+  f.sqe_wgs = get32(c, kSqeWgs);
+  f.copy_wgs = get32(c, kCopyWgs);
+  const uint32_t first = get32(c, kFirst), up = first >> 1 & 1u;  // no branch on the way to the first load
+  f.copy_first = (f.sqe_wgs + 7 * up) & ~(7 * up) & (first != 0 ? ~0u : 0u);
+  f.chip_waves = 128 * get32(c, kChip);
+  f.dense = get32(c, kDense);
+  f.xcd_contiguous = get32(c, kXcd);
+  f.size_a = get32(c, kSizeA) + 1;
+  f.size_b = get32(c, kSizeB) + 1;
+  f.left_out = get32(c, kLeftOut);
+  return f;
+}
+
+}  // namespace tutti

@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
+#include <initializer_list>
 #include <unordered_map>
 #include <vector>
 
@@ -79,6 +80,13 @@ int cu_count() {
 
 bool is_pow2(uint32_t x) { return x != 0 && (x & (x - 1)) == 0; }
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
+
+// Addresses that a process can have memory at (and LayerCall has bits for).
+bool addressable(std::initializer_list<const void *> pointers) {
+  uintptr_t any = 0;
+  for (const void *p : pointers) any |= reinterpret_cast<uintptr_t>(p);
+  return any < kAddressEnd;
+}
 
 // Geometry checks shared by every entry point; *block_bytes = T*h*d*e.
 int check_geometry(const tutti_pool *pool, const tutti_objcfg *cfg, uint32_t *block_bytes) {
@@ -438,6 +446,7 @@ Roles make_roles(const Launch &L, uint64_t entry_quarters, uint32_t *grid) {
     if (cap > limit) limit = cap;
   }
   Roles w;
+  if (limit > kMostWgs) limit = kMostWgs;
   w.sqe_wgs = static_cast<uint32_t>(need < limit ? need : limit);
   w.copy_first = 0;
   w.copy_wgs = L.grid;
@@ -551,26 +560,71 @@ hipError_t launch_move(const Launch &L, uint32_t lds, hipStream_t s, const MoveA
   });
 }
 
+// A fused launch's arguments in few bytes.  Pointers that the call has no use for are left out of it; the others have been
+// checked (addressable).
+template <int DIR, int HND>
+LayerCall layer_call_of(const MoveArgs &m, const SqeArgs &q, const LayoutArgs &a, const Roles &w) {
+  const auto address = [](const void *p, bool used) { return used ? reinterpret_cast<uint64_t>(p) : 0ull; };
+  LayerFields f{};
+  f.k_base = address(m.k_base, true);
+  f.v_base = address(m.v_base, true);
+  f.stage = address(m.stage, true);
+  f.table = address(m.table, m.table_len > 0);
+  f.status = address(m.status, true);
+  f.n_blocks = address(a.n_blocks, a.n_req > 0);
+  f.extents = address(a.extents, a.n_req > 0);
+  f.file_id = address(q.file_id, a.n_req > 0);
+  f.totals = address(a.totals, true);
+  f.sqe = address(q.sqe, q.sqe_cap > 0);
+  f.block_stride = m.block_stride;
+  f.stage_cap = m.stage_cap;
+  f.stage_addr = q.stage_addr;
+  f.num_blocks = m.num_blocks;
+  f.table_len = m.table_len;
+  f.block_bytes = m.block_bytes;
+  f.chunk_bytes = q.chunk_bytes;
+  f.sqe_cap = q.sqe_cap;
+  f.sgl_id = q.sgl_id;
+  f.layer = q.layer;
+  f.n_req = a.n_req;
+  f.align = a.geom.align;
+  f.sqe_wgs = w.sqe_wgs;
+  f.copy_wgs = w.copy_wgs;
+  f.copy_first = w.copy_first;
+  f.chip_waves = m.chip_waves;
+  f.dense = m.dense;
+  f.xcd_contiguous = m.xcd_contiguous;
+  f.size_a = f.size_b = 1;
+  if (HND == kCut) {
+    f.size_a = m.slice_bytes / 128;
+    f.size_b = m.slices_per_block;
+  } else if (HND != kNhd) {
+    put_sizes(f, BlockSizes{m.block_tokens, m.num_kv_heads, m.row_bytes});
+  }
+  return pack(f);
+}
+
 template <typename S, int DIR, int HND, int REQS>
 hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStream_t s, const MoveArgs &m,
                               const SqeArgs &q, const LayoutArgs &a, const Roles &w) {
   const dim3 grid(n_wgs), block(S::WG);
+  const LayerCall c = layer_call_of<DIR, HND>(m, q, a, w);
   if constexpr ((REQS == kFew || REQS == kMany) && any_blocks(HND)) {
     if constexpr (DIR == kUnpack && REQS == kMany) {
       if (m.visit) {  // the caller's visiting order
-        hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>), grid, block, lds, s, m, q, a, w);
+        hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>), grid, block, lds, s, OrderedCall{c, m.visit});
         return hipGetLastError();
       }
     }
     if constexpr (has_pieces<S> && (REQS == kMany || S::WG == kWgThreads)) {
       if (pieces) {
-        hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, false, true>), grid, block, lds, s, m, q, a, w);
+        hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, false, true>), grid, block, lds, s, c);
         return hipGetLastError();
       }
     }
   }
   if (pieces) return hipErrorInvalidValue;  // never through the kernel of whole slices
-  hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS>), grid, block, lds, s, m, q, a, w);
+  hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS>), grid, block, lds, s, c);
   return hipGetLastError();
 }
 
@@ -754,6 +808,10 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
   if (sqe_cap > 0 && (!d_sqe || !aligned16(d_sqe))) return TUTTI_EINVAL;
   if (layer >= cfg->num_layers) return TUTTI_EINVAL;
   if (stage_addr % cfg->align != 0) return TUTTI_EINVAL;
+  if (!addressable({pool->k_base, pool->v_base, d_stage, d_totals, d_status, d_visit}) ||
+      (n_req > 0 && !addressable({d_n_blocks, d_extents, d_file_id})) ||
+      (table_len > 0 && !addressable({d_block_table})) || (sqe_cap > 0 && !addressable({d_sqe})))
+    return TUTTI_EINVAL;
 
   Launch L;
   rc = plan_launch(cu_budget, 0, &L);
@@ -765,6 +823,7 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
   if (rc) return rc;
   if (!L.keeps_order) m.visit = d_visit;
   size_grid(cu_budget, move_wave_items(L, m), &L);
+  if (L.grid > kMostWgs) L.grid = kMostWgs;  // (more than a chip holds: the measurement build's knobs reach there)
   // one lane per 16-byte quarter of an entry; no more entries than the capacity, nor than the table can give
   // (every request has at most obj/chunk + 1 chunks per object, and obj < blocks*block_bytes + align <= ... + chunk)
   uint64_t max_entries = 2ull * ((static_cast<uint64_t>(table_len) * bb) / cfg->chunk_bytes + 2ull * n_req);

@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "launch_rules.h"
+#include "layer_call.h"
 #include "tutti.h"
 
 namespace tutti {
@@ -2252,17 +2253,104 @@ __device__ __forceinline__ void args_at_hand(const MoveArgs &m, const LayoutArgs
                "s"(m.slices_per_block), "s"(m.items_bound), "s"(m.xcd_contiguous), "s"(a.n_blocks), "s"(a.n_req),
                "s"(w.sqe_wgs), "s"(w.copy_first), "s"(w.copy_wgs));
 }
+__device__ __forceinline__ void words_at_hand(const LayerCall &c) {
+  asm volatile("" ::"s"(c.w[0]), "s"(c.w[1]), "s"(c.w[2]), "s"(c.w[3]), "s"(c.w[4]), "s"(c.w[5]), "s"(c.w[6]), "s"(c.w[7]),
+               "s"(c.w[8]), "s"(c.w[9]), "s"(c.w[10]), "s"(c.w[11]), "s"(c.w[12]), "s"(c.w[13]));
+}
 
-// ORD (restore only): the blocks are visited in the order m.visit lists instead of staging order; the first slices
+struct OrderedCall {
+  LayerCall call;
+  const uint32_t *visit;
+};
+
+template <int DIR>
+__device__ __forceinline__ SqeArgs entry_args(const LayerFields &f) {
+  SqeArgs q;
+  q.file_id = reinterpret_cast<const uint32_t *>(as_global(f.file_id));
+  q.sqe = reinterpret_cast<tutti_sqe *>(as_global(f.sqe));
+  q.status = reinterpret_cast<uint32_t *>(as_global(f.status));
+  q.stage_addr = f.stage_addr;
+  q.sqe_cap = f.sqe_cap;
+  q.chunk_bytes = f.chunk_bytes;
+  q.layer = f.layer;
+  q.opcode = DIR == kUnpack ? TUTTI_OP_READ : TUTTI_OP_WRITE;
+  q.sgl_id = f.sgl_id;
+  return q;
+}
+
+// The arguments once more, from memory: what is read again where it is used holds no scalar registers until then.
+__device__ __forceinline__ LayerFields fields_again() {
+  typedef const __attribute__((address_space(4))) uint64_t *const_u64_ptr;
+  const_u64_ptr p = (const_u64_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  LayerCall c;
+#pragma unroll
+  for (uint32_t i = 0; i < kLayerCallWords; ++i) c.w[i] = p[i];
+  return unpack(c);
+}
+
+// A fused launch's arguments as the device code reads them.
+template <int DIR, int HND, int U, bool PIECES>
+__device__ __forceinline__ void take_apart(const LayerCall &c, const uint32_t *visit, MoveArgs &m, SqeArgs &q,
+                                           LayoutArgs &a, Roles &w) {
+  const LayerFields f = unpack(c);
+  m.k_base = as_global(f.k_base);
+  m.v_base = as_global(f.v_base);
+  m.stage = as_global(f.stage);
+  m.table = reinterpret_cast<const uint32_t *>(as_global(f.table));
+  m.status = reinterpret_cast<uint32_t *>(as_global(f.status));
+  m.block_stride = f.block_stride;
+  m.stage_cap = f.stage_cap;
+  m.num_blocks = f.num_blocks;
+  m.block_bytes = f.block_bytes;
+  m.table_len = f.table_len;
+  constexpr uint32_t kSlice = U * kPiece;
+  const uint32_t slices = HND == kCut ? f.size_b : f.block_bytes / kSlice + (f.block_bytes % kSlice != 0 ? 1u : 0u);
+  m.slices_per_block = PIECES ? f.block_bytes / kPiece + (f.block_bytes % kPiece != 0 ? 1u : 0u) : slices;
+  m.items_bound = 2u * f.table_len * slices;
+  m.slice_bytes = HND == kCut ? 128u * f.size_a : 0u;
+  m.row_bytes = m.block_tokens = m.num_kv_heads = 0;
+  m.row_shift = m.head_shift = m.token_shift = m.tile_shift = m.lds_pitch = 0;
+  if (HND == kHnd || HND == kLines) {
+    const BlockSizes b = get_sizes(f, HND == kLines);
+    m.row_bytes = rfl(b.row_bytes);
+    m.block_tokens = rfl(b.tokens);
+    m.num_kv_heads = rfl(b.heads);
+    if (HND == kLines) {
+      m.row_shift = log2_of(m.row_bytes);
+      m.head_shift = log2_of(m.num_kv_heads);
+      m.token_shift = log2_of(m.block_tokens);
+      m.tile_shift = line_tile_shift(m.row_shift, m.head_shift, m.token_shift);
+    }
+  }
+  m.dense = f.dense;
+  m.chip_waves = f.chip_waves;
+  m.xcd_contiguous = f.xcd_contiguous;
+  m.layer = 0;
+  m.file_stride = m.ctx_cap = 0;
+  m.visit = visit;
+  q = entry_args<DIR>(f);
+  a.n_blocks = reinterpret_cast<const uint32_t *>(as_global(f.n_blocks));
+  a.extents = reinterpret_cast<tutti_extent *>(as_global(f.extents));
+  a.totals = reinterpret_cast<uint64_t *>(as_global(f.totals));
+  a.geom = ScanGeom{f.block_bytes, f.align, f.chunk_bytes};
+  a.n_req = f.n_req;
+  w.sqe_wgs = f.sqe_wgs;
+  w.copy_first = f.copy_first;
+  w.copy_wgs = f.copy_wgs;
+}
+
+// ORD (restore only): the blocks are visited in the order `visit` lists instead of staging order; the first slices
 // cannot be preloaded then (where they sit depends on the list).
-template <int DIR, int HND, int U, int NT, int WG, int REQS, bool ORD = false, bool PIECES = false>
-__global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const MoveArgs m, const SqeArgs q_, const LayoutArgs a_, const Roles w) {
+template <int DIR, int HND, int U, int NT, int WG, int REQS, bool ORD, bool PIECES>
+__device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *visit) {
   extern __shared__ __align__(16) unsigned char smem[];
-  SqeArgs q = q_;  // (as in k_layer_ring)
-  LayoutArgs a = a_;
-  q.status = m.status;
-  a.geom.block_bytes = m.block_bytes;
-  a.geom.chunk_bytes = q.chunk_bytes;
+  words_at_hand(c);
+  MoveArgs m;
+  SqeArgs q;
+  LayoutArgs a;
+  Roles w;
+  take_apart<DIR, HND, U, PIECES>(c, visit, m, q, a, w);
   const ReqLds l = carve_lds(smem, a.n_req);
   const uint32_t wg = blockIdx.x - w.copy_first;  // wraps for the workgroups in front of the copy ones
   const bool copies = wg < w.copy_wgs;
@@ -2277,10 +2365,9 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     one_head.live = false;
     if (entries) one_head = sqe_head<WG>(q, l, 1, 0);
     if (copies) move_request<DIR, HND, U, NT, WG, false>(m, one, wg, w.copy_wgs, pre);
-    if (entries) emit_sqes<WG>(q, l, 1, 0, w.sqe_wgs, one_head);
+    if (entries) emit_sqes<WG>(entry_args<DIR>(fields_again()), l, 1, 0, w.sqe_wgs, one_head);
     return;
   }
-  if (reads_under_scan(REQS)) args_at_hand(m, a, w);
   PackItem<U, WG, REQS> first;
   scan_extents<WG, REQS>(
       a.geom, a.n_blocks, a.n_req, l, publish ? a.extents : nullptr, publish ? a.totals : nullptr, m.table_len, m.status,
@@ -2299,6 +2386,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, a.n_req, false));
   SqeHead head;
   head.live = false;
+  if (any_number(REQS)) q = entry_args<DIR>(fields_again());
   if (blockIdx.x < w.sqe_wgs) head = sqe_head<WG>(q, l, a.n_req, 0);
   if (ORD && wg == 0 && m.status) {
     // requests whose objects do not fit the staging buffer are skipped by every item: report them here, once
@@ -2317,7 +2405,16 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const M
     else
       move_items<DIR, HND, U, NT, WG, REQS, false, ORD ? kListOrder : kStagingOrder, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
   }
-  if (blockIdx.x < w.sqe_wgs) emit_sqes<WG>(q, l, a.n_req, 0, w.sqe_wgs, head);
+  if (blockIdx.x < w.sqe_wgs) emit_sqes<WG>(entry_args<DIR>(fields_again()), l, a.n_req, 0, w.sqe_wgs, head);
+}
+
+template <int DIR, int HND, int U, int NT, int WG, int REQS, bool ORD = false, bool PIECES = false>
+__global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(
+    const typename std::conditional<ORD, OrderedCall, LayerCall>::type c) {
+  if constexpr (ORD)
+    run_layer<DIR, HND, U, NT, WG, REQS, true, PIECES>(c.call, c.visit);
+  else
+    run_layer<DIR, HND, U, NT, WG, REQS, false, PIECES>(c, nullptr);
 }
 
 // First item of a wavefront in a retrieve of ONE request: its file bytes sit at
