@@ -53,9 +53,8 @@ constexpr uint32_t log2_of(uint32_t power) { return 31u - static_cast<uint32_t>(
 constexpr BlockSizes get_sizes(const LayerFields &f, bool powers) {
   const uint32_t units = f.block_bytes / 16;
   const uint32_t third = powers ? units >> (log2_of(f.size_a) + log2_of(f.size_b)) : units / (f.size_a * f.size_b);
-  if (f.left_out == 0) return BlockSizes{f.size_a, third, 16 * f.size_b};
-  if (f.left_out == 1) return BlockSizes{third, f.size_a, 16 * f.size_b};
-  return BlockSizes{f.size_a, f.size_b, 16 * third};
+  return BlockSizes{f.left_out == 1 ? third : f.size_a, f.left_out == 0 ? third : f.left_out == 1 ? f.size_a : f.size_b,
+                    16 * (f.left_out == 2 ? third : f.size_b)};
 }
 
 namespace layer_call {

@@ -2291,9 +2291,8 @@ __device__ __forceinline__ LayerFields fields_again() {
 
 // A fused launch's arguments as the device code reads them.
 template <int DIR, int HND, int U, bool PIECES>
-__device__ __forceinline__ void take_apart(const LayerCall &c, const uint32_t *visit, MoveArgs &m, SqeArgs &q,
+__device__ __forceinline__ void take_apart(const LayerFields &f, const uint32_t *visit, MoveArgs &m, SqeArgs &q,
                                            LayoutArgs &a, Roles &w) {
-  const LayerFields f = unpack(c);
   m.k_base = as_global(f.k_base);
   m.v_base = as_global(f.v_base);
   m.stage = as_global(f.stage);
@@ -2350,7 +2349,7 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
   SqeArgs q;
   LayoutArgs a;
   Roles w;
-  take_apart<DIR, HND, U, PIECES>(c, visit, m, q, a, w);
+  take_apart<DIR, HND, U, PIECES>(unpack(c), visit, m, q, a, w);
   const ReqLds l = carve_lds(smem, a.n_req);
   const uint32_t wg = blockIdx.x - w.copy_first;  // wraps for the workgroups in front of the copy ones
   const bool copies = wg < w.copy_wgs;
@@ -2386,7 +2385,8 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
     hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, a.n_req, false));
   SqeHead head;
   head.live = false;
-  if (any_number(REQS)) q = entry_args<DIR>(fields_again());
+  // the scan of many requests needs most scalar registers for itself
+  if (any_number(REQS)) take_apart<DIR, HND, U, PIECES>(fields_again(), visit, m, q, a, w);
   if (blockIdx.x < w.sqe_wgs) head = sqe_head<WG>(q, l, a.n_req, 0);
   if (ORD && wg == 0 && m.status) {
     // requests whose objects do not fit the staging buffer are skipped by every item: report them here, once
