@@ -154,6 +154,50 @@ constexpr bool pack_at_once(uint64_t items, uint32_t chip_waves, uint32_t n_req,
 // and with half of the chip's, 1024 of 8 KiB in 256, 6.3 6.3 / 6.5 6.4 / 6.8 6.6; 150 of 32 KiB in 70 5.5 5.3 / 5.7 5.5 / 5.9 5.7.
 constexpr uint32_t pack_pause(uint32_t items, uint32_t chip_waves) { return 2 * items > chip_waves ? 2 : 0; }
 
+// The same pause where it was missing: for one request's restore on the path of its own, which has no scan to delay its stores
+// and takes up to half of the chip's wavefronts, and for saves of up to 64 requests that read a slice for each wavefront.  By
+// the items there are, of 4 KiB (full_slices), and about as long as their reads take; the scan delays the stores by itself, by
+// three or four steps.  Blocks of 32 KiB, graph replay, us, by the pause (items / chip_waves in brackets):
+//                                      0      2      4      6      8     10     12     14
+//   restore of 1      112 (0.22)     4.62   4.33   4.28   4.65   5.09              (3: 4.15; 96 blocks 3.29, with any pause more)
+//                     160 (0.31)     5.50   5.41   5.29   5.03   5.43
+//                     200 (0.39)     6.52   6.52   5.79   5.74   5.78   6.18       (7: 5.61)
+//                     240 (0.47)     7.24   6.88   6.85   6.15   6.28   6.63       (7: 6.10)
+//   save of 1         144 (0.28)     5.53   5.45   5.42   5.43   5.07   5.45   5.89
+//                     200 (0.39)     7.18   7.19   7.03   7.06   6.47   6.12   6.55   7.01
+//                     260 (0.51)     8.02   8.37   7.90   8.21   8.86   7.65   7.47   7.66
+//                     320 (0.63)     9.05   9.55   9.20   9.03   9.55   9.44   8.07   8.33
+//                     360 (0.70)    10.06  10.60  10.37  10.28  10.22  10.39  11.11   9.83
+//                     380 (0.74)    10.48  10.99  10.64  10.81  11.05  10.65  11.44  10.90
+//   save of 9         144 (0.28)     5.17   4.99   5.02   5.42
+//                     200 (0.39)     6.81   6.49   6.24   6.08   6.46
+//                     240 (0.47)     7.55   7.31   6.43   7.09   6.78   7.18       (3: 6.70, 5: 7.39)
+//                     260 (0.51)     7.87   8.04   8.33   8.25   7.52   7.51   8.07
+//                     320 (0.63)     9.30   9.20   8.98   9.75   9.49   8.01   8.38   9.08
+//                     380 (0.74)    11.01  10.81  10.48  10.65  11.47  11.15  10.22  10.05
+//   save of 40        144 (0.28)     4.62   4.70   5.09                             (1: 4.50)
+//                     240 (0.47)     6.76   6.56   6.11   6.54   6.90   7.26       (3: 6.16)
+//                     320 (0.63)     8.73   8.36   8.45   9.08   8.63   7.95   8.67
+// Runs fall into one of two modes, 5 to 10 % apart, by where their buffers lie; over block sizes, requests and 0.2 to 0.75 of the
+// chip saves gain 3.5 % in the geometric mean, up to 16 %.  Head-major blocks that are moved row by row (rows of 80 bytes) lose
+// with it, saves of 432 to 592 blocks of 20 KiB up to 15 %, and restores of cut slices (307 blocks of 12.5 KiB 4.8 / 5.0): none there.
+constexpr uint32_t one_restore_pause(uint32_t items, uint32_t chip_waves) {
+  const uint32_t i = 32 * items, c = chip_waves;
+  if (items > chip_waves || i < 7 * c || c == 0) return 0;
+  return 3 + (i >= 8 * c) + (i >= 9 * c) + (i >= 10 * c) + (i >= 12 * c);
+}
+constexpr uint32_t one_save_pause(uint32_t items, uint32_t chip_waves) {
+  const uint32_t i = 32 * items, c = chip_waves;
+  if (items > chip_waves || i < 9 * c || 2 * i > 45 * c || c == 0) return 0;
+  return i < 12 * c ? 8 : i < 16 * c ? 10 : i < 17 * c ? 12 : 14;
+}
+constexpr uint32_t few_save_pause(uint32_t items, uint32_t chip_waves, uint32_t n_req) {
+  const uint32_t i = 32 * items, c = chip_waves;
+  if (items > chip_waves || i < 9 * c || c == 0) return 0;
+  if (i < 13 * c) return (i < 11 * c ? 2u : 3u) - (n_req > 32 ? 1u : 0u);
+  return i < 16 * c ? 3 : i < 17 * c ? 8 : i < 21 * c ? 10 : 12;
+}
+
 // Whether a head-major pool goes through LDS tiles or is moved directly, where it is not moved as line tiles
 // (as_line_tiles); where this holds an ordered restore keeps staging order.  On the whole GPU it pays while a row is shorter
 // than a 128-byte line.  Under a CU budget a workgroup has one tile in flight at a time, and only rows of 16 bytes on more

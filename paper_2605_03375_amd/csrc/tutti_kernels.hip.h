@@ -1662,6 +1662,12 @@ __device__ __forceinline__ void move_one(const MoveArgs &a, const Item &d, uint3
   if (DIR == kPack && !DIRECT) zero_tail(a, d, lane);
 }
 
+// Items as slices of U KiB: cut slices are less.
+template <int HND, int U>
+__device__ __forceinline__ uint32_t full_slices(const MoveArgs &a, uint32_t items) {
+  return HND == kCut ? items * (a.slice_bytes / 128) / (8 * U) : items;
+}
+
 // Holds the stores of a wavefront that has read ahead back (hold_back_pause).
 __device__ __forceinline__ void hold_back(uint32_t pause) {
   for (uint32_t i = 0; i < pause; ++i) __builtin_amdgcn_s_sleep(8);
@@ -1935,10 +1941,10 @@ __device__ __forceinline__ OneReq one_request(const MoveArgs &m, const LayoutArg
 }
 
 // The copy loop of one request whose blocks are a whole number of slices; the next item's block id is requested before
-// the current item's loads and stores are issued.
+// the current item's loads and stores are issued.  `pause`: how long the first item's stores are held back.
 template <int DIR, int HND, int U, int NT, int WG, bool DIRECT>
 __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q, uint32_t wg, uint32_t copy_wgs,
-                                             const Preload<U> &pre) {
+                                             const Preload<U> &pre, uint32_t pause) {
   const uint32_t slice = slice_bytes<HND, U>(a);
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t n_waves = copy_wgs * (WG / kWave);
@@ -1950,7 +1956,7 @@ __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q,
   uint32_t u = it / S;
   uint32_t j = u >= q.n ? u - q.n : u;
   uint32_t id = j < a.table_len ? table[j] : a.num_blocks;
-  bool first = DIR == kUnpack && pre.valid;
+  bool first = DIR == kPack || pre.valid;
   for (;;) {
     const uint32_t kind = u >= q.n ? 1u : 0u, part = it - u * S;
     const uint32_t nit = it + n_waves;
@@ -1968,10 +1974,16 @@ __device__ __forceinline__ void move_request(const MoveArgs &a, const OneReq &q,
       unsigned char *obj = q.base + at;
       const uint32_t o0 = part * slice + lane * 16u;
       if (DIR == kUnpack && first) {
+        hold_back(pause);
         store_slice<pool_side(HND), U, NT>(a, blk, o0, pre.buf);
       } else {
         u32x4 buf[U];
         load_slice<DIR == kPack ? pool_side(HND) : obj_side(HND), U, NT>(a, DIR == kPack ? blk : obj, o0, buf);
+        if (DIR == kPack && !DIRECT && first) {
+          __builtin_amdgcn_sched_barrier(0);
+          hold_back(pause);
+          __builtin_amdgcn_sched_barrier(0);
+        }
         store_slice<DIR == kPack ? obj_side(HND) : pool_side(HND), U, NT>(a, DIR == kPack ? obj : blk, o0, buf);
       }
     } else if (lane == 0 && part == 0 && a.status) {
@@ -2363,7 +2375,12 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
     SqeHead one_head;
     one_head.live = false;
     if (entries) one_head = sqe_head<WG>(q, l, 1, 0);
-    if (copies) move_request<DIR, HND, U, NT, WG, false>(m, one, wg, w.copy_wgs, pre);
+    if (copies) {
+      const uint32_t items = full_slices<HND, U>(m, one.units * m.slices_per_block);
+      const uint32_t pause = HND == kHnd || (DIR == kUnpack && HND == kCut) ? 0u
+                             : DIR == kPack ? one_save_pause(items, m.chip_waves) : one_restore_pause(items, m.chip_waves);
+      move_request<DIR, HND, U, NT, WG, false>(m, one, wg, w.copy_wgs, pre, pause);
+    }
     if (entries) emit_sqes<WG>(entry_args<DIR>(fields_again()), l, 1, 0, w.sqe_wgs, one_head);
     return;
   }
@@ -2396,8 +2413,11 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
         atomicOr(m.status, TUTTI_ST_STAGE_CAP);
   }
   if (copies) {
-    if (DIR == kPack && REQS == kManyAhead)
-      hold_back(pack_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves));
+    if (DIR == kPack && (REQS == kManyAhead || ((REQS == kFewAhead || REQS == kFewCounted) && HND != kHnd))) {
+      const uint32_t items = count_units<false>(m, l, a.n_req) * m.slices_per_block;
+      hold_back(REQS == kManyAhead ? pack_pause(items, m.chip_waves)
+                                   : few_save_pause(full_slices<HND, U>(m, items), m.chip_waves, a.n_req));
+    }
     if (DIR == kPack && reads_under_scan(REQS))
       store_pack<HND, U, NT, WG, REQS, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
     else if (PIECES)
@@ -2497,7 +2517,7 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
     DirectHead one_head;
     one_head.live = false;
     if (entries) one_head = iocb_head<WG>(g, q, d, l, 1, lead, w.sqe_wgs);
-    if (copies) move_request<DIR, kNhd, U, 3, WG, true>(m, one, bx - w.copy_first, w.copy_wgs, pre);
+    if (copies) move_request<DIR, kNhd, U, 3, WG, true>(m, one, bx - w.copy_first, w.copy_wgs, pre, 0);
     if (entries) emit_iocbs<WG>(g, q, d, l, 1, lead, w.sqe_wgs, one_head);
     return;
   }
