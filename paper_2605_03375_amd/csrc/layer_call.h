@@ -30,7 +30,7 @@ struct LayerFields {
   uint64_t stage_cap;                                              // rounded down to 16; 2^47 - 16 where it is more
   uint64_t stage_addr;                                             // multiple of 16
   uint32_t num_blocks, table_len, block_bytes, chunk_bytes, sqe_cap, sgl_id, layer, n_req, align;
-  uint32_t sqe_wgs, copy_wgs, copy_first;                          // copy_first: 0, sqe_wgs, or that rounded up to 8
+  uint32_t sqe_wgs, copy_wgs, copy_first;                          // workgroups, at most kMostWgs + 7 each
   uint32_t chip_waves;                                             // rounded down to 128; 127 * 128 where it is more
   uint32_t dense, xcd_contiguous;                                  // 0 or 1
   uint32_t size_a, size_b, left_out;                               // of a block (BlockSizes), or of its slices
@@ -61,11 +61,11 @@ namespace layer_call {
 struct Bits {
   uint32_t at, n;
 };
-// What the way to the first load needs lies in words of its own.
-constexpr Bits kKBase{0, 44}, kCopyWgs{44, 12}, kAlign{56, 5}, kDense{61, 1}, kFirst{62, 2};
-constexpr Bits kVBase{64, 44}, kSqeWgs{108, 12}, kChip{120, 7}, kXcd{127, 1};
-constexpr Bits kStage{128, 44}, kReqs{172, 12}, kLeftOut{184, 2};
-constexpr Bits kStride{192, 44}, kLayer{236, 16};
+// What the way to the first load needs lies in words of its own; the layer's number fills gaps.
+constexpr Bits kKBase{0, 44}, kCopyWgs{44, 12}, kAlign{56, 5}, kDense{61, 1}, kLayerHigh{62, 2};
+constexpr Bits kVBase{64, 44}, kCopyFirst{108, 12}, kChip{120, 7}, kXcd{127, 1};
+constexpr Bits kStage{128, 44}, kSqeWgs{172, 12}, kLeftOut{184, 2}, kLayerMid{186, 6};
+constexpr Bits kStride{192, 44}, kReqs{236, 12}, kLayerLow{248, 8};
 constexpr Bits kNumBlocks{256, 32}, kTableLen{288, 31};
 constexpr Bits kBlockBytes{320, 28}, kSizeA{348, 14}, kSizeB{362, 14}, kSglLow{376, 8};
 constexpr Bits kTable{384, 47}, kNBlocks{431, 47}, kExtents{478, 47}, kTotals{525, 47}, kFileId{572, 47}, kStatus{619, 47};
@@ -114,12 +114,14 @@ constexpr LayerCall pack(const LayerFields &f) {
   put(c, kSqeCap, f.sqe_cap);
   put(c, kSglLow, f.sgl_id);
   put(c, kSglHigh, f.sgl_id >> 8);
-  put(c, kLayer, f.layer);
+  put(c, kLayerLow, f.layer);
+  put(c, kLayerMid, f.layer >> 8);
+  put(c, kLayerHigh, f.layer >> 14);
   put(c, kReqs, f.n_req);
   put(c, kAlign, log2_of(f.align));
   put(c, kSqeWgs, f.sqe_wgs);
   put(c, kCopyWgs, f.copy_wgs);
-  put(c, kFirst, f.copy_first == 0 ? 0 : f.copy_first == f.sqe_wgs ? 1 : 2);
+  put(c, kCopyFirst, f.copy_first);
   put(c, kChip, f.chip_waves / 128 < 127 ? f.chip_waves / 128 : 127);
   put(c, kDense, f.dense);
   put(c, kXcd, f.xcd_contiguous);
@@ -151,13 +153,12 @@ constexpr LayerFields unpack(const LayerCall &c) {
   f.chunk_bytes = get32(c, kChunk) << 4;
   f.sqe_cap = get32(c, kSqeCap);
   f.sgl_id = get32(c, kSglHigh) << 8 | get32(c, kSglLow);
-  f.layer = get32(c, kLayer);
+  f.layer = get32(c, kLayerHigh) << 14 | get32(c, kLayerMid) << 8 | get32(c, kLayerLow);
   f.n_req = get32(c, kReqs);
   f.align = 1u << get32(c, kAlign);
   f.sqe_wgs = get32(c, kSqeWgs);
   f.copy_wgs = get32(c, kCopyWgs);
-  const uint32_t first = get32(c, kFirst), up = first >> 1 & 1u;  // no branch on the way to the first load
-  f.copy_first = (f.sqe_wgs + 7 * up) & ~(7 * up) & (first != 0 ? ~0u : 0u);
+  f.copy_first = get32(c, kCopyFirst);
   f.chip_waves = 128 * get32(c, kChip);
   f.dense = get32(c, kDense);
   f.xcd_contiguous = get32(c, kXcd);

@@ -2290,14 +2290,35 @@ __device__ __forceinline__ SqeArgs entry_args(const LayerFields &f) {
   return q;
 }
 
+typedef const __attribute__((address_space(4))) uint64_t *const_u64_ptr;
+__device__ __forceinline__ const_u64_ptr call_words() {
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wold-style-cast"
+  const_u64_ptr p = (const_u64_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+#pragma clang diagnostic pop
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 // The arguments once more, from memory: what is read again where it is used holds no scalar registers until then.
 __device__ __forceinline__ LayerFields fields_again() {
-  typedef const __attribute__((address_space(4))) uint64_t *const_u64_ptr;
-  const_u64_ptr p = (const_u64_ptr)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
+  const const_u64_ptr p = call_words();
   LayerCall c;
 #pragma unroll
   for (uint32_t i = 0; i < kLayerCallWords; ++i) c.w[i] = p[i];
+  return unpack(c);
+}
+
+// The same for use behind the copy, when they would have to come from HBM again at the very end of the kernel: a word in each
+// lane, asked for in front of it.
+__device__ __forceinline__ uint64_t word_in_lane() {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  return call_words()[lane < kLayerCallWords ? lane : 0u];
+}
+__device__ __forceinline__ LayerFields fields_of_lanes(uint64_t word) {
+  LayerCall c;
+#pragma unroll
+  for (uint32_t i = 0; i < kLayerCallWords; ++i) c.w[i] = readlane_u64(word, i);
   return unpack(c);
 }
 
@@ -2315,10 +2336,11 @@ __device__ __forceinline__ void take_apart(const LayerFields &f, const uint32_t 
   m.num_blocks = f.num_blocks;
   m.block_bytes = f.block_bytes;
   m.table_len = f.table_len;
-  constexpr uint32_t kSlice = U * kPiece;
-  const uint32_t slices = HND == kCut ? f.size_b : f.block_bytes / kSlice + (f.block_bytes % kSlice != 0 ? 1u : 0u);
-  m.slices_per_block = PIECES ? f.block_bytes / kPiece + (f.block_bytes % kPiece != 0 ? 1u : 0u) : slices;
-  m.items_bound = 2u * f.table_len * slices;
+  asm("" : "+s"(m.table_len));  // that it has 31 bits makes the compiler write the scan out twice (1900 / 2860 instructions)
+  const auto covered_by = [&](uint32_t bytes) { return (f.block_bytes / 16 + (bytes / 16 - 1)) / (bytes / 16); };
+  const uint32_t slices = HND == kCut ? f.size_b : covered_by(U * kPiece);
+  m.slices_per_block = PIECES ? covered_by(kPiece) : slices;
+  m.items_bound = 2u * m.table_len * slices;
   m.slice_bytes = HND == kCut ? 128u * f.size_a : 0u;
   m.row_bytes = m.block_tokens = m.num_kv_heads = 0;
   m.row_shift = m.head_shift = m.token_shift = m.tile_shift = m.lds_pitch = 0;
@@ -2336,7 +2358,11 @@ __device__ __forceinline__ void take_apart(const LayerFields &f, const uint32_t 
   }
   m.dense = f.dense;
   m.chip_waves = f.chip_waves;
+#ifdef TUTTI_BENCH_BUILD
   m.xcd_contiguous = f.xcd_contiguous;
+#else
+  m.xcd_contiguous = 0;
+#endif
   m.layer = 0;
   m.file_stride = m.ctx_cap = 0;
   m.visit = visit;
@@ -2374,14 +2400,18 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
     const OneReq one = one_request(m, a, l, publish, entries, nullptr, FileArgs{0, 0, 0});
     SqeHead one_head;
     one_head.live = false;
-    if (entries) one_head = sqe_head<WG>(q, l, 1, 0);
+    uint64_t word = 0;
+    if (entries) {
+      one_head = sqe_head<WG>(q, l, 1, 0);
+      word = word_in_lane();
+    }
     if (copies) {
       const uint32_t items = full_slices<HND, U>(m, one.units * m.slices_per_block);
       const uint32_t pause = HND == kHnd || (DIR == kUnpack && HND == kCut) ? 0u
                              : DIR == kPack ? one_save_pause(items, m.chip_waves) : one_restore_pause(items, m.chip_waves);
       move_request<DIR, HND, U, NT, WG, false>(m, one, wg, w.copy_wgs, pre, pause);
     }
-    if (entries) emit_sqes<WG>(entry_args<DIR>(fields_again()), l, 1, 0, w.sqe_wgs, one_head);
+    if (entries) emit_sqes<WG>(entry_args<DIR>(fields_of_lanes(word)), l, 1, 0, w.sqe_wgs, one_head);
     return;
   }
   PackItem<U, WG, REQS> first;
@@ -2404,7 +2434,11 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
   head.live = false;
   // the scan of many requests needs most scalar registers for itself
   if (any_number(REQS)) take_apart<DIR, HND, U, PIECES>(fields_again(), visit, m, q, a, w);
-  if (blockIdx.x < w.sqe_wgs) head = sqe_head<WG>(q, l, a.n_req, 0);
+  uint64_t word = 0;
+  if (blockIdx.x < w.sqe_wgs) {
+    head = sqe_head<WG>(q, l, a.n_req, 0);
+    word = word_in_lane();
+  }
   if (ORD && wg == 0 && m.status) {
     // requests whose objects do not fit the staging buffer are skipped by every item: report them here, once
     for (uint32_t r = threadIdx.x; r < a.n_req; r += WG)
@@ -2425,7 +2459,7 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
     else
       move_items<DIR, HND, U, NT, WG, REQS, false, ORD ? kListOrder : kStagingOrder, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
   }
-  if (blockIdx.x < w.sqe_wgs) emit_sqes<WG>(entry_args<DIR>(fields_again()), l, a.n_req, 0, w.sqe_wgs, head);
+  if (blockIdx.x < w.sqe_wgs) emit_sqes<WG>(entry_args<DIR>(fields_of_lanes(word)), l, a.n_req, 0, w.sqe_wgs, head);
 }
 
 template <int DIR, int HND, int U, int NT, int WG, int REQS, bool ORD = false, bool PIECES = false>

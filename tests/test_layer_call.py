@@ -47,7 +47,7 @@ LIMITS = {n: ((1 << 47) - 16, 16) for n in ("k_base", "v_base", "stage", "sqe", 
 LIMITS |= {n: ((1 << 47) - 1, 1) for n in ("table", "n_blocks", "extents", "totals", "file_id", "status")}
 LIMITS |= dict(block_stride=((1 << 47) - 16, 16), stage_addr=((1 << 64) - 16, 16), block_bytes=((1 << 32) - 16, 16),
                chunk_bytes=((1 << 32) - 16, 16), table_len=((1 << 31) - 1, 1), layer=(65535, 1), n_req=(2048, 1),
-               sqe_wgs=(4088, 1), copy_wgs=(4088, 1), chip_waves=(127 * 128, 128), dense=(1, 1), xcd_contiguous=(1, 1),
+               sqe_wgs=(4088, 1), copy_wgs=(4088, 1), copy_first=(4095, 1), chip_waves=(127 * 128, 128), dense=(1, 1), xcd_contiguous=(1, 1),
                left_out=(2, 1))
 
 
@@ -72,7 +72,6 @@ def test_every_field_comes_back(lib, seed):
             setattr(f, n, _value(rng, n, end))
         f.align = 16 << rng.randrange(28)
         f.size_a, f.size_b = ((1, 1 << 14)[flip],) * 2 if special else (rng.randint(1, 1 << 14), rng.randint(1, 1 << 14))
-        f.copy_first = rng.choice((0, f.sqe_wgs, (f.sqe_wgs + 7) // 8 * 8))
         out = Fields()
         lib.there_and_back(ctypes.byref(f), ctypes.byref(out))
         for n in U64 + U32:
