@@ -997,19 +997,16 @@ int tutti_iocb_fill_direct(const tutti_ring *ring, uint32_t first_slot, uint32_t
   if (sgl_table_addr % 16 != 0) return TUTTI_EINVAL;
   const int cus = cu_count();
   if (cus < 0) return cus;
-  RingArgs g{ring->d_sq, static_cast<tutti_cq_hdr *>(ring->d_cq), ring->depth, first_slot, n_slots};
-  const SqeArgs q = sqe_args(d_file_id, nullptr, d_status, 0, 0, bb, layer,
-                             opcode, sgl_id);
-  const DirectArgs d = direct_args(d_block_table, sgl_table_addr, table_len, pool->num_blocks, bb);
   // (no IOCBs given: one workgroup still reports the dropped contexts)
   const EntryLaunch E = entry_launch(n_req, 4ull * n_slots * TUTTI_IOCB_SLOTS, cus, 8);
-  const ScanGeom geom{bb, cfg->align, cfg->chunk_bytes};
+  const FillCall c{ring->d_sq, d_file_id, d_status, d_block_table, d_extents, sgl_table_addr, ring->depth, first_slot, n_slots,
+                   layer, opcode, sgl_id, table_len, pool->num_blocks, ScanGeom{bb, cfg->align, cfg->chunk_bytes}, n_req, E.grid};
   if (E.wg_threads == kWgThreads)
     hipLaunchKernelGGL(k_iocb_fill<kWgThreads>, dim3(E.grid), dim3(kWgThreads), req_lds_bytes(n_req),
-                       static_cast<hipStream_t>(stream), g, q, d, geom, d_extents, n_req, E.grid);
+                       static_cast<hipStream_t>(stream), c);
   else
     hipLaunchKernelGGL(k_iocb_fill<kBudgetWgThreads>, dim3(E.grid), dim3(kBudgetWgThreads), req_lds_bytes(n_req),
-                       static_cast<hipStream_t>(stream), g, q, d, geom, d_extents, n_req, E.grid);
+                       static_cast<hipStream_t>(stream), c);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? TUTTI_OK : hip_fail(e);
 }
@@ -1062,8 +1059,10 @@ int issue_io_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slots
   if (lead && cu_budget == 0 && L.grid > 1 && L.grid == whole_gpu_wgs(L)) L.grid -= 1;
   RingArgs g{ring->d_sq, static_cast<tutti_cq_hdr *>(ring->d_cq), ring->depth, first_slot, n_slots};
   const dim3 grid(L.grid + lead);
+  const IoCall c{a, ring->d_sq, static_cast<tutti_cq_hdr *>(ring->d_cq), ring->depth, first_slot, n_slots, done_first, done_n,
+                 grid.x};
 #define TUTTI_ISSUE(U, WG, PIECES) \
-  hipLaunchKernelGGL((k_issue_io<U, WG, PIECES>), grid, dim3(WG), 0, s, g, gd, a, grid.x)
+  hipLaunchKernelGGL((k_issue_io<U, WG, PIECES>), grid, dim3(WG), 0, s, c)
   if (L.wg_threads == kWgThreads) {
     if (pieces) TUTTI_ISSUE(kDefaultUnroll, kWgThreads, true); else TUTTI_ISSUE(kDefaultUnroll, kWgThreads, false);
   } else {
