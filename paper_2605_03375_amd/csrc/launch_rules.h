@@ -4,7 +4,20 @@
 
 #include <stdint.h>
 
+#include "layer_call.h"
+
 namespace tutti {
+
+// Workgroups of a whole-GPU launch that fills every place: what its grid, the wavefronts that the rules count and the entry
+// writers' share are all cut off at, so that a rule never counts on a wavefront that the grid has not got.  (More than a chip
+// holds at once are asked for by the measurement build's knob only.)
+constexpr uint32_t full_grid(uint32_t cus, uint32_t wgs_per_cu) {
+  return static_cast<uint64_t>(cus) * wgs_per_cu < kMostWgs ? cus * wgs_per_cu : kMostWgs;
+}
+
+// Whether a save of several requests gives each wavefront one slice at most and reads it under the scan (store_pack moves no
+// second one): up to 3/4 of the chip's wavefronts.
+constexpr bool one_slice_saves(uint64_t items, uint64_t chip_waves) { return 4 * items <= 3 * chip_waves; }
 
 // A whole-GPU restore reads its first slices, up to 32 MiB, in one burst; stores that start among those reads cost more
 // (the memory turns between reading and writing) than the same stores a little later.  So a wavefront that has read

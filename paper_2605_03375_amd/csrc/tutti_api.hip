@@ -198,10 +198,9 @@ uint32_t log2u(uint32_t x) {
   return n;
 }
 
-// Workgroups of a whole-GPU launch that fills every place (what plan_launch caps its grid at).
 uint32_t whole_gpu_wgs(const Launch &L) {
   const uint32_t per_cu = tuning().wgs_per_cu;
-  return L.cus * (per_cu ? per_cu : kDefaultWgsPerCu);
+  return full_grid(L.cus, per_cu ? per_cu : kDefaultWgsPerCu);
 }
 
 // Launch shape.  Whole GPU (cu_budget = 0): persistent 256-thread workgroups, enough for every
@@ -269,15 +268,15 @@ void separate_entries(const Launch &L, uint32_t n_req, uint32_t lead, Roles *w, 
   *n_wgs = own + L.grid;
 }
 
-// Several requests whose slices are read under the scan.  A pack (preload_pack): whole slices, 3/4 of the chip's wavefronts
-// at most.  A restore of more than 64 requests, which otherwise reads its first slices behind the scan (scan_extents): as
-// long as no wavefront has a second item.  Graph replay, us, behind / under the scan, 32 KiB blocks: 150 in 150 requests
+// Several requests whose slices are read under the scan.  A pack (preload_pack): whole slices, one_slice_saves.  A restore
+// of more than 64 requests, which otherwise reads its first slices behind the scan (scan_extents): as long as no wavefront
+// has a second item.  Graph replay, us, behind / under the scan, 32 KiB blocks: 150 in 150 requests
 // 6.9 / 5.3, 350 in 100 10.4 / 8.6, 480 in 200 12.6 / 11.4; blocks of 4 KiB, 1500 in 500 9.1 / 6.2, 3000 in 1000 14.3 / 11.1;
 // with a second item, 600 requests, 49 MB, 20.3 / 22.0.
 template <int DIR>
 bool scan_reads(const Launch &L, const MoveArgs &m, uint32_t n_req, uint64_t wave_items) {
   if (n_req == 1 || L.pieces || L.hnd_lds || L.wg_threads != kWgThreads || L.unroll != kDefaultUnroll) return false;
-  if (DIR == kPack) return 4 * wave_items <= 3 * whole_gpu_waves(L);
+  if (DIR == kPack) return one_slice_saves(wave_items, whole_gpu_waves(L));
   return n_req > kWave && m.dense != 0 && m.visit == nullptr && wave_items <= whole_gpu_waves(L);
 }
 
@@ -446,7 +445,6 @@ Roles make_roles(const Launch &L, uint64_t entry_quarters, uint32_t *grid) {
     if (cap > limit) limit = cap;
   }
   Roles w;
-  if (limit > kMostWgs) limit = kMostWgs;
   w.sqe_wgs = static_cast<uint32_t>(need < limit ? need : limit);
   w.copy_first = 0;
   w.copy_wgs = L.grid;
@@ -823,7 +821,6 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
   if (rc) return rc;
   if (!L.keeps_order) m.visit = d_visit;
   size_grid(cu_budget, move_wave_items(L, m), &L);
-  if (L.grid > kMostWgs) L.grid = kMostWgs;  // (more than a chip holds: the measurement build's knobs reach there)
   // one lane per 16-byte quarter of an entry; no more entries than the capacity, nor than the table can give
   // (every request has at most obj/chunk + 1 chunks per object, and obj < blocks*block_bytes + align <= ... + chunk)
   uint64_t max_entries = 2ull * ((static_cast<uint64_t>(table_len) * bb) / cfg->chunk_bytes + 2ull * n_req);

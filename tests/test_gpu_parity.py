@@ -528,6 +528,21 @@ def test_random_shapes(orc, H, request, seed):
                                first_slot=seed % (n_slots + 1), n_slots=n_slots, cu_budget=budget)
 
 
+@pytest.mark.parametrize("wgs_per_cu", [15, 16, 32, 1024])
+def test_saves_with_more_workgroups_than_a_chip_holds(orc, H, knobs, wgs_per_cu):
+    """A slice for each of up to 3/4 of the chip's wavefronts, counted with the knob's workgroups per compute unit: every slice
+    has a wavefront, also where the knob asks for more workgroups than a launch's arguments can say."""
+    say("saves with", wgs_per_cu, "workgroups per compute unit")
+    B.tutti_set_tuning(wgs_per_cu, 0)
+    rng = np.random.default_rng(8500 + wgs_per_cu)
+    for blocks in (767, 1250):
+        n = np.full(8, blocks // 8, np.uint32)
+        n[3] += blocks - int(n.sum())
+        c = H.LayerCase(T=16, h=8, d=128, e=2, N=blocks + 5, n_blocks=n, table=rng.permutation(blocks + 5)[:blocks],
+                        name=f"wgs{wgs_per_cu}b{blocks}")
+        H.check_layer_save(orc, c)
+
+
 # ------------------------------------------------------------------ rings: fill IOCBs, execute them, completions
 
 def test_rings_small(orc, H):

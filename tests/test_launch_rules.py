@@ -32,6 +32,8 @@ extern "C" unsigned cut_of(unsigned block_bytes) { return tutti::cut_slice(block
 extern "C" int cuts_of(int unpack, unsigned n_req, unsigned block, unsigned slice, unsigned long long items, unsigned chip) {
   return tutti::cuts_blocks(unpack != 0, n_req, block, slice, items, chip);
 }
+extern "C" unsigned grid_of(unsigned cus, unsigned wgs_per_cu) { return tutti::full_grid(cus, wgs_per_cu); }
+extern "C" int one_slice_of(unsigned long long items, unsigned long long chip) { return tutti::one_slice_saves(items, chip); }
 extern "C" int pieces_of(int whole_gpu, unsigned units) { return tutti::pieces_shape(whole_gpu != 0, units); }
 """
 CHIP = 8192  # wavefronts of a whole-GPU launch on 256 compute units
@@ -197,3 +199,18 @@ def test_blocks_are_cut_up_to_a_slice_a_wavefront(rules):
         assert rules.cuts_of(unpack, n_req, block, slice_, 0, CHIP) and rules.cuts_of(unpack, n_req, block, slice_, most, CHIP)
         assert not rules.cuts_of(unpack, n_req, block, slice_, most + 1, CHIP)
         assert not rules.cuts_of(unpack, n_req, block, slice_, 1 << 33, CHIP)
+
+
+@pytest.mark.parametrize("cus", [1, 64, 256, 304])
+def test_saves_of_one_slice_a_wavefront_have_the_wavefronts(rules, cus):
+    """With every workgroup count that the knob takes: the rule admits no more slices than the launched grid has wavefronts, and
+    the grid is one that the arguments' fields hold."""
+    rules.one_slice_of.argtypes = [ctypes.c_ulonglong] * 2
+    for per_cu in [*range(1, 40), 64, 256, 1024]:
+        most = rules.grid_of(cus, per_cu)
+        assert most == min(cus * per_cu, 4088)
+        assert rules.one_slice_of(3 * most, 4 * most)
+        for items in range(3 * most - 8, 4 * cus * per_cu + 8, 61):
+            grid = min(-(-items // 4), most)
+            if rules.one_slice_of(items, 4 * most):
+                assert items <= 4 * grid, (per_cu, items)
