@@ -174,6 +174,9 @@ int tutti_sqe_build(const tutti_pool *pool, const tutti_objcfg *cfg, const tutti
  * cu_budget stands in for the SM count of the paper's issue_io(IOCB_ids, SMs) (sec. 3.2): 0 = whole
  * GPU; B > 0 limits the grid to B compute units' worth of persistent workgroups so a concurrent
  * compute kernel keeps the rest; B > CU count is TUTTI_ERANGE.
+ * Planes, staging buffer and the d_* arrays that the call has a use for lie below address 2^47, as all memory of a process does
+ * (else TUTTI_EINVAL); of a pool whose block_stride is, as a signed number, below -2^47 or from 2^47 on, block 0 alone is
+ * moved and the others count as bad ids (TUTTI_ST_BAD_BLOCK).  The same holds for tutti_layer_restore_ordered and tutti_layer_save.
  * The launch is sized by table_len (the block counts are device memory): a table longer than the blocks in use costs
  * workgroups that find nothing to do (64 blocks of 32 KiB: 3.2 us with a table of 64 entries, 7.4 with 512 or more). */
 int tutti_layer_restore(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t *d_n_blocks, uint32_t n_req,

@@ -91,6 +91,17 @@ constexpr void put(LayerCall &c, Bits f, uint64_t v) {
 constexpr uint64_t kAddressEnd = 1ull << 47;  // user addresses, of the host and of the GPU alike, lie below
 constexpr uint32_t kMostWgs = 4088;           // workgroups of a launch that the fields hold
 
+// The blocks of a pool that memory can be at.  With a stride that the field does not hold that is block 0 alone: the others count
+// as ids that the pool has not got (a bad id is skipped and reported), instead of lying where the stride's low bits say.
+struct PoolBlocks {
+  uint64_t stride;
+  uint32_t n;
+};
+constexpr PoolBlocks blocks_in_memory(uint64_t stride, uint32_t n) {
+  const bool held = stride + kAddressEnd < 2 * kAddressEnd;  // as a signed number from -2^47 on and below 2^47
+  return PoolBlocks{held ? stride : 0, held || n == 0 ? n : 1};
+}
+
 constexpr LayerCall pack(const LayerFields &f) {
   using namespace layer_call;
   LayerCall c{};

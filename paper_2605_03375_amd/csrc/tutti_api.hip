@@ -806,7 +806,9 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
   if (sqe_cap > 0 && (!d_sqe || !aligned16(d_sqe))) return TUTTI_EINVAL;
   if (layer >= cfg->num_layers) return TUTTI_EINVAL;
   if (stage_addr % cfg->align != 0) return TUTTI_EINVAL;
-  if (!addressable({pool->k_base, pool->v_base, d_stage, d_totals, d_status, d_visit}) ||
+  // what the call may touch (a visiting order goes to the kernel as it is)
+  if (!addressable({pool->k_base, pool->v_base, d_totals, d_status}) ||
+      ((stage_cap > 0 || table_len > 0) && !addressable({d_stage})) ||
       (n_req > 0 && !addressable({d_n_blocks, d_extents, d_file_id})) ||
       (table_len > 0 && !addressable({d_block_table})) || (sqe_cap > 0 && !addressable({d_sqe})))
     return TUTTI_EINVAL;
@@ -819,6 +821,9 @@ int layer_entry(const tutti_pool *pool, const tutti_objcfg *cfg, const uint32_t 
                       DIR == kUnpack, DIR == kUnpack && bb % cfg->align == 0, d_visit != nullptr,
                       true, &L, &m);
   if (rc) return rc;
+  const PoolBlocks blocks = blocks_in_memory(m.block_stride, m.num_blocks);
+  m.block_stride = blocks.stride;
+  m.num_blocks = blocks.n;
   if (!L.keeps_order) m.visit = d_visit;
   size_grid(cu_budget, move_wave_items(L, m), &L);
   // one lane per 16-byte quarter of an entry; no more entries than the capacity, nor than the table can give

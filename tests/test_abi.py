@@ -5,6 +5,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_03375_amd import binding as B
 
@@ -131,6 +132,28 @@ def test_bad_cfg_is_einval(bad):
     p = B.make_pool(FAKE, FAKE, **GOOD)
     _expect(B.EINVAL, B.tutti_obj_layout, p, B.make_cfg(**kw), FAKE, 1, FAKE, FAKE)
     _expect(B.EINVAL, B.tutti_sqe_build, p, B.make_cfg(**kw), FAKE, 1, FAKE, 0, B.OP_READ, 0, 0, FAKE, 4)
+
+
+def test_used_pointers_beyond_all_memory_are_einval():
+    """Fused launches refuse an address from 2^47 on where the call has a use for it, and nowhere else."""
+    cfg, far, none = B.make_cfg(num_layers=2), 1 << 47, 1 << 30    # (no device has that many compute units)
+    p = B.make_pool(FAKE, FAKE, **GOOD)
+
+    def call(fn, code, pool=p, n_req=1, table_len=1, stage_cap=4096, sqe_cap=4, **at):
+        d = dict(dict.fromkeys(("n", "table", "file", "stage", "ext", "tot", "sqe", "status"), FAKE), **at)
+        _expect(code, fn, pool, cfg, d["n"], n_req, d["table"], table_len, d["file"], 0, d["stage"], stage_cap, 0, 0, d["ext"],
+                d["tot"], d["sqe"], sqe_cap, none, d["status"])
+
+    past = B.EHIP if not torch.cuda.is_available() else B.ERANGE   # what a call says that gets as far as the device
+    for fn in (B.tutti_layer_restore, B.tutti_layer_save):
+        for k, v in ((far, FAKE), (FAKE, far)):
+            call(fn, B.EINVAL, pool=B.make_pool(k, v, **GOOD))
+        for name in ("n", "table", "file", "stage", "ext", "tot", "sqe", "status"):
+            call(fn, B.EINVAL, **{name: far})
+            call(fn, past, **{name: far - 16})
+        call(fn, past, n_req=0, n=far, file=far, ext=far)
+        call(fn, past, sqe_cap=0, sqe=far)
+        call(fn, past, table_len=0, stage_cap=0, table=far, stage=far)
 
 
 def test_null_and_misaligned_pointers_are_einval():

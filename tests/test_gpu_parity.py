@@ -1397,6 +1397,39 @@ def test_slices_under_a_budget(orc, H, T, h, d, e, layout):
     H.check_everything(orc, c, cu_budget=3)
 
 
+@pytest.mark.parametrize("stride", [1 << 47, (1 << 48) + 4096, 1 << 60])
+@pytest.mark.parametrize("layout,d", [(0, 64), (1, 64), (1, 8)])
+def test_strides_beyond_all_memory(H, stride, layout, d):
+    """Of blocks that far apart only block 0 can be in memory: it is moved, and another one's id is a bad id."""
+    say("stride", stride, "layout", layout, "rows of", 2 * d)
+    c = H.LayerCase(T=16, h=2, d=d, e=2, N=4, n_blocks=[1, 1], table=[0, 1], layout=layout, name=f"stride{stride}l{layout}d{d}")
+    for op in (B.tutti_layer_save, B.tutti_layer_restore):
+        k, v = c.k_dev.clone(), c.v_dev.clone()
+        pool = B.make_pool(k, v, **dict(c.geom(), block_stride=stride))
+        stage = torch.randint(0, 256, (4 * 4096,), dtype=torch.uint8, device=H.DEV)
+        was = stage.clone()
+        ext = torch.zeros(64, dtype=torch.uint8, device=H.DEV)
+        tot = torch.zeros(2, dtype=torch.int64, device=H.DEV)
+        sqe = torch.zeros(64 * 4, dtype=torch.uint8, device=H.DEV)
+        st = H.new_status()
+        op(pool, c.gpu_cfg(), c.d_n_blocks, 2, c.d_table, 2, c.d_file_id, 0, stage, 4 * 4096, 0, 1, ext, tot, sqe, 4, 0, st)
+        torch.cuda.synchronize()
+        assert int(st.item()) == B.ST_BAD_BLOCK
+        ok, ov, ostage = c.k_dev.clone(), c.v_dev.clone(), was.clone()
+        bb, row = c.bb, 2 * d
+        if op is B.tutti_layer_save:
+            for obj, plane in ((0, c.k_dev), (1, c.v_dev)):
+                b = plane[:bb].reshape(2, 16, row).transpose(0, 1).reshape(-1) if layout else plane[:bb]
+                ostage[4096 * obj:4096 * obj + bb] = b
+                ostage[4096 * obj + bb:4096 * (obj + 1)] = 0
+                ostage[8192 + 4096 * obj + bb:8192 + 4096 * (obj + 1)] = 0
+        else:
+            for obj, plane in ((0, ok), (1, ov)):
+                b = was[4096 * obj:4096 * obj + bb]
+                plane[:bb] = b.reshape(16, 2, row).transpose(0, 1).reshape(-1) if layout else b
+        assert torch.equal(k, ok) and torch.equal(v, ov) and torch.equal(stage, ostage)
+
+
 @pytest.mark.parametrize("n", [0, 1, 1023, 2047, 2048, 2561, 3073, 4096, 4097])
 def test_one_request_on_both_sides_of_each_rule(orc, H, n):
     """One request of whole-slice blocks (4 KiB: 2n items) around the sizes where the launch changes: half, 5/8 and 3/4

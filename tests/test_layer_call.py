@@ -29,6 +29,13 @@ extern "C" void sizes(unsigned tokens, unsigned heads, unsigned row, int powers,
   const tutti::BlockSizes b = tutti::get_sizes(tutti::unpack(tutti::pack(f)), powers != 0);
   out[0] = b.tokens, out[1] = b.heads, out[2] = b.row_bytes;
 }
+extern "C" void blocks(unsigned long stride, unsigned num_blocks, tutti::LayerFields *out) {
+  tutti::LayerFields f{};
+  f.align = 16;
+  const tutti::PoolBlocks b = tutti::blocks_in_memory(stride, num_blocks);
+  f.block_stride = b.stride, f.num_blocks = b.n;
+  *out = tutti::unpack(tutti::pack(f));
+}
 """
 
 
@@ -92,6 +99,20 @@ def test_what_the_fields_cannot_hold(lib):
     f.chip_waves = 1 << 20
     lib.there_and_back(ctypes.byref(f), ctypes.byref(out))
     assert out.chip_waves == 127 * 128
+
+
+@pytest.mark.parametrize("stride, held", [(32768, True), ((1 << 47) - 16, True), ((1 << 64) - 32768, True),
+                                          ((1 << 64) - (1 << 47), True), (1 << 47, False), ((1 << 48) + 4096, False),
+                                          (1 << 60, False), (1 << 63, False), ((1 << 64) - (1 << 47) - 16, False)])
+@pytest.mark.parametrize("num_blocks", [1, 2, 0xffffffff])
+def test_blocks_are_where_the_stride_says_or_nowhere(lib, stride, held, num_blocks):
+    """No id below the count that the kernel gets lies elsewhere than id * stride says."""
+    out = Fields()
+    lib.blocks(ctypes.c_ulong(stride), num_blocks, ctypes.byref(out))
+    assert out.num_blocks == (num_blocks if held else 1)
+    for b in (0, 1, out.num_blocks - 1):
+        if b < out.num_blocks:
+            assert (b * out.block_stride) % (1 << 64) == (b * stride) % (1 << 64)
 
 
 SHAPES = [(16, 8, 256), (16, 5, 160), (1, 1, 16), (16, 64, 16), (1 << 14, 1 << 14, 16), (1 << 28, 1, 16)[:3],
