@@ -55,10 +55,12 @@ LIMITS |= {n: ((1 << 47) - 1, 1) for n in ("table", "n_blocks", "extents", "tota
 LIMITS |= dict(block_stride=((1 << 47) - 16, 16), stage_addr=((1 << 64) - 16, 16), block_bytes=((1 << 32) - 16, 16),
                chunk_bytes=((1 << 32) - 16, 16), table_len=((1 << 31) - 1, 1), layer=(65535, 1), n_req=(2048, 1),
                sqe_wgs=(4088, 1), copy_wgs=(4088, 1), copy_first=(4095, 1), chip_waves=(127 * 128, 128), dense=(1, 1), xcd_contiguous=(1, 1),
-               left_out=(2, 1))
+               left_out=(2, 1), size_a=(1 << 14, 1), size_b=(1 << 14, 1))
 
 
 def _value(rng, name, end):
+    if name == "align":
+        return 16 << (rng.randrange(28) if end is None else 27 * end)
     top, step = LIMITS.get(name, (0xffffffff, 1))
     low = 1 if name in ("sqe_wgs", "size_a", "size_b") else 0
     if end is not None:
@@ -77,8 +79,6 @@ def test_every_field_comes_back(lib, seed):
         for n in U64 + U32:
             end = None if special is None else flip ^ (n == special)
             setattr(f, n, _value(rng, n, end))
-        f.align = 16 << rng.randrange(28)
-        f.size_a, f.size_b = ((1, 1 << 14)[flip],) * 2 if special else (rng.randint(1, 1 << 14), rng.randint(1, 1 << 14))
         out = Fields()
         lib.there_and_back(ctypes.byref(f), ctypes.byref(out))
         for n in U64 + U32:
@@ -115,12 +115,16 @@ def test_blocks_are_where_the_stride_says_or_nowhere(lib, stride, held, num_bloc
             assert (b * out.block_stride) % (1 << 64) == (b * stride) % (1 << 64)
 
 
-SHAPES = [(16, 8, 256), (16, 5, 160), (1, 1, 16), (16, 64, 16), (1 << 14, 1 << 14, 16), (1 << 28, 1, 16)[:3],
-          (1, (1 << 28) - 1, 16), (3, 5, 16 * 65537), (1, 2, 16 << 26), (1 << 20, 2, 32), (2, 1 << 20, 32), (127, 129, 16 * 16383)]
+# (tokens, heads, bytes of a row): the largest size that a field holds, one more beside it, and the longest ones
+SHAPES = [(16, 8, 256), (16, 5, 160), (1, 1, 16), (16, 64, 16), (1 << 14, (1 << 14) - 1, 16), ((1 << 14) - 1, 1 << 14, 16),
+          (1 << 14, 1 << 13, 16), ((1 << 14) + 1, 1 << 13, 16), (1 << 12, 3, 16 << 14), ((1 << 28) - 1, 1, 16),
+          (1, (1 << 28) - 1, 16), (1, 1, (1 << 32) - 16), (3, 5, 16 * 65537), (1, 2, 16 << 26), (1 << 20, 2, 32), (2, 1 << 20, 32),
+          (127, 129, 16 * 16383)]
 
 
-@pytest.mark.parametrize("tokens, heads, row", [s for s in SHAPES if s[0] * s[1] * s[2] < 1 << 32])
+@pytest.mark.parametrize("tokens, heads, row", SHAPES)
 def test_block_sizes_come_back(lib, tokens, heads, row):
+    assert tokens * heads * row < 1 << 32
     powers = all(x & (x - 1) == 0 for x in (tokens, heads, row))
     for p in (0, 1) if powers else (0,):
         out = (ctypes.c_uint32 * 3)()
