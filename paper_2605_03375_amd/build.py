@@ -28,6 +28,8 @@ HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
     # no packed-fp32 instructions in any HIP code of this repository
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # a kernel's first arguments, up to 14 words, are in scalar registers when a wavefront starts
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
 ]
 
 

@@ -17,7 +17,7 @@ namespace tutti {
 //
 // What a field leaves out is what it cannot hold: addresses lie below 2^47 (the host checks the ones that are used), planes,
 // staging, entries, strides and block sizes are multiples of 16, a chunk is a multiple of the alignment, which is a power of two.
-constexpr uint32_t kLayerCallWords = 14;
+constexpr uint32_t kLayerCallWords = 14, kEarlyWords = 7;
 struct LayerCall {
   uint64_t w[kLayerCallWords];
 };
@@ -61,16 +61,37 @@ namespace layer_call {
 struct Bits {
   uint32_t at, n;
 };
-// What the way to the first load needs lies in words of its own; the layer's number fills gaps.
-constexpr Bits kKBase{0, 44}, kCopyWgs{44, 12}, kAlign{56, 5}, kDense{61, 1}, kLayerHigh{62, 2};
-constexpr Bits kVBase{64, 44}, kCopyFirst{108, 12}, kChip{120, 7}, kXcd{127, 1};
-constexpr Bits kStage{128, 44}, kSqeWgs{172, 12}, kLeftOut{184, 2}, kLayerMid{186, 6};
-constexpr Bits kStride{192, 44}, kReqs{236, 12}, kLayerLow{248, 8};
-constexpr Bits kNumBlocks{256, 32}, kTableLen{288, 31};
-constexpr Bits kBlockBytes{320, 28}, kSizeA{348, 14}, kSizeB{362, 14}, kSglLow{376, 8};
-constexpr Bits kTable{384, 47}, kNBlocks{431, 47}, kExtents{478, 47}, kTotals{525, 47}, kFileId{572, 47}, kStatus{619, 47};
-constexpr Bits kSqe{666, 43}, kStageCap{709, 43}, kStageAddr{752, 60}, kSqeCap{812, 32}, kChunk{844, 28}, kSglHigh{872, 24};
-static_assert(kSglHigh.at + kSglHigh.n == 64 * kLayerCallWords, "the last field ends the last word");
+// The first words, kEarlyWords of them, are in scalar registers when a wavefront starts (k_layer): they hold what the way to the
+// first load of a restore needs, and most of a save's.  Each field there is one piece of one word.
+constexpr Bits kCopyWgs{0, 12}, kCopyFirst{12, 12}, kSqeWgs{24, 12}, kChip{36, 7}, kXcd{43, 1}, kAlign{44, 5}, kDense{49, 1},
+    kLeftOut{50, 2}, kLayerLow{52, 12};
+constexpr Bits kBlockBytes{64, 28}, kSizeA{92, 14}, kSizeB{106, 14}, kLayerHigh{120, 4};
+constexpr Bits kNumBlocks{128, 32}, kTableLen{160, 31};
+constexpr Bits kStage{192, 44}, kReqs{236, 12};
+constexpr Bits kNBlocks{256, 47}, kTable{320, 47}, kStageCap{384, 43};
+constexpr Bits kKBase{448, 44}, kVBase{512, 44}, kStride{576, 44};
+constexpr Bits kStageAddr{640, 60}, kSqeCap{704, 32}, kSglId{736, 32}, kExtents{768, 47}, kTotals{832, 47};
+
+// What those leave free, one gap behind the other, holds the fields that only the entry writers and the error paths read.
+constexpr uint32_t kGaps = 11;
+constexpr Bits gap(uint32_t i) {
+  switch (i) {
+    case 0: return Bits{303, 17};  // behind n_blocks
+    case 1: return Bits{367, 17};  // table
+    case 2: return Bits{427, 21};  // stage_cap
+    case 3: return Bits{492, 20};  // k_base
+    case 4: return Bits{556, 20};  // v_base
+    case 5: return Bits{620, 20};  // block_stride
+    case 6: return Bits{815, 17};  // extents
+    case 7: return Bits{879, 17};  // totals
+    case 8: return Bits{248, 8};   // n_req
+    case 9: return Bits{124, 4};   // the layer's upper bits
+    default: return Bits{700, 4};  // stage_addr
+  }
+}
+constexpr Bits kFileId{0, 47}, kStatus{47, 47}, kSqe{94, 43}, kChunk{137, 28};  // `at` counts through the gaps
+constexpr uint32_t gap_bits(uint32_t i = 0) { return i == kGaps ? 0 : gap(i).n + gap_bits(i + 1); }
+static_assert(gap_bits() == kChunk.at + kChunk.n, "the last field ends the last gap");
 
 constexpr uint64_t kBelow(uint32_t n) { return n == 64 ? ~0ull : (1ull << n) - 1; }
 constexpr uint64_t get(const LayerCall &c, Bits f) {
@@ -85,6 +106,24 @@ constexpr void put(LayerCall &c, Bits f, uint64_t v) {
   v &= kBelow(f.n);
   c.w[i] |= v << s;
   if (s + f.n > 64) c.w[i + 1] |= v >> (64 - s);
+}
+
+// The same for a field in the gaps: the part of it that lies in gap `i`, which starts at `pos`, and in those behind.
+constexpr Bits part_in(Bits f, uint32_t i, uint32_t pos) {
+  const uint32_t lo = f.at > pos ? f.at : pos, end = f.at + f.n, gap_end = pos + gap(i).n, hi = end < gap_end ? end : gap_end;
+  return lo < hi ? Bits{lo, hi - lo} : Bits{0, 0};
+}
+constexpr uint64_t get_from_gaps(const LayerCall &c, Bits f, uint32_t i = 0, uint32_t pos = 0) {
+  if (i == kGaps) return 0;
+  const Bits p = part_in(f, i, pos);
+  const uint64_t here = p.n == 0 ? 0 : get(c, Bits{gap(i).at + p.at - pos, p.n}) << (p.at - f.at);
+  return here | get_from_gaps(c, f, i + 1, pos + gap(i).n);
+}
+constexpr void put_into_gaps(LayerCall &c, Bits f, uint64_t v, uint32_t i = 0, uint32_t pos = 0) {
+  if (i == kGaps) return;
+  const Bits p = part_in(f, i, pos);
+  if (p.n != 0) put(c, Bits{gap(i).at + p.at - pos, p.n}, v >> (p.at - f.at));
+  put_into_gaps(c, f, v, i + 1, pos + gap(i).n);
 }
 }  // namespace layer_call
 
@@ -108,26 +147,24 @@ constexpr LayerCall pack(const LayerFields &f) {
   put(c, kKBase, f.k_base >> 4);
   put(c, kVBase, f.v_base >> 4);
   put(c, kStage, f.stage >> 4);
-  put(c, kSqe, f.sqe >> 4);
+  put_into_gaps(c, kSqe, f.sqe >> 4);
   put(c, kTable, f.table);
   put(c, kNBlocks, f.n_blocks);
   put(c, kExtents, f.extents);
   put(c, kTotals, f.totals);
-  put(c, kFileId, f.file_id);
-  put(c, kStatus, f.status);
+  put_into_gaps(c, kFileId, f.file_id);
+  put_into_gaps(c, kStatus, f.status);
   put(c, kStride, f.block_stride >> 4);
   put(c, kStageCap, (f.stage_cap < kAddressEnd ? f.stage_cap : kAddressEnd - 16) >> 4);
   put(c, kStageAddr, f.stage_addr >> 4);
   put(c, kNumBlocks, f.num_blocks);
   put(c, kTableLen, f.table_len);
   put(c, kBlockBytes, f.block_bytes >> 4);
-  put(c, kChunk, f.chunk_bytes >> 4);
+  put_into_gaps(c, kChunk, f.chunk_bytes >> 4);
   put(c, kSqeCap, f.sqe_cap);
-  put(c, kSglLow, f.sgl_id);
-  put(c, kSglHigh, f.sgl_id >> 8);
+  put(c, kSglId, f.sgl_id);
   put(c, kLayerLow, f.layer);
-  put(c, kLayerMid, f.layer >> 8);
-  put(c, kLayerHigh, f.layer >> 14);
+  put(c, kLayerHigh, f.layer >> 12);
   put(c, kReqs, f.n_req);
   put(c, kAlign, log2_of(f.align));
   put(c, kSqeWgs, f.sqe_wgs);
@@ -148,23 +185,23 @@ constexpr LayerFields unpack(const LayerCall &c) {
   f.k_base = get(c, kKBase) << 4;
   f.v_base = get(c, kVBase) << 4;
   f.stage = get(c, kStage) << 4;
-  f.sqe = get(c, kSqe) << 4;
+  f.sqe = get_from_gaps(c, kSqe) << 4;
   f.table = get(c, kTable);
   f.n_blocks = get(c, kNBlocks);
   f.extents = get(c, kExtents);
   f.totals = get(c, kTotals);
-  f.file_id = get(c, kFileId);
-  f.status = get(c, kStatus);
+  f.file_id = get_from_gaps(c, kFileId);
+  f.status = get_from_gaps(c, kStatus);
   f.block_stride = static_cast<uint64_t>(static_cast<int64_t>(get(c, kStride) << 20) >> 16);
   f.stage_cap = get(c, kStageCap) << 4;
   f.stage_addr = get(c, kStageAddr) << 4;
   f.num_blocks = get32(c, kNumBlocks);
   f.table_len = get32(c, kTableLen);
   f.block_bytes = get32(c, kBlockBytes) << 4;
-  f.chunk_bytes = get32(c, kChunk) << 4;
+  f.chunk_bytes = static_cast<uint32_t>(get_from_gaps(c, kChunk)) << 4;
   f.sqe_cap = get32(c, kSqeCap);
-  f.sgl_id = get32(c, kSglHigh) << 8 | get32(c, kSglLow);
-  f.layer = get32(c, kLayerHigh) << 14 | get32(c, kLayerMid) << 8 | get32(c, kLayerLow);
+  f.sgl_id = get32(c, kSglId);
+  f.layer = get32(c, kLayerHigh) << 12 | get32(c, kLayerLow);
   f.n_req = get32(c, kReqs);
   f.align = 1u << get32(c, kAlign);
   f.sqe_wgs = get32(c, kSqeWgs);

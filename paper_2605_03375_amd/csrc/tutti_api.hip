@@ -607,23 +607,23 @@ hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStre
                               const SqeArgs &q, const LayoutArgs &a, const Roles &w) {
   const dim3 grid(n_wgs), block(S::WG);
   const LayerCall c = layer_call_of<DIR, HND>(m, q, a, w);
+  LateWords late;
+  std::copy(c.w + kEarlyWords, c.w + kLayerCallWords, late.w);
+  const auto launch = [&](auto kernel, const auto &rest) {
+    hipLaunchKernelGGL(kernel, grid, block, lds, s, u64x4{c.w[0], c.w[1], c.w[2], c.w[3]}, u64x2{c.w[4], c.w[5]}, c.w[6], rest);
+    return hipGetLastError();
+  };
   if constexpr ((REQS == kFew || REQS == kMany) && any_blocks(HND)) {
     if constexpr (DIR == kUnpack && REQS == kMany) {
-      if (m.visit) {  // the caller's visiting order
-        hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>), grid, block, lds, s, OrderedCall{c, m.visit});
-        return hipGetLastError();
-      }
+      if (m.visit)  // the caller's visiting order
+        return launch(k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>, OrderedLateWords{late, m.visit});
     }
     if constexpr (has_pieces<S> && (REQS == kMany || S::WG == kWgThreads)) {
-      if (pieces) {
-        hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, false, true>), grid, block, lds, s, c);
-        return hipGetLastError();
-      }
+      if (pieces) return launch(k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, false, true>, late);
     }
   }
   if (pieces) return hipErrorInvalidValue;  // never through the kernel of whole slices
-  hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG, REQS>), grid, block, lds, s, c);
-  return hipGetLastError();
+  return launch(k_layer<DIR, HND, S::U, S::NT, S::WG, REQS>, late);
 }
 
 template <int DIR, int HND>

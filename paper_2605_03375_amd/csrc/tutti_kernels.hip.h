@@ -2293,13 +2293,15 @@ __device__ __forceinline__ void args_at_hand(const MoveArgs &m, const LayoutArgs
                "s"(m.slices_per_block), "s"(m.items_bound), "s"(m.xcd_contiguous), "s"(a.n_blocks), "s"(a.n_req),
                "s"(w.sqe_wgs), "s"(w.copy_first), "s"(w.copy_wgs));
 }
-__device__ __forceinline__ void words_at_hand(const LayerCall &c) {
-  asm volatile("" ::"s"(c.w[0]), "s"(c.w[1]), "s"(c.w[2]), "s"(c.w[3]), "s"(c.w[4]), "s"(c.w[5]), "s"(c.w[6]), "s"(c.w[7]),
-               "s"(c.w[8]), "s"(c.w[9]), "s"(c.w[10]), "s"(c.w[11]), "s"(c.w[12]), "s"(c.w[13]));
-}
 
-struct OrderedCall {
-  LayerCall call;
+// The words of a LayerCall behind the first ones, which are arguments of their own.
+typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
+typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+struct LateWords {
+  uint64_t w[kLayerCallWords - kEarlyWords];
+};
+struct OrderedLateWords {
+  LateWords late;
   const uint32_t *visit;
 };
 
@@ -2405,12 +2407,17 @@ __device__ __forceinline__ void take_apart(const LayerFields &f, const uint32_t 
   w.copy_wgs = f.copy_wgs;
 }
 
+// Holds the late words' registers until here: the loads that bring them are on their way from the start, and a register that
+// is put to another use meanwhile would make that use wait for them.
+__device__ __forceinline__ void late_words_at_hand(const LayerCall &c) {
+  asm volatile("" ::"s"(c.w[7]), "s"(c.w[8]), "s"(c.w[9]), "s"(c.w[10]), "s"(c.w[11]), "s"(c.w[12]), "s"(c.w[13]));
+}
+
 // ORD (restore only): the blocks are visited in the order `visit` lists instead of staging order; the first slices
 // cannot be preloaded then (where they sit depends on the list).
 template <int DIR, int HND, int U, int NT, int WG, int REQS, bool ORD, bool PIECES>
 __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *visit) {
   extern __shared__ __align__(16) unsigned char smem[];
-  words_at_hand(c);
   MoveArgs m;
   SqeArgs q;
   LayoutArgs a;
@@ -2424,8 +2431,10 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
   const bool publish = blockIdx.x == 0;  // also an entry-writing workgroup: there is at least one
   if constexpr (REQS == kOne) {
     if (DIR == kUnpack && reads_ahead(U) && copies) pre = preload_first<HND, U, NT, WG>(m, wg, w.copy_wgs);
+    if (DIR == kUnpack) late_words_at_hand(c);
     const bool entries = blockIdx.x < w.sqe_wgs;
     const OneReq one = one_request(m, a, l, publish, entries, nullptr, FileArgs{0, 0, 0});
+    if (DIR == kPack) late_words_at_hand(c);
     SqeHead one_head;
     one_head.live = false;
     uint64_t word = 0;
@@ -2448,10 +2457,12 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
       blockIdx.x < w.sqe_wgs, nullptr, FileArgs{0, 0, 0}, [&] {
         if (DIR == kPack && reads_under_scan(REQS)) {
           first = PackItem<U, WG, REQS>(m, wg, w.copy_wgs);
+          late_words_at_hand(c);
           if (!counts_first(REQS)) pre = preload_pack<HND, U, NT>(m, first);
         } else if (DIR == kUnpack && !ORD && !PIECES && reads_ahead(U) && copies) {
           pre = preload_first<HND, U, NT, WG>(m, wg, w.copy_wgs);
         }
+        if (DIR == kUnpack && !ORD && !PIECES && reads_ahead(U)) late_words_at_hand(c);
       },
       [&](uint32_t blocks) {
         if (DIR == kPack && first.pos < blocks) pre = preload_pack<HND, U, NT>(m, first);
@@ -2490,13 +2501,25 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
   if (blockIdx.x < w.sqe_wgs) emit_sqes<WG>(entry_args<DIR>(fields_of_lanes(word)), l, a.n_req, 0, w.sqe_wgs, head);
 }
 
+// The early words are arguments by themselves because such are in registers when a wavefront starts (-amdgpu-kernarg-preload-count);
+// the members of a struct are read from memory.  Graph replay of a copy kernel of four arguments, us, read / in registers:
+// 4 KiB 2.48 / 2.40, 64 KiB 3.74 / 3.60, 256 KiB 6.9 / 6.7.  Calls with the words from memory / so: save of 1280 blocks in 512
+// requests 8.07 / 7.93, restore of 128 MiB 44.0 / 43.8; where the host is what a train waits for, 3.03 / 3.12 a layer.
 template <int DIR, int HND, int U, int NT, int WG, int REQS, bool ORD = false, bool PIECES = false>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(
-    const typename std::conditional<ORD, OrderedCall, LayerCall>::type c) {
-  if constexpr (ORD)
-    run_layer<DIR, HND, U, NT, WG, REQS, true, PIECES>(c.call, c.visit);
-  else
-    run_layer<DIR, HND, U, NT, WG, REQS, false, PIECES>(c, nullptr);
+    const u64x4 w0, const u64x2 w4, uint64_t w6, const typename std::conditional<ORD, OrderedLateWords, LateWords>::type rest) {
+  LayerCall c{{w0.x, w0.y, w0.z, w0.w, w4.x, w4.y, w6}};
+  const uint32_t *visit = nullptr;
+  const LateWords *late;
+  if constexpr (ORD) {
+    late = &rest.late;
+    visit = rest.visit;
+  } else {
+    late = &rest;
+  }
+#pragma unroll
+  for (uint32_t i = kEarlyWords; i < kLayerCallWords; ++i) c.w[i] = late->w[i - kEarlyWords];
+  run_layer<DIR, HND, U, NT, WG, REQS, ORD, PIECES>(c, visit);
 }
 
 // First item of a wavefront in a retrieve of ONE request: its file bytes sit at
