@@ -671,18 +671,19 @@ hipError_t launch_layer(const Launch &L, uint64_t entry_quarters, uint32_t lds, 
 }
 
 template <typename S, int DIR, int REQS>
-hipError_t launch_ring_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStream_t s, const MoveArgs &m,
-                             const SqeArgs &q, const DirectArgs &d, const RingArgs &g, const RingArgs &done,
-                             const FileArgs &f, const LayoutArgs &a, const Roles &w) {
+hipError_t launch_ring_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStream_t s, RingCall c, const Roles &w) {
   const dim3 grid(n_wgs), block(S::WG);
+  c.sqe_wgs = w.sqe_wgs;
+  c.copy_first = w.copy_first;
+  c.copy_wgs = w.copy_wgs;
   if constexpr (has_pieces<S> && (REQS == kMany || (REQS == kFew && S::WG == kWgThreads))) {
     if (pieces) {
-      hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG, REQS, true>), grid, block, lds, s, m, q, d, g, done, f, a, w);
+      hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG, REQS, true>), grid, block, lds, s, c);
       return hipGetLastError();
     }
   }
   if (pieces) return hipErrorInvalidValue;  // never through the kernel of whole slices
-  hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG, REQS>), grid, block, lds, s, m, q, d, g, done, f, a, w);
+  hipLaunchKernelGGL((k_layer_ring<DIR, S::U, S::WG, REQS>), grid, block, lds, s, c);
   return hipGetLastError();
 }
 
@@ -1146,13 +1147,40 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
   uint64_t n_ctx = static_cast<uint64_t>(n_slots) * TUTTI_IOCB_SLOTS;
   if (n_ctx > 2ull * table_len) n_ctx = 2ull * table_len;
 
-  const SqeArgs q = sqe_args(d_file_id, nullptr, d_status, 0, 0, bb, layer,
-                             (DIR == kUnpack) ? TUTTI_OP_READ : TUTTI_OP_WRITE, sgl_id);
-  const DirectArgs d = direct_args(d_block_table, sgl_table_addr, table_len, pool->num_blocks, bb);
-  RingArgs g{ring->d_sq, static_cast<tutti_cq_hdr *>(ring->d_cq), ring->depth, first_slot, n_slots};
-  RingArgs gd{ring->d_sq, static_cast<tutti_cq_hdr *>(ring->d_cq), ring->depth, done_first, done_n};
-  FileArgs f{store->file_stride, store->first_file_id, store->n_files};
-  const LayoutArgs a = layout_args(d_n_blocks, d_extents, d_totals, bb, cfg, n_req);
+  const RingArgs g{ring->d_sq, static_cast<tutti_cq_hdr *>(ring->d_cq), ring->depth, first_slot, n_slots};
+  const auto address = [](const void *p) { return reinterpret_cast<uint64_t>(p); };
+  RingCall c{};
+  c.k_base = address(m.k_base);
+  c.v_base = address(m.v_base);
+  c.stage = address(m.stage);
+  c.table = address(d_block_table);
+  c.n_blocks = address(d_n_blocks);
+  c.file_id = address(d_file_id);
+  c.status = address(d_status);
+  c.extents = address(d_extents);
+  c.totals = address(d_totals);
+  c.sq = address(g.sq);
+  c.cq = address(g.cq);
+  c.block_stride = m.block_stride;
+  c.file_stride = store->file_stride;
+  c.sgl_table_addr = sgl_table_addr;
+  c.num_blocks = m.num_blocks;
+  c.block_bytes = bb;
+  c.table_len = table_len;
+  c.chip_waves = m.chip_waves;
+  c.n_req = n_req;
+  c.align = cfg->align;
+  c.chunk_bytes = cfg->chunk_bytes;
+  c.layer = layer;
+  c.sgl_id = sgl_id;
+  c.first_file_id = store->first_file_id;
+  c.n_files = store->n_files;
+  c.depth = g.depth;
+  c.first_slot = first_slot;
+  c.n_slots = n_slots;
+  c.done_first = done_first;
+  c.done_n = done_n;
+  c.xcd_contiguous = m.xcd_contiguous;
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint32_t n_wgs = 0;
@@ -1166,15 +1194,15 @@ int ring_layer_entry(const tutti_ring *ring, uint32_t first_slot, uint32_t n_slo
       const bool one = one_request_path<DIR>(R, m, n_req, move_wave_items(R, m));
       const bool ahead = DIR == kPack && n_req <= kWave && scan_reads<DIR>(R, m, n_req, move_wave_items(R, m));
       if (one || ahead || few_requests(R, m, n_req)) separate_entries(R, n_req, lead, &w, &n_wgs);
-      if (one) return launch_ring_shape<S, DIR, kOne>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+      if (one) return launch_ring_shape<S, DIR, kOne>(false, n_wgs + lead, lds, s, c, w);
       if constexpr (DIR == kPack && S::WG == kWgThreads) {
         if (ahead && !pack_at_once(move_wave_items(R, m), m.chip_waves, n_req, m.table_len))
-          return launch_ring_shape<S, DIR, kFewCounted>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
-        if (ahead) return launch_ring_shape<S, DIR, kFewAhead>(false, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+          return launch_ring_shape<S, DIR, kFewCounted>(false, n_wgs + lead, lds, s, c, w);
+        if (ahead) return launch_ring_shape<S, DIR, kFewAhead>(false, n_wgs + lead, lds, s, c, w);
       }
-      if (few_requests(R, m, n_req)) return launch_ring_shape<S, DIR, kFew>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+      if (few_requests(R, m, n_req)) return launch_ring_shape<S, DIR, kFew>(R.pieces, n_wgs + lead, lds, s, c, w);
     }
-    return launch_ring_shape<S, DIR, kMany>(R.pieces, n_wgs + lead, lds, s, m, q, d, g, gd, f, a, w);
+    return launch_ring_shape<S, DIR, kMany>(R.pieces, n_wgs + lead, lds, s, c, w);
   });
   if (e != hipSuccess) return hip_fail(e);
   if (!complete) return TUTTI_OK;

@@ -2565,6 +2565,75 @@ __device__ __forceinline__ Preload<U> preload_first_direct(const MoveArgs &m, co
   return p;
 }
 
+// The arguments of k_layer_ring, each once: 192 bytes, and few enough that the kernels of many requests spill half as many scalar
+// registers (as eight records that repeated each other they were 372; they do not fit a LayerCall's 112).  As records / so, us:
+// retrieve of 64 blocks of 32 KiB 7.5 / 7.2, of 512 in one request 14.7 / 13.4, in 40 16.5 / 16.1, in 200 18.9 / 18.0; store of 512
+// in one request 15.6 / 14.7, in 200 18.9 / 18.2; trains of 16 layers of 129 blocks, retrieve 106.5 / 102.5, store 98.1 / 89.3.
+struct RingCall {
+  uint64_t k_base, v_base, stage, table, n_blocks, file_id, status, extents, totals, sq, cq;  // addresses
+  uint64_t block_stride, file_stride, sgl_table_addr;
+  uint32_t num_blocks, block_bytes, table_len, chip_waves, n_req, align, chunk_bytes, layer, sgl_id, first_file_id, n_files;
+  uint32_t depth, first_slot, n_slots, done_first, done_n, sqe_wgs, copy_first, copy_wgs, xcd_contiguous;
+};
+constexpr uint32_t kRingCallWords = sizeof(RingCall) / sizeof(uint64_t);
+static_assert(sizeof(RingCall) == 24 * sizeof(uint64_t), "whole words");
+
+struct RingParts {
+  MoveArgs m;
+  SqeArgs q;
+  DirectArgs d;
+  RingArgs g, done;
+  FileArgs f;
+  LayoutArgs a;
+  Roles w;
+};
+template <int DIR, int U, bool PIECES>
+__device__ __forceinline__ RingParts take_apart(const RingCall &c) {
+  const auto words = [](uint64_t address) { return reinterpret_cast<uint32_t *>(as_global(address)); };
+  const auto covered_by = [&](uint32_t bytes) { return (c.block_bytes / 16 + (bytes / 16 - 1)) / (bytes / 16); };
+  RingParts p;
+  p.m = MoveArgs{};
+  p.m.k_base = as_global(c.k_base);
+  p.m.v_base = as_global(c.v_base);
+  p.m.stage = as_global(c.stage);
+  p.m.table = words(c.table);
+  p.m.status = words(c.status);
+  p.m.block_stride = c.block_stride;
+  p.m.num_blocks = c.num_blocks;
+  p.m.block_bytes = c.block_bytes;
+  p.m.table_len = c.table_len;
+  p.m.slices_per_block = covered_by(PIECES ? kPiece : U * kPiece);
+  p.m.items_bound = 2u * c.table_len * covered_by(U * kPiece);
+  p.m.chip_waves = c.chip_waves;
+#ifdef TUTTI_BENCH_BUILD
+  p.m.xcd_contiguous = c.xcd_contiguous;
+#endif
+  p.m.layer = c.layer;
+  p.m.file_stride = c.file_stride;
+  p.m.ctx_cap = static_cast<uint64_t>(c.n_slots) * TUTTI_IOCB_SLOTS;
+  p.q = SqeArgs{words(c.file_id), nullptr, p.m.status, 0, 0, c.block_bytes, c.layer,
+                static_cast<uint32_t>(DIR == kUnpack ? TUTTI_OP_READ : TUTTI_OP_WRITE), c.sgl_id};
+  p.d = DirectArgs{p.m.table, c.sgl_table_addr, c.table_len, c.num_blocks, c.block_bytes};
+  p.g = RingArgs{reinterpret_cast<tutti_iocb *>(as_global(c.sq)), reinterpret_cast<tutti_cq_hdr *>(as_global(c.cq)), c.depth,
+                 c.first_slot, c.n_slots};
+  p.done = RingArgs{p.g.sq, p.g.cq, c.depth, c.done_first, c.done_n};
+  p.f = FileArgs{c.file_stride, c.first_file_id, c.n_files};
+  p.a = LayoutArgs{words(c.n_blocks), reinterpret_cast<tutti_extent *>(as_global(c.extents)),
+                   reinterpret_cast<uint64_t *>(as_global(c.totals)), ScanGeom{c.block_bytes, c.align, c.chunk_bytes}, c.n_req};
+  p.w = Roles{c.sqe_wgs, c.copy_first, c.copy_wgs};
+  return p;
+}
+// Read from memory once more, as in fields_again.
+__device__ __forceinline__ RingCall ring_call_again() {
+  const const_u64_ptr p = call_words();
+  uint64_t w[kRingCallWords];
+#pragma unroll
+  for (uint32_t i = 0; i < kRingCallWords; ++i) w[i] = p[i];
+  RingCall c;
+  __builtin_memcpy(&c, w, sizeof(c));
+  return c;
+}
+
 // retrieve_layer / store_layer through the rings in one launch (direct-to-block mode): the scan puts the start
 // of every request's file in the store where the staging offsets would be, then the first `sqe_wgs`
 // workgroups record the layer's contexts in the IOCBs while the copy workgroups move the very same blocks,
@@ -2575,24 +2644,16 @@ __device__ __forceinline__ Preload<U> preload_first_direct(const MoveArgs &m, co
 // done.n_slots is not 0 the grid has one workgroup more, in front, whose first wavefront completes them and leaves,
 // so a train of layers pays for no kernel boundary between a layer's data and the next layer's).
 template <int DIR, int U, int WG, int REQS, bool PIECES = false>
-__global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(const MoveArgs m, const SqeArgs q_, const DirectArgs d_,
-                                                    const RingArgs g, const RingArgs done, const FileArgs f_,
-                                                    const LayoutArgs a_, const Roles w) {
+__global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(const RingCall call) {
   extern __shared__ __align__(16) unsigned char smem[];
-  // what several argument records hold is read from one of them: the scalar registers are short, and what they spill
-  // takes vector registers and, in the end, scratch memory (in the scan of many requests it is the longer lives that do)
-  SqeArgs q = q_;
-  DirectArgs d = d_;
-  FileArgs f = f_;
-  LayoutArgs a = a_;
-  if (REQS != kMany) {
-    q.status = m.status;
-    d.table = m.table;
-    d.table_len = m.table_len;
-    d.num_blocks = m.num_blocks;
-    d.block_bytes = a.geom.block_bytes = m.block_bytes;
-    f.file_stride = m.file_stride;
-  }
+  RingParts parts = take_apart<DIR, U, PIECES>(call);
+  MoveArgs &m = parts.m;
+  SqeArgs &q = parts.q;
+  DirectArgs &d = parts.d;
+  RingArgs &g = parts.g, &done = parts.done;
+  FileArgs &f = parts.f;
+  LayoutArgs &a = parts.a;
+  Roles &w = parts.w;
   const uint32_t lead = done.n_slots != 0 ? 1u : 0u;
   if (lead && blockIdx.x == 0) {  // the whole workgroup takes this branch: no barrier is left waiting
     if (threadIdx.x < kWave) complete_iocbs(done, threadIdx.x);
@@ -2634,7 +2695,10 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer_ring(co
       });
   if (REQS == kFew && DIR == kUnpack && pre.valid)
     hold_back(hold_back_pause(count_units<false, kStagingOrder, true>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, 1, true));
-  if (any_number(REQS)) l.unordered = rfl(l.wraps()) != 0;
+  if (any_number(REQS)) {
+    l.unordered = rfl(l.wraps()) != 0;
+    parts = take_apart<DIR, U, PIECES>(ring_call_again());  // the scan of many requests needs most scalar registers for itself
+  }
   DirectHead head;
   head.live = false;
   if (bx < w.sqe_wgs) head = iocb_head<WG>(g, q, d, l, a.n_req, lead, w.sqe_wgs);
