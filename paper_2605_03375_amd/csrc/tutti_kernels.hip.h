@@ -24,6 +24,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <type_traits>
@@ -2314,6 +2315,24 @@ struct OrderedLateWords {
   LateWords late;
   const uint32_t *visit;
 };
+// Where k_layer's arguments lie: fields_again and word_in_lane read them as one run of words.  An ordered restore hands over 8
+// bytes more than malloc's smallest chunks hold (layer_call.h): of the ordinary fields only the gaps are left, and those are full.
+template <typename Rest>
+struct LayerArguments {
+  u64x4 w0;
+  u64x2 w4;
+  uint64_t w6;
+  Rest rest;
+};
+static_assert(offsetof(LayerArguments<LateWords>, w0) == 0 && offsetof(LayerArguments<LateWords>, w4) == 4 * sizeof(uint64_t) &&
+                  offsetof(LayerArguments<LateWords>, w6) == 6 * sizeof(uint64_t) &&
+                  offsetof(LayerArguments<LateWords>, rest) == kEarlyWords * sizeof(uint64_t) &&
+                  offsetof(LayerArguments<OrderedLateWords>, rest) == kEarlyWords * sizeof(uint64_t) &&
+                  offsetof(OrderedLateWords, late) == 0,
+              "a LayerCall's words, one behind the other");
+static_assert(offsetof(LayerArguments<LateWords>, rest) + sizeof(LateWords) == sizeof(LayerCall) &&
+                  offsetof(LayerArguments<OrderedLateWords>, rest) + sizeof(OrderedLateWords) == sizeof(LayerCall) + 8,
+              "what the runtime copies");
 
 template <int DIR>
 __device__ __forceinline__ SqeArgs entry_args(const LayerFields &f) {
@@ -2531,6 +2550,12 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(
   for (uint32_t i = kEarlyWords; i < kLayerCallWords; ++i) c.w[i] = late->w[i - kEarlyWords];
   run_layer<DIR, HND, U, NT, WG, REQS, ORD, PIECES>(c, visit);
 }
+
+template <typename Rest>
+using LayerKernel = void (*)(u64x4, u64x2, uint64_t, Rest);  // parameters in the order of LayerArguments' members
+static_assert(std::is_same_v<decltype(&k_layer<kPack, kNhd, 4, 3, kWgThreads, kFew>), LayerKernel<LateWords>> &&
+                  std::is_same_v<decltype(&k_layer<kUnpack, kNhd, 4, 3, kWgThreads, kMany, true>), LayerKernel<OrderedLateWords>>,
+              "LayerArguments mirrors k_layer");
 
 // First item of a wavefront in a retrieve of ONE request: its file bytes sit at
 //   file start + 2*layer*obj_bytes + item*slice        (obj_bytes = n_blocks*block_bytes: blocks are whole
