@@ -607,23 +607,29 @@ hipError_t launch_layer_shape(bool pieces, uint32_t n_wgs, uint32_t lds, hipStre
                               const SqeArgs &q, const LayoutArgs &a, const Roles &w) {
   const dim3 grid(n_wgs), block(S::WG);
   const LayerCall c = layer_call_of<DIR, HND>(m, q, a, w);
-  LateWords late;
-  std::copy(c.w + kEarlyWords, c.w + kLayerCallWords, late.w);
-  const auto launch = [&](auto kernel, const auto &rest) {
-    hipLaunchKernelGGL(kernel, grid, block, lds, s, u64x4{c.w[0], c.w[1], c.w[2], c.w[3]}, u64x2{c.w[4], c.w[5]}, c.w[6], rest);
+  if constexpr (REQS == kOne) {
+    if (pieces) return hipErrorInvalidValue;  // never through the kernel of whole slices
+    hipLaunchKernelGGL((k_layer<DIR, HND, S::U, S::NT, S::WG>), grid, block, lds, s, c);
     return hipGetLastError();
-  };
-  if constexpr ((REQS == kFew || REQS == kMany) && any_blocks(HND)) {
-    if constexpr (DIR == kUnpack && REQS == kMany) {
-      if (m.visit)  // the caller's visiting order
-        return launch(k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>, OrderedLateWords{late, m.visit});
+  } else {
+    LateWords late;
+    std::copy(c.w + kEarlyWords, c.w + kLayerCallWords, late.w);
+    const auto launch = [&](auto kernel, const auto &rest) {
+      hipLaunchKernelGGL(kernel, grid, block, lds, s, u64x4{c.w[0], c.w[1], c.w[2], c.w[3]}, u64x2{c.w[4], c.w[5]}, c.w[6], rest);
+      return hipGetLastError();
+    };
+    if constexpr ((REQS == kFew || REQS == kMany) && any_blocks(HND)) {
+      if constexpr (DIR == kUnpack && REQS == kMany) {
+        if (m.visit)  // the caller's visiting order
+          return launch(k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, true>, OrderedLateWords{late, m.visit});
+      }
+      if constexpr (has_pieces<S> && (REQS == kMany || S::WG == kWgThreads)) {
+        if (pieces) return launch(k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, false, true>, late);
+      }
     }
-    if constexpr (has_pieces<S> && (REQS == kMany || S::WG == kWgThreads)) {
-      if (pieces) return launch(k_layer<DIR, HND, S::U, S::NT, S::WG, REQS, false, true>, late);
-    }
+    if (pieces) return hipErrorInvalidValue;  // never through the kernel of whole slices
+    return launch(k_layer<DIR, HND, S::U, S::NT, S::WG, REQS>, late);
   }
-  if (pieces) return hipErrorInvalidValue;  // never through the kernel of whole slices
-  return launch(k_layer<DIR, HND, S::U, S::NT, S::WG, REQS>, late);
 }
 
 template <int DIR, int HND>
@@ -1893,7 +1899,7 @@ void least_resident(int *worst, uint32_t lds, K... kernels) {
 template <int DIR, int HND>
 void least_resident_layer(int *worst) {
   constexpr uint32_t few = req_lds_bytes(kWave), many = req_lds_bytes(512);
-  least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kOne>, k_layer<DIR, HND, 4, 3, kWgThreads, kFew>);
+  least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads>, k_layer<DIR, HND, 4, 3, kWgThreads, kFew>);
   least_resident(worst, many, k_layer<DIR, HND, 4, 3, kWgThreads, kMany>, k_layer<DIR, HND, 4, 3, kWgThreads, kManyAhead>);
   if constexpr (any_blocks(HND)) {
     least_resident(worst, few, k_layer<DIR, HND, 4, 3, kWgThreads, kFew, false, true>);

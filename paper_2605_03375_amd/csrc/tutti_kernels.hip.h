@@ -2442,6 +2442,12 @@ __device__ __forceinline__ void late_words_at_hand(const LayerCall &c) {
   asm volatile("" ::"s"(c.w[7]), "s"(c.w[8]), "s"(c.w[9]), "s"(c.w[10]), "s"(c.w[11]), "s"(c.w[12]), "s"(c.w[13]));
 }
 
+// The same for all of them, in front of everything else: one wait.
+__device__ __forceinline__ void words_at_hand(const LayerCall &c) {
+  asm volatile("" ::"s"(c.w[0]), "s"(c.w[1]), "s"(c.w[2]), "s"(c.w[3]), "s"(c.w[4]), "s"(c.w[5]), "s"(c.w[6]));
+  late_words_at_hand(c);
+}
+
 // ORD (restore only): the blocks are visited in the order `visit` lists instead of staging order; the first slices
 // cannot be preloaded then (where they sit depends on the list).
 template <int DIR, int HND, int U, int NT, int WG, int REQS, bool ORD, bool PIECES>
@@ -2530,10 +2536,21 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
   if (blockIdx.x < w.sqe_wgs) emit_sqes<WG>(entry_args<DIR>(fields_of_lanes(word)), l, a.n_req, 0, w.sqe_wgs, head);
 }
 
+// One request's kernels take the words in one argument, which is read from memory, all of it behind one wait: there it is the launch
+// on the host that a train waits for, and a kernel of four arguments takes longer to launch.  Calls from Python, us, least of 12
+// trains in each of three processes, the four arguments below / so: restore of 256 KiB 3.22 to 3.31 / 3.06 to 3.20, 32 layers of
+// 4 MiB 104 to 107 / 96 to 104 (with every kernel's words in one argument 3.05 to 3.13 and 95 to 101, but then those of 8 requests
+// take 127 instead of 120, 32 layers of 16 MiB in 8 requests 221 instead of 205).
+template <int DIR, int HND, int U, int NT, int WG>
+__global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(const LayerCall c) {
+  words_at_hand(c);
+  run_layer<DIR, HND, U, NT, WG, kOne, false, false>(c, nullptr);
+}
+
 // The early words are arguments by themselves because such are in registers when a wavefront starts (-amdgpu-kernarg-preload-count);
 // the members of a struct are read from memory.  Graph replay of a copy kernel of four arguments, us, read / in registers:
 // 4 KiB 2.48 / 2.40, 64 KiB 3.74 / 3.60, 256 KiB 6.9 / 6.7.  Calls with the words from memory / so: save of 1280 blocks in 512
-// requests 8.07 / 7.93, restore of 128 MiB 44.0 / 43.8; where the host is what a train waits for, 3.03 / 3.12 a layer.
+// requests 8.07 / 7.93, restore of 128 MiB 44.0 / 43.8.
 template <int DIR, int HND, int U, int NT, int WG, int REQS, bool ORD = false, bool PIECES = false>
 __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(
     const u64x4 w0, const u64x2 w4, uint64_t w6, const typename std::conditional<ORD, OrderedLateWords, LateWords>::type rest) {
@@ -2553,7 +2570,8 @@ __global__ __launch_bounds__(WG, min_waves_per_simd(WG, U)) void k_layer(
 
 template <typename Rest>
 using LayerKernel = void (*)(u64x4, u64x2, uint64_t, Rest);  // parameters in the order of LayerArguments' members
-static_assert(std::is_same_v<decltype(&k_layer<kPack, kNhd, 4, 3, kWgThreads, kFew>), LayerKernel<LateWords>> &&
+static_assert(std::is_same_v<decltype(&k_layer<kPack, kNhd, 4, 3, kWgThreads>), void (*)(LayerCall)> &&
+                  std::is_same_v<decltype(&k_layer<kPack, kNhd, 4, 3, kWgThreads, kFew>), LayerKernel<LateWords>> &&
                   std::is_same_v<decltype(&k_layer<kUnpack, kNhd, 4, 3, kWgThreads, kMany, true>), LayerKernel<OrderedLateWords>>,
               "LayerArguments mirrors k_layer");
 
