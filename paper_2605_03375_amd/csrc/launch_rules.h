@@ -158,8 +158,8 @@ constexpr bool pack_at_once(uint64_t items, uint32_t chip_waves, uint32_t n_req,
   return 4 * items <= chip_waves || (n_req > 64 && n_req <= 1024 && table_len <= 8 * n_req);
 }
 
-// The same pause as hold_back_pause for a save of more than 64 requests that has read its slices at once, by the items the
-// requests have: more than half of the chip's wavefronts.  Us, graph replay and eager calls on warm data, pause 0 / 1 / 2 / 3:
+// The same pause as hold_back_pause for a save of more than 64 requests that has read its slices at once, by the items of 4 KiB
+// that the requests have: more than half of the chip's wavefronts.  Us, graph replay and eager calls on warm data, pause 0 / 1 / 2 / 3:
 //   1280 of 8 KiB in 512   8.7 8.5 / 8.5 8.3 / 8.5 8.3 / 8.7 8.5    350 of 32 KiB in 100   10.2 9.7 / 10.1 9.3 / 9.8 9.3 / 9.8 9.1
 //   3000 of 4 KiB in 1000  12.0 11.3 / 11.9 11.3 / 11.8 11.2 / 11.6 10.9
 //   1500 of 8 KiB in 300   10.1 9.6 / 10.5 10.1 / 9.9 9.4 / 10.1 9.6
@@ -193,7 +193,10 @@ constexpr uint32_t pack_pause(uint32_t items, uint32_t chip_waves) { return 2 * 
 //                     320 (0.63)     8.73   8.36   8.45   9.08   8.63   7.95   8.67
 // Runs fall into one of two modes, 5 to 10 % apart, by where their buffers lie; over block sizes, requests and 0.2 to 0.75 of the
 // chip saves gain 3.5 % in the geometric mean, up to 16 %.  Head-major blocks that are moved row by row (rows of 80 bytes) lose
-// with it, saves of 432 to 592 blocks of 20 KiB up to 15 %, and restores of cut slices (307 blocks of 12.5 KiB 4.8 / 5.0): none there.
+// with it, saves of 432 to 592 blocks of 20 KiB up to 15 %, and one request's restores of cut slices (307 blocks of 12.5 KiB 4.8 / 5.0):
+// none there.  Cut slices count as the 4 KiB slices that they make up here, in pack_pause and in hold_back_pause: restores of 2 to
+// 40 requests at 0.7 to 1.0 of the chip take the same time with either unit and without a pause, saves of 563 blocks of 12.5 KiB in
+// 100 / 300 requests, by slices / so, 7.6 7.6 / 7.8 7.7 and 8.2 8.2 / 8.0 8.0, larger ones the same.
 constexpr uint32_t one_restore_pause(uint32_t items, uint32_t chip_waves) {
   const uint32_t i = 32 * items, c = chip_waves;
   if (items > chip_waves || i < 7 * c || c == 0) return 0;

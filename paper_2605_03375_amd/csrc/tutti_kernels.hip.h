@@ -2503,7 +2503,8 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
         if (DIR == kPack && first.pos < blocks) pre = preload_pack<HND, U, NT>(m, first);
       });
   if (REQS == kFew && DIR == kUnpack && pre.valid)
-    hold_back(hold_back_pause(count_units<false>(m, l, a.n_req) * m.slices_per_block, m.chip_waves, a.n_req, false));
+    hold_back(hold_back_pause(full_slices<HND, U>(m, count_units<false>(m, l, a.n_req) * m.slices_per_block), m.chip_waves,
+                              a.n_req, false));
   SqeHead head;
   head.live = false;
   // the scan of many requests needs most scalar registers for itself
@@ -2522,9 +2523,8 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
   }
   if (copies) {
     if (DIR == kPack && (REQS == kManyAhead || ((REQS == kFewAhead || REQS == kFewCounted) && HND != kHnd))) {
-      const uint32_t items = count_units<false>(m, l, a.n_req) * m.slices_per_block;
-      hold_back(REQS == kManyAhead ? pack_pause(items, m.chip_waves)
-                                   : few_save_pause(full_slices<HND, U>(m, items), m.chip_waves, a.n_req));
+      const uint32_t items = full_slices<HND, U>(m, count_units<false>(m, l, a.n_req) * m.slices_per_block);
+      hold_back(REQS == kManyAhead ? pack_pause(items, m.chip_waves) : few_save_pause(items, m.chip_waves, a.n_req));
     }
     if (DIR == kPack && reads_under_scan(REQS))
       store_pack<HND, U, NT, WG, REQS, false>(m, l, a.n_req, wg, w.copy_wgs, pre);
