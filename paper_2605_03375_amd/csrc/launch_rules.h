@@ -202,14 +202,25 @@ constexpr uint32_t one_restore_pause(uint32_t items, uint32_t chip_waves) {
   if (items > chip_waves || i < 7 * c || c == 0) return 0;
   return 3 + (i >= 8 * c) + (i >= 9 * c) + (i >= 10 * c) + (i >= 12 * c);
 }
-constexpr uint32_t one_save_pause(uint32_t items, uint32_t chip_waves) {
+// `lines`: a head-major pool moved as line tiles, whose reads take longer.  Rows of 64 bytes, 16 heads / rows of 32 bytes, 32 heads,
+// 16 tokens, by the part of the chip, without / with the pause of the others (three processes each, medians):
+//                      0.36        0.40        0.45        0.50        0.55        0.60        0.63         0.66         0.70
+//   save of 1                               8.1 / 7.5   8.5 / 8.0   9.1 / 9.0   9.6 / 9.2  10.5 / 9.7   10.8 / 11.0  10.8 / 11.3
+//                                           8.2 / 7.6   8.6 / 8.0   9.2 / 9.1   9.6 / 9.1  10.6 / 10.0  10.9 / 11.1  11.2 / 12.1
+//   save of 9        7.1 / 6.8   7.9 / 8.1   8.1 / 8.1   8.7 / 9.0   9.5 / 9.6   9.8 / 9.5  (0.65) 10.9 / 10.2
+//                    7.1 / 6.9   8.0 / 8.2   8.2 / 8.1   8.8 / 9.2   9.7 / 9.7   9.9 / 9.6         11.0 / 10.4
+//   save of 40       7.2 / 6.8   8.0 / 8.2   8.3 / 8.7   8.7 / 9.2   9.5 / 9.7   9.8 / 9.6         11.0 / 10.2
+//                    7.3 / 7.0   8.0 / 8.5   8.3 / 8.6   8.7 / 9.3   9.6 / 9.8   9.9 / 9.7         11.0 / 10.5
+// and restores of one request 5.7 / 5.3 at 0.25, 7.6 / 6.6 at 0.4, 8.1 / 6.9 at 0.48.
+constexpr uint32_t one_save_pause(uint32_t items, uint32_t chip_waves, bool lines = false) {
   const uint32_t i = 32 * items, c = chip_waves;
-  if (items > chip_waves || i < 9 * c || 2 * i > 45 * c || c == 0) return 0;
+  if (items > chip_waves || i < 9 * c || 2 * i > (lines ? 41 : 45) * c || c == 0) return 0;
   return i < 12 * c ? 8 : i < 16 * c ? 10 : i < 17 * c ? 12 : 14;
 }
-constexpr uint32_t few_save_pause(uint32_t items, uint32_t chip_waves, uint32_t n_req) {
+constexpr uint32_t few_save_pause(uint32_t items, uint32_t chip_waves, uint32_t n_req, bool lines = false) {
   const uint32_t i = 32 * items, c = chip_waves;
   if (items > chip_waves || i < 9 * c || c == 0) return 0;
+  if (lines && i >= 12 * c && i <= 16 * c) return 0;
   if (i < 13 * c) return (i < 11 * c ? 2u : 3u) - (n_req > 32 ? 1u : 0u);
   return i < 16 * c ? 3 : i < 17 * c ? 8 : i < 21 * c ? 10 : 12;
 }
