@@ -1366,6 +1366,32 @@ def test_blocks_cut_into_slices_of_their_own_size(orc, H, T, h, d, e, layout, n_
                 H.check_layer_restore(orc, c, table_len=blocks, stage_cap=2 * blocks * bb - 16)
 
 
+@pytest.mark.parametrize("T,h,d,e,op,n_req,chip_part", [
+    # saves of one request, slices of 2176, 3968 and 3200 bytes: up to two items for each of the chip's wavefronts
+    (17, 1, 64, 2, "save", 1, 2), (1, 31, 128, 1, "save", 1, 2), (16, 5, 80, 2, "save", 1, 2),
+    # blocks of 10 and 15 KiB, slices of 2560 and 3840 bytes: restores up to half of the chip, saves like the others
+    (16, 4, 80, 2, "restore", 1, 0.5), (16, 4, 80, 2, "restore", 8, 0.5), (32, 5, 96, 1, "restore", 1, 0.5),
+    (16, 4, 80, 2, "save", 1, 2), (32, 5, 96, 1, "save", 8, 1)])
+def test_last_blocks_that_are_cut(orc, H, T, h, d, e, op, n_req, chip_part):
+    """Cut slices at the most that a rule admits, one block less and one block more (pieces): wavefronts with no second item, all
+    but a few with one, and padded and dense objects."""
+    bb = T * h * d * e
+    slices = -(-bb // 4096)
+    last = int(chip_part * 8192) // (2 * slices)
+    rng = np.random.default_rng(8800 + bb + n_req)
+    for blocks in (last - 1, last, last + 1):
+        say("cut blocks of", bb, "bytes,", op, "of", blocks, "in", n_req, "requests")
+        n = np.full(n_req, blocks // n_req, np.uint32)
+        n[n_req // 2] += blocks - int(n.sum())
+        N = blocks + 9
+        table = rng.permutation(N).astype(np.uint32)
+        table[[blocks // 2, blocks - 1]] = N
+        for align in (4096, 128):
+            c = H.LayerCase(T=T, h=h, d=d, e=e, N=N, n_blocks=n, table=table, align=align, chunk=8192, L=2, pad=48,
+                            name=f"last{bb}{op}n{n_req}b{blocks}a{align}")
+            (H.check_layer_save if op == "save" else H.check_layer_restore)(orc, c, layer=1, table_len=blocks)
+
+
 @pytest.mark.parametrize("T,h,d,e,layout", [(16, 1, 128, 2, 0), (16, 2, 128, 2, 0), (16, 5, 80, 2, 0), (16, 4, 128, 2, 0),
                                             (16, 6, 128, 2, 0), (16, 5, 128, 2, 0), (16, 16, 32, 1, 1), (16, 32, 32, 1, 1),
                                             (16, 8, 64, 1, 1), (16, 16, 64, 1, 1), (16, 24, 64, 1, 1), (8, 32, 64, 2, 1),
