@@ -12,8 +12,10 @@ namespace tutti {
 //   32  2.64   64  2.80   96  2.85   104  2.88   112  2.88   120  3.45   128  3.6   160  3.65   264  3.7   384  3.8
 // So a fused launch hands over bit fields (its arguments as separate words are 260 bytes), and the kernel takes them apart
 // with some thirty scalar instructions.  Calls from Python, us, words / fields: restore of 256 KiB 4.2 / 3.4, a train of 32 of
-// 4 MiB 131 / 113 and 139 / 116; the kernels by themselves (graph replay of 60 kinds of call) take the same time within 0.2 %,
-// the smallest 0.03 us more.
+// 4 MiB 131 / 113 and 139 / 116; the kernels by themselves (graph replay of 60 kinds of call) take the same time within 0.2 %;
+// the smallest 0.03 us more, and small ones on 32 compute units whose blocks are moved as pieces 0.05 to 0.2 (8 blocks of one request,
+// token-major of 12.5 KiB 5.4 / 5.5, head-major of 10 and 30 KiB 5.7 / 5.9; 256 blocks the same).  An ordered restore hands over 120
+// bytes (OrderedLateWords).
 //
 // What a field leaves out is what it cannot hold: addresses lie below 2^47 (the host checks the ones that are used), planes,
 // staging, entries, strides and block sizes are multiples of 16, a chunk is a multiple of the alignment, which is a power of two.
@@ -61,7 +63,7 @@ namespace layer_call {
 struct Bits {
   uint32_t at, n;
 };
-// The first words, kEarlyWords of them, are in scalar registers when a wavefront starts (k_layer): they hold what the way to the
+// The first words, kEarlyWords of them, are in scalar registers when a wavefront of several requests' kernels starts (k_layer): they hold what the way to the
 // first load of a restore needs, and most of a save's.  Each field there is one piece of one word.
 constexpr Bits kCopyWgs{0, 12}, kCopyFirst{12, 12}, kSqeWgs{24, 12}, kChip{36, 7}, kXcd{43, 1}, kAlign{44, 5}, kDense{49, 1},
     kLeftOut{50, 2}, kLayerLow{52, 12};
