@@ -212,9 +212,11 @@ constexpr uint32_t one_restore_pause(uint32_t items, uint32_t chip_waves) {
 //   save of 40       7.2 / 6.8   8.0 / 8.2   8.3 / 8.7   8.7 / 9.2   9.5 / 9.7   9.8 / 9.6         11.0 / 10.2
 //                    7.3 / 7.0   8.0 / 8.5   8.3 / 8.6   8.7 / 9.3   9.6 / 9.8   9.9 / 9.7         11.0 / 10.5
 // and restores of one request 5.7 / 5.3 at 0.25, 7.6 / 6.6 at 0.4, 8.1 / 6.9 at 0.48.
-constexpr uint32_t one_save_pause(uint32_t items, uint32_t chip_waves, bool lines = false) {
+// `early_end`: none from 2/3 on, which is what the kernels ask for with any blocks: with the buffers elsewhere than for the table
+// above, saves of token-major 32 KiB blocks, without / with it, 320 of them (0.63) 9.5 / 8.9, but 360 (0.70) 10.8 / 12.1.
+constexpr uint32_t one_save_pause(uint32_t items, uint32_t chip_waves, bool early_end = false) {
   const uint32_t i = 32 * items, c = chip_waves;
-  if (items > chip_waves || i < 9 * c || 2 * i > (lines ? 41 : 45) * c || c == 0) return 0;
+  if (items > chip_waves || i < 9 * c || 2 * i > (early_end ? 41 : 45) * c || c == 0) return 0;
   return i < 12 * c ? 8 : i < 16 * c ? 10 : i < 17 * c ? 12 : 14;
 }
 constexpr uint32_t few_save_pause(uint32_t items, uint32_t chip_waves, uint32_t n_req, bool lines = false) {

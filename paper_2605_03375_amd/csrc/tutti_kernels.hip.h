@@ -2480,7 +2480,7 @@ __device__ __forceinline__ void run_layer(const LayerCall &c, const uint32_t *vi
     if (copies) {
       const uint32_t items = full_slices<HND, U>(m, one.units * m.slices_per_block);
       const uint32_t pause = HND == kHnd || (DIR == kUnpack && HND == kCut) ? 0u
-                             : DIR == kPack ? one_save_pause(items, m.chip_waves, HND == kLines) : one_restore_pause(items, m.chip_waves);
+                             : DIR == kPack ? one_save_pause(items, m.chip_waves, true) : one_restore_pause(items, m.chip_waves);
       move_request<DIR, HND, U, NT, WG, false>(m, one, wg, w.copy_wgs, pre, pause);
     }
     if (entries) emit_sqes<WG>(entry_args<DIR>(fields_of_lanes(word)), l, 1, 0, w.sqe_wgs, one_head);
